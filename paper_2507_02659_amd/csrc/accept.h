@@ -49,21 +49,12 @@ __device__ inline void merge_partials(const float* __restrict__ pmax, const doub
   }
 }
 
-// Lanes of a wavefront hold running statistics r of parts of one row (exponent scale sc): merges them by shuffles in a
-// fixed order; lane 0 publishes the row's (max, sum, argmax) to LDS slot `at` and, if asked, to the workspace.
+// Lanes of a wavefront hold running statistics r of parts of one row (exponent scale sc): merges them in a fixed order; lane 0 publishes the row's (max, sum, argmax) to LDS slot `at` and, if asked, to the workspace.
 __device__ inline void wave_publish_row(const RunStat& r, float sc, int row, int lane, float* s_mx, double* s_S,
                                         int* s_arg, int at, bool to_workspace, float* g_mx, double* g_S, int32_t* g_arg) {
-  float mx = r.mx;
-  int arg = r.arg;
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    const float om = __shfl_xor(mx, off);
-    const int oa = __shfl_xor(arg, off);
-    if (om > mx || (om == mx && oa < arg)) { mx = om; arg = oa; }
-  }
-  double S = r.mx == -INFINITY ? 0.0 : r.sum * (double)__builtin_amdgcn_exp2f((r.mx - mx) * sc);
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) S += __shfl_xor(S, off);
+  const float mx = wave_max(r.mx);
+  const int arg = wave_min(r.mx == mx ? r.arg : 0x7FFFFFFF);
+  const double S = wave_sum(r.mx == -INFINITY ? 0.0 : r.sum * (double)__builtin_amdgcn_exp2f((r.mx - mx) * sc));
   if (lane == 0) {
     s_mx[at] = mx; s_S[at] = S; s_arg[at] = arg;
     if (to_workspace) { g_mx[row] = mx; g_S[row] = S; g_arg[row] = arg; }
@@ -138,18 +129,27 @@ __device__ inline void merge_chunk_row(const float* __restrict__ pmax, const dou
 __device__ inline void merge_draft_chunks(const StepArgs& a, int q, float Td, float* out_mx, double* out_S, int* out_arg) {
   const int64_t o = (int64_t)q * a.nchd;
   const float sc = Td > 0.f ? kLog2eF / Td : kLog2eF;
-  float bm = -INFINITY;
-  int ba = 0x7FFFFFFF;
-  for (int c = 0; c < a.nchd; ++c) {
-    const float m = a.dpart_max[o + c];
-    if (m > bm) { bm = m; ba = a.dpart_arg[o + c]; }       // ascending chunks: a later equal maximum does not replace
+  constexpr int kAtOnce = 4;                               // chunks asked for before any of them is looked at
+  RunStat r;
+  for (int c0 = 0; c0 < a.nchd; c0 += kAtOnce) {
+    float m[kAtOnce];
+    int arg[kAtOnce];
+    double sum[kAtOnce];
+#pragma unroll
+    for (int j = 0; j < kAtOnce; ++j) {
+      const int c = min(c0 + j, a.nchd - 1);
+      m[j] = a.dpart_max[o + c]; arg[j] = a.dpart_arg[o + c]; sum[j] = a.dpart_sum[o + c];
+    }
+    const float before = r.mx;
+#pragma unroll
+    for (int j = 0; j < kAtOnce; ++j)
+      if (c0 + j < a.nchd && m[j] > r.mx) { r.mx = m[j]; r.arg = arg[j]; }   // ascending chunks: a later equal maximum does not replace
+    if (before != -INFINITY) r.sum *= (double)__builtin_amdgcn_exp2f((before - r.mx) * sc);
+#pragma unroll
+    for (int j = 0; j < kAtOnce; ++j)
+      if (c0 + j < a.nchd && m[j] != -INFINITY) r.sum += sum[j] * (double)__builtin_amdgcn_exp2f((m[j] - r.mx) * sc);
   }
-  double total = 0.0;
-  for (int c = 0; c < a.nchd; ++c) {
-    const float m = a.dpart_max[o + c];
-    if (m != -INFINITY) total += a.dpart_sum[o + c] * (double)__builtin_amdgcn_exp2f((m - bm) * sc);
-  }
-  *out_mx = bm; *out_S = total; *out_arg = ba;
+  *out_mx = r.mx; *out_S = r.sum; *out_arg = r.arg;
 }
 
 // The acceptance test of sequence b by one wavefront (lane = mapped position).  P is the lane's proposal (P.m, P.flags
@@ -207,9 +207,10 @@ __device__ inline FinalInfo accept_wave(const StepArgs& a, int b, int r0, int k,
     // belongs to the draw (which may run before or after this store)
     if (lane != n || !(T > 0.f)) a.out.out_tokens[r0 + lane] = (lane < n) ? t_j : (lane == n ? arg : -1);
   }
-  int len_acc = (lane < n) ? L_j : 0;
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) len_acc += __shfl_xor(len_acc, off);
+  // accepted draft tokens: mapped position n starts where the n accepted spans end (lane n holds a start unless the
+  // whole window was accepted)
+  const int len_n = __shfl(P.start, n);
+  const int len_acc = n < m || (flags & OT_FLAG_UNMAPPABLE) ? len_n : k;
   const int hits_acc = __popcll(__ballot(lane < n && L_j > 1));
 
   // ---- final token at row n: its values live in lane n

@@ -129,7 +129,7 @@ int ot_verify_init(const ot_verify_config* cfg, ot_ctx** out) {
     c->loss_rows = rows;
   }
   ok = ok && dev_alloc(c, &c->adapt_part, 2 * Bm);
-  ok = ok && dev_alloc(c, &c->tile_r, Bm * c->ntiles) && dev_alloc(c, &c->tile_p, Bm * c->ntiles);
+  ok = ok && dev_alloc(c, &c->tile_r, Bm * c->ntiles);
   ok = ok && dev_alloc(c, &c->resid_count, Bm);
   if (!ok) { free_ctx(c); return fail(OT_ERR_NOMEM, "ot_verify_init: device allocation failed"); }
 
@@ -198,7 +198,7 @@ static int step_impl(ot_ctx* ctx, ot_ngram_cache* cache, const ot_step_in* in, c
   a.fin = ctx->fin;
   a.probe = ctx->probe;
   a.dpiece = ctx->dpiece;
-  a.tile_r = ctx->tile_r; a.tile_p = ctx->tile_p; a.resid_count = ctx->resid_count;
+  a.tile_r = ctx->tile_r; a.resid_count = ctx->resid_count;
   a.out = *o;
 
   hipStream_t st = ctx->stream;
@@ -246,7 +246,7 @@ static int step_impl(ot_ctx* ctx, ot_ngram_cache* cache, const ot_step_in* in, c
   OT_MARK(2);
   if (e == hipSuccess && !a.hosted && !a.chunked) e = launch_translate_accept(a, st);
   OT_MARK(3);
-  if (e == hipSuccess) e = launch_final_draw(a, in->row_off_host, st);
+  if (e == hipSuccess) e = launch_final_draw(a, in->row_off_host, ctx->n_cu, st);
   OT_MARK(4);
 #undef OT_MARK
   if (e != hipSuccess) return fail_hip(e, "ot_verify_step: launch");

@@ -19,6 +19,58 @@ __device__ inline double exp_neg_fast(double x) {
   return ldexp((double)e, (int)n);
 }
 
+// A value that every lane of the wavefront holds alike, moved to scalar registers (addresses formed from it cost no
+// vector instructions).
+__device__ inline int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ inline float uniform(float x) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))); }
+__device__ inline double uniform(double x) {
+  return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(x)), __builtin_amdgcn_readfirstlane(__double2loint(x)));
+}
+
+// Sum over the 64 lanes in one fixed order, the result in every lane.  The partners come through data-parallel moves
+// inside a row of 16 lanes and row broadcasts above it: no trip through the LDS permute network, whose latency six steps
+// of __shfl_xor would pay one after the other.
+template <int kCtrl, int kRowMask = 0xF>
+__device__ inline double dpp_f64(double x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), kCtrl, kRowMask, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), kCtrl, kRowMask, 0xF, false);
+  return __hiloint2double(hi, lo);                       // rows outside the mask receive +0.0
+}
+__device__ inline double wave_sum(double x) {
+  x += dpp_f64<0xB1>(x);             // neighbours 1 apart
+  x += dpp_f64<0x4E>(x);             // 2 apart
+  x += dpp_f64<0x141>(x);            // mirrored halves of eight lanes
+  x += dpp_f64<0x140>(x);            // mirrored row of sixteen: every lane holds its row's sum
+  x += dpp_f64<0x142, 0xA>(x);       // lane 15 of row 0 into row 1, of row 2 into row 3
+  x += dpp_f64<0x143, 0xC>(x);       // lane 31 into rows 2 and 3: lane 63 holds the total
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), 63), __builtin_amdgcn_readlane(__double2loint(x), 63));
+}
+// Inclusive running sum over the lanes in ascending order.
+__device__ inline double wave_scan(double x) {
+  x += dpp_f64<0x111>(x);            // from 1, 2, 4, 8 lanes below within the row of sixteen (nothing: +0.0)
+  x += dpp_f64<0x112>(x);
+  x += dpp_f64<0x114>(x);
+  x += dpp_f64<0x118>(x);
+  x += dpp_f64<0x142, 0xA>(x);
+  x += dpp_f64<0x143, 0xC>(x);
+  return x;
+}
+// Maximum / minimum over the 64 lanes, in every lane (a masked-off lane meets its own value).
+template <int kCtrl, int kRowMask = 0xF>
+__device__ inline int dpp_self(int x) { return __builtin_amdgcn_update_dpp(x, x, kCtrl, kRowMask, 0xF, false); }
+template <int kCtrl, int kRowMask = 0xF>
+__device__ inline float dpp_self(float x) { return __int_as_float(dpp_self<kCtrl, kRowMask>(__float_as_int(x))); }
+__device__ inline float wave_max(float x) {
+  x = fmaxf(x, dpp_self<0xB1>(x)); x = fmaxf(x, dpp_self<0x4E>(x)); x = fmaxf(x, dpp_self<0x141>(x));
+  x = fmaxf(x, dpp_self<0x140>(x)); x = fmaxf(x, dpp_self<0x142, 0xA>(x)); x = fmaxf(x, dpp_self<0x143, 0xC>(x));
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
+}
+__device__ inline int wave_min(int x) {
+  x = min(x, dpp_self<0xB1>(x)); x = min(x, dpp_self<0x4E>(x)); x = min(x, dpp_self<0x141>(x));
+  x = min(x, dpp_self<0x140>(x)); x = min(x, dpp_self<0x142, 0xA>(x)); x = min(x, dpp_self<0x143, 0xC>(x));
+  return __builtin_amdgcn_readlane(x, 63);
+}
+
 // Philox4x32-10 (Salmon et al., SC'11): ten rounds of two 32x32->64 multiplies and key-mixed xors.
 __device__ inline void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1,
                                      uint32_t out[4]) {

@@ -30,7 +30,7 @@ struct ot_ctx {
   int n_cu = 0;                       // compute units of the device
   otv::DraftPiece* dpiece = nullptr;  // [max_K, kDraftPieces] pieces of the draft rows' statistics, as the probe records
   otv::ProbeRecord* probe = nullptr;  // [max_batch] lookups of the drafted ids, between the LM-head launch and the next
-  double *tile_r = nullptr, *tile_p = nullptr;
+  double* tile_r = nullptr;
   int32_t* resid_count = nullptr;     // [max_batch] arrival counters of the residual launch, zero between launches
   otv::FinalInfo* fin = nullptr;
   void* loss_rows = nullptr;          // [max_rows] records of kLossRowBytes: per-token constants of the loss kernels

@@ -162,7 +162,7 @@ struct StepArgs {
                          // one launch follows it (at most kFusedMaxB sequences)
   FinalInfo* fin;        // [B]
   int32_t ntiles;        // residual tiles per row
-  double* tile_r; double* tile_p;                            // [B, ntiles]
+  double* tile_r;        // [B, ntiles]
   int32_t* resid_count;  // [B] tile workgroups of the residual launch that have delivered their mass; 0 between launches
   // outputs (device)
   ot_step_out out;
@@ -192,6 +192,6 @@ hipError_t launch_lmhead_f32(const float* H, int M, int d, const float* W, float
 hipError_t launch_softmax_stats(const StepArgs& a, hipStream_t stream);
 hipError_t launch_translate_accept(const StepArgs& a, hipStream_t stream);
 // translation and acceptance test (when the LM-head launch hosted the draft side) and the draw of the final tokens
-hipError_t launch_final_draw(const StepArgs& a, const int32_t* row_off_host, hipStream_t stream);
+hipError_t launch_final_draw(const StepArgs& a, const int32_t* row_off_host, int n_cu, hipStream_t stream);
 
 }  // namespace otv

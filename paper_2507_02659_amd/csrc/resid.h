@@ -6,15 +6,19 @@
 // pre-image), except that the n-gram matched at this position gets the product pi of its sub-token probabilities
 // and the direct image of its first sub-token gets q_s(d_1) - pi.  When everything was accepted the draw is from p.
 //
-// Only the ONE row per sequence where the draw happens is touched.  A workgroup of 16 wavefronts takes 8 consecutive
-// tiles of kResidTile target ids of one sequence, two wavefronts per tile:
-//   every workgroup  forms the masses of max(0, p - q') of its tiles in binary64 (and the masses of p, the fallback
-//                    when the residual is empty), publishes them and counts itself in;
+// Only the ONE row per sequence where the draw happens is touched.  A workgroup of 16 wavefronts takes a run of
+// consecutive tiles of kResidTile target ids of one sequence (draw_groups), eight at a time, two wavefronts per tile:
+//   every workgroup  forms the masses of max(0, p - q') of its tiles in binary64, publishes them and counts itself in;
 //   the workgroup that arrives last for its sequence  walks the tile masses in ascending order with a wavefront scan
 //                    to the tile that holds u * total, re-forms that tile with each thread owning 4 consecutive ids,
 //                    scans the running sum in ascending id order and emits the first id whose running sum exceeds the
 //                    target (inverse CDF).  Which workgroup that is varies from run to run; what it computes does not.
+//                    When the residual is empty (reachable only through underflow) it first forms the masses of p, the
+//                    fallback distribution, by itself.
 // Nothing waits: a workgroup that is not last simply ends.
+// What bounds a small batch is the chain of instructions and round trips in one workgroup (16 x 128256 ids: 17 us of
+// kernel, 21 before its gathers were freed and its scans and reductions moved from the LDS permute network to
+// data-parallel moves; one sequence of 32000 ids 12.5 against 16.2 us).
 #pragma once
 
 #include "device_math.h"
@@ -24,7 +28,7 @@ namespace otv {
 
 constexpr int kDrawWaves = 16;                       // wavefronts per workgroup
 constexpr int kDrawThreads = kDrawWaves * 64;
-constexpr int kGroupTiles = kDrawWaves / 2;          // tiles per workgroup: two wavefronts share one
+constexpr int kTurnTiles = kDrawWaves / 2;           // tiles a workgroup sums at a time: two wavefronts share one
 constexpr int kPerLane = kResidTile / 128;           // ids per lane while two wavefronts sum one tile
 constexpr int kPickThreads = 256;
 constexpr int kPer = kResidTile / kPickThreads;      // consecutive ids per thread while the chosen tile is scanned
@@ -36,13 +40,13 @@ struct FinalRow {
   float mx, sc_hi, sc_lo;        // row maximum; log2(e) / T split into two floats
   double invS;
   const void* zq;
+  int lds_at;                    // where the draft row's copy starts in the dynamic LDS, in bytes (-1: there is none)
   int dtype;
   float mxq, scq_hi, scq_lo;     // the same for the draft row
   double invSq;
   int argq;
   bool greedy_draft;
   bool residual;
-  const int32_t* tmap;
   int t_ng, t_pre;
   double pi, q_pre;
 
@@ -55,9 +59,6 @@ struct FinalRow {
     return (double)__builtin_amdgcn_exp2f(fmaf(d, sc_hi, d * sc_lo)) * invS;
   }
   __device__ inline double p_of(float zv) const { return softmax_term(zv, mx, sc_hi, sc_lo, invS); }
-  __device__ inline float draft_logit(int dv) const {
-    return dtype == OT_BF16 ? bf16_to_f32(static_cast<const uint16_t*>(zq)[dv]) : static_cast<const float*>(zq)[dv];
-  }
   // q'(v) given the draft id dv = tmap[v] (or -1) and, when dv >= 0 and the draft is not greedy, its logit
   __device__ inline double qprime(int v, int dv, float xq) const {
     double q = 0.0;
@@ -68,74 +69,98 @@ struct FinalRow {
   }
 };
 
+// The record is the same for every lane: all of it goes to scalar registers.
 __device__ inline FinalRow make_final_row(const StepArgs& a, const FinalInfo& f) {
   FinalRow R;
-  R.z = a.Z + (int64_t)f.row * a.ldz;
+  R.z = a.Z + (int64_t)uniform(f.row) * a.ldz;
   const double sc = f.invT * 1.4426950408889634, scq = f.invTd * 1.4426950408889634;
-  R.mx = (float)f.mx; R.sc_hi = (float)sc; R.sc_lo = (float)(sc - (double)R.sc_hi); R.invS = f.invS;
-  R.residual = f.mode == 3;
+  const float sc_hi = (float)sc, scq_hi = (float)scq;
+  R.mx = uniform((float)f.mx); R.sc_hi = uniform(sc_hi); R.sc_lo = uniform((float)(sc - (double)sc_hi)); R.invS = uniform(f.invS);
+  R.residual = uniform(f.mode) == 3;
+  R.lds_at = -1;
   R.dtype = a.dtype;
-  R.tmap = a.tmap;
-  R.t_ng = f.t_ng; R.t_pre = f.t_pre; R.pi = f.pi; R.q_pre = f.q_pre;
-  R.zq = static_cast<const char*>(a.draft_logits) + (size_t)f.drow * a.V_d * (a.dtype == OT_BF16 ? 2 : 4);
-  R.mxq = (float)f.mxq; R.scq_hi = (float)scq; R.scq_lo = (float)(scq - (double)R.scq_hi); R.invSq = f.invSq; R.argq = f.argq;
-  R.greedy_draft = f.greedy_draft != 0;
+  R.t_ng = uniform(f.t_ng); R.t_pre = uniform(f.t_pre); R.pi = uniform(f.pi); R.q_pre = uniform(f.q_pre);
+  R.zq = static_cast<const char*>(a.draft_logits) + (size_t)uniform(f.drow) * a.V_d * (a.dtype == OT_BF16 ? 2 : 4);
+  R.mxq = uniform((float)f.mxq); R.scq_hi = uniform(scq_hi); R.scq_lo = uniform((float)(scq - (double)scq_hi));
+  R.invSq = uniform(f.invSq); R.argq = uniform(f.argq);
+  R.greedy_draft = uniform(f.greedy_draft) != 0;
   return R;
 }
 
-// Inverse direct map of N ids v = first + e * stride (independent of which row is drawn from: issued early).
+// Inverse direct map of N ids v = first + e * stride (independent of which row is drawn from: issued early).  Ids past
+// the vocabulary read the last entry and are masked afterwards: no branch around the loads.
 template <int N>
 __device__ inline void load_tmap(const int32_t* __restrict__ tmap, int V_t, int first, int stride, int* dv) {
 #pragma unroll
-  for (int e = 0; e < N; ++e) {
-    const int v = first + e * stride;
-    dv[e] = v < V_t ? tmap[v] : -1;
-  }
+  for (int e = 0; e < N; ++e) dv[e] = tmap[min(first + e * stride, V_t - 1)];
 }
 
 // Stand-in logit of an id that does not exist or has no pre-image: finite, so that the two-float scaling below never
 // meets inf * 0, and so far below any maximum that its exponential is exactly 0.
 constexpr float kFarBelow = -1e30f;
 
-// Residual mass r(v) and p(v) for N ids v = first + e * stride.  All loads are issued before any arithmetic.  The
-// common case (every id below V_t, a sampling drafter, no id of Eq. 2's two overrides among them) runs without any
-// per-element test other than "has a pre-image".
+// The dynamic LDS of the draw kernels: the tiles' masses, then (where a workgroup takes several turns) the draft row.
+typedef __attribute__((address_space(3))) char* lds_chars;
+extern __shared__ double s_draw_dynamic[];
+__device__ inline lds_chars draw_lds() { return (lds_chars)(void __attribute__((address_space(3)))*)s_draw_dynamic; }
+
+// What tile_values needs from memory for N ids v = first + e * stride, as loaded: the row's logits and, where the draw is
+// from a residual of a sampling drafter, the logits of the ids' pre-images.
+template <int N> struct TileRaw { float z[N]; uint32_t xq[N]; };
+
+// All 2 N loads leave before anything waits: no lane is masked off (an id without a pre-image reads the row's first
+// logit) and nothing is converted between two loads.  With the conversion inside a conditional block per id every
+// gather was waited for by itself, eight round trips of about 1 us in a row.
 template <int N>
-__device__ inline void tile_values(const FinalRow& R, int V_t, int first, int stride, const int* dv, double* r,
-                                   double* p) {
-  float zv[N];
-  float xq[N];
-  const int last = first + (N - 1) * stride;
-  const bool gather = R.residual && !R.greedy_draft;
-  if (last < V_t) {
+__device__ inline void load_tile(const FinalRow& R, int V_t, int first, int stride, const int* dv, TileRaw<N>& raw) {
 #pragma unroll
-    for (int e = 0; e < N; ++e) zv[e] = R.z[first + e * stride];
+  for (int e = 0; e < N; ++e) raw.z[e] = R.z[min(first + e * stride, V_t - 1)];
+  if (!R.residual || R.greedy_draft) {                   // wavefront-uniform
+#pragma unroll
+    for (int e = 0; e < N; ++e) raw.xq[e] = 0u;
+  } else if (R.lds_at >= 0) {
+    const lds_chars s_row = draw_lds() + R.lds_at;
+    if (R.dtype == OT_BF16) {
+#pragma unroll
+      for (int e = 0; e < N; ++e) raw.xq[e] = *(const __attribute__((address_space(3))) uint16_t*)(s_row + 2 * max(dv[e], 0));
+    } else {
+#pragma unroll
+      for (int e = 0; e < N; ++e) raw.xq[e] = *(const __attribute__((address_space(3))) uint32_t*)(s_row + 4 * max(dv[e], 0));
+    }
+  } else if (R.dtype == OT_BF16) {
+#pragma unroll
+    for (int e = 0; e < N; ++e) raw.xq[e] = static_cast<const uint16_t*>(R.zq)[max(dv[e], 0)];
   } else {
 #pragma unroll
-    for (int e = 0; e < N; ++e) zv[e] = first + e * stride < V_t ? R.z[first + e * stride] : kFarBelow;
+    for (int e = 0; e < N; ++e) raw.xq[e] = static_cast<const uint32_t*>(R.zq)[max(dv[e], 0)];
   }
+}
+
+// Mass r(v) of those ids, the N of them across the wavefront inside [lo, hi): max(0, p - q'), or p where the draw is from
+// p.  The common case (all ids exist, a sampling drafter, no id of Eq. 2's two overrides among them: tested once per
+// wavefront) costs an id about twenty instructions; this is what bounds a turn, not the memory.
+template <int N>
+__device__ inline void tile_values(const FinalRow& R, int V_t, int first, int stride, int lo, int hi, const int* dv,
+                                   const TileRaw<N>& raw, double* r) {
+  const bool all_exist = hi <= V_t;
 #pragma unroll
-  for (int e = 0; e < N; ++e) xq[e] = (gather && dv[e] >= 0) ? R.draft_logit(dv[e]) : kFarBelow;
+  for (int e = 0; e < N; ++e)                                     // beyond V_t: 2^(-huge) = 0
+    r[e] = R.p_of(all_exist || first + e * stride < V_t ? raw.z[e] : kFarBelow);
+  if (!R.residual) return;
+  const uint32_t shift = R.dtype == OT_BF16 ? 16u : 0u;
+  float xq[N];
 #pragma unroll
-  for (int e = 0; e < N; ++e) p[e] = R.p_of(zv[e]);             // beyond V_t: 2^(-huge) = 0
-  if (!R.residual) {
+  for (int e = 0; e < N; ++e) xq[e] = dv[e] >= 0 ? __uint_as_float(raw.xq[e] << shift) : kFarBelow;
+  const bool special = R.greedy_draft || (R.t_pre >= lo && R.t_pre < hi) || (R.t_ng >= lo && R.t_ng < hi);
+  if (!special) {
 #pragma unroll
-    for (int e = 0; e < N; ++e) r[e] = p[e];
-    return;
-  }
-  // wavefront-uniform: does any lane hold an id that Eq. 2 overrides, or is the drafter greedy?
-  bool special = R.greedy_draft;
-#pragma unroll
-  for (int e = 0; e < N; ++e) special = special || first + e * stride == R.t_pre || first + e * stride == R.t_ng;
-  if (!__any(special)) {
-#pragma unroll
-    for (int e = 0; e < N; ++e)                                   // no pre-image: 2^(-huge) = 0
-      r[e] = fmax(0.0, p[e] - FinalRow::softmax_term(xq[e], R.mxq, R.scq_hi, R.scq_lo, R.invSq));
+    for (int e = 0; e < N; ++e)                                   // no pre-image: 2^(-huge) = 0; beyond V_t: max(0, 0 - q) = 0
+      r[e] = fmax(0.0, r[e] - FinalRow::softmax_term(xq[e], R.mxq, R.scq_hi, R.scq_lo, R.invSq));
   } else {
 #pragma unroll
     for (int e = 0; e < N; ++e) {
       const int v = first + e * stride;
-      r[e] = v < V_t ? fmax(0.0, p[e] - R.qprime(v, dv[e], xq[e])) : 0.0;
+      r[e] = v < V_t ? fmax(0.0, r[e] - R.qprime(v, dv[e], xq[e])) : 0.0;
     }
   }
 }
@@ -152,94 +177,125 @@ __device__ inline double observe(double* p) {
                                                            __HIP_MEMORY_SCOPE_AGENT));
 }
 
-// first id a lane sums in workgroup `grp`
-__device__ inline int draw_first_id(int grp, int wave, int lane) {
-  return (grp * kGroupTiles + (wave >> 1)) * kResidTile + (wave & 1) * (kResidTile / 2) + lane;
+// first id a lane sums among the eight tiles that start at `tile0`
+__device__ inline int draw_first_id(int tile0, int wave, int lane) {
+  return (tile0 + (wave >> 1)) * kResidTile + (wave & 1) * (kResidTile / 2) + lane;
+}
+
+// Copies the draft row to byte `at` of the dynamic LDS (all threads call it, a barrier follows): whole 16-byte chunks where
+// the row covers them, element by element at its ends, each byte at its own offset within a chunk.  Returns where the row
+// starts there.
+__device__ inline int stage_draft_row(const FinalRow& R, int V_d, int tid, int at) {
+  const int esz = R.dtype == OT_BF16 ? 2 : 4;
+  const char* row = static_cast<const char*>(R.zq);
+  const int head = (int)(reinterpret_cast<uintptr_t>(row) & 15), bytes = V_d * esz;
+  const int chunks = (head + bytes + 15) / 16;
+  const int whole0 = head ? 1 : 0, whole1 = (head + bytes) / 16;     // chunks [whole0, whole1) lie inside the row
+  const lds_chars s_row = draw_lds() + at;
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  constexpr int kAtOnce = 4;
+  for (int c0 = tid; c0 < chunks; c0 += kAtOnce * kDrawThreads) {
+    u32x4 x[kAtOnce];
+#pragma unroll
+    for (int j = 0; j < kAtOnce; ++j) {                    // any other chunk number loads the nearest of those
+      const int c = min(max(c0 + j * kDrawThreads, whole0), whole1 - 1);
+      x[j] = whole0 < whole1 ? *reinterpret_cast<const u32x4*>(row + (c * 16 - head)) : u32x4{0, 0, 0, 0};
+    }
+#pragma unroll
+    for (int j = 0; j < kAtOnce; ++j) {
+      const int c = c0 + j * kDrawThreads, from = c * 16 - head;
+      if (c >= whole0 && c < whole1) {
+        *(__attribute__((address_space(3))) u32x4*)(s_row + c * 16) = x[j];
+      } else if (c < chunks) {
+        for (int o = max(from, 0); o < min(from + 16, bytes); o += esz) {
+          if (esz == 2) *(__attribute__((address_space(3))) uint16_t*)(s_row + head + o) = *reinterpret_cast<const uint16_t*>(row + o);
+          else *(__attribute__((address_space(3))) uint32_t*)(s_row + head + o) = *reinterpret_cast<const uint32_t*>(row + o);
+        }
+      }
+    }
+  }
+  return at + head;
 }
 
 struct DrawLds {
-  double half[2][kGroupTiles];   // masses of the second halves of the tiles
+  double half[kTurnTiles];       // fallback: masses of the second halves of a turn's tiles
   double w[kPickThreads / 64];
   double base, target;
-  int pick, fallback, first, lastnz, last;
+  int first[kPickThreads / 64], lastnz[kPickThreads / 64];
+  int pick, fallback, last;
 };
 
-// Workgroup `grp` of sequence b (all kDrawThreads threads call this; f is the sequence's outcome record with
-// f.mode != 0; dv holds tmap of the ids draw_first_id(grp, wave, lane) + e * 64, e < kPerLane, of this wavefront's
-// half tile).  s_tiles is
-// dynamic LDS of 2 * ntiles doubles.
-__device__ inline void draw_final_token(const StepArgs& a, int b, int grp, const FinalInfo& f, const int* dv, DrawLds* L,
-                                        double* s_tiles) {
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  FinalRow R = make_final_row(a, f);
-  const int n_groups = (a.ntiles + kGroupTiles - 1) / kGroupTiles;
+// Mass of the 512 ids from `lo` on (this lane: first + e * 64), in every lane.
+__device__ inline double half_tile_mass(const FinalRow& R, int V_t, int first, int lo, const int* dv, const TileRaw<kPerLane>& raw) {
+  double r[kPerLane];
+  tile_values<kPerLane>(R, V_t, first, 64, lo, lo + kResidTile / 2, dv, raw, r);
+  double sum = 0.0;
+#pragma unroll
+  for (int e = 0; e < kPerLane; e += 4) sum += (r[e] + r[e + 1]) + (r[e + 2] + r[e + 3]);
+  return wave_sum(sum);
+}
 
-  // ---- masses of this workgroup's tiles: wavefronts 2i and 2i+1 take the two halves of tile i (coalesced:
-  // consecutive lanes on consecutive ids), wavefront 2i adds the halves and publishes
-  const int tile = grp * kGroupTiles + (wave >> 1);
-  double sr = 0.0, sp = 0.0;
-  if (tile < a.ntiles) {
-    double r[kPerLane], p[kPerLane];
-    tile_values<kPerLane>(R, a.V_t, tile * kResidTile + (wave & 1) * (kResidTile / 2) + lane, 64, dv, r, p);
+// Workgroup `grp` of sequence b takes tiles [grp * group_tiles, (grp + 1) * group_tiles), group_tiles a multiple of
+// kTurnTiles (all kDrawThreads threads call this; f is the sequence's outcome record with f.mode != 0; dv holds tmap of
+// the ids draw_first_id(grp * group_tiles, wave, lane) + e * 64, e < kPerLane).  The dynamic LDS holds
+// max(ntiles, 2 * group_tiles) doubles and, if row_at > 0, from double row_at on room for the draft row and 32 bytes.
+__device__ inline void draw_final_token(const StepArgs& a, int b, int grp, int group_tiles, const FinalInfo& f, int* dv,
+                                        DrawLds* L, int row_at) {
+  double* s_tiles = s_draw_dynamic;
+  const int tid = threadIdx.x, wave = uniform((int)(threadIdx.x >> 6)), lane = tid & 63;
+  FinalRow R = make_final_row(a, f);
+  const int tile0 = grp * group_tiles, tile1 = min(tile0 + group_tiles, a.ntiles);
+  if (row_at > 0 && R.residual && !R.greedy_draft) {     // workgroup-uniform
+    R.lds_at = stage_draft_row(R, a.V_d, tid, 8 * row_at);
+    __syncthreads();
+  }
+
+  // ---- masses of this workgroup's tiles: wavefronts 2i and 2i+1 take the two halves of a tile (coalesced: consecutive
+  // lanes on consecutive ids) and leave them in LDS; after the last turn one thread per tile adds the halves and publishes
+  for (int t0 = tile0; t0 < tile1; t0 += kTurnTiles) {
+    const int tile = t0 + (wave >> 1), first = draw_first_id(t0, wave, lane);
+    if (tile >= tile1) break;
+    TileRaw<kPerLane> raw;
+    load_tile<kPerLane>(R, a.V_t, first, 64, dv, raw);
+    int dv_next[kPerLane] = {};                          // asked for behind what this turn waits for
+    if (t0 + kTurnTiles < tile1) load_tmap<kPerLane>(a.tmap, a.V_t, first + kTurnTiles * kResidTile, 64, dv_next);
+    const double mass = half_tile_mass(R, a.V_t, first, draw_first_id(t0, wave, 0), dv, raw);
+    if (lane == 0) s_tiles[2 * (tile - tile0) + (wave & 1)] = mass;
 #pragma unroll
-    for (int e = 0; e < kPerLane; e += 4) {
-      sr += (r[e] + r[e + 1]) + (r[e + 2] + r[e + 3]);
-      sp += (p[e] + p[e + 1]) + (p[e + 2] + p[e + 3]);
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) { sr += __shfl_xor(sr, off); sp += __shfl_xor(sp, off); }
-    if (lane == 0 && (wave & 1)) { L->half[0][wave >> 1] = sr; L->half[1][wave >> 1] = sp; }
+    for (int e = 0; e < kPerLane; ++e) dv[e] = dv_next[e];
   }
   __syncthreads();
-  if (tile < a.ntiles && lane == 0 && !(wave & 1)) {
-    publish(&a.tile_r[(int64_t)b * a.ntiles + tile], sr + L->half[0][wave >> 1]);
-    publish(&a.tile_p[(int64_t)b * a.ntiles + tile], sp + L->half[1][wave >> 1]);
-    // the two stores have reached memory before this workgroup is counted
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): vector-memory stores count there as well
-    asm volatile("" ::: "memory");
-  }
+  for (int i = tid; i < tile1 - tile0; i += kDrawThreads)
+    publish(&a.tile_r[(int64_t)b * a.ntiles + tile0 + i], s_tiles[2 * i] + s_tiles[2 * i + 1]);
+  // the stores have reached memory before this workgroup is counted
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): vector-memory stores count there as well
+  asm volatile("" ::: "memory");
   __syncthreads();
   if (tid == 0) {
     const int arrived = __hip_atomic_fetch_add(&a.resid_count[b], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    L->last = arrived == n_groups - 1;
+    L->last = arrived == (int)gridDim.x - 1;
     if (L->last) __hip_atomic_store(&a.resid_count[b], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
   }
   __syncthreads();
   if (!L->last) return;
 
   // ---- the last workgroup of the sequence: inverse CDF over the tile masses, then inside the tile that holds the draw
-  for (int t = tid; t < a.ntiles; t += kDrawThreads) {
-    s_tiles[t] = observe(&a.tile_r[(int64_t)b * a.ntiles + t]);
-    s_tiles[a.ntiles + t] = observe(&a.tile_p[(int64_t)b * a.ntiles + t]);
-  }
+  for (int t = tid; t < a.ntiles; t += kDrawThreads) s_tiles[t] = observe(&a.tile_r[(int64_t)b * a.ntiles + t]);
   __syncthreads();
-  if (wave == 0) {
-    // Running mass over the tiles in ascending order, in place: wavefront scan of 64 tiles at a time plus a carry.
-    // The total and the crossing both come from these same sums.
-    auto prefix = [&](double* m) -> double {
-      double carry = 0.0;
-      for (int t0 = 0; t0 < a.ntiles; t0 += 64) {
-        const int t = t0 + lane;
-        double incl = t < a.ntiles ? m[t] : 0.0;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-          const double up = __shfl_up(incl, off);
-          if (lane >= off) incl += up;
-        }
-        incl += carry;
-        if (t < a.ntiles) m[t] = incl;
-        carry = __shfl(incl, 63);
-      }
-      return carry;
-    };
+  // Wavefront 0: running mass over the tiles in ascending order, in place (a wavefront scan of 64 tiles at a time plus a
+  // carry), and the tile where it crosses u * total.  The total and the crossing both come from these same sums.
+  auto pick_tile = [&](bool may_fall_back) {
     double* m = s_tiles;
-    double total = prefix(m);
-    const int fallback = !(total > 0.0);    // residual of zero mass: draw from p
-    if (fallback) {
-      m = s_tiles + a.ntiles;
-      total = prefix(m);
+    double carry = 0.0;
+    for (int t0 = 0; t0 < a.ntiles; t0 += 64) {
+      const int t = t0 + lane;
+      const double incl = wave_scan(t < a.ntiles ? m[t] : 0.0) + carry;
+      if (t < a.ntiles) m[t] = incl;
+      carry = __shfl(incl, 63);
     }
+    const double total = carry;
+    const int fallback = may_fall_back && !(total > 0.0);    // residual of zero mass: draw from p
     const double target = f.u2 * total;
     int pick = -1;
     for (int t0 = 0; t0 < a.ntiles && pick < 0; t0 += 64) {
@@ -255,27 +311,41 @@ __device__ inline void draw_final_token(const StepArgs& a, int b, int grp, const
     if (lane == 0) {
       if (fallback) a.out.flags[b] |= OT_FLAG_RESID_ZERO;
       L->pick = pick; L->base = base; L->target = target; L->fallback = fallback;
-      L->first = 0x7FFFFFFF; L->lastnz = -1;
     }
-  }
+  };
+  if (wave == 0) pick_tile(true);
   __syncthreads();
-  if (L->fallback) R.residual = false;
+  if (L->fallback) {                         // workgroup-uniform
+    R.residual = false;
+    for (int t0 = 0; t0 < a.ntiles; t0 += kTurnTiles) {
+      const int tile = t0 + (wave >> 1), first = draw_first_id(t0, wave, lane);
+      double mass = 0.0;
+      if (tile < a.ntiles) {
+        TileRaw<kPerLane> raw;
+        load_tile<kPerLane>(R, a.V_t, first, 64, dv, raw);
+        mass = half_tile_mass(R, a.V_t, first, draw_first_id(t0, wave, 0), dv, raw);
+        if (lane == 0 && (wave & 1)) L->half[wave >> 1] = mass;
+      }
+      __syncthreads();
+      if (tile < a.ntiles && lane == 0 && !(wave & 1)) s_tiles[tile] = mass + L->half[wave >> 1];
+      __syncthreads();
+    }
+    if (wave == 0) pick_tile(false);
+    __syncthreads();
+  }
   const double target = L->target;
-  const bool picker = tid < kPickThreads;
-  const int v0 = L->pick * kResidTile + tid * kPer;      // a picking thread owns kPer consecutive ids: ascending running sum
-  double r[kPer] = {0.0, 0.0, 0.0, 0.0}, p[kPer];
+  const bool picker = wave < kPickThreads / 64;
+  const int pick = uniform(L->pick);
+  const int v0 = pick * kResidTile + tid * kPer;         // a picking thread owns kPer consecutive ids: ascending running sum
+  double r[kPer] = {0.0, 0.0, 0.0, 0.0};
   double excl = 0.0;
   if (picker) {
     int dvp[kPer];
+    TileRaw<kPer> raw;
     load_tmap<kPer>(a.tmap, a.V_t, v0, 1, dvp);
-    tile_values<kPer>(R, a.V_t, v0, 1, dvp, r, p);
-    const double local = ((r[0] + r[1]) + r[2]) + r[3];
-    double incl = local;                                 // inclusive scan over the wavefront, fixed order
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const double up = __shfl_up(incl, off);
-      if (lane >= off) incl += up;
-    }
+    load_tile<kPer>(R, a.V_t, v0, 1, dvp, raw);
+    tile_values<kPer>(R, a.V_t, v0, 1, pick * kResidTile, (pick + 1) * kResidTile, dvp, raw, r);
+    const double incl = wave_scan(((r[0] + r[1]) + r[2]) + r[3]);
     excl = __shfl_up(incl, 1);
     if (lane == 0) excl = 0.0;
     if (lane == 63) L->w[wave] = incl;
@@ -294,11 +364,20 @@ __device__ inline void draw_final_token(const StepArgs& a, int b, int grp, const
         if (first == 0x7FFFFFFF && c > target) first = v0 + e;
       }
     }
-    if (first != 0x7FFFFFFF) atomicMin(&L->first, first);
-    if (last >= 0) atomicMax(&L->lastnz, last);
+    // ids ascend with the lanes: the lowest lane that crossed, the highest that holds mass.  (By ballots: LDS atomics of a
+    // whole wavefront on one word are unrolled lane by lane, which took 3 to 4 us here.)
+    const unsigned long long crossed = __ballot(first != 0x7FFFFFFF), mass = __ballot(last >= 0);
+    const int w_first = crossed ? __builtin_amdgcn_readlane(first, (int)__ffsll((long long)crossed) - 1) : -1;
+    const int w_last = mass ? __builtin_amdgcn_readlane(last, 63 - (int)__clzll((long long)mass)) : -1;
+    if (lane == 0) { L->first[wave] = w_first; L->lastnz[wave] = w_last; }
   }
   __syncthreads();
-  if (tid == 0) a.out.out_tokens[f.row] = (L->first != 0x7FFFFFFF) ? L->first : L->lastnz;
+  if (tid == 0) {
+    int token = -1;
+    for (int w = 0; w < kPickThreads / 64 && token < 0; ++w) token = L->first[w];
+    for (int w = kPickThreads / 64 - 1; w >= 0 && token < 0; --w) token = L->lastnz[w];
+    a.out.out_tokens[f.row] = token;
+  }
 }
 
 }  // namespace otv

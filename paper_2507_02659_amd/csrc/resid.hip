@@ -1,5 +1,5 @@
 // The launches that draw the final token of every sequence (Algorithm 1: correction token from the residual of Eq. 2,
-// or free token from p), grid = (groups of 8 tiles of kResidTile target ids) x (sequences).
+// or free token from p), grid = (groups of tiles of kResidTile target ids) x (sequences).
 //   final_draw_kernel   the outcome records of the acceptance test are in memory (written by the launch before).
 //   accept_draw_kernel  follows an LM-head launch that hosted the draft side: every workgroup first repeats the
 //                       translation and the acceptance test of its sequence (one wavefront merges the pieces of the
@@ -9,22 +9,24 @@
 //                       takes part in the draw.  The workgroups of a sequence reach the same outcome; only group 0
 //                       writes the outputs of the translation and the test, the draft rows' merged statistics and
 //                       the cache's use statistics.
+#include <algorithm>
+
 #include "accept.h"
 #include "resid.h"
 
 namespace otv {
 namespace {
 
-__global__ __launch_bounds__(kDrawThreads) void final_draw_kernel(StepArgs a) {
+// row_at: where the draft row's copy starts in the dynamic LDS, in doubles (0: no copy)
+__global__ __launch_bounds__(kDrawThreads) void final_draw_kernel(StepArgs a, int group_tiles, int row_at) {
   const int b = blockIdx.y, grp = blockIdx.x, tid = threadIdx.x;
-  const int wave = tid >> 6, lane = tid & 63;
-  extern __shared__ double s_tiles[];       // [2][ntiles]: residual masses, then p masses
+  const int wave = uniform(tid >> 6), lane = tid & 63;
   __shared__ DrawLds s_draw;
   int dv[kPerLane];
-  load_tmap<kPerLane>(a.tmap, a.V_t, draw_first_id(grp, wave, lane), 64, dv);   // overlaps the next load
+  load_tmap<kPerLane>(a.tmap, a.V_t, draw_first_id(grp * group_tiles, wave, lane), 64, dv);   // overlaps the next load
   const FinalInfo f = a.fin[b];
   if (f.mode == 0) return;                  // greedy or flagged sequence: nothing to draw
-  draw_final_token(a, b, grp, f, dv, &s_draw, s_tiles);
+  draw_final_token(a, b, grp, group_tiles, f, dv, &s_draw, row_at);
 }
 
 // Row offsets of the sequences as a kernel argument (the host has them): the workgroup knows its rows without a
@@ -37,10 +39,9 @@ constexpr int64_t kRepeatedMergeBytes = 32 << 20;
 // kChunks: the partials come from the statistics launch (chunk partials in three arrays per side) instead of the
 // LM head's epilogue and draft-row pieces.
 template <bool kDraw, bool kChunks>
-__global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, RowOffsets ro) {
+__global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, RowOffsets ro, int group_tiles, int row_at) {
   const int b = blockIdx.y, grp = blockIdx.x, tid = threadIdx.x;
-  const int wave = tid >> 6, lane = tid & 63;
-  extern __shared__ double s_tiles[];
+  const int wave = uniform(tid >> 6), lane = tid & 63;
   __shared__ DrawLds s_draw;
   __shared__ DraftLds s_d;
   __shared__ FinalInfo s_fin;
@@ -102,7 +103,7 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, R
   }
   // The inverse map of this wavefront's ids is needed last (by the tile masses) and asked for here, behind the loads
   // that the test waits for: loads return in issue order, and asked for first it held those back by its own latency.
-  if (kDraw) load_tmap<kPerLane>(a.tmap, a.V_t, draw_first_id(grp, wave, lane), 64, dv);
+  if (kDraw) load_tmap<kPerLane>(a.tmap, a.V_t, draw_first_id(grp * group_tiles, wave, lane), 64, dv);
   __syncthreads();
   if (wave == kTestWave) {
     const FinalInfo fin = accept_wave(a, b, r0, k, q0, T, Td, invT, invTd, sid, P, true, z_tok, s_pmx, s_pS, s_parg, lane, lead);
@@ -115,23 +116,47 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, R
   __syncthreads();
   const FinalInfo f = s_fin;
   if (f.mode == 0) return;
-  draw_final_token(a, b, grp, f, dv, &s_draw, s_tiles);
+  draw_final_token(a, b, grp, group_tiles, f, dv, &s_draw, row_at);
 }
 
 }  // namespace
 
+constexpr size_t kDrawLdsBytes = 150 << 10;    // dynamic LDS of a draw workgroup at most (160 KB a compute unit)
+
+// Tiles per workgroup of the draw.  Eight (one turn) as long as that leaves no more than a workgroup per compute unit:
+// a small batch is bound by the chain of round trips in one workgroup, which every further turn would lengthen.  With
+// more, each workgroup takes as many turns as bring their number back to one per compute unit (a workgroup of 1024
+// threads fills one): its start, its share of the merge and its count at the end are then paid once for several turns,
+// and a turn's loads overlap the sums of the turn before.  At most 64 turns, so that the halves' scratch stays small.
+// Measured (kernel time, one turn per workgroup against this rule): 128 sequences x 128256 ids 109 + 10 us of a test
+// launch against 39 us in one launch (2 us a turn), 64 x 152064 (half greedy) 39 + 10 against 30, 300 x 32003 65 against
+// 30; 16 x 128256 and below stay at one turn.
+int draw_group_tiles(int ntiles, int B, int n_cu) {
+  const int64_t groups = (int64_t)ceil_div(ntiles, kTurnTiles) * B;
+  return kTurnTiles * std::min(64, std::max(1, ceil_div(groups, std::max(n_cu, 1))));
+}
+
 // hosted: the LM-head launch left its softmax partials, the draft rows' pieces and the probe records; chunked: the
 // statistics launch left its chunk partials and the probe records (in both cases B <= kFusedMaxB and row_off_host holds
 // the B + 1 row offsets); otherwise a.fin is filled.
-hipError_t launch_final_draw(const StepArgs& a, const int32_t* row_off_host, hipStream_t stream) {
+hipError_t launch_final_draw(const StepArgs& a, const int32_t* row_off_host, int n_cu, hipStream_t stream) {
   if (a.B == 0) return hipSuccess;
-  const dim3 grid(ceil_div(a.ntiles, kGroupTiles), a.B), block(kDrawThreads);
-  const size_t lds = 2 * (size_t)a.ntiles * sizeof(double);
+  const int group_tiles = draw_group_tiles(a.ntiles, a.B, n_cu);
+  const dim3 grid(ceil_div(a.ntiles, group_tiles), a.B), block(kDrawThreads);
+  size_t lds = std::max((size_t)a.ntiles, 2 * (size_t)group_tiles) * sizeof(double);
+  // From two turns on the workgroup keeps the draft row in LDS where it fits: a gather from memory moves a 128-byte line
+  // per id, about 2 us of a turn, the copy costs that once (128 sequences x 128256 ids: 51 us without, 39 with).
+  int row_at = 0;
+  const size_t row_bytes = (size_t)a.V_d * (a.dtype == OT_BF16 ? 2 : 4) + 32;
+  if (group_tiles > kTurnTiles && lds + 16 + row_bytes <= kDrawLdsBytes) {
+    row_at = (int)((lds + 15) / 16) * 2;
+    lds = (size_t)row_at * sizeof(double) + row_bytes;
+  }
   if (a.chunked) {
     if (a.B > kFusedMaxB || a.hosted) return hipErrorInvalidValue;
     RowOffsets ro;
     for (int b = 0; b <= kFusedMaxB; ++b) ro.v[b] = row_off_host[b <= a.B ? b : a.B];
-    hipLaunchKernelGGL((accept_draw_kernel<true, true>), grid, block, lds, stream, a, ro);   // a few chunks per row: always one launch
+    hipLaunchKernelGGL((accept_draw_kernel<true, true>), grid, block, lds, stream, a, ro, group_tiles, row_at);   // a few chunks per row: always one launch
     return hipGetLastError();
   }
   if (a.hosted) {
@@ -142,12 +167,12 @@ hipError_t launch_final_draw(const StepArgs& a, const int32_t* row_off_host, hip
     // about the traffic that costs as much as a launch this is one launch; beyond it the test gets a launch of its own.
     const int64_t repeated = (int64_t)a.M * a.fused.nfine * (int64_t)sizeof(Partial) * grid.x;
     if (repeated <= kRepeatedMergeBytes) {
-      hipLaunchKernelGGL((accept_draw_kernel<true, false>), grid, block, lds, stream, a, ro);
+      hipLaunchKernelGGL((accept_draw_kernel<true, false>), grid, block, lds, stream, a, ro, group_tiles, row_at);
       return hipGetLastError();
     }
-    hipLaunchKernelGGL((accept_draw_kernel<false, false>), dim3(1, a.B), block, 0, stream, a, ro);
+    hipLaunchKernelGGL((accept_draw_kernel<false, false>), dim3(1, a.B), block, 0, stream, a, ro, group_tiles, row_at);
   }
-  hipLaunchKernelGGL(final_draw_kernel, grid, block, lds, stream, a);
+  hipLaunchKernelGGL(final_draw_kernel, grid, block, lds, stream, a, group_tiles, row_at);
   return hipGetLastError();
 }
 

@@ -1,0 +1,49 @@
+"""The final draw when a workgroup takes several turns of eight tiles: enough sequences that the launch would otherwise
+hold more workgroups than compute units.  Against the oracle, with the draft row in LDS and (a row too large) without."""
+import numpy as np
+import pytest
+
+from test_gpu_parity import _imports, _run_and_compare
+from workloads import CaseSpec, make_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype,V_t,V_d,B", [
+    ("bf16", 40001, 4001, 120),      # 3 turns, 2 groups; rows at every 2-byte alignment, last tile of 65 ids
+    ("f32", 40000, 4003, 120),       # rows at every 4-byte alignment
+    ("bf16", 8193, 3000, 300),       # 9 tiles in one group, the second turn holds a single tile of one id
+    ("bf16", 70000, 76000, 64),      # 152 KB per draft row: gathered from memory
+    ("f32", 30000, 5, 300),          # a draft row shorter than two 16-byte chunks
+])
+def test_several_turns_per_workgroup(dtype, V_t, V_d, B):
+    rng = np.random.default_rng(V_t)
+    temps = rng.choice([1.0, 0.7, 0.0], size=B, p=[0.5, 0.4, 0.1]).tolist()
+    case = make_case(CaseSpec(name=f"turns_{dtype}_{V_t}_{V_d}", dtype=dtype, d=8, V_t=V_t, V_d=V_d, k=rng.integers(0, 4, size=B).tolist(),
+                              temperature=temps, n_direct=int(0.8 * min(V_d, V_t)), n_ngram=min(200, V_d * V_d // 2), ngram_len=(2, 3),
+                              plant_cover=0.3, align=0.5, data_seed=V_d, philox_seed=5, logits_only=True,
+                              draft_temperature=[0.0 if b % 17 == 3 else max(t, 0.5) for b, t in enumerate(temps)]))
+    _, ref, _ = _run_and_compare(case)
+    drawn = np.asarray(case.temperature) > 0
+    assert (ref["n_accept"][drawn] < ref["n_mapped"][drawn]).any() and (ref["n_accept"][drawn] == ref["n_mapped"][drawn]).any()
+
+
+def test_empty_residual_over_several_turns():
+    """Every residual underflows to zero mass: the last workgroup forms the masses of p itself (9 tiles, the last ragged)."""
+    ov, ot, Verifier, parity = _imports()
+    B, V_t, V_d = 300, 8200, 40
+    case = make_case(CaseSpec(name="turns_zero", dtype="f32", d=8, V_t=V_t, V_d=V_d, k=[1] * B, temperature=[1.0] * B, n_direct=0,
+                              data_seed=92, philox_seed=10, logits_only=True))
+    hot = (np.arange(B) * 137 + 5) % V_t               # p and q' are one-hot at a target id of each sequence's own tile
+    case.direct_map[:] = -1
+    spread = np.unique(hot)[:V_d - 1]
+    case.direct_map[1:1 + spread.size] = spread
+    case.target_logits[:] = 0
+    case.draft_logits[:] = 0
+    for b in range(B):
+        d = 1 + b % spread.size
+        case.target_logits[2 * b, case.direct_map[d]] = 2000.0
+        case.draft_logits[b, d] = 2000.0
+    case.draft_ids[:] = 0                              # no image: the proposal is empty
+    gpu, ref, _ = _run_and_compare(case)
+    assert np.all(gpu["flags"] == (ot.OT_FLAG_UNMAPPABLE | ot.OT_FLAG_RESID_ZERO))
