@@ -48,9 +48,9 @@ extern "C" {
 /* ---- storage types of hidden states, LM-head weights and draft logits --------------------------------- */
 /* OT_BF16 is the production type: the LM head runs on the matrix cores, bound by the weight stream.
  * OT_F32 exists for small problems that want fp32 arithmetic end to end (checks against an fp32 model, toy
- * vocabularies): its LM head is a vector-ALU kernel that re-reads W once per 8 rows and never hosts the draft side,
- * so a step costs several times the bf16 one at the same shape (measured: about 6x at d = 4096, V_t = 128256,
- * 144 rows).  Nothing is refused for size; it is simply slow there.                                          */
+ * vocabularies): its LM head runs on the fp32 matrix instructions, a sixteenth of the bf16 rate, and never hosts the
+ * draft side, so a step costs several times the bf16 one where the rows are many (measured: about 7x at d = 4096,
+ * V_t = 128256, 144 rows; 1.4x at d = 1024, V_t = 32000, 6 rows).  Nothing is refused for size.              */
 #define OT_BF16 0
 #define OT_F32  1
 

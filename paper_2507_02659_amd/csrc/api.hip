@@ -110,7 +110,7 @@ int ot_verify_init(const ot_verify_config* cfg, ot_ctx** out) {
   const size_t R = (size_t)c->max_rows, KQ = (size_t)c->max_K, Bm = (size_t)c->max_batch;
   bool ok = true;
   if (c->dtype == OT_BF16) ok = ok && dev_alloc(c, &c->Wp, (size_t)(c->Vp / 64) * (size_t)packed_tile_units(c->Kp / 32) * 8) && dev_alloc(c, &c->zeros, 32);
-  else ok = ok && dev_alloc(c, &c->Wf, (size_t)c->d * c->V_t);
+  else ok = ok && dev_alloc(c, &c->Wf, (size_t)ceil_div(c->V_t, 64) * (size_t)packed_f32_tile_units(ceil_div(c->d, 16)) * 4);
   ok = ok && dev_alloc(c, &c->dmap, (size_t)c->V_d) && dev_alloc(c, &c->tmap, (size_t)c->V_t);
   ok = ok && dev_alloc(c, &c->Z, R * (size_t)c->V_t);
   ok = ok && dev_alloc(c, &c->tpart_max, R * c->ncht) && dev_alloc(c, &c->tpart_sum, R * c->ncht) && dev_alloc(c, &c->tpart_arg, R * c->ncht);
@@ -141,7 +141,7 @@ int ot_verify_init(const ot_verify_config* cfg, ot_ctx** out) {
     if (c->dtype == OT_BF16)
       e = launch_pack_w_bf16(static_cast<const uint16_t*>(cfg->W), c->d, c->V_t, c->Wp, c->Kp, c->Vp, c->stream);
     else
-      e = hipMemcpyAsync(c->Wf, cfg->W, sizeof(float) * (size_t)c->d * c->V_t, hipMemcpyDeviceToDevice, c->stream);
+      e = launch_pack_w_f32(static_cast<const float*>(cfg->W), c->d, c->V_t, c->Wf, c->stream);
   }
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);    // tmap_h and the caller's W are released here
   if (e != hipSuccess) { free_ctx(c); return fail_hip(e, "ot_verify_init"); }

@@ -661,29 +661,141 @@ __global__ __launch_bounds__(512) void lmhead_bf16_skinny_kernel(const uint16_t*
   }
 }
 
-// fp32 path (meant for small fp32 problems; no matrix cores): a thread owns one vocabulary column for kF32Rows rows, so
-// a weight is read once per kF32Rows rows, coalesced over the vocabulary, and the hidden values are wave-uniform
-// (scalar loads).  Each logit is one chain of fused multiply-adds in ascending hidden index.
-constexpr int kF32Rows = 8;
-__global__ __launch_bounds__(256) void lmhead_f32_kernel(const float* __restrict__ H, int M, int d,
-                                                         const float* __restrict__ W, float* __restrict__ Z, int V_t,
-                                                         int64_t ldz) {
-  const int n = blockIdx.x * 256 + threadIdx.x;
-  const int m0 = blockIdx.y * kF32Rows;
-  if (n >= V_t) return;
-  const int rows = min(kF32Rows, M - m0);
-  float acc[kF32Rows];
+// ---------------------------------------------------------------------------------------------------------------
+// fp32 head, on v_mfma_f32_16x16x4_f32 (binary32 products and sums, twice the rate of the vector units' fused
+// multiply-adds).  Bound by the matrix cores from about 48 rows on (147 TFLOP/s is what a large fp32 product reaches on
+// this card), by the weight stream below.  W is re-tiled once at init so that a wavefront's loads are contiguous:
+// unit(wt, kb, s, lane), one float4, holds W[16*kb + 4*(lane/16) + s][64*wt + 4*(lane%16) + 0..3], zero outside [d, V_t].
+// The four floats of a lane feed four MFMAs, one per interleaved set of 16 columns {64*wt + 4*i + nw}, and a lane's
+// float4 of hidden values H[row][16*kb + 4*(lane/16) + 0..3] feeds the four steps s: the hidden index that a lane group
+// contributes to an MFMA may be any, as long as both operands take the same.
+// A workgroup owns 64 columns and up to 48 rows and splits the hidden dimension over its wavefronts, whose partial tiles
+// are summed through LDS in a fixed order: a head of 1024 columns is 16 workgroups of 8 wavefronts, one of 32000 is 500
+// per row block.  The row blocks of a column tile run on the same XCD back to back and meet in its L2.
+// Measured (64 rows, d = 1024, V_t = 32000 / 5 rows, d = 256, V_t = 1024): 47 / 4.3 us, against 575 / 68 us of a kernel
+// whose threads owned one column each over all of the hidden dimension (1000 and 4 workgroups of serial chains); error
+// against 64 bits 4.7e-7 and 1.1e-7, with one long chain per logit 2e-6 and 6e-7.
+typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));   // rows may start at any float
+
+__global__ __launch_bounds__(256) void pack_w_f32_kernel(const float* __restrict__ W, int d, int V_t,
+                                                         float4* __restrict__ Wp, int nkb, int64_t n_units) {
+  const int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (u >= n_units) return;
+  const int lane = (int)(u & 63), s = (int)((u >> 6) & 3);
+  const int64_t rest = u >> 8;
+  const int kb = (int)(rest % nkb), wt = (int)(rest / nkb);
+  const int k = kb * 16 + 4 * (lane >> 4) + s, n = wt * 64 + 4 * (lane & 15);
+  float w[4] = {0.f, 0.f, 0.f, 0.f};
+  if (k < d)
 #pragma unroll
-  for (int i = 0; i < kF32Rows; ++i) acc[i] = 0.f;
-  for (int kk = 0; kk < d; ++kk) {
-    const float w = W[(int64_t)kk * V_t + n];
+    for (int e = 0; e < 4; ++e)
+      if (n + e < V_t) w[e] = W[(int64_t)k * V_t + n + e];
+  Wp[(int64_t)wt * packed_f32_tile_units(nkb) + ((int64_t)kb * 4 + s) * 64 + lane] = make_float4(w[0], w[1], w[2], w[3]);
+}
+
+template <int MT, int WAVES, int PF>
+__global__ __launch_bounds__(WAVES * 64) void lmhead_f32_kernel(const float* __restrict__ H, int M, int d,
+                                                                const f32x4* __restrict__ Wp, int nkb, int n_wtiles,
+                                                                float* __restrict__ Z, int V_t, int64_t ldz, int m_blocks) {
+  constexpr int kRow = 17;                              // float4 per padded row of the reduction scratch
+  __shared__ f32x4 sRed[WAVES][MT * 16 * kRow];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int slot = (int)blockIdx.x >> 3;
+  const int wt = (slot / m_blocks) * 8 + ((int)blockIdx.x & 7), row0 = (slot % m_blocks) * (MT * 16);
+  if (wt >= n_wtiles) return;                           // padding of the id space
+  const int whole = d / 16;                             // blocks without a ragged end, split over the wavefronts
+  const int kb0 = (int)(((int64_t)whole * wave) / WAVES), kb1 = (int)(((int64_t)whole * (wave + 1)) / WAVES);
+  const f32x4* wp = Wp + (int64_t)wt * packed_f32_tile_units(nkb) + lane;
+  const int g = lane >> 4;
+  const float* hp[MT];                                  // rows past M are never stored: any valid row will do
 #pragma unroll
-    for (int i = 0; i < kF32Rows; ++i)
-      if (i < rows) acc[i] = fmaf(H[(int64_t)(m0 + i) * d + kk], w, acc[i]);
+  for (int mt = 0; mt < MT; ++mt) hp[mt] = H + (int64_t)min(row0 + mt * 16 + (lane & 15), M - 1) * d + 4 * g;
+
+  f32x4 acc[MT][4];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int nw = 0; nw < 4; ++nw) acc[mt][nw] = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 wq[PF][4], hq[PF][MT];
+  auto fetch = [&](int st, int kb) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const f32x4* src = wp + ((int64_t)kb * 4 + s) * 64;
+      wq[st][s] = m_blocks == 1 ? __builtin_nontemporal_load(src) : *src;   // read once by the whole launch: nontemporal
+    }
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) hq[st][mt] = *reinterpret_cast<const f32x4_u*>(hp[mt] + kb * 16);
+  };
+  auto multiply = [&](int st) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nw = 0; nw < 4; ++nw)
+          acc[mt][nw] = __builtin_amdgcn_mfma_f32_16x16x4f32(wq[st][s][nw], hq[st][mt][s], acc[mt][nw], 0, 0, 0);
+  };
+#pragma unroll
+  for (int st = 0; st < PF; ++st)
+    if (kb0 + st < kb1) fetch(st, kb0 + st);
+  int base = kb0;
+  for (; base + 2 * PF <= kb1; base += PF) {            // every refill in range: no branch inside
+#pragma unroll
+    for (int st = 0; st < PF; ++st) {
+      multiply(st);
+      fetch(st, base + st + PF);
+    }
   }
 #pragma unroll
-  for (int i = 0; i < kF32Rows; ++i)
-    if (i < rows) Z[(int64_t)(m0 + i) * ldz + n] = acc[i];
+  for (int st = 0; st < 2 * PF - 1; ++st) {
+    if (base + st < kb1) {
+      multiply(st % PF);
+      if (st < PF - 1 && base + st + PF < kb1) fetch(st % PF, base + st + PF);
+    }
+  }
+  if (wave == WAVES - 1 && whole < nkb) {               // the ragged end of the hidden dimension reads as zero
+    const int left = d - (whole * 16 + 4 * g);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) wq[0][s] = wp[((int64_t)whole * 4 + s) * 64];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) hq[0][mt][e] = e < left ? hp[mt][whole * 16 + e] : 0.f;
+    multiply(0);
+  }
+  // acc[mt][nw][e] = partial Z[row0 + 16*mt + lane%16][64*wt + 4*(4*(lane/16) + e) + nw]
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      sRed[wave][(mt * 16 + (lane & 15)) * kRow + 4 * g + e] = f32x4{acc[mt][0][e], acc[mt][1][e], acc[mt][2][e], acc[mt][3][e]};
+  __syncthreads();
+  for (int i = tid; i < MT * 256; i += WAVES * 64) {
+    const int r = i >> 4, c = i & 15;
+    f32x4 sum = sRed[0][r * kRow + c];
+#pragma unroll
+    for (int w = 1; w < WAVES; ++w) sum += sRed[w][r * kRow + c];
+    const int m = row0 + r, n = wt * 64 + 4 * c;
+    if (m < M) {
+      float* dst = Z + (int64_t)m * ldz + n;
+      if (n + 4 <= V_t) {
+        *reinterpret_cast<f32x4_u*>(dst) = sum;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (n + e < V_t) dst[e] = sum[e];
+      }
+    }
+  }
+}
+
+template <int MT, int WAVES, int PF>
+hipError_t launch_f32(const float* H, int M, int d, const float* Wp, float* Z, int V_t, int64_t ldz, hipStream_t stream) {
+  const int nkb = ceil_div(d, 16), n_wtiles = ceil_div(V_t, 64), m_blocks = ceil_div(M, MT * 16);
+  hipLaunchKernelGGL((lmhead_f32_kernel<MT, WAVES, PF>), dim3((unsigned)(ceil_div(n_wtiles, 8) * 8 * m_blocks)),
+                     dim3(WAVES * 64), 0, stream, H, M, d, reinterpret_cast<const f32x4*>(Wp), nkb, n_wtiles, Z, V_t, ldz,
+                     m_blocks);
+  return hipGetLastError();
 }
 
 // Rows above which an M-block is split: up to 11 row tiles run as one block that streams every weight once (9 with
@@ -877,11 +989,25 @@ hipError_t launch_lmhead_bf16(const uint16_t* H, int M, int d, const uint16_t* W
   }
 }
 
-hipError_t launch_lmhead_f32(const float* H, int M, int d, const float* W, float* Z, int V_t, int64_t ldz,
+hipError_t launch_pack_w_f32(const float* W, int d, int V_t, float* Wp, hipStream_t stream) {
+  const int nkb = ceil_div(d, 16);
+  const int64_t n_units = (int64_t)ceil_div(V_t, 64) * nkb * 256;
+  hipLaunchKernelGGL(pack_w_f32_kernel, dim3((unsigned)((n_units + 255) / 256)), dim3(256), 0, stream, W, d, V_t,
+                     reinterpret_cast<float4*>(Wp), nkb, n_units);
+  return hipGetLastError();
+}
+
+// Row tiles per block: two, or three where that pads less (48 rows, 144 rows).  Smaller blocks read the weights again out
+// of L2 but put more wavefronts on a compute unit, and this product needs them to cover its loads: 64 rows as two blocks
+// of two tiles 47 us, as one of four 50 us (d = 1024, V_t = 32000).  A single row tile splits the hidden dimension over
+// eight wavefronts (more bytes in flight, small heads fill more of the chip), the others over four (eight: 51 us).
+hipError_t launch_lmhead_f32(const float* H, int M, int d, const float* Wp, float* Z, int V_t, int64_t ldz,
                              hipStream_t stream) {
   if (M == 0) return hipSuccess;
-  hipLaunchKernelGGL(lmhead_f32_kernel, dim3(ceil_div(V_t, 256), ceil_div(M, kF32Rows)), dim3(256), 0, stream, H, M, d, W, Z, V_t, ldz);
-  return hipGetLastError();
+  const int tiles = ceil_div(M, 16);
+  if (tiles == 1) return launch_f32<1, 8, 4>(H, M, d, Wp, Z, V_t, ldz, stream);
+  if (ceil_div(tiles, 3) * 3 < ceil_div(tiles, 2) * 2) return launch_f32<3, 4, 2>(H, M, d, Wp, Z, V_t, ldz, stream);
+  return launch_f32<2, 4, 2>(H, M, d, Wp, Z, V_t, ldz, stream);
 }
 
 }  // namespace otv

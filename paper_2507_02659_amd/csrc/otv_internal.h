@@ -22,6 +22,8 @@ constexpr int kGemmKPad = 128;       // packed K extent is a multiple of this
 constexpr int kGemmTileGapUnits = 1032;
 // 16-byte units from one 64-column tile of the packed weights to the next (nks 32-deep steps of 4 fragments each)
 constexpr int64_t packed_tile_units(int nks) { return (int64_t)nks * 256 + kGemmTileGapUnits; }
+// the same for the fp32 head: nkb 16-deep blocks of 4 x 64 float4
+constexpr int64_t packed_f32_tile_units(int nkb) { return (int64_t)nkb * 256 + kGemmTileGapUnits; }
 constexpr int kLossRowBytes = 128;   // size of the per-token record of the distillation-loss kernels
 
 inline int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
@@ -187,7 +189,8 @@ int lmhead_bf16_draft_workers(int M, int Vp, int B, int K, int n_cu);
 hipError_t launch_lmhead_bf16(const uint16_t* H, int M, int d, const uint16_t* Wp, int Kp, int Vp, float* Z, int V_t,
                               int64_t ldz, const uint16_t* zeros, const FusedStats* fused, const StepArgs* draft_side,
                               int n_cu, hipStream_t stream);
-hipError_t launch_lmhead_f32(const float* H, int M, int d, const float* W, float* Z, int V_t, int64_t ldz,
+hipError_t launch_pack_w_f32(const float* W, int d, int V_t, float* Wp, hipStream_t stream);
+hipError_t launch_lmhead_f32(const float* H, int M, int d, const float* Wp, float* Z, int V_t, int64_t ldz,
                              hipStream_t stream);
 hipError_t launch_softmax_stats(const StepArgs& a, hipStream_t stream);
 hipError_t launch_translate_accept(const StepArgs& a, hipStream_t stream);
