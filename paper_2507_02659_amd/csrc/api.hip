@@ -115,7 +115,7 @@ int ot_verify_init(const ot_verify_config* cfg, ot_ctx** out) {
   ok = ok && dev_alloc(c, &c->Z, R * (size_t)c->V_t);
   ok = ok && dev_alloc(c, &c->tpart_max, R * c->ncht) && dev_alloc(c, &c->tpart_sum, R * c->ncht) && dev_alloc(c, &c->tpart_arg, R * c->ncht);
   if (c->dtype == OT_BF16) {
-    const size_t nf = (size_t)(c->Vp / 256);
+    const size_t nf = (size_t)(c->Vp / 128);              // the narrowest workgroups
     ok = ok && dev_alloc(c, &c->fpart, R * nf);
   }
   ok = ok && dev_alloc(c, &c->dpart_max, KQ * c->nchd) && dev_alloc(c, &c->dpart_sum, KQ * c->nchd) && dev_alloc(c, &c->dpart_arg, KQ * c->nchd);

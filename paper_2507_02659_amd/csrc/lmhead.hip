@@ -17,8 +17,8 @@
 //     HBM latency.
 //   * The epilogue also reduces each row's logits over the workgroup's columns to softmax partials (maximum, its
 //     column, sum of exponentials at the row's temperature), so that no later pass has to read the logits for them.
-//   * A workgroup owns 256 columns, or 512 where that lets the launch fit into fewer rounds of one workgroup per
-//     compute unit (what a workgroup does outside its main loop is time its compute unit does not stream).
+//   * A workgroup owns 128 to 640 columns, so that the launch fits into few, full rounds of one workgroup per compute
+//     unit (what a workgroup does outside its main loop is time its compute unit does not stream).
 //   * The launch can host the draft side of the step, the work that needs no target logits (see draft-side jobs in
 //     the kernel): with one M-block inside the multiplying workgroups, behind their first loads; with several in a
 //     few workgroups at the front of the launch.
@@ -29,6 +29,7 @@
 // four consecutive vocabulary columns of one row and stores them as one float4.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "translate.h"
 
@@ -116,17 +117,21 @@ __global__ __launch_bounds__(WPG * 64) void lmhead_bf16_wide_kernel(const uint16
   constexpr int kSliceChunks = MT * 16 * kCPR;
   constexpr int kDma = (kSliceChunks + WPG * 64 - 1) / (WPG * 64);
   static_assert(kSliceChunks % 64 == 0 && kSliceChunks >= 64, "a slice is a whole number of wavefront-wide loads");
-  constexpr int kPatchRow = NW * 16 + 4;           // floats per padded row of the epilogue patch
+  constexpr int kPatchNW = NW <= 4 ? NW : 3;        // column tiles that the epilogue turns at a time
+  constexpr int kPatchRow = kPatchNW * 16 + 4;     // floats per padded row of the epilogue patch
   // steps per trip of the main loop: whole pairs of slices (buffers A, B) and whole turns of the weight ring, so
   // that both the buffer and the ring array of every step are known at compile time
   constexpr int kUnroll = 2 * kKSteps * PF / gcd_c(2 * kKSteps, PF);
-  static_assert(PF % kKSteps == 0 && PF <= 6, "a weight fetch is used a whole number of slices later");
+  static_assert(PF % kKSteps == 0 && PF <= 8, "a weight fetch is used a whole number of slices later");
   static_assert(kGemmKPad % KC == 0 && (kCPR == 8 || kCPR == 16), "slice geometry");
   static_assert((PF - 1) * NW + (PF / kKSteps) * kDma + NW < 64, "the load counter has 6 bits");
-  static_assert(NW == 1 || NW == 2 || NW == 4, "a wavefront owns 16, 32 or 64 columns");
+  static_assert(NW >= 1 && NW <= 5, "a wavefront owns 16 to 80 columns");
   __shared__ __attribute__((aligned(16))) uint16_t sA[MT * 16 * KC];
   __shared__ __attribute__((aligned(16))) uint16_t sB[MT * 16 * KC];
-  __shared__ __attribute__((aligned(16))) float sPatch[WPG][16 * kPatchRow];   // epilogue: one 16-row tile per wavefront
+  // epilogue: one 16-row tile per wavefront; before the main loop: scratch of the draft-side jobs, four sequences' lookups
+  constexpr int kLookupFloats = (int)(sizeof(DraftLds) * (WPG * 64 / 128) / (sizeof(float) * WPG) + 4) / 4 * 4;
+  constexpr int kPatchFloats = 16 * kPatchRow > kLookupFloats ? 16 * kPatchRow : kLookupFloats;
+  __shared__ __attribute__((aligned(16))) float sPatch[WPG][kPatchFloats];
   // The weight fragments travel by direct global->LDS loads as well, into a ring of PF steps: one array per step (so
   // that the compiler can tell them apart), each wavefront using its own NW KB of every array.  A register prefetch
   // next to direct-to-LDS loads would make the compiler drain the load counter at each first use of a register.
@@ -134,7 +139,7 @@ __global__ __launch_bounds__(WPG * 64) void lmhead_bf16_wide_kernel(const uint16
   // and keeps them out of LDS, is no faster at 144 rows: 222 against 218 us per step.)
   constexpr int kRing = WPG * NW * 64;
   __shared__ uint4 sW0[kRing], sW1[kRing], sW2[PF > 2 ? kRing : 1], sW3[PF > 3 ? kRing : 1], sW4[PF > 4 ? kRing : 1],
-      sW5[PF > 5 ? kRing : 1];
+      sW5[PF > 5 ? kRing : 1], sW6[PF > 6 ? kRing : 1], sW7[PF > 7 ? kRing : 1];
   // fused row statistics: row offsets and temperatures of the sequences (staged by direct loads in the prologue),
   // and the exponent scale log2(e)/T of each row of the M-block
   __shared__ int32_t sRowOff[kFusedMaxB + 1];
@@ -325,10 +330,18 @@ __global__ __launch_bounds__(WPG * 64) void lmhead_bf16_wide_kernel(const uint16
   const bool active = t16_own < n_wtiles * 4;
   // A wavefront past the last tile (only in the last workgroup) multiplies the last tile again and stores nothing:
   // the main loop then has no wavefront-dependent branch and every wavefront issues the same loads in the same order.
+  // (With 48 or 80 columns a wavefront can straddle the end: its surplus tiles are the last one as well, and the columns
+  // they stand for lie past V_t, where nothing is counted or stored.)
   const int t16 = active ? t16_own : n_wtiles * 4 - NW;
   const int row0 = m_block * (MT * 16);
   // fragment (16-column tile t, step ks) sits at 16-byte unit (t/4) * packed_tile_units(nks) + (ks * 4 + t%4) * 64 + lane
-  const uint4* wp = Wp + (int64_t)(t16 / 4) * packed_tile_units(nks) + (t16 % 4) * 64 + lane;
+  constexpr bool kOneTile = 4 % NW == 0;               // all fragments of a step lie in one 64-column tile, back to back
+  const uint4* wp[kOneTile ? 1 : NW];
+#pragma unroll
+  for (int nw = 0; nw < (kOneTile ? 1 : NW); ++nw) {
+    const int t = min(uniform(t16) + nw, n_wtiles * 4 - 1);
+    wp[nw] = Wp + (int64_t)(t / 4) * packed_tile_units(nks) + (t % 4) * 64 + lane;
+  }
 
   // Swizzle key of a row: the 16-byte chunks of a row are XORed with the low bits of the row index (measured: with
   // 128-byte rows, folding bit 3 of the row into the key as well stalls 46 % of the LDS cycles on bank conflicts,
@@ -357,7 +370,8 @@ __global__ __launch_bounds__(WPG * 64) void lmhead_bf16_wide_kernel(const uint16
     }
   };
   auto ring = [&](int s) -> uint4* {
-    return (s == 0 ? sW0 : s == 1 ? sW1 : s == 2 ? sW2 : s == 3 ? sW3 : s == 4 ? sW4 : sW5) + wave * (NW * 64);
+    return (s == 0 ? sW0 : s == 1 ? sW1 : s == 2 ? sW2 : s == 3 ? sW3 : s == 4 ? sW4 : s == 5 ? sW5 : s == 6 ? sW6 : sW7) +
+           wave * (NW * 64);
   };
   // fetch the fragments of step kf into this wavefront's part of ring array s
   // With a single M-block every weight is read exactly once by the whole launch: those loads are marked nontemporal
@@ -367,8 +381,8 @@ __global__ __launch_bounds__(WPG * 64) void lmhead_bf16_wide_kernel(const uint16
   auto fetch_w = [&](int kf, int s) {
 #pragma unroll
     for (int nw = 0; nw < NW; ++nw)
-      __builtin_amdgcn_global_load_lds((glb_ptr_t)(wp + ((int64_t)kf * 4 + nw) * 64), (lds_ptr_t)(ring(s) + nw * 64), 16,
-                                       0, kWeightPolicy);
+      __builtin_amdgcn_global_load_lds((glb_ptr_t)(kOneTile ? wp[0] + ((int64_t)kf * 4 + nw) * 64 : wp[kOneTile ? 0 : nw] + (int64_t)kf * 256),
+                                       (lds_ptr_t)(ring(s) + nw * 64), 16, 0, kWeightPolicy);
   };
 
   // This workgroup's piece of the draft rows is asked for first: it is reduced while the first weight fragments and the
@@ -556,20 +570,19 @@ __global__ __launch_bounds__(WPG * 64) void lmhead_bf16_wide_kernel(const uint16
   // other M-blocks of the column tile are about to find in L2 (measured at 160 rows: 242 against 253 us per step).  With
   // one M-block nothing in L2 is worth keeping, and plain stores were measured 1 % faster (144 rows: 205 against 207 us).
   float* patch = sPatch[wave];
-  constexpr int kVecPerRow = NW * 4;                   // float4 per patch row
-  constexpr int kIters = 16 * kVecPerRow / 64;
+  auto store_tiles = [&](auto first_tile, auto n_tiles, int mt) {
+    constexpr int nw0 = decltype(first_tile)::value, kTiles = decltype(n_tiles)::value;
+    constexpr int kVecPerRow = kTiles * 4;               // float4 per patch row
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt) {
+    for (int nw = 0; nw < kTiles; ++nw)
+      *reinterpret_cast<f32x4*>(&patch[(lane & 15) * kPatchRow + nw * 16 + 4 * (lane >> 4)]) = acc[mt][nw0 + nw];
 #pragma unroll
-    for (int nw = 0; nw < NW; ++nw)
-      *reinterpret_cast<f32x4*>(&patch[(lane & 15) * kPatchRow + nw * 16 + 4 * (lane >> 4)]) = acc[mt][nw];
-#pragma unroll
-    for (int i = 0; i < kIters; ++i) {
+    for (int i = 0; i < kTiles; ++i) {
       const int idx = i * 64 + lane;
       const int r = idx / kVecPerRow, c4 = idx % kVecPerRow;
       const f32x4 v = *reinterpret_cast<const f32x4*>(&patch[r * kPatchRow + 4 * c4]);
       const int m = row0 + mt * 16 + r;
-      const int n = t16 * 16 + 4 * c4;
+      const int n = (t16 + nw0) * 16 + 4 * c4;
       if (m < M) {
         float* dst = Z + (int64_t)m * ldz + n;
         if (vec_store && n + 3 < V_t) {
@@ -582,6 +595,12 @@ __global__ __launch_bounds__(WPG * 64) void lmhead_bf16_wide_kernel(const uint16
         }
       }
     }
+  };
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    store_tiles(std::integral_constant<int, 0>(), std::integral_constant<int, kPatchNW>(), mt);
+    if constexpr (NW > kPatchNW)
+      store_tiles(std::integral_constant<int, kPatchNW>(), std::integral_constant<int, NW - kPatchNW>(), mt);
   }
 }
 
@@ -798,9 +817,8 @@ hipError_t launch_f32(const float* H, int M, int d, const float* Wp, float* Z, i
   return hipGetLastError();
 }
 
-// Rows above which an M-block is split: up to 11 row tiles run as one block that streams every weight once (9 with
-// either wavefront width, 10 and 11 only with 64 columns per wavefront, whose accumulators just fit).  Measured at 160 /
-// 176 rows: 217 / 225 us per step as one block against 244 / 246 us as two.
+// Rows above which an M-block is split: up to 11 row tiles run as one block that streams every weight once.  Measured at
+// 160 / 176 rows (d = 4096, V_t = 128256): 217 / 225 us per step as one block against 244 / 246 us as two.
 constexpr int kSingleBlockRows = 176;
 
 // Rough duration of an LM-head launch: the weights stream at 6 TB/s or the product runs at 1 PFLOP/s, whichever is longer.
@@ -892,20 +910,27 @@ hipError_t launch_pack_w_bf16(const uint16_t* W, int d, int V_t, uint16_t* Wp, i
   return hipGetLastError();
 }
 
-// Columns per workgroup of the wide kernels.  A single M-block streams every weight once, bound by HBM, and what a
-// workgroup does outside its main loop (first loads, row statistics, stores: about 12 us) is time its CU does not
-// stream; with one workgroup per CU the launch runs in rounds, and a round costs its stream time whether or not all CUs
-// take part.  512 columns per workgroup halve the rounds where that lets the launch fit into fewer, e.g. one round of
-// 251 workgroups instead of two of 256-column ones on 256 CUs for a 128256-column head (measured: 175 against 196 us).
+// Columns per workgroup of the wide kernels.  A single M-block streams every weight once, bound by HBM, one workgroup per
+// CU: the launch runs in rounds, a round costs its stream time whether or not all CUs take part, and what a workgroup
+// does outside its main loop (first loads, row statistics, stores: about 12 us) is time its CU does not stream.  So the
+// width is the one whose rounds stream the fewest columns, 40 more counted per round: up to 32768 columns run as one round
+// of 128-column workgroups, up to 65536 of 256, and so on.  Measured on 256 CUs, us per step at 24 / 80 / 128 rows:
+//   V_t = 32000, d = 4096:  128 columns 62 / 74 / 86, 256: 75 / 87 / 100 (125 workgroups)
+//   V_t = 80000, d = 4096:  384 columns 123 / 136 / 149, 256: 144 / 164 / 196 (two rounds), 512: 132 / 150 / 165
+//   V_t = 152064, d = 3584: 640 columns 191 / 204 / 223, 256: 221 / 244 / 278 (three rounds), 384: 214 / 237 / 255 (two)
+// 80 columns per wavefront leave accumulators for 8 row tiles (9 spill: 590 us).  Workgroups of 128 columns are taken in a
+// single round only: in several they lose to every other width, and a row would have more than 256 partials.
 int lmhead_bf16_tile_cols(int M, int Vp, int n_cu) {
   if (M > kSingleBlockRows) return tall_plan(M).wide ? 512 : 256;
-  if (M > 144) return 512;             // 10 or 11 row tiles in one block: only the 64-column wavefronts hold them
   if (M <= 16 || n_cu < 1) return 256;
-  const int tiles256 = Vp / 256, tiles512 = ceil_div(Vp, 512);
-  constexpr int kOutsideLoop = 40;                    // per round, in units of columns streamed
-  const int cost256 = ceil_div(tiles256, n_cu) * (256 + kOutsideLoop);
-  const int cost512 = ceil_div(tiles512, n_cu) * (512 + kOutsideLoop);
-  return cost512 < cost256 ? 512 : 256;
+  constexpr int kOutsideLoop = 40;
+  int best = 256, best_cost = ceil_div(ceil_div(Vp, 256), n_cu) * (256 + kOutsideLoop);
+  for (int cols : {128, 384, 512, 640}) {
+    if ((cols == 128 && Vp > cols * n_cu) || (cols == 640 && M > 128)) continue;
+    const int cost = ceil_div(ceil_div(Vp, cols), n_cu) * (cols + kOutsideLoop);
+    if (cost < best_cost) { best = cols; best_cost = cost; }
+  }
+  return best;
 }
 
 int lmhead_bf16_fused_partials(int M, int Vp, int n_cu) {
@@ -923,16 +948,22 @@ int lmhead_bf16_draft_workers(int M, int Vp, int B, int K, int n_cu) {
 }
 
 // Whether the LM-head launch should host the draft side (the draft rows' statistics, the drafted ids' lookups, and the
-// target rows' softmax partials from its epilogue).  With a single M-block the launch is bound by the weight stream
-// and a multiplying workgroup's piece of a draft row costs it about the 3 us that it would otherwise wait for its first
-// loads: hosted when a workgroup gets at most two rows.  With several M-blocks front workgroups take the draft side:
-// hosted when they are done within three quarters of the launch (their bytes at the rate above, 15 us per round of
-// lookups).
+// target rows' softmax partials from its epilogue).  With a single M-block hosting spares the statistics launch and its
+// pass over the logits (about 5 TB/s), and costs a workgroup its piece of a draft row and the row statistics of its tile.
+// Hosted where a piece is at most half a row, or where the pass over the logits would take 9 us per row of a workgroup.
+// Heads of 128-column workgroups are never hosted: their logits are few and their epilogues many.  Measured, us per step
+// hosted / separate: V_t = 128256, 128 rows 82 / 92 (d = 1024); V_t = 48000, 96 rows 98 / 101, 128 rows (whole draft rows)
+// 117 / 108; V_t = 60000, 168 rows 102 / 87 (d = 2048); V_t = 32000, 80 rows 74 / 72; V_t = 8000, 80 rows 64 / 58.
+// With several M-blocks front workgroups take the draft side: hosted when they are done within three quarters of the
+// launch (their bytes at the rate above, 15 us per round of lookups).
 bool lmhead_bf16_hosts_draft_side(int M, int d, int Vp, int B, int K, int V_d, int n_cu) {
   if (B < 1 || B > kFusedMaxB || K < 1) return false;
   const int workers = lmhead_bf16_draft_workers(M, Vp, B, K, n_cu);
   if (workers == 0) return false;
-  if (M <= kSingleBlockRows) return K <= 2 * workers;
+  if (M <= kSingleBlockRows) {
+    if (lmhead_bf16_tile_cols(M, Vp, n_cu) < 256) return false;
+    return 2 * K <= workers || 4.0 * M * Vp / 5.0e6 >= 9.0 * ceil_div(K, workers);
+  }
   const int n_front = workers / kWideWaves;
   const double front_us = 2.0 * K * (double)V_d / (n_front * kFrontBytesPerUs) + ceil_div(B, 4 * n_front) * 15.0;
   return front_us <= 0.75 * lmhead_launch_us(M, d, Vp);
@@ -955,19 +986,21 @@ hipError_t launch_lmhead_bf16(const uint16_t* H, int M, int d, const uint16_t* W
                        reinterpret_cast<const uint4*>(Wp), nks, Z, V_t, ldz);
     return hipGetLastError();
   }
-  if (tiles == 10) return launch_wide<10, 2, 8, 64, 4, true>(H, M, d, Wp, Kp, Vp, Z, V_t, ldz, zeros, fs, draft_side, n_cu, stream);
-  if (tiles == 11) return launch_wide<11, 2, 8, 64, 4, true>(H, M, d, Wp, Kp, Vp, Z, V_t, ldz, zeros, fs, draft_side, n_cu, stream);
-  if (tiles <= 9 && lmhead_bf16_tile_cols(M, Vp, n_cu) == 512) {
-    // wavefronts of 64 columns, hidden slices of 64 columns and a ring two (twice as long) steps deep: the same bytes
-    // in flight per CU as the 256-column shape
-    if (tiles <= 4) return launch_wide<4, 2, 8, 64, 4, true>(H, M, d, Wp, Kp, Vp, Z, V_t, ldz, zeros, fs, draft_side, n_cu, stream);
-    if (tiles <= 6) return launch_wide<6, 2, 8, 64, 4, true>(H, M, d, Wp, Kp, Vp, Z, V_t, ldz, zeros, fs, draft_side, n_cu, stream);
-    return launch_wide<9, 2, 8, 64, 4, true>(H, M, d, Wp, Kp, Vp, Z, V_t, ldz, zeros, fs, draft_side, n_cu, stream);
+  if (M <= kSingleBlockRows) {
+    // 64 to 96 KB of weights in flight per workgroup at every width; hidden slices of 64 columns where LDS holds no 128
+    const int tile_cols = lmhead_bf16_tile_cols(M, Vp, n_cu);
+#define OT_WIDE(cols, mt, pf, kc)                                                                                        \
+  if (tile_cols == cols && tiles <= mt)                                                                                  \
+    return launch_wide<mt, pf, 8, kc, cols / 128, true>(H, M, d, Wp, Kp, Vp, Z, V_t, ldz, zeros, fs, draft_side, n_cu, stream)
+    OT_WIDE(128, 2, 8, 64); OT_WIDE(128, 4, 8, 64); OT_WIDE(128, 6, 8, 64); OT_WIDE(128, 9, 8, 64); OT_WIDE(128, 11, 8, 64);
+    OT_WIDE(256, 2, 4, 128); OT_WIDE(256, 4, 4, 128); OT_WIDE(256, 6, 4, 128); OT_WIDE(256, 9, 4, 128); OT_WIDE(256, 11, 4, 64);
+    OT_WIDE(384, 2, 4, 64); OT_WIDE(384, 4, 4, 64); OT_WIDE(384, 6, 4, 64); OT_WIDE(384, 9, 2, 64); OT_WIDE(384, 11, 2, 64);
+    OT_WIDE(512, 2, 2, 64); OT_WIDE(512, 4, 2, 64); OT_WIDE(512, 6, 2, 64); OT_WIDE(512, 9, 2, 64); OT_WIDE(512, 10, 2, 64);
+    OT_WIDE(512, 11, 2, 64);
+    OT_WIDE(640, 2, 2, 64); OT_WIDE(640, 4, 2, 64); OT_WIDE(640, 6, 2, 64); OT_WIDE(640, 8, 2, 64);
+#undef OT_WIDE
+    return hipErrorInvalidValue;
   }
-  if (tiles <= 2) return launch_wide<2, 4, 8, 128, 2, true>(H, M, d, Wp, Kp, Vp, Z, V_t, ldz, zeros, fs, draft_side, n_cu, stream);
-  if (tiles <= 4) return launch_wide<4, 4, 8, 128, 2, true>(H, M, d, Wp, Kp, Vp, Z, V_t, ldz, zeros, fs, draft_side, n_cu, stream);
-  if (tiles <= 6) return launch_wide<6, 4, 8, 128, 2, true>(H, M, d, Wp, Kp, Vp, Z, V_t, ldz, zeros, fs, draft_side, n_cu, stream);
-  if (tiles <= 9) return launch_wide<9, 4, 8, 128, 2, true>(H, M, d, Wp, Kp, Vp, Z, V_t, ldz, zeros, fs, draft_side, n_cu, stream);
   // More than 176 rows run as several M-blocks per column tile (tall_plan).  Heights above 144 rows use hidden
   // slices of 64 columns and a weight ring two steps deep to fit in LDS.
   const TallPlan plan = tall_plan(M);

@@ -1,0 +1,36 @@
+"""The bf16 LM head with one M-block at every width of its workgroups (128 to 640 columns, chosen by the vocabulary so that
+256 compute units run few full rounds), at the row counts where its kernel changes, ragged ends of the vocabulary and of the
+hidden dimension included: logits against float64, and the row statistics that its epilogue leaves."""
+import numpy as np
+import pytest
+
+from test_gpu_parity import _imports, _say
+from workloads import CaseSpec, make_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("V_t", [32768, 32769, 66001, 98500, 131073, 152064])
+@pytest.mark.parametrize("M", [17, 33, 65, 97, 128, 129, 145, 176])
+def test_widths(M, V_t):
+    ov, ot, Verifier, parity = _imports()
+    ks = [min(40, M - r) - 1 for r in range(0, M, 40)]
+    temps = [[1.0, 0.5, 0.0, 2.0][i % 4] for i in range(len(ks))]
+    case = make_case(CaseSpec(name=f"width_{M}x{V_t}", dtype="bf16", d=40, V_t=V_t, V_d=64, k=ks, temperature=temps, n_direct=32,
+                              data_seed=M + V_t, philox_seed=1))
+    assert case.M == M
+    Z = ov.lm_head_logits(case.hidden, case.W, "bf16")
+    for side in (ot.OT_DRAFT_SIDE_IN_LM_HEAD, ot.OT_DRAFT_SIDE_SEPARATE):
+        _say(f"head width case M={M} V_t={V_t} draft_side={side}")
+        v = Verifier.for_case(case, draft_side=side)
+        try:
+            v.step(v.upload(case))
+            ws = v.workspace(case.M, case.K, with_logits=True)
+        finally:
+            v.close()
+        # 40 products per logit: one rounding of 2^-24 each of sums that stay below 4 times their spread
+        np.testing.assert_allclose(ws["logits"], Z, rtol=1e-5, atol=5e-6)
+        got = ws["logits"].astype(np.float64)
+        assert np.array_equal(ws["row_max"], ws["logits"].max(axis=1)) and np.array_equal(ws["row_argmax"], got.argmax(axis=1))
+        T = np.repeat([t or 1.0 for t in temps], [k + 1 for k in ks])[:, None]
+        np.testing.assert_allclose(ws["row_sumexp"], np.exp((got - got.max(axis=1, keepdims=True)) / T).sum(axis=1), rtol=2e-6)
