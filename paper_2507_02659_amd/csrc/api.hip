@@ -221,16 +221,16 @@ static int step_impl(ot_ctx* ctx, ot_ngram_cache* cache, const ot_step_in* in, c
       // Where its kernel supports it, the LM-head launch leaves per-tile softmax partials of the target rows (no second
       // pass over the logits) and hosts the draft side of the step (the draft rows' statistics in pieces, the drafted
       // ids' lookups): what follows it is then one launch that merges both, walks the windows, tests and draws.
-      const bool supported = lmhead_bf16_draft_workers(M, ctx->Vp, in->B, K, ctx->n_cu) > 0 && K >= 1 && in->B <= kFusedMaxB;
+      const bool supported = lmhead_bf16_draft_workers(M, ctx->d, ctx->Vp, in->B, K, ctx->n_cu) > 0 && K >= 1 && in->B <= kFusedMaxB;
       const bool host_it = supported && (ctx->draft_side == OT_DRAFT_SIDE_IN_LM_HEAD ||
                                          (ctx->draft_side == OT_DRAFT_SIDE_AUTO &&
                                           lmhead_bf16_hosts_draft_side(M, ctx->d, ctx->Vp, in->B, K, ctx->V_d, ctx->n_cu)));
-      const int nfine = host_it ? lmhead_bf16_fused_partials(M, ctx->Vp, ctx->n_cu) : 0;
+      const int nfine = host_it ? lmhead_bf16_fused_partials(M, ctx->d, ctx->Vp, ctx->n_cu) : 0;
       if (nfine > 0) {
         a.fused.row_off = in->row_off; a.fused.temperature = in->temperature; a.fused.B = in->B; a.fused.nfine = nfine;
         a.fused.part = ctx->fpart;
         a.hosted = 1;
-        a.plan = make_piece_plan(lmhead_bf16_draft_workers(M, ctx->Vp, in->B, K, ctx->n_cu), K);
+        a.plan = make_piece_plan(lmhead_bf16_draft_workers(M, ctx->d, ctx->Vp, in->B, K, ctx->n_cu), K);
       }
       e = launch_lmhead_bf16(static_cast<const uint16_t*>(in->hidden), M, ctx->d, ctx->Wp, ctx->Kp, ctx->Vp, ctx->Z,
                              ctx->V_t, a.ldz, ctx->zeros, &a.fused, a.hosted ? &a : nullptr, ctx->n_cu, st);

@@ -826,37 +826,35 @@ double lmhead_launch_us(int M, int d, int Vp) { return std::max(2.0 * d * (doubl
 
 // How more than 176 rows run: as several M-blocks per column tile (their weight streams meet in one L2), of `tiles` row
 // tiles each, by the kernel whose wavefronts own 32 columns or by the one whose wavefronts own 64 (`wide`).  That regime
-// is bound by the L2 -> LDS traffic and by LDS reads, and the time of an M-block was measured to grow almost in
-// proportion to its height (about 1.3 row tiles of fixed cost per block: 144, 256, 288 rows take 150, 251, 284 us at
-// d = 4096, V_t = 128256), so the plan that minimises blocks x (1.3 + row tiles) is taken: mostly the height that pads
-// least.  With 64 columns per wavefront a hidden fragment read from LDS feeds four MFMAs instead of two and the same
-// cost comes out about 7 % lower, but the accumulators leave room for 11 row tiles at most.  Measured, us per step,
-// best 32-column plan against the 64-column one: 176 rows 264 / 244, 320 rows 417 / 386, 352 rows 461 / 408,
-// 425 rows 538 / 507, 432 rows 517 / 493, 576 rows 677 / 663, 1024 rows 1118 / 1076; 384 rows 468 / 519 (stays).
-struct TallPlan { int tiles; bool wide; };
-TallPlan tall_plan(int M) {
-  TallPlan best{9, false};
-  int best_cost = 100 * ceil_div(M, 144) * (13 + 10 * 9);
-  for (int mt : {10, 12, 14, 16, 18}) {
-    const int cost = 100 * ceil_div(M, 16 * mt) * (13 + 10 * mt);
-    if (cost <= best_cost) { best_cost = cost; best = TallPlan{mt, false}; }
-  }
-  for (int mt : {9, 10, 11}) {
-    const int cost = 93 * ceil_div(M, 16 * mt) * (13 + 10 * mt);
-    if (cost < best_cost) { best_cost = cost; best = TallPlan{mt, true}; }
-  }
+// is bound by the L2 -> LDS traffic, LDS reads and the card's power, and the launch runs in rounds of one workgroup per
+// compute unit.  The estimate, fitted to d = 3584 heads of 152064 columns (us per round: 4 tiles 44, 6: 58, 9: 79,
+// 12: 100, 16: 135): 12 us outside the loop plus 4 + 7 per row tile in it for 256 columns; with 64 columns per wavefront a
+// hidden fragment read from LDS feeds four MFMAs instead of two and a column costs 7 % less, but the accumulators leave
+// room for 11 row tiles at most.  A last round that is partly empty costs about half of what it leaves idle (the clock of
+// the busy part rises).  Measured, us per step, against blocks chosen by their height alone: 192 / 512 rows on
+// V_t = 8000 (d = 4096) 52 / 62 against 99 / 145, on V_t = 32000 81 / 155 against 103 / 175; 512 rows on V_t = 50000
+// (d = 2048) 161 against 208, 1024 rows on V_t = 128256 1018 against 1076.
+struct TallPlan { int tiles; bool wide; double per_cu, round_us; };   // workgroups per compute unit, time of a round
+double tall_rounds(double per_cu) { return std::max(1.0, 0.5 * (per_cu + std::ceil(per_cu))); }
+TallPlan tall_plan(int M, int d, int Vp, int n_cu) {
+  TallPlan best{9, false, 1.0, INFINITY};
+  auto consider = [&](int mt, int cols, double outside, double per_column) {
+    const TallPlan p{mt, cols == 512, (double)ceil_div(Vp, cols) * ceil_div(M, 16 * mt) / std::max(1, n_cu),
+                     outside + d / 3584.0 * (4 + 7 * mt) * per_column * cols / 256};
+    if (tall_rounds(p.per_cu) * p.round_us < tall_rounds(best.per_cu) * best.round_us) best = p;
+  };
+  for (int mt : {4, 6, 9, 10, 12, 14, 16, 18}) consider(mt, 256, 12.0, 1.0);
+  for (int mt : {9, 10, 11}) consider(mt, 512, 18.0, 0.93);
   return best;
 }
 
 // Front workgroups of a launch that hosts the draft side with several M-blocks: one per four sequences (the lookups go
 // four sequences at a time), a multiple of 8 (the XCD mapping of the multiplying workgroups holds), 8 to 64.  A
-// workgroup that only reads, next to the multiplying ones, draws 5 to 10 GB/s however much it keeps in flight (measured:
-// 8 of them need about 230 us for the 9.2 MB of 144 draft rows, 64 of them 35 us for 23 MB), so the compute-unit time
-// the draft rows cost is given by their bytes; few front workgroups keep that time inside the slack of the last round
-// of multiplying workgroups, many push some of those into a round of their own (160 rows, 501 multiplying workgroups in
-// two rounds on 256 CUs: 64 front workgroups 257 us per step, separate launches 243).  0: one M-block, where the
-// multiplying workgroups take the draft side themselves.
-constexpr double kFrontBytesPerUs = 5e3;     // one front workgroup, next to the multiplying ones
+// workgroup that only reads, next to the multiplying ones, draws about 8 GB/s however much it keeps in flight (measured:
+// 8 of them need 280 us for the 18.4 MB of 288 draft rows), so the compute-unit time the draft rows cost is given by
+// their bytes; few front workgroups keep that time inside the slack of the last round of multiplying workgroups, many push
+// some of those into a round of their own.  0: one M-block, where the multiplying workgroups take the draft side themselves.
+constexpr double kFrontBytesPerUs = 8e3;     // one front workgroup, next to the multiplying ones
 int lmhead_bf16_front_workgroups(int M, int B) {
   if (M <= kSingleBlockRows) return 0;
   return std::min(64, std::max(8, ceil_div(ceil_div(B, 4), 8) * 8));
@@ -920,8 +918,8 @@ hipError_t launch_pack_w_bf16(const uint16_t* W, int d, int V_t, uint16_t* Wp, i
 //   V_t = 152064, d = 3584: 640 columns 191 / 204 / 223, 256: 221 / 244 / 278 (three rounds), 384: 214 / 237 / 255 (two)
 // 80 columns per wavefront leave accumulators for 8 row tiles (9 spill: 590 us).  Workgroups of 128 columns are taken in a
 // single round only: in several they lose to every other width, and a row would have more than 256 partials.
-int lmhead_bf16_tile_cols(int M, int Vp, int n_cu) {
-  if (M > kSingleBlockRows) return tall_plan(M).wide ? 512 : 256;
+int lmhead_bf16_tile_cols(int M, int d, int Vp, int n_cu) {
+  if (M > kSingleBlockRows) return tall_plan(M, d, Vp, n_cu).wide ? 512 : 256;
   if (M <= 16 || n_cu < 1) return 256;
   constexpr int kOutsideLoop = 40;
   int best = 256, best_cost = ceil_div(ceil_div(Vp, 256), n_cu) * (256 + kOutsideLoop);
@@ -933,16 +931,16 @@ int lmhead_bf16_tile_cols(int M, int Vp, int n_cu) {
   return best;
 }
 
-int lmhead_bf16_fused_partials(int M, int Vp, int n_cu) {
+int lmhead_bf16_fused_partials(int M, int d, int Vp, int n_cu) {
   if (M <= 16) return 0;             // the skinny kernel does not fuse
-  return ceil_div(Vp, lmhead_bf16_tile_cols(M, Vp, n_cu));
+  return ceil_div(Vp, lmhead_bf16_tile_cols(M, d, Vp, n_cu));
 }
 
 // Workgroups of launch_lmhead_bf16 that share the draft rows when the launch hosts the draft side: the multiplying
 // ones with a single M-block (their number: one per tile of columns), the front ones otherwise.  0: the shape leaves no
 // partials and hosts nothing.
-int lmhead_bf16_draft_workers(int M, int Vp, int B, int K, int n_cu) {
-  const int nfine = lmhead_bf16_fused_partials(M, Vp, n_cu);
+int lmhead_bf16_draft_workers(int M, int d, int Vp, int B, int K, int n_cu) {
+  const int nfine = lmhead_bf16_fused_partials(M, d, Vp, n_cu);
   if (nfine == 0) return 0;
   return M > kSingleBlockRows ? lmhead_bf16_front_workgroups(M, B) * kWideWaves : nfine;
 }
@@ -954,19 +952,37 @@ int lmhead_bf16_draft_workers(int M, int Vp, int B, int K, int n_cu) {
 // Heads of 128-column workgroups are never hosted: their logits are few and their epilogues many.  Measured, us per step
 // hosted / separate: V_t = 128256, 128 rows 82 / 92 (d = 1024); V_t = 48000, 96 rows 98 / 101, 128 rows (whole draft rows)
 // 117 / 108; V_t = 60000, 168 rows 102 / 87 (d = 2048); V_t = 32000, 80 rows 74 / 72; V_t = 8000, 80 rows 64 / 58.
-// With several M-blocks front workgroups take the draft side: hosted when they are done within three quarters of the
-// launch (their bytes at the rate above, 15 us per round of lookups).
+// With several M-blocks front workgroups take the draft side: hosted where the launch, with them in its rounds, is
+// estimated to end before a launch without them and the statistics pass.  They cost most where they push multiplying
+// workgroups into a round more: V_t = 128256, 320 rows (502 + 16 workgroups) 412 us hosted, 365 separate; 152064, 320 rows
+// 399 / 424; 1024 rows 1057 / 1104.
 bool lmhead_bf16_hosts_draft_side(int M, int d, int Vp, int B, int K, int V_d, int n_cu) {
   if (B < 1 || B > kFusedMaxB || K < 1) return false;
-  const int workers = lmhead_bf16_draft_workers(M, Vp, B, K, n_cu);
+  const int workers = lmhead_bf16_draft_workers(M, d, Vp, B, K, n_cu);
   if (workers == 0) return false;
   if (M <= kSingleBlockRows) {
-    if (lmhead_bf16_tile_cols(M, Vp, n_cu) < 256) return false;
+    if (lmhead_bf16_tile_cols(M, d, Vp, n_cu) < 256) return false;
     return 2 * K <= workers || 4.0 * M * Vp / 5.0e6 >= 9.0 * ceil_div(K, workers);
   }
   const int n_front = workers / kWideWaves;
+  const TallPlan plan = tall_plan(M, d, Vp, n_cu);
   const double front_us = 2.0 * K * (double)V_d / (n_front * kFrontBytesPerUs) + ceil_div(B, 4 * n_front) * 15.0;
-  return front_us <= 0.75 * lmhead_launch_us(M, d, Vp);
+  if (n_front >= n_cu) return false;
+  // The launch ends at the first moment by which n_front compute units that come free after front_us and the others have
+  // had room for all workgroups, each kStatsUs longer for the row statistics; half of what stays idle counts, as above.
+  constexpr double kStatsUs = 5.0;
+  const double t = plan.round_us + kStatsUs, n = plan.per_cu * n_cu;
+  const double rounds_alone = std::ceil(n / (n_cu - n_front) - 1e-9);          // the front's compute units never join
+  double end = rounds_alone * t;
+  for (int front_rounds = 1; front_us + front_rounds * t < end; ++front_rounds) {
+    const double at = front_us + front_rounds * t;
+    if ((n_cu - n_front) * std::floor(at / t) + n_front * front_rounds >= n) end = at;
+  }
+  for (double at = t; at < end; at += t)
+    if ((n_cu - n_front) * std::round(at / t) + n_front * std::floor(std::max(0.0, at - front_us) / t) >= n) end = at;
+  const double hosted = std::max(front_us, 0.5 * (end + (n * t + n_front * front_us) / n_cu));
+  const double separate = tall_rounds(plan.per_cu) * plan.round_us + 4.0 + (4.0 * M * Vp + 2.0 * K * (double)V_d) / 5.0e6;
+  return hosted < separate;
 }
 
 hipError_t launch_lmhead_bf16(const uint16_t* H, int M, int d, const uint16_t* Wp, int Kp, int Vp, float* Z, int V_t,
@@ -976,7 +992,7 @@ hipError_t launch_lmhead_bf16(const uint16_t* H, int M, int d, const uint16_t* W
   const int tiles = ceil_div(M, 16);
   FusedStats fs{};
   if (fused && fused->part) {
-    if (fused->nfine != lmhead_bf16_fused_partials(M, Vp, n_cu) || fused->nfine == 0 || fused->B < 1 || fused->B > kFusedMaxB)
+    if (fused->nfine != lmhead_bf16_fused_partials(M, d, Vp, n_cu) || fused->nfine == 0 || fused->B < 1 || fused->B > kFusedMaxB)
       return hipErrorInvalidValue;
     fs = *fused;
   }
@@ -988,7 +1004,7 @@ hipError_t launch_lmhead_bf16(const uint16_t* H, int M, int d, const uint16_t* W
   }
   if (M <= kSingleBlockRows) {
     // 64 to 96 KB of weights in flight per workgroup at every width; hidden slices of 64 columns where LDS holds no 128
-    const int tile_cols = lmhead_bf16_tile_cols(M, Vp, n_cu);
+    const int tile_cols = lmhead_bf16_tile_cols(M, d, Vp, n_cu);
 #define OT_WIDE(cols, mt, pf, kc)                                                                                        \
   if (tile_cols == cols && tiles <= mt)                                                                                  \
     return launch_wide<mt, pf, 8, kc, cols / 128, true>(H, M, d, Wp, Kp, Vp, Z, V_t, ldz, zeros, fs, draft_side, n_cu, stream)
@@ -1003,7 +1019,7 @@ hipError_t launch_lmhead_bf16(const uint16_t* H, int M, int d, const uint16_t* W
   }
   // More than 176 rows run as several M-blocks per column tile (tall_plan).  Heights above 144 rows use hidden
   // slices of 64 columns and a weight ring two steps deep to fit in LDS.
-  const TallPlan plan = tall_plan(M);
+  const TallPlan plan = tall_plan(M, d, Vp, n_cu);
   if (plan.wide) {
     switch (plan.tiles) {
       case 10: return launch_wide<10, 2, 8, 64, 4>(H, M, d, Wp, Kp, Vp, Z, V_t, ldz, zeros, fs, draft_side, n_cu, stream);
@@ -1013,6 +1029,8 @@ hipError_t launch_lmhead_bf16(const uint16_t* H, int M, int d, const uint16_t* W
   }
   const int best_mt = plan.tiles;
   switch (best_mt) {
+    case 4: return launch_wide<4, 4, 8, 128, 2>(H, M, d, Wp, Kp, Vp, Z, V_t, ldz, zeros, fs, draft_side, n_cu, stream);
+    case 6: return launch_wide<6, 4, 8, 128, 2>(H, M, d, Wp, Kp, Vp, Z, V_t, ldz, zeros, fs, draft_side, n_cu, stream);
     case 10: return launch_wide<10, 2, 8, 64, 2>(H, M, d, Wp, Kp, Vp, Z, V_t, ldz, zeros, fs, draft_side, n_cu, stream);
     case 12: return launch_wide<12, 2, 8, 64, 2>(H, M, d, Wp, Kp, Vp, Z, V_t, ldz, zeros, fs, draft_side, n_cu, stream);
     case 14: return launch_wide<14, 2, 8, 64, 2>(H, M, d, Wp, Kp, Vp, Z, V_t, ldz, zeros, fs, draft_side, n_cu, stream);

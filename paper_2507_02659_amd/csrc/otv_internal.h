@@ -176,14 +176,14 @@ hipError_t launch_pack_w_bf16(const uint16_t* W, int d, int V_t, uint16_t* Wp, i
 // Partials per row that launch_lmhead_bf16 emits for M rows of a Vp-column (padded) head; 0: that shape runs a
 // kernel without the fused statistics.
 // (n_cu = compute units of the device: the column width of a workgroup is chosen so that the launch takes few rounds.)
-int lmhead_bf16_fused_partials(int M, int Vp, int n_cu);
+int lmhead_bf16_fused_partials(int M, int d, int Vp, int n_cu);
 // Whether a step of this shape lets the LM-head launch host the draft side and emit the partials (else the step runs
 // the statistics and the translation as launches of their own).
 bool lmhead_bf16_hosts_draft_side(int M, int d, int Vp, int B, int K, int V_d, int n_cu);
 // workgroups of launch_lmhead_bf16 that share the draft rows (0: that shape leaves no partials and hosts nothing)
-int lmhead_bf16_draft_workers(int M, int Vp, int B, int K, int n_cu);
+int lmhead_bf16_draft_workers(int M, int d, int Vp, int B, int K, int n_cu);
 // `fused` may be nullptr or have part == nullptr (no statistics); otherwise fused->nfine must be
-// lmhead_bf16_fused_partials(M, Vp, n_cu) > 0 and fused->B <= kFusedMaxB.  With fused statistics and `draft_side` not
+// lmhead_bf16_fused_partials(M, d, Vp, n_cu) > 0 and fused->B <= kFusedMaxB.  With fused statistics and `draft_side` not
 // nullptr, the workgroups of the launch also compute the softmax statistics of the draft rows of *draft_side (one row
 // each, before their main loop) into its drow_* arrays.
 hipError_t launch_lmhead_bf16(const uint16_t* H, int M, int d, const uint16_t* Wp, int Kp, int Vp, float* Z, int V_t,

@@ -1,6 +1,7 @@
-"""The bf16 LM head with one M-block at every width of its workgroups (128 to 640 columns, chosen by the vocabulary so that
+"""The bf16 LM head: with one M-block at every width of its workgroups (128 to 640 columns, chosen by the vocabulary so that
 256 compute units run few full rounds), at the row counts where its kernel changes, ragged ends of the vocabulary and of the
-hidden dimension included: logits against float64, and the row statistics that its epilogue leaves."""
+hidden dimension included, and with several M-blocks at every height and width that the plan can choose: logits against
+float64, and the row statistics that its epilogue leaves."""
 import numpy as np
 import pytest
 
@@ -10,9 +11,7 @@ from workloads import CaseSpec, make_case
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("V_t", [32768, 32769, 66001, 98500, 131073, 152064])
-@pytest.mark.parametrize("M", [17, 33, 65, 97, 128, 129, 145, 176])
-def test_widths(M, V_t):
+def _check(M, V_t):
     ov, ot, Verifier, parity = _imports()
     ks = [min(40, M - r) - 1 for r in range(0, M, 40)]
     temps = [[1.0, 0.5, 0.0, 2.0][i % 4] for i in range(len(ks))]
@@ -34,3 +33,16 @@ def test_widths(M, V_t):
         assert np.array_equal(ws["row_max"], ws["logits"].max(axis=1)) and np.array_equal(ws["row_argmax"], got.argmax(axis=1))
         T = np.repeat([t or 1.0 for t in temps], [k + 1 for k in ks])[:, None]
         np.testing.assert_allclose(ws["row_sumexp"], np.exp((got - got.max(axis=1, keepdims=True)) / T).sum(axis=1), rtol=2e-6)
+
+
+@pytest.mark.parametrize("V_t", [32768, 32769, 66001, 98500, 131073, 152064])
+@pytest.mark.parametrize("M", [17, 33, 65, 97, 128, 129, 145, 176])
+def test_widths(M, V_t):
+    _check(M, V_t)
+
+
+# at d = 40 and 256 compute units: 4, 6, 9, 10 row tiles x 256 columns in several blocks, 12 to 18 in one, 9 to 11 x 512 columns
+@pytest.mark.parametrize("M,V_t", [(177, 1500), (193, 17000), (289, 17001), (433, 17000), (177, 33001), (193, 33000), (225, 33001),
+                                   (257, 33002), (330, 33001), (433, 33000), (512, 33001)])
+def test_several_blocks(M, V_t):
+    _check(M, V_t)
