@@ -11,50 +11,20 @@
 
 namespace otv {
 
-// Merges the chunk partials of up to 64 rows starting at row `first`: 4 threads per row, every 4th chunk each,
-// combined in a fixed order.  Thread 4*r publishes row r's (max, sum, argmax) to LDS and to the workspace.
-__device__ inline void merge_partials(const float* __restrict__ pmax, const double* __restrict__ psum,
-                                      const int32_t* __restrict__ parg, int nch, int first, int n_rows, double invT,
-                                      float* s_mx, double* s_S, int* s_arg, float* g_mx, double* g_S, int32_t* g_arg,
-                                      int local_tid) {
-  const int row = local_tid >> 2, part = local_tid & 3;
-  const bool live = row < n_rows;
-  const int64_t o = (int64_t)(first + (live ? row : 0)) * nch;
-  float mx = -INFINITY;
-  int arg = 0x7FFFFFFF;
-  if (live) {
-    for (int c = part; c < nch; c += 4) {
-      const float m = pmax[o + c];
-      const int ai = parg[o + c];
-      if (m > mx || (m == mx && ai < arg)) { mx = m; arg = ai; }
-    }
-  }
-#pragma unroll
-  for (int off = 1; off <= 2; off <<= 1) {
-    const float om = __shfl_xor(mx, off);
-    const int oa = __shfl_xor(arg, off);
-    if (om > mx || (om == mx && oa < arg)) { mx = om; arg = oa; }
-  }
-  double S = 0.0;
-  if (live) {
-    for (int c = part; c < nch; c += 4) S += psum[o + c] * exp(((double)pmax[o + c] - (double)mx) * invT);
-  }
-  const double s1 = __shfl_xor(S, 1);
-  const double lo = (part & 1) ? s1 + S : S + s1;          // (part0 + part1) or (part2 + part3), same order in both lanes
-  const double s2 = __shfl_xor(lo, 2);
-  const double total = (part & 2) ? s2 + lo : lo + s2;     // (p0 + p1) + (p2 + p3)
-  if (live && part == 0) {
-    s_mx[row] = mx; s_S[row] = total; s_arg[row] = arg;
-    g_mx[first + row] = mx; g_S[first + row] = total; g_arg[first + row] = arg;
-  }
+// exp((x - mx) / T) for x <= mx, by which the sum of a part with maximum x is rescaled to the row's: through the hardware 2^x
+// (exponent scale sc), or in binary64 (exact; wavefront-uniform).
+__device__ __forceinline__ double rescale(float x, float mx, float sc, double invT, bool exact) {
+  return exact ? exp(((double)x - (double)mx) * invT) : (double)__builtin_amdgcn_exp2f((x - mx) * sc);
 }
 
-// Lanes of a wavefront hold running statistics r of parts of one row (exponent scale sc): merges them in a fixed order; lane 0 publishes the row's (max, sum, argmax) to LDS slot `at` and, if asked, to the workspace.
-__device__ inline void wave_publish_row(const RunStat& r, float sc, int row, int lane, float* s_mx, double* s_S,
-                                        int* s_arg, int at, bool to_workspace, float* g_mx, double* g_S, int32_t* g_arg) {
+// Lanes of a wavefront hold running statistics r of parts of one row (exponent scale sc): merges them in a fixed order; lane 0
+// publishes the row's (max, sum, argmax) to LDS slot `at` and, if asked, to the workspace.
+__device__ __forceinline__ void wave_publish_row(const RunStat& r, float sc, int row, int lane, float* s_mx, double* s_S,
+                                        int* s_arg, int at, bool to_workspace, float* g_mx, double* g_S, int32_t* g_arg,
+                                        double invT = 1.0, bool exact = false) {
   const float mx = wave_max(r.mx);
   const int arg = wave_min(r.mx == mx ? r.arg : 0x7FFFFFFF);
-  const double S = wave_sum(r.mx == -INFINITY ? 0.0 : r.sum * (double)__builtin_amdgcn_exp2f((r.mx - mx) * sc));
+  const double S = wave_sum(r.mx == -INFINITY ? 0.0 : r.sum * rescale(r.mx, mx, sc, invT, exact));
   if (lane == 0) {
     s_mx[at] = mx; s_S[at] = S; s_arg[at] = arg;
     if (to_workspace) { g_mx[row] = mx; g_S[row] = S; g_arg[row] = arg; }
@@ -104,11 +74,11 @@ __device__ inline void merge_fused_row(const Partial* __restrict__ part, int nfi
 }
 
 // The same for the chunk partials of the statistics launch (three arrays, nch entries per row): lane c takes chunks
-// c, c + 64, ...
-__device__ inline void merge_chunk_row(const float* __restrict__ pmax, const double* __restrict__ psum,
+// c, c + 64, ...  exact: as above; steps of many sequences, which no single chain of instructions bounds, ask for it.
+__device__ __forceinline__ void merge_chunk_row(const float* __restrict__ pmax, const double* __restrict__ psum,
                                        const int32_t* __restrict__ parg, int nch, int row, double invT, int lane,
                                        float* s_mx, double* s_S, int* s_arg, int at, bool to_workspace, float* g_mx,
-                                       double* g_S, int32_t* g_arg) {
+                                       double* g_S, int32_t* g_arg, bool exact) {
   const int64_t o = (int64_t)row * nch;
   const float sc = (float)invT * kLog2eF;
   RunStat r;
@@ -117,18 +87,20 @@ __device__ inline void merge_chunk_row(const float* __restrict__ pmax, const dou
     const int ai = parg[o + c];
     const double sum = psum[o + c];
     if (m > r.mx || (m == r.mx && ai < r.arg)) {
-      r.sum *= (double)__builtin_amdgcn_exp2f((r.mx - m) * sc);        // r.mx = -inf: the sum is 0 and stays 0
+      if (r.mx != -INFINITY) r.sum *= rescale(r.mx, m, sc, invT, exact);
       r.mx = m; r.arg = ai;
     }
-    if (m != -INFINITY) r.sum += sum * (double)__builtin_amdgcn_exp2f((m - r.mx) * sc);
+    if (m != -INFINITY) r.sum += sum * rescale(m, r.mx, sc, invT, exact);
   }
-  wave_publish_row(r, sc, row, lane, s_mx, s_S, s_arg, at, to_workspace, g_mx, g_S, g_arg);
+  wave_publish_row(r, sc, row, lane, s_mx, s_S, s_arg, at, to_workspace, g_mx, g_S, g_arg, invT, exact);
 }
 
 // Statistics of draft row q from the chunk partials of the statistics launch (ascending chunks): lane-local.
-__device__ inline void merge_draft_chunks(const StepArgs& a, int q, float Td, float* out_mx, double* out_S, int* out_arg) {
+__device__ __forceinline__ void merge_draft_chunks(const StepArgs& a, int q, float Td, float* out_mx, double* out_S, int* out_arg,
+                                          bool exact) {
   const int64_t o = (int64_t)q * a.nchd;
   const float sc = Td > 0.f ? kLog2eF / Td : kLog2eF;
+  const double invTd = Td > 0.f ? 1.0 / (double)Td : 1.0;
   constexpr int kAtOnce = 4;                               // chunks asked for before any of them is looked at
   RunStat r;
   for (int c0 = 0; c0 < a.nchd; c0 += kAtOnce) {
@@ -144,10 +116,10 @@ __device__ inline void merge_draft_chunks(const StepArgs& a, int q, float Td, fl
 #pragma unroll
     for (int j = 0; j < kAtOnce; ++j)
       if (c0 + j < a.nchd && m[j] > r.mx) { r.mx = m[j]; r.arg = arg[j]; }   // ascending chunks: a later equal maximum does not replace
-    if (before != -INFINITY) r.sum *= (double)__builtin_amdgcn_exp2f((before - r.mx) * sc);
+    if (before != -INFINITY) r.sum *= rescale(before, r.mx, sc, invTd, exact);
 #pragma unroll
     for (int j = 0; j < kAtOnce; ++j)
-      if (c0 + j < a.nchd && m[j] != -INFINITY) r.sum += sum[j] * (double)__builtin_amdgcn_exp2f((m[j] - r.mx) * sc);
+      if (c0 + j < a.nchd && m[j] != -INFINITY) r.sum += sum[j] * rescale(m[j], r.mx, sc, invTd, exact);
   }
   *out_mx = r.mx; *out_S = r.sum; *out_arg = r.arg;
 }

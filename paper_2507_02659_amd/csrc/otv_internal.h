@@ -159,9 +159,8 @@ struct StepArgs {
   PiecePlan plan;        // how the LM-head launch shared out the draft rows
   ProbeRecord* probe;    // [B] what the drafted ids of each sequence look up (see ProbeRecord), left by the LM-head launch
   int32_t hosted;        // the LM-head launch left the target rows' softmax partials (`fused`), the draft rows' pieces
-                         // and the probe records: one launch follows it, which translates, tests and draws
-  int32_t chunked;       // the statistics launch left chunk partials (tpart_*, dpart_*) and the probe records: the same
-                         // one launch follows it (at most kFusedMaxB sequences)
+                         // and the probe records: one launch follows it, which translates, tests and draws;
+                         // 0: the statistics launch left chunk partials (tpart_*, dpart_*) and the probe records for it
   FinalInfo* fin;        // [B]
   int32_t ntiles;        // residual tiles per row
   double* tile_r;        // [B, ntiles]
@@ -193,7 +192,6 @@ hipError_t launch_pack_w_f32(const float* W, int d, int V_t, float* Wp, hipStrea
 hipError_t launch_lmhead_f32(const float* H, int M, int d, const float* Wp, float* Z, int V_t, int64_t ldz,
                              hipStream_t stream);
 hipError_t launch_softmax_stats(const StepArgs& a, hipStream_t stream);
-hipError_t launch_translate_accept(const StepArgs& a, hipStream_t stream);
 // translation and acceptance test (when the LM-head launch hosted the draft side) and the draw of the final tokens
 hipError_t launch_final_draw(const StepArgs& a, const int32_t* row_off_host, int n_cu, hipStream_t stream);
 

@@ -29,8 +29,8 @@ __global__ __launch_bounds__(kDrawThreads) void final_draw_kernel(StepArgs a, in
   draw_final_token(a, b, grp, group_tiles, f, dv, &s_draw, row_at);
 }
 
-// Row offsets of the sequences as a kernel argument (the host has them): the workgroup knows its rows without a
-// dependent load in front of everything else.
+// Row offsets of up to kFusedMaxB sequences as a kernel argument (the host has them): the workgroup knows its rows without
+// a dependent load in front of everything else.  With more sequences they come from memory.
 struct RowOffsets { int32_t v[kFusedMaxB + 1]; };
 constexpr int64_t kRepeatedMergeBytes = 32 << 20;
 
@@ -38,7 +38,9 @@ constexpr int64_t kRepeatedMergeBytes = 32 << 20;
 // a final_draw_kernel launch (used when repeating the test in every tile group would cost more than a launch).
 // kChunks: the partials come from the statistics launch (chunk partials in three arrays per side) instead of the
 // LM head's epilogue and draft-row pieces.
-template <bool kDraw, bool kChunks>
+// kMany: more than kFusedMaxB sequences: row offsets from memory, partials merged in binary64 (as a runtime flag these two
+// cost a single sequence 0.7 of 13 us).
+template <bool kDraw, bool kChunks, bool kMany>
 __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, RowOffsets ro, int group_tiles, int row_at) {
   const int b = blockIdx.y, grp = blockIdx.x, tid = threadIdx.x;
   const int wave = uniform(tid >> 6), lane = tid & 63;
@@ -50,8 +52,8 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, R
   __shared__ int s_parg[64];
   int dv[kPerLane];
 
-  const int r0 = ro.v[b];
-  const int k = ro.v[b + 1] - r0 - 1;
+  const int r0 = kMany ? a.row_off[b] : ro.v[b];
+  const int k = (kMany ? a.row_off[b + 1] : ro.v[b + 1]) - r0 - 1;
   const float T = a.temperature[b];
   const float Td = a.draft_temperature ? a.draft_temperature[b] : T;
   const uint64_t sid = a.seq_id[b];
@@ -76,7 +78,7 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, R
     s_d.hit[lane] = rec->hit[lane]; s_d.zq[lane] = rec->zq[lane]; s_d.dm[lane] = rec->dm[lane];
     if (lane < k) {
       float mxq; double Sq; int argq;
-      if (kChunks) merge_draft_chunks(a, q0 + lane, Td, &mxq, &Sq, &argq);
+      if (kChunks) merge_draft_chunks(a, q0 + lane, Td, &mxq, &Sq, &argq, kMany);
       else merge_draft_pieces(a, q0 + lane, Td, &mxq, &Sq, &argq);
       s_d.qmx[lane] = mxq; s_d.qS[lane] = Sq; s_d.qarg[lane] = argq;
       if (lead) { a.drow_max[q0 + lane] = mxq; a.drow_sum[q0 + lane] = Sq; a.drow_arg[q0 + lane] = argq; }
@@ -96,7 +98,7 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, R
   for (int row = wave; row <= k; row += kDrawWaves) {
     if (kChunks)
       merge_chunk_row(a.tpart_max, a.tpart_sum, a.tpart_arg, a.ncht, r0 + row, invT, lane, s_pmx, s_pS, s_parg, row, lead,
-                      a.row_max, a.row_sum, a.row_arg);
+                      a.row_max, a.row_sum, a.row_arg, kMany);
     else
       merge_fused_row(a.fused.part, a.fused.nfine, r0 + row, invT, lane, s_pmx, s_pS, s_parg, row, lead, a.row_max,
                       a.row_sum, a.row_arg);
@@ -136,9 +138,8 @@ int draw_group_tiles(int ntiles, int B, int n_cu) {
   return kTurnTiles * std::min(64, std::max(1, ceil_div(groups, std::max(n_cu, 1))));
 }
 
-// hosted: the LM-head launch left its softmax partials, the draft rows' pieces and the probe records; chunked: the
-// statistics launch left its chunk partials and the probe records (in both cases B <= kFusedMaxB and row_off_host holds
-// the B + 1 row offsets); otherwise a.fin is filled.
+// hosted: the LM-head launch left its softmax partials, the draft rows' pieces and the probe records; otherwise the
+// statistics launch left its chunk partials and the probe records.  row_off_host holds the B + 1 row offsets.
 hipError_t launch_final_draw(const StepArgs& a, const int32_t* row_off_host, int n_cu, hipStream_t stream) {
   if (a.B == 0) return hipSuccess;
   const int group_tiles = draw_group_tiles(a.ntiles, a.B, n_cu);
@@ -152,26 +153,22 @@ hipError_t launch_final_draw(const StepArgs& a, const int32_t* row_off_host, int
     row_at = (int)((lds + 15) / 16) * 2;
     lds = (size_t)row_at * sizeof(double) + row_bytes;
   }
-  if (a.chunked) {
-    if (a.B > kFusedMaxB || a.hosted) return hipErrorInvalidValue;
-    RowOffsets ro;
-    for (int b = 0; b <= kFusedMaxB; ++b) ro.v[b] = row_off_host[b <= a.B ? b : a.B];
-    hipLaunchKernelGGL((accept_draw_kernel<true, true>), grid, block, lds, stream, a, ro, group_tiles, row_at);   // a few chunks per row: always one launch
+  RowOffsets ro;
+  for (int b = 0; b <= kFusedMaxB; ++b) ro.v[b] = row_off_host[b <= a.B ? b : a.B];
+  if (!a.hosted) {                                         // a few chunks per row: always one launch
+    if (a.B > kFusedMaxB) hipLaunchKernelGGL((accept_draw_kernel<true, true, true>), grid, block, lds, stream, a, ro, group_tiles, row_at);
+    else hipLaunchKernelGGL((accept_draw_kernel<true, true, false>), grid, block, lds, stream, a, ro, group_tiles, row_at);
     return hipGetLastError();
   }
-  if (a.hosted) {
-    if (a.B > kFusedMaxB) return hipErrorInvalidValue;
-    RowOffsets ro;
-    for (int b = 0; b <= kFusedMaxB; ++b) ro.v[b] = row_off_host[b <= a.B ? b : a.B];
-    // Every tile group of a sequence repeats the merge of its rows' partials: M x nfine x 16 bytes per group.  Up to
-    // about the traffic that costs as much as a launch this is one launch; beyond it the test gets a launch of its own.
-    const int64_t repeated = (int64_t)a.M * a.fused.nfine * (int64_t)sizeof(Partial) * grid.x;
-    if (repeated <= kRepeatedMergeBytes) {
-      hipLaunchKernelGGL((accept_draw_kernel<true, false>), grid, block, lds, stream, a, ro, group_tiles, row_at);
-      return hipGetLastError();
-    }
-    hipLaunchKernelGGL((accept_draw_kernel<false, false>), dim3(1, a.B), block, 0, stream, a, ro, group_tiles, row_at);
+  if (a.B > kFusedMaxB) return hipErrorInvalidValue;
+  // Every tile group of a sequence repeats the merge of its rows' partials: M x nfine x 16 bytes per group.  Up to
+  // about the traffic that costs as much as a launch this is one launch; beyond it the test gets a launch of its own.
+  const int64_t repeated = (int64_t)a.M * a.fused.nfine * (int64_t)sizeof(Partial) * grid.x;
+  if (repeated <= kRepeatedMergeBytes) {
+    hipLaunchKernelGGL((accept_draw_kernel<true, false, false>), grid, block, lds, stream, a, ro, group_tiles, row_at);
+    return hipGetLastError();
   }
+  hipLaunchKernelGGL((accept_draw_kernel<false, false, false>), dim3(1, a.B), block, 0, stream, a, ro, group_tiles, row_at);
   hipLaunchKernelGGL(final_draw_kernel, grid, block, lds, stream, a, group_tiles, row_at);
   return hipGetLastError();
 }

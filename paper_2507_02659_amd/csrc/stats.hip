@@ -6,7 +6,7 @@
 // dtype): one workgroup reduces one chunk of kStatChunk logits of one row.  The chunk is read once into registers
 // (16-byte loads, consecutive lanes on consecutive vectors), reduced to its maximum through wavefront shuffles and
 // LDS, and only then exponentiated, so every logit is read from HBM exactly once.  The per-chunk partials are
-// merged in a fixed order by the consumer.  With a.chunked the launch also carries one workgroup per sequence that
+// merged in a fixed order by the consumer.  The launch also carries one workgroup per sequence that
 // looks up what its drafted ids need (drafted logit, direct image, n-gram table probes: Eq. 1) and leaves a
 // ProbeRecord, so that a single launch can follow (walk, acceptance test, final draw).
 #include "device_math.h"
@@ -19,17 +19,22 @@ namespace {
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kPerThread = kStatChunk / kStatThreads;   // 32 logits per thread
 
-// Sequence that owns `row`: rows of sequence b start at off[b] - shift*b (shift = 0 target rows, 1 draft rows).
-__device__ inline int find_sequence(const int32_t* off, int B, int row, int shift) {
-  int lo = 0, hi = B - 1;
-  while (lo < hi) {
-    int mid = (lo + hi + 1) >> 1;
-    if (off[mid] - shift * mid <= row) lo = mid; else hi = mid - 1;
+// Sequence that owns `row`: rows of sequence b start at off[b] - shift*b (shift = 0 target rows, 1 draft rows).  Called by
+// a whole wavefront: 64 evenly spaced sequences are looked at in one round trip, then 64 between two of those, and so on
+// (two round trips up to 4096 sequences; a binary search was nine at 300).
+__device__ inline int find_sequence(const int32_t* off, int B, int row, int shift, int lane) {
+  int base = 0, n = B;
+  for (;;) {
+    const int step = (n + 63) / 64, b = base + lane * step;
+    const bool before = b < base + n && off[min(b, B - 1)] - shift * b <= row;
+    const int at = max(0, (int)__popcll(__ballot(before)) - 1);
+    base += at * step;
+    if (step == 1) return base;
+    n = min(step, n - at * step);
   }
-  return lo;
 }
 
-// The same for up to 256 sequences without a chain of dependent loads: every lane of the wavefront holds the first
+// The same for up to 256 sequences in one round trip: every lane of the wavefront holds the first
 // row of sequences lane, lane + 64, ... (four independent loads, issued together), the predicate "starts at or before
 // `row`" is monotone in b, and the owner is the number of sequences it holds for, less one.  A workgroup's first loads
 // of logits then leave one round trip after its start, not five.
@@ -90,7 +95,12 @@ template <> struct Loader<uint16_t> {
 // are issued before anything waits; scale_of() (the row's sequence and its temperature: it waits for loads issued before
 // the call, and issues one more) is called behind them, so that a workgroup's logits are on their way one instruction
 // after its start.
-template <typename T, bool kAligned, typename ScaleFn>
+//
+// A row starts at any element (an odd vocabulary: every row at another alignment), so the 16-byte loads are laid out from
+// the boundary at or before the chunk's first element: thread 0's first vector and the one that holds the row's end are
+// read element by element, and the elements that the shift leaves over, fewer than a vector, by the first threads.  Read
+// element by element throughout, such rows took 44 us for 1200 x 32003 + 900 x 8000 logits (3.8 TB/s); now 34 (4.9 TB/s).
+template <typename T, typename ScaleFn>
 __device__ __forceinline__ void chunk_stats(const T* __restrict__ x_row, int V, int c, ScaleFn scale_of,
                                             float* __restrict__ pmax, double* __restrict__ psum,
                                             int32_t* __restrict__ parg, int64_t slot) {
@@ -100,6 +110,7 @@ __device__ __forceinline__ void chunk_stats(const T* __restrict__ x_row, int V, 
   const int base = c * kStatChunk;
   const int n = min(kStatChunk, V - base);
   const T* x = x_row + base;
+  const int shift = (int)(reinterpret_cast<uintptr_t>(x) / sizeof(T)) & (kVec - 1);
 
   float v[kPerThread];
   float best = -INFINITY;
@@ -107,28 +118,31 @@ __device__ __forceinline__ void chunk_stats(const T* __restrict__ x_row, int V, 
   typename Loader<T>::Raw raw[kLoads];
 #pragma unroll
   for (int i = 0; i < kLoads; ++i) {
-    const int at = (i * kStatThreads + tid) * kVec;
-    if (kAligned && at + kVec <= n) raw[i] = Loader<T>::load(x + at);
+    const int at = (i * kStatThreads + tid) * kVec - shift;
+    if (at >= 0 && at + kVec <= n) raw[i] = Loader<T>::load(x + at);
   }
+  const int at_over = kStatChunk - shift + tid;
+  const float over = at_over < n && tid < shift ? Loader<T>::one(x + at_over) : -INFINITY;
   const float scale = scale_of();
 #pragma unroll
   for (int i = 0; i < kLoads; ++i) {
-    const int at = (i * kStatThreads + tid) * kVec;
-    if (kAligned && at + kVec <= n) {
+    const int at = (i * kStatThreads + tid) * kVec - shift;
+    if (at >= 0 && at + kVec <= n) {
       Loader<T>::unpack(raw[i], &v[i * kVec]);
-    } else {                                 // the ragged end of a row, or a row that is not 16-byte aligned
+    } else {                                 // the ragged ends
 #pragma unroll
-      for (int e = 0; e < kVec; ++e) v[i * kVec + e] = (at + e < n) ? Loader<T>::one(x + at + e) : -INFINITY;
+      for (int e = 0; e < kVec; ++e) v[i * kVec + e] = (at + e >= 0 && at + e < n) ? Loader<T>::one(x + at + e) : -INFINITY;
     }
   }
 #pragma unroll
   for (int i = 0; i < kLoads; ++i) {
-    const int at = (i * kStatThreads + tid) * kVec;
+    const int at = (i * kStatThreads + tid) * kVec - shift;
 #pragma unroll
     for (int e = 0; e < kVec; ++e) {
       if (v[i * kVec + e] > best) { best = v[i * kVec + e]; best_i = at + e; }   // ascending index: first maximum kept
     }
   }
+  if (over > best) { best = over; best_i = at_over; }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
     float ob = __shfl_xor(best, off);
@@ -147,7 +161,7 @@ __device__ __forceinline__ void chunk_stats(const T* __restrict__ x_row, int V, 
     if (s_max[w] > best || (s_max[w] == best && s_idx[w] < best_i)) { best = s_max[w]; best_i = s_idx[w]; }
   }
   // exponentials relative to the chunk maximum; masked slots hold -inf and contribute exp2(-inf) = 0
-  float acc = 0.f;
+  float acc = __builtin_amdgcn_exp2f((over - best) * scale);
 #pragma unroll
   for (int i = 0; i < kPerThread; ++i) acc += __builtin_amdgcn_exp2f((v[i] - best) * scale);
   double sum = (double)acc;
@@ -166,12 +180,11 @@ __device__ __forceinline__ void chunk_stats(const T* __restrict__ x_row, int V, 
 }
 
 // Rows 0..M-1 are target rows, rows M..M+K-1 draft rows.  TD is the draft logits' storage type.
-template <typename TD, bool kAlignedT, bool kAlignedD>
+template <typename TD>
 __global__ __launch_bounds__(kStatThreads) void softmax_stats_kernel(StepArgs a) {
-  // With a.chunked the first B workgroups look up one sequence's drafted ids each: chains of dependent loads, started
-  // first so that they run underneath the stream of the others.  Then n_target workgroups take target chunks, the rest
-  // draft chunks.
-  const int n_lookup = a.chunked ? a.B : 0;
+  // The first B workgroups look up one sequence's drafted ids each: chains of dependent loads, started first so that they
+  // run underneath the stream of the others.  Then n_target workgroups take target chunks, the rest draft chunks.
+  const int n_lookup = a.B;
   const int wg = (int)blockIdx.x - n_lookup;
   const int n_target = a.M * a.ncht;
   const int lane = threadIdx.x & 63;
@@ -195,10 +208,10 @@ __global__ __launch_bounds__(kStatThreads) void softmax_stats_kernel(StepArgs a)
     if (by_ballot) starts = load_sequence_starts(a.row_off, a.temperature, a.B, 0, lane);
     auto scale_of = [&]() {
       const float T_b = by_ballot ? owner_temperature(starts, a.B, row, lane)
-                                  : a.temperature[find_sequence(a.row_off, a.B, row, 0)];
+                                  : a.temperature[find_sequence(a.row_off, a.B, row, 0, lane)];
       return T_b > 0.f ? kLog2e / T_b : kLog2e;
     };
-    chunk_stats<float, kAlignedT>(a.Z + (int64_t)row * a.ldz, a.V_t, c, scale_of, a.tpart_max, a.tpart_sum, a.tpart_arg,
+    chunk_stats<float>(a.Z + (int64_t)row * a.ldz, a.V_t, c, scale_of, a.tpart_max, a.tpart_sum, a.tpart_arg,
                                   (int64_t)row * a.ncht + c);
   } else {
     const int id = wg - n_target;
@@ -208,32 +221,22 @@ __global__ __launch_bounds__(kStatThreads) void softmax_stats_kernel(StepArgs a)
     if (by_ballot) starts = load_sequence_starts(a.row_off, temps, a.B, 1, lane);
     auto scale_of = [&]() {
       const float T_b = by_ballot ? owner_temperature(starts, a.B, drow, lane)
-                                  : temps[find_sequence(a.row_off, a.B, drow, 1)];
+                                  : temps[find_sequence(a.row_off, a.B, drow, 1, lane)];
       return T_b > 0.f ? kLog2e / T_b : kLog2e;
     };
     const TD* x = static_cast<const TD*>(a.draft_logits) + (int64_t)drow * a.V_d;
-    chunk_stats<TD, kAlignedD>(x, a.V_d, c, scale_of, a.dpart_max, a.dpart_sum, a.dpart_arg, (int64_t)drow * a.nchd + c);
+    chunk_stats<TD>(x, a.V_d, c, scale_of, a.dpart_max, a.dpart_sum, a.dpart_arg, (int64_t)drow * a.nchd + c);
   }
-}
-
-template <typename TD>
-hipError_t launch_typed(const StepArgs& a, bool at, bool ad, hipStream_t stream) {
-  dim3 grid(a.M * a.ncht + a.K * a.nchd + (a.chunked ? a.B : 0)), block(kStatThreads);
-  if (at && ad) hipLaunchKernelGGL((softmax_stats_kernel<TD, true, true>), grid, block, 0, stream, a);
-  else if (at) hipLaunchKernelGGL((softmax_stats_kernel<TD, true, false>), grid, block, 0, stream, a);
-  else if (ad) hipLaunchKernelGGL((softmax_stats_kernel<TD, false, true>), grid, block, 0, stream, a);
-  else hipLaunchKernelGGL((softmax_stats_kernel<TD, false, false>), grid, block, 0, stream, a);
-  return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_softmax_stats(const StepArgs& a, hipStream_t stream) {
-  if (a.M + a.K + (a.chunked ? a.B : 0) == 0) return hipSuccess;
-  const bool at = (a.ldz % 4) == 0 && (reinterpret_cast<uintptr_t>(a.Z) % 16) == 0;
-  const bool base16 = (reinterpret_cast<uintptr_t>(a.draft_logits) % 16) == 0;
-  if (a.dtype == OT_BF16) return launch_typed<uint16_t>(a, at, base16 && a.V_d % 8 == 0, stream);
-  return launch_typed<float>(a, at, base16 && a.V_d % 4 == 0, stream);
+  if (a.B == 0) return hipSuccess;
+  const dim3 grid(a.M * a.ncht + a.K * a.nchd + a.B), block(kStatThreads);
+  if (a.dtype == OT_BF16) hipLaunchKernelGGL(softmax_stats_kernel<uint16_t>, grid, block, 0, stream, a);
+  else hipLaunchKernelGGL(softmax_stats_kernel<float>, grid, block, 0, stream, a);
+  return hipGetLastError();
 }
 
 }  // namespace otv

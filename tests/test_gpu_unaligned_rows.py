@@ -1,0 +1,45 @@
+"""The softmax statistics launch on rows that start at any element: every alignment of a 16-byte vector, chunks of 8192 that
+end inside, at and just past the shift, for target rows (fp32) and draft rows (bf16 and fp32); and a step of more sequences
+than the LM-head launch stages."""
+import numpy as np
+import pytest
+
+from test_gpu_parity import _imports, _run_and_compare, _say
+from workloads import CaseSpec, make_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V_t,V_d", [(8191, 8191), (8192, 8193), (8193, 8190), (8195, 8185), (16383, 16385), (257, 3), (5, 1), (16386, 24571)])
+def test_statistics_at_every_alignment(dtype, V_t, V_d):
+    ov, ot, Verifier, parity = _imports()
+    ks = [7, 3, 0, 9, 2]
+    temps = [1.0, 0.5, 0.0, 2.0, 0.7]
+    case = make_case(CaseSpec(name=f"align_{dtype}_{V_t}_{V_d}", dtype=dtype, d=8, V_t=V_t, V_d=V_d, k=ks, temperature=temps,
+                              n_direct=min(V_d, V_t) // 2, data_seed=V_t + V_d, philox_seed=3, logits_only=True))
+    rng = np.random.default_rng(V_t)
+    Z = case.target_logits
+    for r in range(case.M):                              # maxima at the ends of the row and of the chunks
+        Z[r, [0, V_t - 1, min(8191, V_t - 1), min(8192, V_t - 1)][r % 4]] = 30.0 + rng.random()
+    _say(f"alignment case {case.name}")
+    v = Verifier.for_case(case)
+    try:
+        v.step(v.upload(case), from_logits=True)
+        ws = v.workspace(case.M, case.K)
+    finally:
+        v.close()
+    Zq = ov.widen(case.draft_logits, dtype)
+    for what, X, shift in (("", Z.astype(np.float64), 0), ("draft_", Zq, 1)):
+        T = np.repeat([t or 1.0 for t in temps], [k + 1 - shift for k in ks])[:, None]
+        assert np.array_equal(ws[what + "row_max"].astype(np.float64), X.max(axis=1))
+        assert np.array_equal(ws[what + "row_argmax"], X.argmax(axis=1))
+        np.testing.assert_allclose(ws[what + "row_sumexp"], np.exp((X - X.max(axis=1, keepdims=True)) / T).sum(axis=1), rtol=2e-6)
+
+
+@pytest.mark.parametrize("B", [255, 256, 257, 700])
+def test_many_sequences(B):
+    rng = np.random.default_rng(B)
+    _run_and_compare(make_case(CaseSpec(name=f"many_{B}", dtype="bf16", d=8, V_t=2503, V_d=901, k=rng.integers(0, 5, size=B).tolist(),
+                                        temperature=rng.choice([1.0, 0.0, 0.7], size=B).tolist(), n_direct=700, n_ngram=200, ngram_len=(2, 4),
+                                        plant_cover=0.4, align=0.6, data_seed=B, philox_seed=8, logits_only=True)))
