@@ -90,6 +90,14 @@ int ot_verify_init(const ot_verify_config* cfg, ot_ctx** out) {
     tmap_h[t] = dd;
   }
 
+  std::vector<int2> pairs_h;                             // the mapped pairs in ascending target id
+  try {
+    for (int32_t t = 0; t < cfg->V_t; ++t)
+      if (tmap_h[t] != -1) pairs_h.push_back(make_int2(t, tmap_h[t]));
+  } catch (const std::bad_alloc&) {
+    return fail(OT_ERR_NOMEM, "ot_verify_init: host allocation failed");
+  }
+
   ot_ctx* c = new (std::nothrow) ot_ctx();
   if (!c) return fail(OT_ERR_NOMEM, "ot_verify_init: host allocation failed");
   c->d = cfg->d; c->V_t = cfg->V_t; c->V_d = cfg->V_d; c->max_batch = cfg->max_batch; c->max_k = cfg->max_k;
@@ -111,7 +119,7 @@ int ot_verify_init(const ot_verify_config* cfg, ot_ctx** out) {
   bool ok = true;
   if (c->dtype == OT_BF16) ok = ok && dev_alloc(c, &c->Wp, (size_t)(c->Vp / 64) * (size_t)packed_tile_units(c->Kp / 32) * 8) && dev_alloc(c, &c->zeros, 32);
   else ok = ok && dev_alloc(c, &c->Wf, (size_t)ceil_div(c->V_t, 64) * (size_t)packed_f32_tile_units(ceil_div(c->d, 16)) * 4);
-  ok = ok && dev_alloc(c, &c->dmap, (size_t)c->V_d) && dev_alloc(c, &c->tmap, (size_t)c->V_t);
+  ok = ok && dev_alloc(c, &c->dmap, (size_t)c->V_d) && dev_alloc(c, &c->tmap, (size_t)c->V_t) && dev_alloc(c, &c->pairs, pairs_h.size());
   ok = ok && dev_alloc(c, &c->Z, R * (size_t)c->V_t);
   ok = ok && dev_alloc(c, &c->tpart_max, R * c->ncht) && dev_alloc(c, &c->tpart_sum, R * c->ncht) && dev_alloc(c, &c->tpart_arg, R * c->ncht);
   if (c->dtype == OT_BF16) {
@@ -123,11 +131,7 @@ int ot_verify_init(const ot_verify_config* cfg, ot_ctx** out) {
   ok = ok && dev_alloc(c, &c->drow_max, KQ) && dev_alloc(c, &c->drow_sum, KQ) && dev_alloc(c, &c->drow_arg, KQ);
   ok = ok && dev_alloc(c, &c->fin, Bm) && dev_alloc(c, &c->probe, Bm) &&
        dev_alloc(c, &c->dpiece, KQ * otv::kDraftPieces);
-  {
-    char* rows = nullptr;
-    ok = ok && dev_alloc(c, &rows, R * kLossRowBytes) && dev_alloc(c, &c->loss_tiles, R * c->ntiles);
-    c->loss_rows = rows;
-  }
+  ok = ok && dev_alloc(c, &c->loss_part, R * kLossGroups) && dev_alloc(c, &c->loss_count, R + 1);
   ok = ok && dev_alloc(c, &c->adapt_part, 2 * Bm);
   ok = ok && dev_alloc(c, &c->tile_r, Bm * c->ntiles);
   ok = ok && dev_alloc(c, &c->resid_count, Bm);
@@ -135,15 +139,18 @@ int ot_verify_init(const ot_verify_config* cfg, ot_ctx** out) {
 
   if (c->zeros) e = hipMemsetAsync(c->zeros, 0, 64, c->stream);
   if (e == hipSuccess) e = hipMemsetAsync(c->resid_count, 0, sizeof(int32_t) * Bm, c->stream);
+  if (e == hipSuccess) e = hipMemsetAsync(c->loss_count, 0, sizeof(int32_t) * (R + 1), c->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(c->dmap, cfg->direct_map, sizeof(int32_t) * c->V_d, hipMemcpyHostToDevice, c->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(c->tmap, tmap_h.data(), sizeof(int32_t) * c->V_t, hipMemcpyHostToDevice, c->stream);
+  c->n_pairs = (int32_t)pairs_h.size();
+  if (e == hipSuccess && !pairs_h.empty()) e = hipMemcpyAsync(c->pairs, pairs_h.data(), sizeof(int2) * pairs_h.size(), hipMemcpyHostToDevice, c->stream);
   if (e == hipSuccess) {
     if (c->dtype == OT_BF16)
       e = launch_pack_w_bf16(static_cast<const uint16_t*>(cfg->W), c->d, c->V_t, c->Wp, c->Kp, c->Vp, c->stream);
     else
       e = launch_pack_w_f32(static_cast<const float*>(cfg->W), c->d, c->V_t, c->Wf, c->stream);
   }
-  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);    // tmap_h and the caller's W are released here
+  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);    // tmap_h, pairs_h and the caller's W are released here
   if (e != hipSuccess) { free_ctx(c); return fail_hip(e, "ot_verify_init"); }
   *out = c;
   return OT_OK;

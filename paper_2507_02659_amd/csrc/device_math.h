@@ -71,6 +71,21 @@ __device__ inline int wave_min(int x) {
   return __builtin_amdgcn_readlane(x, 63);
 }
 
+// Sequence that owns `row`: rows of sequence b start at off[b] - shift*b (shift = 0 target rows, 1 draft rows).  Called by
+// a whole wavefront: 64 evenly spaced sequences are looked at in one round trip, then 64 between two of those, and so on
+// (two round trips up to 4096 sequences; a binary search was nine at 300).
+__device__ inline int find_sequence(const int32_t* off, int B, int row, int shift, int lane) {
+  int base = 0, n = B;
+  for (;;) {
+    const int step = (n + 63) / 64, b = base + lane * step;
+    const bool before = b < base + n && off[min(b, B - 1)] - shift * b <= row;
+    const int at = max(0, (int)__popcll(__ballot(before)) - 1);
+    base += at * step;
+    if (step == 1) return base;
+    n = min(step, n - at * step);
+  }
+}
+
 // Philox4x32-10 (Salmon et al., SC'11): ten rounds of two 32x32->64 multiplies and key-mixed xors.
 __device__ inline void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1,
                                      uint32_t out[4]) {

@@ -22,6 +22,8 @@ struct ot_ctx {
   uint16_t* zeros = nullptr;          // 64 zero bytes: source of the K tail in the LM-head's hidden slices
   float* Wf = nullptr;
   int32_t *dmap = nullptr, *tmap = nullptr;
+  int2* pairs = nullptr;              // [n_pairs] (target id, draft id) of the direct map in ascending target id
+  int32_t n_pairs = 0;
   float* Z = nullptr;
   float *tpart_max = nullptr, *dpart_max = nullptr, *row_max = nullptr, *drow_max = nullptr;
   double *tpart_sum = nullptr, *dpart_sum = nullptr, *row_sum = nullptr, *drow_sum = nullptr;
@@ -33,8 +35,8 @@ struct ot_ctx {
   double* tile_r = nullptr;
   int32_t* resid_count = nullptr;     // [max_batch] arrival counters of the residual launch, zero between launches
   otv::FinalInfo* fin = nullptr;
-  void* loss_rows = nullptr;          // [max_rows] records of kLossRowBytes: per-token constants of the loss kernels
-  double* loss_tiles = nullptr;       // [max_rows, ntiles] KL tile sums
+  double* loss_part = nullptr;        // [max_rows, kLossGroups] KL sums of a row's groups
+  int32_t* loss_count = nullptr;      // [max_rows + 1] arrival counters of the loss launch, 0 between launches
   double* adapt_part = nullptr;       // [max_batch, 2] per-sequence partials of the acceptance head's loss
   // profiling
   bool profiling = false;

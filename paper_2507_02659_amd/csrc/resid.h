@@ -101,8 +101,29 @@ constexpr float kFarBelow = -1e30f;
 
 // The dynamic LDS of the draw kernels: the tiles' masses, then (where a workgroup takes several turns) the draft row.
 typedef __attribute__((address_space(3))) char* lds_chars;
-extern __shared__ double s_draw_dynamic[];
+extern __shared__ __attribute__((aligned(16))) double s_draw_dynamic[];
 __device__ inline lds_chars draw_lds() { return (lds_chars)(void __attribute__((address_space(3)))*)s_draw_dynamic; }
+
+// Logits of draft ids dv (negative: the row's first) as stored, from the row's copy in the dynamic LDS where there is one.
+template <int N>
+__device__ inline void load_draft_logits(const void* zq, int dtype, int lds_at, const int* dv, uint32_t* xq) {
+  if (lds_at >= 0) {
+    const lds_chars s_row = draw_lds() + lds_at;
+    if (dtype == OT_BF16) {
+#pragma unroll
+      for (int e = 0; e < N; ++e) xq[e] = *(const __attribute__((address_space(3))) uint16_t*)(s_row + 2 * max(dv[e], 0));
+    } else {
+#pragma unroll
+      for (int e = 0; e < N; ++e) xq[e] = *(const __attribute__((address_space(3))) uint32_t*)(s_row + 4 * max(dv[e], 0));
+    }
+  } else if (dtype == OT_BF16) {
+#pragma unroll
+    for (int e = 0; e < N; ++e) xq[e] = static_cast<const uint16_t*>(zq)[max(dv[e], 0)];
+  } else {
+#pragma unroll
+    for (int e = 0; e < N; ++e) xq[e] = static_cast<const uint32_t*>(zq)[max(dv[e], 0)];
+  }
+}
 
 // What tile_values needs from memory for N ids v = first + e * stride, as loaded: the row's logits and, where the draw is
 // from a residual of a sampling drafter, the logits of the ids' pre-images.
@@ -118,21 +139,8 @@ __device__ inline void load_tile(const FinalRow& R, int V_t, int first, int stri
   if (!R.residual || R.greedy_draft) {                   // wavefront-uniform
 #pragma unroll
     for (int e = 0; e < N; ++e) raw.xq[e] = 0u;
-  } else if (R.lds_at >= 0) {
-    const lds_chars s_row = draw_lds() + R.lds_at;
-    if (R.dtype == OT_BF16) {
-#pragma unroll
-      for (int e = 0; e < N; ++e) raw.xq[e] = *(const __attribute__((address_space(3))) uint16_t*)(s_row + 2 * max(dv[e], 0));
-    } else {
-#pragma unroll
-      for (int e = 0; e < N; ++e) raw.xq[e] = *(const __attribute__((address_space(3))) uint32_t*)(s_row + 4 * max(dv[e], 0));
-    }
-  } else if (R.dtype == OT_BF16) {
-#pragma unroll
-    for (int e = 0; e < N; ++e) raw.xq[e] = static_cast<const uint16_t*>(R.zq)[max(dv[e], 0)];
   } else {
-#pragma unroll
-    for (int e = 0; e < N; ++e) raw.xq[e] = static_cast<const uint32_t*>(R.zq)[max(dv[e], 0)];
+    load_draft_logits<N>(R.zq, R.dtype, R.lds_at, dv, raw.xq);
   }
 }
 
@@ -177,6 +185,9 @@ __device__ inline double observe(double* p) {
                                                            __HIP_MEMORY_SCOPE_AGENT));
 }
 
+__device__ inline void publish(int32_t* p, int32_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline int32_t observe(int32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
 // first id a lane sums among the eight tiles that start at `tile0`
 __device__ inline int draw_first_id(int tile0, int wave, int lane) {
   return (tile0 + (wave >> 1)) * kResidTile + (wave & 1) * (kResidTile / 2) + lane;
@@ -185,9 +196,9 @@ __device__ inline int draw_first_id(int tile0, int wave, int lane) {
 // Copies the draft row to byte `at` of the dynamic LDS (all threads call it, a barrier follows): whole 16-byte chunks where
 // the row covers them, element by element at its ends, each byte at its own offset within a chunk.  Returns where the row
 // starts there.
-__device__ inline int stage_draft_row(const FinalRow& R, int V_d, int tid, int at) {
-  const int esz = R.dtype == OT_BF16 ? 2 : 4;
-  const char* row = static_cast<const char*>(R.zq);
+__device__ inline int stage_draft_row(const void* zq, int dtype, int V_d, int tid, int at) {
+  const int esz = dtype == OT_BF16 ? 2 : 4;
+  const char* row = static_cast<const char*>(zq);
   const int head = (int)(reinterpret_cast<uintptr_t>(row) & 15), bytes = V_d * esz;
   const int chunks = (head + bytes + 15) / 16;
   const int whole0 = head ? 1 : 0, whole1 = (head + bytes) / 16;     // chunks [whole0, whole1) lie inside the row
@@ -225,6 +236,8 @@ struct DrawLds {
   int pick, fallback, last;
 };
 
+constexpr size_t kDrawLdsBytes = 150 << 10;    // dynamic LDS of a workgroup with a copy of the draft row at most (160 KB a compute unit)
+
 // Mass of the 512 ids from `lo` on (this lane: first + e * 64), in every lane.
 __device__ inline double half_tile_mass(const FinalRow& R, int V_t, int first, int lo, const int* dv, const TileRaw<kPerLane>& raw) {
   double r[kPerLane];
@@ -246,7 +259,7 @@ __device__ inline void draw_final_token(const StepArgs& a, int b, int grp, int g
   FinalRow R = make_final_row(a, f);
   const int tile0 = grp * group_tiles, tile1 = min(tile0 + group_tiles, a.ntiles);
   if (row_at > 0 && R.residual && !R.greedy_draft) {     // workgroup-uniform
-    R.lds_at = stage_draft_row(R, a.V_d, tid, 8 * row_at);
+    R.lds_at = stage_draft_row(R.zq, R.dtype, a.V_d, tid, 8 * row_at);
     __syncthreads();
   }
 

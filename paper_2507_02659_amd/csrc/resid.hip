@@ -123,8 +123,6 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, R
 
 }  // namespace
 
-constexpr size_t kDrawLdsBytes = 150 << 10;    // dynamic LDS of a draw workgroup at most (160 KB a compute unit)
-
 // Tiles per workgroup of the draw.  Eight (one turn) as long as that leaves no more than a workgroup per compute unit:
 // a small batch is bound by the chain of round trips in one workgroup, which every further turn would lengthen.  With
 // more, each workgroup takes as many turns as bring their number back to one per compute unit (a workgroup of 1024

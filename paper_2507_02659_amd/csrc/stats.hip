@@ -19,22 +19,7 @@ namespace {
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kPerThread = kStatChunk / kStatThreads;   // 32 logits per thread
 
-// Sequence that owns `row`: rows of sequence b start at off[b] - shift*b (shift = 0 target rows, 1 draft rows).  Called by
-// a whole wavefront: 64 evenly spaced sequences are looked at in one round trip, then 64 between two of those, and so on
-// (two round trips up to 4096 sequences; a binary search was nine at 300).
-__device__ inline int find_sequence(const int32_t* off, int B, int row, int shift, int lane) {
-  int base = 0, n = B;
-  for (;;) {
-    const int step = (n + 63) / 64, b = base + lane * step;
-    const bool before = b < base + n && off[min(b, B - 1)] - shift * b <= row;
-    const int at = max(0, (int)__popcll(__ballot(before)) - 1);
-    base += at * step;
-    if (step == 1) return base;
-    n = min(step, n - at * step);
-  }
-}
-
-// The same for up to 256 sequences in one round trip: every lane of the wavefront holds the first
+// find_sequence for up to 256 sequences in one round trip: every lane of the wavefront holds the first
 // row of sequences lane, lane + 64, ... (four independent loads, issued together), the predicate "starts at or before
 // `row`" is monotone in b, and the owner is the number of sequences it holds for, less one.  A workgroup's first loads
 // of logits then leave one round trip after its start, not five.
