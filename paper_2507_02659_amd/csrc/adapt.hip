@@ -2,13 +2,16 @@
 // proposed tokens of every sequence, and the value of the weighted binary cross-entropy that trains the head
 // against the acceptance ratios min(1, p/q).  The head's logits are an input.
 //
-//   adapt_rule_kernel   one workgroup (one wavefront) per sequence: lane i forms sigmoid(a_i) and its two
+//   adapt_rule_kernel   one wavefront per sequence, four per workgroup: lane i forms sigmoid(a_i) and its two
 //                       log-probabilities in binary64; lane 0 walks the running product left to right (at most 63
 //                       factors) so that the product has one fixed order; per-sequence loss partials go to the
-//                       workspace.
-//   adapt_total_kernel  one workgroup adds the partials in a fixed order.
+//                       workspace.  With an arrival counter the last workgroup adds them in a fixed order: a call is
+//                       bound by its launches (64 sequences: 7.1 us with one, 10.1 with two).
+//   adapt_total_kernel  the same sum as a launch of its own, for the entry point whose scratch overlapping calls may
+//                       share: they spoil each other's values there, and must not spoil a counter for later calls.
 #include <mutex>
 
+#include "device_math.h"
 #include "otv_host.h"
 
 namespace otv {
@@ -18,14 +21,39 @@ struct AdaptArgs {
   ot_adapt_in in;
   ot_adapt_out out;
   double* part;      // [B, 2] loss sum and token count of each sequence
+  int32_t* count;    // workgroups that have delivered, 0 between launches; nullptr: the sum is a launch of its own
 };
 
-__global__ __launch_bounds__(64) void adapt_rule_kernel(AdaptArgs a) {
-  const int b = blockIdx.x, i = threadIdx.x;
-  const int r0 = a.in.row_off[b], k = a.in.row_off[b + 1] - r0 - 1;
-  const int n = a.in.n_valid ? min(k, max(a.in.n_valid[b], 0)) : k;
-  __shared__ double s_sig[64];
-  __shared__ double s_cost[64];
+constexpr int kThreads = 256, kWaves = kThreads / 64;
+
+// Sums of the B partials in a fixed order (all kThreads threads).
+__device__ inline void adapt_total(const AdaptArgs& a, double (*s_w)[kWaves], int tid) {
+  const int wave = tid >> 6, lane = tid & 63;
+  double total = 0.0, count = 0.0;
+  for (int b = tid; b < a.in.B; b += kThreads) { total += observe(a.part + 2 * b); count += observe(a.part + 2 * b + 1); }
+  total = wave_sum(total);
+  count = wave_sum(count);
+  if (lane == 0) { s_w[0][wave] = total; s_w[1][wave] = count; }
+  __syncthreads();
+  if (tid == 0) {
+    const double t = (s_w[0][0] + s_w[0][1]) + (s_w[0][2] + s_w[0][3]);
+    const double c = (s_w[1][0] + s_w[1][1]) + (s_w[1][2] + s_w[1][3]);
+    a.out.bce[0] = t;
+    a.out.bce[1] = c;
+    a.out.bce[2] = t / fmax(1.0, c);
+  }
+}
+
+__global__ __launch_bounds__(kThreads) void adapt_rule_kernel(AdaptArgs a) {
+  const int tid = threadIdx.x, wave = tid >> 6, i = tid & 63;
+  const int b = blockIdx.x * kWaves + wave;
+  __shared__ double s_sig[kWaves][64];
+  __shared__ double s_cost[kWaves][64];
+  __shared__ double s_w[2][kWaves];
+  __shared__ int s_last;
+  const bool live = b < a.in.B;
+  const int r0 = live ? a.in.row_off[b] : 0, k = live ? a.in.row_off[b + 1] - r0 - 1 : -1;
+  const int n = live && a.in.n_valid ? min(k, max(a.in.n_valid[b], 0)) : k;
   double sig = 0.0, cost = 0.0;
   if (i < n) {
     const double x = (double)a.in.head_logits[r0 + i];
@@ -37,46 +65,39 @@ __global__ __launch_bounds__(64) void adapt_rule_kernel(AdaptArgs a) {
       cost = (double)a.in.w_accept * l * (t + fmax(-x, 0.0)) + (double)a.in.w_reject * (1.0 - l) * (t + fmax(x, 0.0));
     }
   }
-  s_sig[i] = sig;
-  s_cost[i] = cost;
+  s_sig[wave][i] = sig;
+  s_cost[wave][i] = cost;
   if (i <= k) a.out.p_accept[r0 + i] = (float)sig;       // the sequence's unused entries read 0
   __syncthreads();
-  if (i == 0) {
+  if (i == 0 && live) {
     const double gamma = (double)a.in.gamma;
     double alive = 1.0, total = 0.0;
     int keep = n;
     for (int j = 0; j <= k; ++j) {
       double rej = 0.0;
       if (j < n) {
-        alive *= s_sig[j];
+        alive *= s_sig[wave][j];
         rej = 1.0 - alive;
-        total += s_cost[j];
+        total += s_cost[wave][j];
         if (keep == n && rej > gamma) keep = j + 1;
       }
       a.out.p_any_reject[r0 + j] = (float)rej;
     }
     a.out.n_keep[b] = keep;
-    a.part[2 * b] = total;
-    a.part[2 * b + 1] = (double)n;
+    publish(a.part + 2 * b, total);
+    publish(a.part + 2 * b + 1, (double)n);
+    stores_done();
   }
+  if (!a.count || !a.out.bce) return;
+  __syncthreads();
+  if (tid == 0) s_last = arrive(a.count, gridDim.x);
+  __syncthreads();
+  if (s_last) adapt_total(a, s_w, tid);
 }
 
-__global__ __launch_bounds__(256) void adapt_total_kernel(AdaptArgs a) {
-  __shared__ double s_w[2][4];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  double total = 0.0, count = 0.0;
-  for (int b = tid; b < a.in.B; b += 256) { total += a.part[2 * b]; count += a.part[2 * b + 1]; }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) { total += __shfl_xor(total, off); count += __shfl_xor(count, off); }
-  if (lane == 0) { s_w[0][wave] = total; s_w[1][wave] = count; }
-  __syncthreads();
-  if (tid == 0) {
-    const double t = (s_w[0][0] + s_w[0][1]) + (s_w[0][2] + s_w[0][3]);
-    const double c = (s_w[1][0] + s_w[1][1]) + (s_w[1][2] + s_w[1][3]);
-    a.out.bce[0] = t;
-    a.out.bce[1] = c;
-    a.out.bce[2] = t / fmax(1.0, c);
-  }
+__global__ __launch_bounds__(kThreads) void adapt_total_kernel(AdaptArgs a) {
+  __shared__ double s_w[2][kWaves];
+  adapt_total(a, s_w, threadIdx.x);
 }
 
 }  // namespace
@@ -111,16 +132,17 @@ double* static_scratch() {
   return g_scratch_ptr[dev];
 }
 
-// Validates the arguments shared by the two entry points and launches on `stream` with the loss partials in `part`.
+// Validates the arguments shared by the two entry points and launches on `stream` with the loss partials in `part` and the
+// arrival counter at `count` (or none).
 int adaptive_drafting(const char* who, const ot_adapt_in* in, ot_adapt_out* out, int max_batch, int max_k, double* part,
-                      hipStream_t stream) {
+                      int32_t* count, hipStream_t stream) {
   if (in->reserved != 0) return ot_fail(OT_ERR_SHAPE, "%s: reserved must be 0", who);
   if (in->B < 0 || in->B > max_batch) return ot_fail(OT_ERR_SHAPE, "%s: B = %d exceeds the limit of %d sequences", who, in->B, max_batch);
   if (!(in->gamma >= 0.f && in->gamma <= 1.f)) return ot_fail(OT_ERR_SHAPE, "%s: gamma must be in [0, 1]", who);
   if (out->bce && !in->labels) return ot_fail(OT_ERR_NULL, "%s: the loss value needs labels", who);
   if (out->bce && !(in->w_accept >= 0.f && in->w_reject >= 0.f)) return ot_fail(OT_ERR_SHAPE, "%s: weights must be non-negative", who);
   AdaptArgs a{};
-  a.in = *in; a.out = *out; a.part = part;
+  a.in = *in; a.out = *out; a.part = part; a.count = count;
   if (in->B > 0) {
     if (!in->row_off || !in->row_off_host || !in->head_logits) return ot_fail(OT_ERR_NULL, "%s: row_off, row_off_host and head_logits must not be NULL", who);
     if (!out->p_accept || !out->p_any_reject || !out->n_keep) return ot_fail(OT_ERR_NULL, "%s: p_accept, p_any_reject and n_keep are required", who);
@@ -129,9 +151,9 @@ int adaptive_drafting(const char* who, const ot_adapt_in* in, ot_adapt_out* out,
       const int64_t rows = (int64_t)in->row_off_host[b + 1] - in->row_off_host[b];
       if (rows < 1 || rows - 1 > max_k) return ot_fail(OT_ERR_SHAPE, "%s: sequence %d owns %lld rows", who, b, (long long)rows);
     }
-    hipLaunchKernelGGL(adapt_rule_kernel, dim3(in->B), dim3(64), 0, stream, a);
+    hipLaunchKernelGGL(adapt_rule_kernel, dim3(ceil_div(in->B, kWaves)), dim3(kThreads), 0, stream, a);
   }
-  if (out->bce) hipLaunchKernelGGL(adapt_total_kernel, dim3(1), dim3(256), 0, stream, a);
+  if (out->bce && (in->B == 0 || !count)) hipLaunchKernelGGL(adapt_total_kernel, dim3(1), dim3(kThreads), 0, stream, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return ot_fail_hip(e, who);
   return OT_OK;
@@ -148,7 +170,7 @@ extern "C" {
 
 int ot_adaptive_drafting(ot_ctx* ctx, const ot_adapt_in* in, ot_adapt_out* out) {
   if (!ctx || !in || !out) return ot_fail(OT_ERR_NULL, "ot_adaptive_drafting: ctx, in and out must not be NULL");
-  return adaptive_drafting("ot_adaptive_drafting", in, out, ctx->max_batch, ctx->max_k, ctx->adapt_part, ctx->stream);
+  return adaptive_drafting("ot_adaptive_drafting", in, out, ctx->max_batch, ctx->max_k, ctx->adapt_part, ctx->adapt_count, ctx->stream);
 }
 
 int ot_adaptive_drafting_static(const ot_adapt_in* in, ot_adapt_out* out, void* stream) {
@@ -158,7 +180,7 @@ int ot_adaptive_drafting_static(const ot_adapt_in* in, ot_adapt_out* out, void* 
                    "scratch; use ot_adaptive_drafting", in->B, OT_STATIC_MAX_BATCH);
   double* part = static_scratch();
   if (!part) return OT_ERR_HIP;
-  return adaptive_drafting("ot_adaptive_drafting_static", in, out, OT_STATIC_MAX_BATCH, OT_MAX_K, part, static_cast<hipStream_t>(stream));
+  return adaptive_drafting("ot_adaptive_drafting_static", in, out, OT_STATIC_MAX_BATCH, OT_MAX_K, part, nullptr, static_cast<hipStream_t>(stream));
 }
 
 }  // extern "C"

@@ -132,13 +132,14 @@ int ot_verify_init(const ot_verify_config* cfg, ot_ctx** out) {
   ok = ok && dev_alloc(c, &c->fin, Bm) && dev_alloc(c, &c->probe, Bm) &&
        dev_alloc(c, &c->dpiece, KQ * otv::kDraftPieces);
   ok = ok && dev_alloc(c, &c->loss_part, R * kLossGroups) && dev_alloc(c, &c->loss_count, R + 1);
-  ok = ok && dev_alloc(c, &c->adapt_part, 2 * Bm);
+  ok = ok && dev_alloc(c, &c->adapt_part, 2 * Bm) && dev_alloc(c, &c->adapt_count, 1);
   ok = ok && dev_alloc(c, &c->tile_r, Bm * c->ntiles);
   ok = ok && dev_alloc(c, &c->resid_count, Bm);
   if (!ok) { free_ctx(c); return fail(OT_ERR_NOMEM, "ot_verify_init: device allocation failed"); }
 
   if (c->zeros) e = hipMemsetAsync(c->zeros, 0, 64, c->stream);
   if (e == hipSuccess) e = hipMemsetAsync(c->resid_count, 0, sizeof(int32_t) * Bm, c->stream);
+  if (e == hipSuccess) e = hipMemsetAsync(c->adapt_count, 0, sizeof(int32_t), c->stream);
   if (e == hipSuccess) e = hipMemsetAsync(c->loss_count, 0, sizeof(int32_t) * (R + 1), c->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(c->dmap, cfg->direct_map, sizeof(int32_t) * c->V_d, hipMemcpyHostToDevice, c->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(c->tmap, tmap_h.data(), sizeof(int32_t) * c->V_t, hipMemcpyHostToDevice, c->stream);

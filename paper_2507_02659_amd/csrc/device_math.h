@@ -86,6 +86,36 @@ __device__ inline int find_sequence(const int32_t* off, int B, int row, int shif
   }
 }
 
+// Agent-scope accesses to what the workgroups of one launch hand to each other and to their arrival counters.  They run on
+// different XCDs,
+// each with its own L2, and exchange these few words through memory: the stores are write-through, the loads bypass
+// the local L2 and the counter lives in memory, so no whole-cache write-back or invalidate is needed.
+__device__ inline void publish(double* p, double v) {
+  __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), (unsigned long long)__double_as_longlong(v), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline double observe(double* p) {
+  return __longlong_as_double((long long)__hip_atomic_load(reinterpret_cast<unsigned long long*>(p), __ATOMIC_RELAXED,
+                                                           __HIP_MEMORY_SCOPE_AGENT));
+}
+
+__device__ inline void publish(int32_t* p, int32_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline int32_t observe(int32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// Returns when this wavefront's stores have reached memory.
+__device__ inline void stores_done() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): vector-memory stores count there as well
+  asm volatile("" ::: "memory");
+}
+// Counts this thread's earlier stores in (they have reached memory first); true for the n-th of n, which resets the counter.
+__device__ inline bool arrive(int32_t* count, int n) {
+  stores_done();
+  const bool last = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
+  if (last) publish(count, 0);
+  return last;
+}
+
 // Philox4x32-10 (Salmon et al., SC'11): ten rounds of two 32x32->64 multiplies and key-mixed xors.
 __device__ inline void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1,
                                      uint32_t out[4]) {

@@ -75,16 +75,6 @@ __device__ inline float draft_logit(const LossArgs& a, int drow, int dv) {
                             : static_cast<const float*>(a.draft_logits)[at];
 }
 
-// Counts this thread's earlier stores in (they have reached memory first); true for the n-th of n, which resets the counter.
-__device__ inline bool arrive(int32_t* count, int n) {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): vector-memory stores count there as well
-  asm volatile("" ::: "memory");
-  const bool last = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
-  if (last) publish(count, 0);
-  return last;
-}
-
 // The constants of row `row` (token t of L drafted tokens from draft row drow on), by one wavefront; lane 0 holds the
 // token's NLL and weight.
 __device__ inline LossRow make_loss_row(const LossArgs& a, int row, int kind, int drow, int L, int t, float T, float Td, int lane,

@@ -37,6 +37,7 @@ struct ot_ctx {
   otv::FinalInfo* fin = nullptr;
   double* loss_part = nullptr;        // [max_rows, kLossGroups] KL sums of a row's groups
   int32_t* loss_count = nullptr;      // [max_rows + 1] arrival counters of the loss launch, 0 between launches
+  int32_t* adapt_count = nullptr;     // arrival counter of the adaptive-drafting launch, 0 between launches
   double* adapt_part = nullptr;       // [max_batch, 2] per-sequence partials of the acceptance head's loss
   // profiling
   bool profiling = false;

@@ -173,21 +173,6 @@ __device__ inline void tile_values(const FinalRow& R, int V_t, int first, int st
   }
 }
 
-// Agent-scope accesses to the tile masses and the arrival counter.  Workgroups of one launch run on different XCDs,
-// each with its own L2, and exchange these few words through memory: the stores are write-through, the loads bypass
-// the local L2 and the counter lives in memory, so no whole-cache write-back or invalidate is needed.
-__device__ inline void publish(double* p, double v) {
-  __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), (unsigned long long)__double_as_longlong(v), __ATOMIC_RELAXED,
-                     __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ inline double observe(double* p) {
-  return __longlong_as_double((long long)__hip_atomic_load(reinterpret_cast<unsigned long long*>(p), __ATOMIC_RELAXED,
-                                                           __HIP_MEMORY_SCOPE_AGENT));
-}
-
-__device__ inline void publish(int32_t* p, int32_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ inline int32_t observe(int32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-
 // first id a lane sums among the eight tiles that start at `tile0`
 __device__ inline int draw_first_id(int tile0, int wave, int lane) {
   return (tile0 + (wave >> 1)) * kResidTile + (wave & 1) * (kResidTile / 2) + lane;
@@ -280,16 +265,9 @@ __device__ inline void draw_final_token(const StepArgs& a, int b, int grp, int g
   __syncthreads();
   for (int i = tid; i < tile1 - tile0; i += kDrawThreads)
     publish(&a.tile_r[(int64_t)b * a.ntiles + tile0 + i], s_tiles[2 * i] + s_tiles[2 * i + 1]);
-  // the stores have reached memory before this workgroup is counted
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): vector-memory stores count there as well
-  asm volatile("" ::: "memory");
+  stores_done();                                          // before this workgroup is counted
   __syncthreads();
-  if (tid == 0) {
-    const int arrived = __hip_atomic_fetch_add(&a.resid_count[b], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    L->last = arrived == (int)gridDim.x - 1;
-    if (L->last) __hip_atomic_store(&a.resid_count[b], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
-  }
+  if (tid == 0) L->last = arrive(&a.resid_count[b], gridDim.x);
   __syncthreads();
   if (!L->last) return;
 
