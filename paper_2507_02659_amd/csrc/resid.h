@@ -15,7 +15,8 @@
 //                    target (inverse CDF).  Which workgroup that is varies from run to run; what it computes does not.
 //                    When the residual is empty (reachable only through underflow) it first forms the masses of p, the
 //                    fallback distribution, by itself.
-// Nothing waits: a workgroup that is not last simply ends.
+// Nothing waits: a workgroup that is not last simply ends.  A workgroup that has all tiles of its sequence (a small
+// vocabulary, or many sequences) keeps the masses in LDS and counts nothing: three round trips to memory less.
 // What bounds a small batch is the chain of instructions and round trips in one workgroup (16 x 128256 ids: 17 us of
 // kernel, 21 before its gathers were freed and its scans and reductions moved from the LDS permute network to
 // data-parallel moves; one sequence of 32000 ids 12.5 against 16.2 us).
@@ -263,17 +264,23 @@ __device__ inline void draw_final_token(const StepArgs& a, int b, int grp, int g
     for (int e = 0; e < kPerLane; ++e) dv[e] = dv_next[e];
   }
   __syncthreads();
-  for (int i = tid; i < tile1 - tile0; i += kDrawThreads)
-    publish(&a.tile_r[(int64_t)b * a.ntiles + tile0 + i], s_tiles[2 * i] + s_tiles[2 * i + 1]);
-  stores_done();                                          // before this workgroup is counted
+  if (gridDim.x == 1) {                                  // all tiles are this workgroup's (at most kDrawThreads): they stay in LDS
+    const double mass = tid < a.ntiles ? s_tiles[2 * tid] + s_tiles[2 * tid + 1] : 0.0;
+    __syncthreads();
+    if (tid < a.ntiles) s_tiles[tid] = mass;
+  } else {
+    for (int i = tid; i < tile1 - tile0; i += kDrawThreads)
+      publish(&a.tile_r[(int64_t)b * a.ntiles + tile0 + i], s_tiles[2 * i] + s_tiles[2 * i + 1]);
+    stores_done();                                        // before this workgroup is counted
+    __syncthreads();
+    if (tid == 0) L->last = arrive(&a.resid_count[b], gridDim.x);
+    __syncthreads();
+    if (!L->last) return;
+    for (int t = tid; t < a.ntiles; t += kDrawThreads) s_tiles[t] = observe(&a.tile_r[(int64_t)b * a.ntiles + t]);
+  }
   __syncthreads();
-  if (tid == 0) L->last = arrive(&a.resid_count[b], gridDim.x);
-  __syncthreads();
-  if (!L->last) return;
 
   // ---- the last workgroup of the sequence: inverse CDF over the tile masses, then inside the tile that holds the draw
-  for (int t = tid; t < a.ntiles; t += kDrawThreads) s_tiles[t] = observe(&a.tile_r[(int64_t)b * a.ntiles + t]);
-  __syncthreads();
   // Wavefront 0: running mass over the tiles in ascending order, in place (a wavefront scan of 64 tiles at a time plus a
   // carry), and the tile where it crosses u * total.  The total and the crossing both come from these same sums.
   auto pick_tile = [&](bool may_fall_back) {
