@@ -72,16 +72,14 @@ typedef struct ot_ngram_cache ot_ngram_cache; /* owns the device hash table of o
  * launch is bound by the weight stream, every multiplying workgroup takes a piece of a draft row while its first loads
  * are in flight; with more rows a few workgroups at the front of the launch take all of it.  The launch then also
  * leaves the target rows' softmax partials, and one launch follows it (window walk, acceptance test, final draw)
- * instead of three. */
+ * instead of two. */
 /* Capacity edges (all shapes inside max_batch / max_k are served; what changes is the launch structure):
- *   - 16 rows or fewer, OT_F32, or a step entered through ot_verify_step_from_logits: the draft side always runs
- *     after the LM head (the softmax statistics of all rows and the lookups as a launch of their own, then the launch
- *     that walks, tests and draws: one launch more, a few microseconds);
- *   - more than 255 sequences in a step: the same, and the translation with the acceptance test gets a launch of its
- *     own as well (two launches more, about 25 us at 256 sequences with a 32000-id draft vocabulary);
- *   - OT_DRAFT_SIDE_AUTO also chooses the first of these when hosting would lengthen the LM-head launch: more than two
- *     draft rows per multiplying workgroup (up to 176 rows), or front workgroups that would need more than half
- *     of the launch (above).                                                                                     */
+ *   - 16 rows or fewer, more than 255 sequences, OT_F32, or a step entered through ot_verify_step_from_logits: the draft
+ *     side always runs after the LM head (the softmax statistics of all rows and the lookups as a launch of their own,
+ *     then the launch that walks, tests and draws: one launch more, a few microseconds and a pass over the logits);
+ *   - OT_DRAFT_SIDE_AUTO also chooses that where hosting is estimated to cost more: heads of up to about 32768 columns,
+ *     more than half a draft row per multiplying workgroup next to few logits (up to 176 rows), or front workgroups
+ *     that lengthen the launch (above).                                                                        */
 #define OT_DRAFT_SIDE_AUTO        0   /* decide per step from its shape (estimate of both durations)               */
 #define OT_DRAFT_SIDE_IN_LM_HEAD  1   /* inside the LM-head launch whenever the kernel supports the shape          */
 #define OT_DRAFT_SIDE_SEPARATE    2   /* always as launches of their own after the LM head                         */
@@ -308,7 +306,7 @@ int ot_verify_workspace(ot_ctx* ctx, ot_workspace_view* view);
 #define OT_STAGE_LM_HEAD          0   /* z = h . W                                                            */
 #define OT_STAGE_SOFTMAX_STATS    1   /* softmax statistics of the target and draft rows; 0 when the LM-head
                                          launch computes them itself                                          */
-#define OT_STAGE_TRANSLATE_ACCEPT 2   /* translation scan + n-gram probes (Eq. 1), acceptance ratios, Philox  */
+#define OT_STAGE_TRANSLATE_ACCEPT 2   /* nothing: translation and acceptance test run in the launch of the next stage */
 #define OT_STAGE_RESIDUAL_DRAW    3   /* masses of max(0, p - q') (Eq. 2) at the final row, inverse-CDF draw  */
 #define OT_N_STAGES               4
 int ot_verify_profile(ot_ctx* ctx, int32_t enable);

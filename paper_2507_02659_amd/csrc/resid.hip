@@ -1,11 +1,12 @@
 // The launches that draw the final token of every sequence (Algorithm 1: correction token from the residual of Eq. 2,
 // or free token from p), grid = (groups of tiles of kResidTile target ids) x (sequences).
 //   final_draw_kernel   the outcome records of the acceptance test are in memory (written by the launch before).
-//   accept_draw_kernel  follows an LM-head launch that hosted the draft side: every workgroup first repeats the
-//                       translation and the acceptance test of its sequence (one wavefront merges the pieces of the
-//                       draft rows' statistics and walks the window from the probe record while the others merge the
-//                       LM head's softmax partials, one wavefront per target row; then that wavefront runs the test:
-//                       a few microseconds of work on data that sits in L2, cheaper than a launch of its own), then
+//   accept_draw_kernel  follows the launch that did the draft side and the softmax partials, the LM head's or the
+//                       statistics launch: every workgroup first repeats the translation and the acceptance test of its
+//                       sequence (one wavefront merges the partials of the draft rows and walks the window from the
+//                       probe record while the others merge the target rows' partials, one wavefront per row; then that
+//                       wavefront runs the test: a few microseconds of work on data that sits in L2, cheaper than a
+//                       launch of its own: 300 sequences x 32003 ids 42 us, against 10.5 + 30.6 and a launch), then
 //                       takes part in the draw.  The workgroups of a sequence reach the same outcome; only group 0
 //                       writes the outputs of the translation and the test, the draft rows' merged statistics and
 //                       the cache's use statistics.
