@@ -1,6 +1,7 @@
 // Host side of libotverify: argument validation, context / workspace / n-gram table management, and the launch
 // order of one verification step.  Exports the C ABI declared in otverify.h; nothing here does arithmetic of
 // the method itself.
+#include <algorithm>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -78,24 +79,32 @@ int ot_verify_init(const ot_verify_config* cfg, ot_ctx** out) {
   // direct map: in range and one-to-one on its mapped part
   std::vector<int32_t> tmap_h;
   try {
+    tmap_h.reserve((size_t)cfg->V_t + 1 + 2 * (size_t)std::min(cfg->V_d, cfg->V_t));
     tmap_h.assign((size_t)cfg->V_t, -1);
   } catch (const std::bad_alloc&) {
     return fail(OT_ERR_NOMEM, "ot_verify_init: host allocation failed");
   }
+  size_t n_pairs = 0;
   for (int32_t dd = 0; dd < cfg->V_d; ++dd) {
     const int32_t t = cfg->direct_map[dd];
     if (t == -1) continue;
     if (t < 0 || t >= cfg->V_t) return fail(OT_ERR_MAP, "ot_verify_init: direct_map[%d] = %d is outside [0, V_t)", dd, t);
     if (tmap_h[t] != -1) return fail(OT_ERR_MAP, "ot_verify_init: draft ids %d and %d both map to target id %d", tmap_h[t], dd, t);
     tmap_h[t] = dd;
+    n_pairs += 1;
   }
 
-  std::vector<int2> pairs_h;                             // the mapped pairs in ascending target id
+  // behind the inverse map: the mapped pairs (target id, draft id) in ascending target id, from an even element on
+  const size_t pairs_at = ((size_t)cfg->V_t + 1) / 2 * 2;
   try {
-    for (int32_t t = 0; t < cfg->V_t; ++t)
-      if (tmap_h[t] != -1) pairs_h.push_back(make_int2(t, tmap_h[t]));
+    tmap_h.resize(pairs_at + 2 * n_pairs);
   } catch (const std::bad_alloc&) {
     return fail(OT_ERR_NOMEM, "ot_verify_init: host allocation failed");
+  }
+  for (size_t t = 0, at = pairs_at; t < (size_t)cfg->V_t; ++t) {
+    if (tmap_h[t] == -1) continue;
+    tmap_h[at++] = (int32_t)t;
+    tmap_h[at++] = tmap_h[t];
   }
 
   ot_ctx* c = new (std::nothrow) ot_ctx();
@@ -119,7 +128,7 @@ int ot_verify_init(const ot_verify_config* cfg, ot_ctx** out) {
   bool ok = true;
   if (c->dtype == OT_BF16) ok = ok && dev_alloc(c, &c->Wp, (size_t)(c->Vp / 64) * (size_t)packed_tile_units(c->Kp / 32) * 8) && dev_alloc(c, &c->zeros, 32);
   else ok = ok && dev_alloc(c, &c->Wf, (size_t)ceil_div(c->V_t, 64) * (size_t)packed_f32_tile_units(ceil_div(c->d, 16)) * 4);
-  ok = ok && dev_alloc(c, &c->dmap, (size_t)c->V_d) && dev_alloc(c, &c->tmap, (size_t)c->V_t) && dev_alloc(c, &c->pairs, pairs_h.size());
+  ok = ok && dev_alloc(c, &c->dmap, (size_t)c->V_d) && dev_alloc(c, &c->tmap, tmap_h.size());
   ok = ok && dev_alloc(c, &c->Z, R * (size_t)c->V_t);
   ok = ok && dev_alloc(c, &c->tpart_max, R * c->ncht) && dev_alloc(c, &c->tpart_sum, R * c->ncht) && dev_alloc(c, &c->tpart_arg, R * c->ncht);
   if (c->dtype == OT_BF16) {
@@ -131,27 +140,28 @@ int ot_verify_init(const ot_verify_config* cfg, ot_ctx** out) {
   ok = ok && dev_alloc(c, &c->drow_max, KQ) && dev_alloc(c, &c->drow_sum, KQ) && dev_alloc(c, &c->drow_arg, KQ);
   ok = ok && dev_alloc(c, &c->fin, Bm) && dev_alloc(c, &c->probe, Bm) &&
        dev_alloc(c, &c->dpiece, KQ * otv::kDraftPieces);
-  ok = ok && dev_alloc(c, &c->loss_part, R * kLossGroups) && dev_alloc(c, &c->loss_count, R + 1);
-  ok = ok && dev_alloc(c, &c->adapt_part, 2 * Bm) && dev_alloc(c, &c->adapt_count, 1);
+  ok = ok && dev_alloc(c, &c->loss_part, R * kLossGroups);
+  ok = ok && dev_alloc(c, &c->adapt_part, 2 * Bm);
   ok = ok && dev_alloc(c, &c->tile_r, Bm * c->ntiles);
-  ok = ok && dev_alloc(c, &c->resid_count, Bm);
+  const size_t n_counters = Bm + 1 + (R + 1);            // of the draw, of adaptive drafting, of the loss
+  ok = ok && dev_alloc(c, &c->resid_count, n_counters);
   if (!ok) { free_ctx(c); return fail(OT_ERR_NOMEM, "ot_verify_init: device allocation failed"); }
 
   if (c->zeros) e = hipMemsetAsync(c->zeros, 0, 64, c->stream);
-  if (e == hipSuccess) e = hipMemsetAsync(c->resid_count, 0, sizeof(int32_t) * Bm, c->stream);
-  if (e == hipSuccess) e = hipMemsetAsync(c->adapt_count, 0, sizeof(int32_t), c->stream);
-  if (e == hipSuccess) e = hipMemsetAsync(c->loss_count, 0, sizeof(int32_t) * (R + 1), c->stream);
+  if (e == hipSuccess) e = hipMemsetAsync(c->resid_count, 0, sizeof(int32_t) * n_counters, c->stream);
+  c->adapt_count = c->resid_count + Bm;
+  c->loss_count = c->adapt_count + 1;
   if (e == hipSuccess) e = hipMemcpyAsync(c->dmap, cfg->direct_map, sizeof(int32_t) * c->V_d, hipMemcpyHostToDevice, c->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(c->tmap, tmap_h.data(), sizeof(int32_t) * c->V_t, hipMemcpyHostToDevice, c->stream);
-  c->n_pairs = (int32_t)pairs_h.size();
-  if (e == hipSuccess && !pairs_h.empty()) e = hipMemcpyAsync(c->pairs, pairs_h.data(), sizeof(int2) * pairs_h.size(), hipMemcpyHostToDevice, c->stream);
+  if (e == hipSuccess) e = hipMemcpyAsync(c->tmap, tmap_h.data(), sizeof(int32_t) * tmap_h.size(), hipMemcpyHostToDevice, c->stream);
+  c->pairs = reinterpret_cast<const int2*>(c->tmap + pairs_at);
+  c->n_pairs = (int32_t)n_pairs;
   if (e == hipSuccess) {
     if (c->dtype == OT_BF16)
       e = launch_pack_w_bf16(static_cast<const uint16_t*>(cfg->W), c->d, c->V_t, c->Wp, c->Kp, c->Vp, c->stream);
     else
       e = launch_pack_w_f32(static_cast<const float*>(cfg->W), c->d, c->V_t, c->Wf, c->stream);
   }
-  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);    // tmap_h, pairs_h and the caller's W are released here
+  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);    // tmap_h and the caller's W are released here
   if (e != hipSuccess) { free_ctx(c); return fail_hip(e, "ot_verify_init"); }
   *out = c;
   return OT_OK;

@@ -22,7 +22,7 @@ struct ot_ctx {
   uint16_t* zeros = nullptr;          // 64 zero bytes: source of the K tail in the LM-head's hidden slices
   float* Wf = nullptr;
   int32_t *dmap = nullptr, *tmap = nullptr;
-  int2* pairs = nullptr;              // [n_pairs] (target id, draft id) of the direct map in ascending target id
+  const int2* pairs = nullptr;        // [n_pairs] (target id, draft id) of the direct map in ascending target id, behind tmap
   int32_t n_pairs = 0;
   float* Z = nullptr;
   float *tpart_max = nullptr, *dpart_max = nullptr, *row_max = nullptr, *drow_max = nullptr;
