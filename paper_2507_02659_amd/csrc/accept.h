@@ -134,7 +134,7 @@ __device__ inline FinalInfo accept_wave(const StepArgs& a, int b, int r0, int k,
                                         bool write_out) {
   FinalInfo fin;
   fin.mode = 0; fin.row = r0; fin.drow = 0; fin.t_ng = -1; fin.t_pre = -1; fin.argq = -1; fin.greedy_draft = 0;
-  fin.pad = 0; fin.pi = 0.0; fin.q_pre = 0.0; fin.u2 = 0.0;
+  fin.flags = P.flags; fin.pi = 0.0; fin.q_pre = 0.0; fin.u2 = 0.0;
   fin.mx = 0.0; fin.invT = 1.0; fin.invS = 1.0; fin.mxq = 0.0; fin.invTd = 1.0; fin.invSq = 1.0;
   if (P.flags & OT_FLAG_BAD_ID) {   // a drafted id outside [0, V_d): the sequence emits nothing
     if (write_out) {

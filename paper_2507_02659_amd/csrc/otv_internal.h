@@ -66,7 +66,7 @@ struct FinalInfo {
   int32_t t_pre;         // direct image of that n-gram's first sub-token, or -1
   int32_t argq;          // argmax of the draft row (used when the draft temperature is 0)
   int32_t greedy_draft;  // draft temperature is 0: q is one-hot at argq
-  int32_t pad;
+  int32_t flags;         // the sequence's OT_FLAG_* bits before the draw
   double pi;             // product of the n-gram's sub-token probabilities
   double q_pre;          // q(d_1) - pi
   double u2;             // uniform of the draw

@@ -307,7 +307,9 @@ __device__ inline void draw_final_token(const StepArgs& a, int b, int grp, int g
     }
     const double base = pick > 0 ? m[pick - 1] : 0.0;
     if (lane == 0) {
-      if (fallback) a.out.flags[b] |= OT_FLAG_RESID_ZERO;
+      // The word is not read back: the leading workgroup stored it in this launch, on an XCD with its own L2.  That store was
+      // written through before the workgroup was counted in, so this one comes after it.
+      if (fallback) publish(&a.out.flags[b], f.flags | OT_FLAG_RESID_ZERO);
       L->pick = pick; L->base = base; L->target = target; L->fallback = fallback;
     }
   };

@@ -318,7 +318,7 @@ __device__ inline void translate_walk(const StepArgs& a, int b, int r0, int k, i
   if (lead && lane == 0) {
     a.out.n_mapped[b] = m;
     a.out.hits_proposed[b] = hits;
-    a.out.flags[b] = flags;
+    publish(&a.out.flags[b], flags);   // another workgroup may add a bit to it in the same launch (draw_final_token)
   }
   if (lead && lane <= k) {
     a.out.mapped_ids[r0 + lane] = P->t;

@@ -47,3 +47,39 @@ def test_empty_residual_over_several_turns():
     case.draft_ids[:] = 0                              # no image: the proposal is empty
     gpu, ref, _ = _run_and_compare(case)
     assert np.all(gpu["flags"] == (ot.OT_FLAG_UNMAPPABLE | ot.OT_FLAG_RESID_ZERO))
+
+
+def test_flags_of_a_sequence_drawn_by_several_workgroups():
+    """The draw adds a bit to flags that another workgroup of the same launch wrote: every bit of this step arrives, whatever
+    the output buffer held before.  Five workgroups per sequence; empty residuals, ordinary ones, a free token, a greedy
+    sequence and one with a drafted id out of range."""
+    ov, ot, Verifier, parity = _imports()
+    B, V_t, V_d = 8, 40001, 40
+    case = make_case(CaseSpec(name="flags_groups", dtype="f32", d=8, V_t=V_t, V_d=V_d, k=[1] * B, temperature=[1.0] * 6 + [0.0, 1.0],
+                              n_direct=0, data_seed=95, philox_seed=12, logits_only=True))
+    case.direct_map[:] = -1
+    case.direct_map[1:7] = [3, 9000, 17001, 25003, 33004, V_t - 1]
+    case.target_logits[:] = 0
+    case.draft_logits[:] = 0
+    case.draft_ids[:] = 0                              # no image: the proposal is empty
+    for b in range(3):                                 # p and q' are one-hot at the same id
+        case.target_logits[2 * b, case.direct_map[1 + 2 * b]] = 2000.0
+        case.draft_logits[b, 1 + 2 * b] = 2000.0
+    case.draft_ids[5] = 1                              # its image has all of p: accepted, then a free token
+    case.target_logits[10, case.direct_map[1]] = 2000.0
+    case.draft_ids[7] = V_d
+    ref = ov.verify_case(case)
+    both = ot.OT_FLAG_UNMAPPABLE | ot.OT_FLAG_RESID_ZERO
+    assert ref["flags"].tolist() == [both] * 3 + [ot.OT_FLAG_UNMAPPABLE] * 2 + [0, ot.OT_FLAG_UNMAPPABLE, ot.OT_FLAG_BAD_ID]
+    v = Verifier.for_case(case)
+    try:
+        inp = v.upload(case)
+        for before in (0, -1, both, ot.OT_FLAG_BAD_ID):
+            inp["out"]["flags"].fill_(before)
+            v.step(inp, from_logits=True)
+            got = v.results(inp)
+            rep = parity.compare(case, got, ref, logits_from_gpu=False)
+            assert not rep.failures and rep.exact == B, rep.failures
+            assert np.array_equal(got["flags"], ref["flags"])
+    finally:
+        v.close()
