@@ -116,7 +116,9 @@ __device__ __forceinline__ void merge_draft_chunks(const StepArgs& a, int q, flo
 #pragma unroll
     for (int j = 0; j < kAtOnce; ++j)
       if (c0 + j < a.nchd && m[j] > r.mx) { r.mx = m[j]; r.arg = arg[j]; }   // ascending chunks: a later equal maximum does not replace
-    if (before != -INFINITY) r.sum *= rescale(before, r.mx, sc, invTd, exact);
+    // in binary64 always: a factor per group of chunks, each with the error of a binary32 2^x, would add up in the sums of the
+    // first chunks, which carry one such error already
+    if (before != -INFINITY && r.mx > before) r.sum *= rescale(before, r.mx, sc, invTd, true);
 #pragma unroll
     for (int j = 0; j < kAtOnce; ++j)
       if (c0 + j < a.nchd && m[j] != -INFINITY) r.sum += sum[j] * rescale(m[j], r.mx, sc, invTd, exact);

@@ -43,3 +43,28 @@ def test_many_sequences(B):
     _run_and_compare(make_case(CaseSpec(name=f"many_{B}", dtype="bf16", d=8, V_t=2503, V_d=901, k=rng.integers(0, 5, size=B).tolist(),
                                         temperature=rng.choice([1.0, 0.0, 0.7], size=B).tolist(), n_direct=700, n_ngram=200, ngram_len=(2, 4),
                                         plant_cover=0.4, align=0.6, data_seed=B, philox_seed=8, logits_only=True)))
+
+
+@pytest.mark.parametrize("V_d", [40000, 100001])
+def test_sum_of_a_draft_row_whose_maximum_rises_from_chunk_to_chunk(V_d):
+    """One finite logit in every fourth chunk of 8192, each larger than the one before: a chunk's sum is exactly 1, and what is
+    left is how a sum is carried over to a larger maximum.  That factor is formed in binary64 (a few 1e-16; in binary32 it was
+    off by 1e-8, once for every group of four chunks that raised the maximum)."""
+    ov, ot, Verifier, parity = _imports()
+    ks, temps = [7, 7, 7], [1.0, 0.7, 1.3]
+    case = make_case(CaseSpec(name=f"rising_{V_d}", dtype="f32", d=8, V_t=300, V_d=V_d, k=ks, temperature=temps, n_direct=100,
+                              data_seed=V_d, philox_seed=3, logits_only=True))
+    rng = np.random.default_rng(V_d)
+    at = np.arange(0, V_d, 4 * 8192)
+    case.draft_logits[:] = -np.inf
+    case.draft_logits[:, at + 5] = np.cumsum(rng.uniform(0.1, 1.0, size=(case.K, at.size)), axis=1, dtype=np.float32)
+    case.draft_ids[:] = at[0] + 5
+    _say(f"rising maxima case {case.name}")
+    v = Verifier.for_case(case)
+    try:
+        v.step(v.upload(case), from_logits=True)
+        ws = v.workspace(case.M, case.K)
+    finally:
+        v.close()
+    X, T = case.draft_logits.astype(np.float64), np.repeat(case.temperature.astype(np.float64), ks)[:, None]
+    np.testing.assert_allclose(ws["draft_row_sumexp"], np.exp((X - X.max(axis=1, keepdims=True)) / T).sum(axis=1), rtol=1e-13)
