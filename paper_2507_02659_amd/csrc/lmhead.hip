@@ -524,10 +524,20 @@ __global__ __launch_bounds__(WPG * 64) void lmhead_bf16_wide_kernel(const uint16
         for (int i = 1; i < NW * 4; ++i)            // ascending columns: the first maximum is kept
           if (v[i] > best) { best = v[i]; bi = i; }
         const int barg = best == -INFINITY ? 0x7FFFFFFF : t16 * 16 + 4 * (lane >> 4) + (bi >> 2) * 16 + (bi & 3);
+        // exponents v * sc + nb, one fused multiply-add each.  nb is rounded, by up to 1e-6 where the maximum is large: the
+        // sum is off by that power of two as a whole and is put right as a whole.  (Added up four by four: 20 terms in a
+        // row would round away more than the 8 of a narrower workgroup.)
         const float nb = best == -INFINITY ? 0.f : -best * sc;
+        const float nb_off = best == -INFINITY ? 0.f : fmaf(-best, sc, -nb);
         float sum = 0.f;
 #pragma unroll
-        for (int i = 0; i < NW * 4; ++i) sum += __builtin_amdgcn_exp2f(fmaf(v[i], sc, nb));   // masked: exp2(-inf) = 0
+        for (int i = 0; i < NW * 4; i += 4) {                                                 // masked: exp2(-inf) = 0
+          float t[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) t[e] = __builtin_amdgcn_exp2f(fmaf(v[i + e], sc, nb));
+          sum += (t[0] + t[1]) + (t[2] + t[3]);
+        }
+        sum *= __builtin_amdgcn_exp2f(nb_off);
         const int at = (wave * (kStatMT * 16) + ml * 16 + (lane & 15)) * 4 + (lane >> 4);
         st_max[at] = best; st_sum[at] = sum; st_arg[at] = barg;
       }
@@ -546,17 +556,17 @@ __global__ __launch_bounds__(WPG * 64) void lmhead_bf16_wide_kernel(const uint16
           for (int g = 0; g < 4; ++g)
             if (m4[g] > best || (m4[g] == best && a[g] < barg)) { best = m4[g]; barg = a[g]; }
         }
-        float sum = 0.f;
+        double sum = 0.0;
 #pragma unroll
         for (int w = 0; w < WPG; ++w) {
           const f32x4 m4 = *reinterpret_cast<const f32x4*>(&st_max[(w * (kStatMT * 16) + tid) * 4]);
           const f32x4 s4 = *reinterpret_cast<const f32x4*>(&st_sum[(w * (kStatMT * 16) + tid) * 4]);
 #pragma unroll
           for (int g = 0; g < 4; ++g)
-            if (m4[g] != -INFINITY) sum += s4[g] * __builtin_amdgcn_exp2f((m4[g] - best) * sc);
+            if (m4[g] != -INFINITY) sum += (double)s4[g] * (double)__builtin_amdgcn_exp2f((m4[g] - best) * sc);
         }
         Partial out;
-        out.mx = best; out.arg = barg; out.sum = (double)sum;
+        out.mx = best; out.arg = barg; out.sum = sum;
         fs.part[(int64_t)(row0 + h * 16 + tid) * fs.nfine + col_tile] = out;
       }
       if (h + kStatMT < MT) lds_barrier();         // the next group overwrites the scratch

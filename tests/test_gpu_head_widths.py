@@ -46,3 +46,27 @@ def test_widths(M, V_t):
                                    (257, 33002), (330, 33001), (433, 33000), (512, 33001)])
 def test_several_blocks(M, V_t):
     _check(M, V_t)
+
+
+@pytest.mark.parametrize("M,V_t", [(65, 33001), (128, 66001), (65, 131073), (257, 33002)])
+def test_row_sums_of_large_logits(M, V_t):
+    """The sums that the epilogue leaves, against 64-bit sums of the kernel's own logits, for rows whose maximum (about 30) times
+    log2(e) / T is rounded by up to 2e-6 in binary32.  What stays are the roundings of single terms, of either sign: the
+    2^x (6e-8) and its argument (2^-24 of about 8), averaged over the dozens of terms that carry a sum, and log2(e) itself (1.3e-8
+    of the argument).  Measured 3.0e-8 to 3.6e-8, and 4.0e-7 to 4.7e-7 with that first rounding left in."""
+    ov, ot, Verifier, parity = _imports()
+    ks = [min(40, M - r) - 1 for r in range(0, M, 40)]
+    case = make_case(CaseSpec(name=f"sums_{M}x{V_t}", dtype="bf16", d=40, V_t=V_t, V_d=64, k=ks, temperature=[1.0] * len(ks), n_direct=32,
+                              data_seed=M + V_t, philox_seed=1, sigma_h=50.0))
+    _say(f"row sums case M={M} V_t={V_t}")
+    v = Verifier.for_case(case, draft_side=ot.OT_DRAFT_SIDE_IN_LM_HEAD)
+    try:
+        v.step(v.upload(case))
+        ws = v.workspace(case.M, case.K, with_logits=True)
+    finally:
+        v.close()
+    Z = ws["logits"].astype(np.float64)
+    want = np.exp(Z - Z.max(axis=1, keepdims=True)).sum(axis=1)
+    rms = np.sqrt(np.mean((ws["row_sumexp"] / want - 1.0) ** 2))
+    _say(f"  rms {rms:.3g}, largest logit {Z.max():.1f}")
+    assert rms < 1.2e-7
