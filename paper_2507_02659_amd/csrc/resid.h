@@ -38,7 +38,7 @@ static_assert(kPer == 4, "the fixed summation trees below are written for 4 ids 
 // p(v) and q'(v) of Eq. 2 at the final row of one sequence.
 struct FinalRow {
   const float* z;
-  float mx, sc_hi, sc_lo;        // row maximum; log2(e) / T split into two floats
+  float mx, sc_hi, sc_lo;        // row maximum; log2(e) / T split into two positive floats
   double invS;
   const void* zq;
   int lds_at;                    // where the draft row's copy starts in the dynamic LDS, in bytes (-1: there is none)
@@ -70,12 +70,19 @@ struct FinalRow {
   }
 };
 
+// Largest float below x > 0.  The two floats of a scale are then both positive, and -inf times either is -inf: split at the
+// nearest float, the lower one is negative for about half of all temperatures (0.7, 0.9, ..), and a masked logit gave NaN.
+__device__ inline float float_below(double x) {
+  const float h = (float)x;
+  return (double)h >= x && h > 0.f ? __uint_as_float(__float_as_uint(h) - 1) : h;
+}
+
 // The record is the same for every lane: all of it goes to scalar registers.
 __device__ inline FinalRow make_final_row(const StepArgs& a, const FinalInfo& f) {
   FinalRow R;
   R.z = a.Z + (int64_t)uniform(f.row) * a.ldz;
   const double sc = f.invT * 1.4426950408889634, scq = f.invTd * 1.4426950408889634;
-  const float sc_hi = (float)sc, scq_hi = (float)scq;
+  const float sc_hi = float_below(sc), scq_hi = float_below(scq);
   R.mx = uniform((float)f.mx); R.sc_hi = uniform(sc_hi); R.sc_lo = uniform((float)(sc - (double)sc_hi)); R.invS = uniform(f.invS);
   R.residual = uniform(f.mode) == 3;
   R.lds_at = -1;

@@ -83,3 +83,21 @@ def test_flags_of_a_sequence_drawn_by_several_workgroups():
             assert np.array_equal(got["flags"], ref["flags"])
     finally:
         v.close()
+
+
+@pytest.mark.parametrize("temperature", [0.7, 0.9, 1.0, 1.1])
+def test_masked_logits(temperature):
+    """Logits of -inf (a caller's mask) on both sides: those ids have no mass, the others keep theirs, whether the low part of
+    log2(e) / T rounds up or down."""
+    ov, ot, Verifier, parity = _imports()
+    B, V_t, V_d = 40, 9001, 2003
+    case = make_case(CaseSpec(name=f"masked_{temperature}", dtype="f32", d=8, V_t=V_t, V_d=V_d, k=[3] * B, temperature=[temperature] * B,
+                              n_direct=1600, n_ngram=100, ngram_len=(2, 3), plant_cover=0.3, align=0.6, data_seed=21, philox_seed=5,
+                              logits_only=True))
+    rng = np.random.default_rng(3)
+    for row, x in enumerate(case.draft_logits):
+        x[np.setdiff1d(rng.choice(V_d, V_d // 2, replace=False), case.draft_ids[row])] = -np.inf
+    case.target_logits[:, rng.choice(V_t, V_t // 3, replace=False)] = -np.inf
+    gpu, ref, _ = _run_and_compare(case)
+    drawn = ref["out_tokens"][ref["final_row"]]
+    assert np.isfinite(case.target_logits[ref["final_row"], drawn]).all() and (ref["n_accept"] < ref["n_mapped"]).any()
