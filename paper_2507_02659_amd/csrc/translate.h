@@ -233,7 +233,7 @@ __device__ __forceinline__ void wave_row_stats(const T* __restrict__ x, int V, f
   for (int at = n_vec * kVec + lane; at < V; at += 64) {
     const float v = RowVec<T>::one(x + at);
     r.raise(v, at, scale);
-    r.sum += (double)__builtin_amdgcn_exp2f((v - r.mx) * scale);
+    if (r.mx != -INFINITY) r.sum += (double)__builtin_amdgcn_exp2f((v - r.mx) * scale);   // nothing but -inf so far: no (-inf) - (-inf)
   }
   float mx = r.mx;
   int arg = r.arg;

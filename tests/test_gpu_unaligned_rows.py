@@ -68,3 +68,38 @@ def test_sum_of_a_draft_row_whose_maximum_rises_from_chunk_to_chunk(V_d):
         v.close()
     X, T = case.draft_logits.astype(np.float64), np.repeat(case.temperature.astype(np.float64), ks)[:, None]
     np.testing.assert_allclose(ws["draft_row_sumexp"], np.exp((X - X.max(axis=1, keepdims=True)) / T).sum(axis=1), rtol=1e-13)
+
+
+@pytest.mark.parametrize("B", [2, 21])                   # the multiplying workgroups take pieces; front workgroups take rows
+@pytest.mark.parametrize("V_d", [1, 5, 7, 8, 9, 15, 16, 23, 601, 4093, 4096, 8001, 31999])
+def test_draft_rows_of_the_lm_head_launch_at_every_alignment(B, V_d):
+    """Draft rows whose statistics the LM-head launch forms: rows at every 2-byte alignment of a 16-byte vector, half of the logits
+    masked (-inf), masked runs at the row's ends, the maximum at the first element, at the last, or twice."""
+    ov, ot, Verifier, parity = _imports()
+    ks = [9, 8] + [9] * (B - 2)
+    temps = [[1.0, 0.5, 0.0, 2.0, 0.7][i % 5] for i in range(B)]
+    case = make_case(CaseSpec(name=f"hosted_{B}_{V_d}", dtype="bf16", d=16, V_t=1500, V_d=V_d, k=ks, temperature=temps, n_direct=min(V_d, 1400) // 2,
+                              data_seed=V_d, philox_seed=3))
+    rng = np.random.default_rng(V_d)
+    masked, one, big = 0xFF80, 0x3F80, 0x4120             # -inf, 1, 10
+    for q, x in enumerate(case.draft_logits):
+        x[rng.choice(V_d, V_d // 2, replace=False)] = masked
+        if q % 7 == 0: x[:V_d // 3] = masked
+        if q % 7 == 1: x[V_d // 2:] = masked
+        if q % 7 == 2: x[0] = big
+        if q % 7 == 3: x[-1] = big
+        if q % 7 == 4: x[rng.integers(0, V_d, 2)] = big
+        if q % 7 == 5: x[[0, -1]] = big
+        if (x == masked).all(): x[rng.integers(0, V_d)] = one
+    _say(f"hosted draft rows case {case.name}")
+    v = Verifier.for_case(case, draft_side=ot.OT_DRAFT_SIDE_IN_LM_HEAD)
+    try:
+        v.step(v.upload(case))
+        ws = v.workspace(case.M, case.K)
+    finally:
+        v.close()
+    X = ov.widen(case.draft_logits, "bf16")
+    T = np.repeat([t or 1.0 for t in temps], ks)[:, None]
+    assert np.array_equal(ws["draft_row_max"].astype(np.float64), X.max(axis=1))
+    assert np.array_equal(ws["draft_row_argmax"], X.argmax(axis=1))
+    np.testing.assert_allclose(ws["draft_row_sumexp"], np.exp((X - X.max(axis=1, keepdims=True)) / T).sum(axis=1), rtol=2e-6)
