@@ -168,21 +168,30 @@ struct RunStat {
 // kernel that saturates the memory system, where a load takes several microseconds to return, so the bytes in flight
 // decide how long a row takes.  A lane keeps a running maximum and a running sum relative to it (rescaled when the
 // maximum moves); the 64 lanes are merged at the end by shuffles in a fixed order.  Sums of one vector are formed in
-// binary32, everything above that in binary64.  Rows that do not start on a 16-byte boundary, and the last V % kVec
-// elements of the others, are read element by element.  All lanes return the row's statistics.
+// binary32, everything above that in binary64.  A row may start at any element (an odd vocabulary: every row at another
+// alignment): the vectors begin at its first 16-byte boundary, and the few elements before and behind them are read one by
+// one, by a lane each.  (Rows off the boundary read one by one throughout take a front workgroup five times as long: 200 rows
+// of 50257 ids next to a head of 50257 columns 435 us per step, 170 when the statistics run as a launch of their own.)
+// All lanes return the row's statistics.
 // kFirst: the first batch was requested earlier (row_first_batch_load with the same x and V) and is taken from `first`.
 template <typename T, int kBatch> struct RowFirstBatch { typename RowVec<T>::Raw raw[kBatch]; };
+
+// elements of row x (V of them) before its first 16-byte boundary
+template <typename T>
+__device__ __forceinline__ int row_head(const T* x, int V) {
+  return min((int)((16 - (reinterpret_cast<uintptr_t>(x) & 15)) & 15) / (int)sizeof(T), V);
+}
 
 template <typename T, int kBatch>
 __device__ __forceinline__ void row_first_batch_load(const T* __restrict__ x, int V, int lane,
                                                      RowFirstBatch<T, kBatch>& first) {
   constexpr int kVec = RowVec<T>::kVec;
-  const bool aligned = (reinterpret_cast<uintptr_t>(x) % 16) == 0;
-  const int n_vec = aligned && V > 0 ? V / kVec : 0;
+  const int head = V > 0 ? row_head(x, V) : 0;
+  const int n_vec = V > 0 ? (V - head) / kVec : 0;
 #pragma unroll
   for (int j = 0; j < kBatch; ++j) {
     const int at = j * 64 + lane;
-    first.raw[j] = at < n_vec ? RowVec<T>::load(x + (int64_t)at * kVec) : RowVec<T>::lowest();
+    first.raw[j] = at < n_vec ? RowVec<T>::load(x + head + (int64_t)at * kVec) : RowVec<T>::lowest();
   }
 }
 
@@ -192,8 +201,8 @@ __device__ __forceinline__ void wave_row_stats(const T* __restrict__ x, int V, f
                                                const RowFirstBatch<T, kBatch>* first = nullptr) {
   constexpr int kVec = RowVec<T>::kVec;
   typedef typename RowVec<T>::Raw Raw;
-  const bool aligned = (reinterpret_cast<uintptr_t>(x) % 16) == 0;
-  const int n_vec = aligned ? V / kVec : 0;       // whole vectors read as such
+  const int head = row_head(x, V);
+  const int n_vec = (V - head) / kVec;            // whole vectors read as such
   RunStat r;
   for (int base = 0; base < n_vec; base += 64 * kBatch) {
     Raw raw[kBatch];
@@ -201,7 +210,7 @@ __device__ __forceinline__ void wave_row_stats(const T* __restrict__ x, int V, f
     for (int j = 0; j < kBatch; ++j) {
       const int at = base + j * 64 + lane;
       if (kFirst && base == 0) raw[j] = first->raw[j];
-      else raw[j] = at < n_vec ? RowVec<T>::load(x + (int64_t)at * kVec) : RowVec<T>::lowest();
+      else raw[j] = at < n_vec ? RowVec<T>::load(x + head + (int64_t)at * kVec) : RowVec<T>::lowest();
     }
     float bm = -INFINITY;
     int bi = 0x7FFFFFFF;
@@ -212,7 +221,7 @@ __device__ __forceinline__ void wave_row_stats(const T* __restrict__ x, int V, f
       RowVec<T>::unpack(raw[j], v);
 #pragma unroll
       for (int e = 0; e < kVec; ++e)
-        if (v[e] > bm) { bm = v[e]; bi = (base + j * 64 + lane) * kVec + e; }   // ascending index: first maximum kept
+        if (v[e] > bm) { bm = v[e]; bi = head + (base + j * 64 + lane) * kVec + e; }   // ascending index: first maximum kept
     }
     r.raise(bm, bi, scale);
     if (r.mx != -INFINITY) {
@@ -230,9 +239,11 @@ __device__ __forceinline__ void wave_row_stats(const T* __restrict__ x, int V, f
       }
     }
   }
-  for (int at = n_vec * kVec + lane; at < V; at += 64) {
+  if (lane < V - n_vec * kVec) {                  // fewer than two vectors' elements are left
+    const int at = lane < head ? lane : lane + n_vec * kVec;
     const float v = RowVec<T>::one(x + at);
     r.raise(v, at, scale);
+    if (v == r.mx) r.arg = min(r.arg, at);        // an element in front of an equal maximum
     if (r.mx != -INFINITY) r.sum += (double)__builtin_amdgcn_exp2f((v - r.mx) * scale);   // nothing but -inf so far: no (-inf) - (-inf)
   }
   float mx = r.mx;
