@@ -122,6 +122,10 @@ __global__ __launch_bounds__(WPG * 64) void lmhead_bf16_wide_kernel(const uint16
   // steps per trip of the main loop: whole pairs of slices (buffers A, B) and whole turns of the weight ring, so
   // that both the buffer and the ring array of every step are known at compile time
   constexpr int kUnroll = 2 * kKSteps * PF / gcd_c(2 * kKSteps, PF);
+  // Where the refill of the weight ring stands among the MFMAs of a step counts in the 128-column kernels, whose steps are one
+  // load each: left to the compiler it moved with unrelated code, 50.5 or 51.9 us for 80 rows x 32000 columns (d = 4096).
+  // Up to six row tiles it is held behind the first; with more, that is 1 to 3 % slower than where the compiler puts it.
+  constexpr bool kEarlyRefill = PF == 8 && MT <= 6;
   static_assert(PF % kKSteps == 0 && PF <= 8, "a weight fetch is used a whole number of slices later");
   static_assert(kGemmKPad % KC == 0 && (kCPR == 8 || kCPR == 16), "slice geometry");
   static_assert((PF - 1) * NW + (PF / kKSteps) * kDma + NW < 64, "the load counter has 6 bits");
@@ -436,9 +440,14 @@ __global__ __launch_bounds__(WPG * 64) void lmhead_bf16_wide_kernel(const uint16
           acc[mt][nw] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, bw[nw]), hf, acc[mt][nw],
                                                                 0, 0, 0);
         }
+        // The ring array is free again: refill it with the fragments PF steps ahead (past the end: the last ones again)
+        if (kEarlyRefill && mt == 0) {
+          __builtin_amdgcn_sched_barrier(0);
+          fetch_w(min(kk + PF, nks - 1), rs);
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
-      // the ring array is free again: refill it with the fragments PF steps ahead (past the end: the last ones again)
-      fetch_w(min(kk + PF, nks - 1), rs);
+      if (!kEarlyRefill) fetch_w(min(kk + PF, nks - 1), rs);
       __builtin_amdgcn_sched_barrier(0);   // keep the next step's LDS reads from being hoisted (register budget)
     }
   };

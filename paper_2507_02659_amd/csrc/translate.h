@@ -188,10 +188,11 @@ __device__ __forceinline__ void row_first_batch_load(const T* __restrict__ x, in
   constexpr int kVec = RowVec<T>::kVec;
   const int head = V > 0 ? row_head(x, V) : 0;
   const int n_vec = V > 0 ? (V - head) / kVec : 0;
+  const T* xv = x + head;
 #pragma unroll
   for (int j = 0; j < kBatch; ++j) {
     const int at = j * 64 + lane;
-    first.raw[j] = at < n_vec ? RowVec<T>::load(x + head + (int64_t)at * kVec) : RowVec<T>::lowest();
+    first.raw[j] = at < n_vec ? RowVec<T>::load(xv + (int64_t)at * kVec) : RowVec<T>::lowest();
   }
 }
 
@@ -203,6 +204,7 @@ __device__ __forceinline__ void wave_row_stats(const T* __restrict__ x, int V, f
   typedef typename RowVec<T>::Raw Raw;
   const int head = row_head(x, V);
   const int n_vec = (V - head) / kVec;            // whole vectors read as such
+  const T* xv = x + head;
   RunStat r;
   for (int base = 0; base < n_vec; base += 64 * kBatch) {
     Raw raw[kBatch];
@@ -210,7 +212,7 @@ __device__ __forceinline__ void wave_row_stats(const T* __restrict__ x, int V, f
     for (int j = 0; j < kBatch; ++j) {
       const int at = base + j * 64 + lane;
       if (kFirst && base == 0) raw[j] = first->raw[j];
-      else raw[j] = at < n_vec ? RowVec<T>::load(x + head + (int64_t)at * kVec) : RowVec<T>::lowest();
+      else raw[j] = at < n_vec ? RowVec<T>::load(xv + (int64_t)at * kVec) : RowVec<T>::lowest();
     }
     float bm = -INFINITY;
     int bi = 0x7FFFFFFF;
@@ -221,7 +223,7 @@ __device__ __forceinline__ void wave_row_stats(const T* __restrict__ x, int V, f
       RowVec<T>::unpack(raw[j], v);
 #pragma unroll
       for (int e = 0; e < kVec; ++e)
-        if (v[e] > bm) { bm = v[e]; bi = head + (base + j * 64 + lane) * kVec + e; }   // ascending index: first maximum kept
+        if (v[e] > bm) { bm = v[e]; bi = (base + j * 64 + lane) * kVec + e; }   // ascending index: first maximum kept
     }
     r.raise(bm, bi, scale);
     if (r.mx != -INFINITY) {
@@ -239,6 +241,7 @@ __device__ __forceinline__ void wave_row_stats(const T* __restrict__ x, int V, f
       }
     }
   }
+  if (r.mx != -INFINITY) r.arg += head;
   if (lane < V - n_vec * kVec) {                  // fewer than two vectors' elements are left
     const int at = lane < head ? lane : lane + n_vec * kVec;
     const float v = RowVec<T>::one(x + at);
