@@ -846,24 +846,27 @@ double lmhead_launch_us(int M, int d, int Vp) { return std::max(2.0 * d * (doubl
 // How more than 176 rows run: as several M-blocks per column tile (their weight streams meet in one L2), of `tiles` row
 // tiles each, by the kernel whose wavefronts own 32 columns or by the one whose wavefronts own 64 (`wide`).  That regime
 // is bound by the L2 -> LDS traffic, LDS reads and the card's power, and the launch runs in rounds of one workgroup per
-// compute unit.  The estimate, fitted to d = 3584 heads of 152064 columns (us per round: 4 tiles 44, 6: 58, 9: 79,
-// 12: 100, 16: 135): 12 us outside the loop plus 4 + 7 per row tile in it for 256 columns; with 64 columns per wavefront a
-// hidden fragment read from LDS feeds four MFMAs instead of two and a column costs 7 % less, but the accumulators leave
-// room for 11 row tiles at most.  A last round that is partly empty costs about half of what it leaves idle (the clock of
-// the busy part rises).  Measured, us per step, against blocks chosen by their height alone: 192 / 512 rows on
-// V_t = 8000 (d = 4096) 52 / 62 against 99 / 145, on V_t = 32000 81 / 155 against 103 / 175; 512 rows on V_t = 50000
-// (d = 2048) 161 against 208, 1024 rows on V_t = 128256 1018 against 1076.
-struct TallPlan { int tiles; bool wide; double per_cu, round_us; };   // workgroups per compute unit, time of a round
-double tall_rounds(double per_cu) { return std::max(1.0, 0.5 * (per_cu + std::ceil(per_cu))); }
+// compute unit, on each of the eight XCDs by itself (a column tile and its M-blocks stay on one: 99 tiles of 5 blocks are 65
+// workgroups on three of them, a third round on 32 compute units).  The estimate was fitted to all eleven blocks at 247
+// shapes (d = 512 to 4096, 8000 to 152064 columns, 184 to 1024 rows): a few us outside the loop plus 14 + 5.6 per row tile in
+// it for 256 columns at d = 3584; with 64 columns per wavefront a hidden fragment read from LDS feeds four MFMAs instead of two
+// and a column costs 17 % less, but the accumulators leave room for 11 row tiles at most.  A round that is partly empty
+// costs about 0.6 of what it leaves idle (the clock of the busy part rises).  The block it takes is 0.25 % slower than the
+// best one on average and 4 % at most; blocks chosen by their height alone were 13 % slower on average and up to 2.4 times
+// (and better by 2 to 3 % at five shapes).  Measured, us per step, against those: 192 / 512 rows on V_t = 8000 (d = 4096)
+// 52 / 62 against 99 / 145, on V_t = 33024 184 / 400 rows 97 / 142 against 97 / 142, 1024 rows on V_t = 128256 1018 against 1076.
+struct TallPlan { int tiles; bool wide; int workgroups; double rounds, round_us; };
 TallPlan tall_plan(int M, int d, int Vp, int n_cu) {
-  TallPlan best{9, false, 1.0, INFINITY};
+  TallPlan best{9, false, 0, 1.0, INFINITY};
   auto consider = [&](int mt, int cols, double outside, double per_column) {
-    const TallPlan p{mt, cols == 512, (double)ceil_div(Vp, cols) * ceil_div(M, 16 * mt) / std::max(1, n_cu),
-                     outside + d / 3584.0 * (4 + 7 * mt) * per_column * cols / 256};
-    if (tall_rounds(p.per_cu) * p.round_us < tall_rounds(best.per_cu) * best.round_us) best = p;
+    const int workgroups = ceil_div(ceil_div(Vp, cols), 8) * 8 * ceil_div(M, 16 * mt);   // eight times those of the fullest XCD
+    const double per_cu = workgroups / std::max(1.0, (double)n_cu);
+    const double rounds = per_cu < 1.0 ? 0.61 + 0.39 * per_cu : 0.42 * per_cu + 0.58 * std::ceil(per_cu);
+    const TallPlan p{mt, cols == 512, workgroups, rounds, outside + d / 3584.0 * (14 + 5.6 * mt) * per_column * cols / 256};
+    if (p.rounds * p.round_us < best.rounds * best.round_us) best = p;
   };
-  for (int mt : {4, 6, 9, 10, 12, 14, 16, 18}) consider(mt, 256, 12.0, 1.0);
-  for (int mt : {9, 10, 11}) consider(mt, 512, 18.0, 0.93);
+  for (int mt : {4, 6, 9, 10, 12, 14, 16, 18}) consider(mt, 256, 5.0, 1.0);
+  for (int mt : {9, 10, 11}) consider(mt, 512, 9.0, 0.83);
   return best;
 }
 
@@ -990,7 +993,7 @@ bool lmhead_bf16_hosts_draft_side(int M, int d, int Vp, int B, int K, int V_d, i
   // The launch ends at the first moment by which n_front compute units that come free after front_us and the others have
   // had room for all workgroups, each kStatsUs longer for the row statistics; half of what stays idle counts, as above.
   constexpr double kStatsUs = 5.0;
-  const double t = plan.round_us + kStatsUs, n = plan.per_cu * n_cu;
+  const double t = plan.round_us + kStatsUs, n = plan.workgroups;
   const double rounds_alone = std::ceil(n / (n_cu - n_front) - 1e-9);          // the front's compute units never join
   double end = rounds_alone * t;
   for (int front_rounds = 1; front_us + front_rounds * t < end; ++front_rounds) {
@@ -1000,7 +1003,7 @@ bool lmhead_bf16_hosts_draft_side(int M, int d, int Vp, int B, int K, int V_d, i
   for (double at = t; at < end; at += t)
     if ((n_cu - n_front) * std::round(at / t) + n_front * std::floor(std::max(0.0, at - front_us) / t) >= n) end = at;
   const double hosted = std::max(front_us, 0.5 * (end + (n * t + n_front * front_us) / n_cu));
-  const double separate = tall_rounds(plan.per_cu) * plan.round_us + 4.0 + (4.0 * M * Vp + 2.0 * K * (double)V_d) / 5.0e6;
+  const double separate = plan.rounds * plan.round_us + 4.0 + (4.0 * M * Vp + 2.0 * K * (double)V_d) / 5.0e6;
   return hosted < separate;
 }
 
