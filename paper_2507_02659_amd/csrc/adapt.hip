@@ -3,10 +3,13 @@
 // against the acceptance ratios min(1, p/q).  The head's logits are an input.
 //
 //   adapt_rule_kernel   one wavefront per sequence, four per workgroup: lane i forms sigmoid(a_i) and its two
-//                       log-probabilities in binary64; lane 0 walks the running product left to right (at most 63
-//                       factors) so that the product has one fixed order; per-sequence loss partials go to the
-//                       workspace.  With an arrival counter the last workgroup adds them in a fixed order: a call is
-//                       bound by its launches (64 sequences: 7.1 us with one, 10.1 with two).
+//                       log-probabilities in binary64; the running product is formed left to right (at most 63
+//                       factors) so that it has one fixed order, by every lane alike from lane reads, and lane i keeps
+//                       its own term; per-sequence loss partials go to the workspace.  With an arrival counter the last
+//                       workgroup adds them in a fixed order: a call is bound by its launches (64 sequences of up to 10 positions 7.4 us with
+//                       one, 10.2 with two).  The chain counts where windows are long: walked by one lane that also
+//                       stored every position, 16 sequences of 63 took 13.4 us, 8.0 now (10.6 with two launches).  Above 1024 sequences the sum is a launch of its own: the arrivals, one a
+//                       workgroup at one word, take longer than that (3000 sequences 13.9 / 11.1 us, 512 7.7 / 10.2).
 //   adapt_total_kernel  the same sum as a launch of its own, for the entry point whose scratch overlapping calls may
 //                       share: they spoil each other's values there, and must not spoil a counter for later calls.
 #include <mutex>
@@ -25,12 +28,25 @@ struct AdaptArgs {
 };
 
 constexpr int kThreads = 256, kWaves = kThreads / 64;
+constexpr int kOneLaunchB = 1024;
 
 // Sums of the B partials in a fixed order (all kThreads threads).
 __device__ inline void adapt_total(const AdaptArgs& a, double (*s_w)[kWaves], int tid) {
   const int wave = tid >> 6, lane = tid & 63;
   double total = 0.0, count = 0.0;
-  for (int b = tid; b < a.in.B; b += kThreads) { total += observe(a.part + 2 * b); count += observe(a.part + 2 * b + 1); }
+  constexpr int kAtOnce = 4;                             // sequences asked for before any of them is added
+  for (int b0 = tid; b0 < a.in.B; b0 += kAtOnce * kThreads) {
+    double t[kAtOnce], c[kAtOnce];
+#pragma unroll
+    for (int j = 0; j < kAtOnce; ++j) {
+      const int b = min(b0 + j * kThreads, a.in.B - 1);
+      t[j] = observe(a.part + 2 * b);
+      c[j] = observe(a.part + 2 * b + 1);
+    }
+#pragma unroll
+    for (int j = 0; j < kAtOnce; ++j)
+      if (b0 + j * kThreads < a.in.B) { total += t[j]; count += c[j]; }
+  }
   total = wave_sum(total);
   count = wave_sum(count);
   if (lane == 0) { s_w[0][wave] = total; s_w[1][wave] = count; }
@@ -45,10 +61,8 @@ __device__ inline void adapt_total(const AdaptArgs& a, double (*s_w)[kWaves], in
 }
 
 __global__ __launch_bounds__(kThreads) void adapt_rule_kernel(AdaptArgs a) {
-  const int tid = threadIdx.x, wave = tid >> 6, i = tid & 63;
+  const int tid = threadIdx.x, wave = uniform(tid >> 6), i = tid & 63;
   const int b = blockIdx.x * kWaves + wave;
-  __shared__ double s_sig[kWaves][64];
-  __shared__ double s_cost[kWaves][64];
   __shared__ double s_w[2][kWaves];
   __shared__ int s_last;
   const bool live = b < a.in.B;
@@ -65,32 +79,31 @@ __global__ __launch_bounds__(kThreads) void adapt_rule_kernel(AdaptArgs a) {
       cost = (double)a.in.w_accept * l * (t + fmax(-x, 0.0)) + (double)a.in.w_reject * (1.0 - l) * (t + fmax(x, 0.0));
     }
   }
-  s_sig[wave][i] = sig;
-  s_cost[wave][i] = cost;
-  if (i <= k) a.out.p_accept[r0 + i] = (float)sig;       // the sequence's unused entries read 0
-  __syncthreads();
+  const int n_all = uniform(n);
+  double alive = 1.0, mine = 1.0, total = 0.0;           // mine: the product up to and including position i
+  for (int j = 0; j < n_all; ++j) {
+    alive *= lane_value(sig, j);
+    total += lane_value(cost, j);
+    if (i == j) mine = alive;
+  }
+  const bool summed = a.count && a.out.bce;              // by the last workgroup of this launch
   if (i == 0 && live) {
-    const double gamma = (double)a.in.gamma;
-    double alive = 1.0, total = 0.0;
-    int keep = n;
-    for (int j = 0; j <= k; ++j) {
-      double rej = 0.0;
-      if (j < n) {
-        alive *= s_sig[wave][j];
-        rej = 1.0 - alive;
-        total += s_cost[wave][j];
-        if (keep == n && rej > gamma) keep = j + 1;
-      }
-      a.out.p_any_reject[r0 + j] = (float)rej;
-    }
-    a.out.n_keep[b] = keep;
     publish(a.part + 2 * b, total);
     publish(a.part + 2 * b + 1, (double)n);
-    stores_done();
   }
-  if (!a.count || !a.out.bce) return;
-  __syncthreads();
-  if (tid == 0) s_last = arrive(a.count, gridDim.x);
+  if (summed) {                                          // the partials are counted in before the outputs are stored
+    stores_done();
+    __syncthreads();
+    if (tid == 0) s_last = arrive(a.count, gridDim.x);
+  }
+  const double rej = i < n ? 1.0 - mine : 0.0;
+  const unsigned long long stop = __ballot(i < n && rej > (double)a.in.gamma);
+  if (i <= k) {                                          // the sequence's unused entries read 0
+    a.out.p_accept[r0 + i] = (float)sig;
+    a.out.p_any_reject[r0 + i] = (float)rej;
+  }
+  if (i == 0 && live) a.out.n_keep[b] = stop ? (int)__ffsll((long long)stop) : n;
+  if (!summed) return;
   __syncthreads();
   if (s_last) adapt_total(a, s_w, tid);
 }
@@ -142,6 +155,7 @@ int adaptive_drafting(const char* who, const ot_adapt_in* in, ot_adapt_out* out,
   if (out->bce && !in->labels) return ot_fail(OT_ERR_NULL, "%s: the loss value needs labels", who);
   if (out->bce && !(in->w_accept >= 0.f && in->w_reject >= 0.f)) return ot_fail(OT_ERR_SHAPE, "%s: weights must be non-negative", who);
   AdaptArgs a{};
+  if (in->B > kOneLaunchB) count = nullptr;
   a.in = *in; a.out = *out; a.part = part; a.count = count;
   if (in->B > 0) {
     if (!in->row_off || !in->row_off_host || !in->head_logits) return ot_fail(OT_ERR_NULL, "%s: row_off, row_off_host and head_logits must not be NULL", who);

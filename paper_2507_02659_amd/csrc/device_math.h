@@ -27,6 +27,11 @@ __device__ inline double uniform(double x) {
   return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(x)), __builtin_amdgcn_readfirstlane(__double2loint(x)));
 }
 
+// The value that lane l holds (l the same in every lane), in every lane.
+__device__ inline double lane_value(double x, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l), __builtin_amdgcn_readlane(__double2loint(x), l));
+}
+
 // Sum over the 64 lanes in one fixed order, the result in every lane.  The partners come through data-parallel moves
 // inside a row of 16 lanes and row broadcasts above it: no trip through the LDS permute network, whose latency six steps
 // of __shfl_xor would pay one after the other.

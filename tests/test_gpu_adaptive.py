@@ -118,3 +118,30 @@ def test_adaptive_argument_errors():
         assert got["n_keep"].tolist() == [2, 1] and got["bce"] is None
     finally:
         ot.ot_verify_destroy(ctx)
+
+
+@pytest.mark.parametrize("B,k_max", [(1, 63), (5, 63), (64, 1), (1024, 9), (1025, 9)])
+def test_long_windows_and_many_sequences(B, k_max):
+    """One workgroup to 256 of them count their partials in (1024 sequences); with more the sum is a launch of its own."""
+    torch, oa, ot = _imports()
+    rng = np.random.default_rng(B)
+    k = rng.integers(0, k_max + 1, size=B)
+    k[-1] = k_max
+    row_off = np.concatenate([[0], np.cumsum(k + 1)]).astype(np.int32)
+    M = int(row_off[-1])
+    a = (rng.standard_normal(M) * 2.0 + 3.0).astype(np.float32)
+    labels = rng.uniform(0, 1, M).astype(np.float32)
+    n_valid = rng.integers(0, k_max + 2, size=B).astype(np.int32)
+    want = oa.stop_rule(row_off=row_off, head_logits=a, gamma=0.6, n_valid=n_valid)
+    bce = oa.weighted_bce(row_off=row_off, head_logits=a, labels=labels, w_accept=1.0, w_reject=6.0, n_valid=n_valid)
+    ctx = _context(ot, torch, max_batch=B, max_k=63)
+    try:
+        for _ in range(3):
+            got = _run(ot, torch, ctx, row_off, a, labels, n_valid, 0.6, 1.0, 6.0)
+            np.testing.assert_allclose(got["p_accept"], want["p_accept"], rtol=1e-6, atol=1e-38)
+            np.testing.assert_allclose(got["p_any_reject"], want["p_any_reject"], rtol=1e-6, atol=1e-7)
+            differ = np.flatnonzero(got["n_keep"] != want["n_keep"])
+            assert all(want["stop_margin"][b] < 1e-12 for b in differ), differ
+            assert got["bce"][1] == bce["count"] and got["bce"][0] == pytest.approx(bce["sum"], rel=1e-12)
+    finally:
+        ot.ot_verify_destroy(ctx)
