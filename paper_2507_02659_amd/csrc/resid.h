@@ -13,8 +13,10 @@
 //                    to the tile that holds u * total, re-forms that tile with each thread owning 4 consecutive ids,
 //                    scans the running sum in ascending id order and emits the first id whose running sum exceeds the
 //                    target (inverse CDF).  Which workgroup that is varies from run to run; what it computes does not.
-//                    When the residual is empty (reachable only through underflow) it first forms the masses of p, the
-//                    fallback distribution, by itself.
+//                    When the residual is empty (reachable only through underflow) it walks the masses of p, the
+//                    fallback distribution, instead: every workgroup leaves that of a tile without residual mass in its
+//                    place, negative (nothing to do in the common case; formed by the last workgroup alone, 32 such
+//                    sequences of 128256 ids took 50 us, 29 now).
 // Nothing waits: a workgroup that is not last simply ends.  A workgroup that has all tiles of its sequence (a small
 // vocabulary, or many sequences) keeps the masses in LDS and counts nothing: three round trips to memory less.
 // What bounds a small batch is the chain of instructions and round trips in one workgroup (16 x 128256 ids: 17 us of
@@ -222,7 +224,6 @@ __device__ inline int stage_draft_row(const void* zq, int dtype, int V_d, int ti
 }
 
 struct DrawLds {
-  double half[kTurnTiles];       // fallback: masses of the second halves of a turn's tiles
   double w[kPickThreads / 64];
   double base, target;
   int first[kPickThreads / 64], lastnz[kPickThreads / 64];
@@ -231,20 +232,30 @@ struct DrawLds {
 
 constexpr size_t kDrawLdsBytes = 150 << 10;    // dynamic LDS of a workgroup with a copy of the draft row at most (160 KB a compute unit)
 
-// Mass of the 512 ids from `lo` on (this lane: first + e * 64), in every lane.
+// Mass of the 512 ids from `lo` on (this lane: first + e * 64), in every lane: of the residual or, where that is zero, minus
+// that of p.
 __device__ inline double half_tile_mass(const FinalRow& R, int V_t, int first, int lo, const int* dv, const TileRaw<kPerLane>& raw) {
   double r[kPerLane];
-  tile_values<kPerLane>(R, V_t, first, 64, lo, lo + kResidTile / 2, dv, raw, r);
-  double sum = 0.0;
+  auto sum = [&](const FinalRow& S) {
+    tile_values<kPerLane>(S, V_t, first, 64, lo, lo + kResidTile / 2, dv, raw, r);
+    double x = 0.0;
 #pragma unroll
-  for (int e = 0; e < kPerLane; e += 4) sum += (r[e] + r[e + 1]) + (r[e + 2] + r[e + 3]);
-  return wave_sum(sum);
+    for (int e = 0; e < kPerLane; e += 4) x += (r[e] + r[e + 1]) + (r[e + 2] + r[e + 3]);
+    return wave_sum(x);
+  };
+  const double mass = sum(R);
+  if (!R.residual || !(mass == 0.0)) return mass;
+  FinalRow P = R;
+  P.residual = false;
+  return -sum(P);
 }
+// The same of a tile from its halves.
+__device__ inline double tile_mass(double a, double b) { return a <= 0.0 && b <= 0.0 ? a + b : fmax(a, 0.0) + fmax(b, 0.0); }
 
 // Workgroup `grp` of sequence b takes tiles [grp * group_tiles, (grp + 1) * group_tiles), group_tiles a multiple of
 // kTurnTiles (all kDrawThreads threads call this; f is the sequence's outcome record with f.mode != 0; dv holds tmap of
 // the ids draw_first_id(grp * group_tiles, wave, lane) + e * 64, e < kPerLane).  The dynamic LDS holds
-// max(ntiles, 2 * group_tiles) doubles and, if row_at > 0, from double row_at on room for the draft row and 32 bytes.
+// max(ntiles, 2 * group_tiles) doubles (twice ntiles where one workgroup has all tiles) and, if row_at > 0, from double row_at on room for the draft row and 32 bytes.
 __device__ inline void draw_final_token(const StepArgs& a, int b, int grp, int group_tiles, const FinalInfo& f, int* dv,
                                         DrawLds* L, int row_at) {
   double* s_tiles = s_draw_dynamic;
@@ -272,18 +283,18 @@ __device__ inline void draw_final_token(const StepArgs& a, int b, int grp, int g
   }
   __syncthreads();
   if (gridDim.x == 1) {                                  // all tiles are this workgroup's (at most kDrawThreads): they stay in LDS
-    const double mass = tid < a.ntiles ? s_tiles[2 * tid] + s_tiles[2 * tid + 1] : 0.0;
+    const double mass = tid < a.ntiles ? tile_mass(s_tiles[2 * tid], s_tiles[2 * tid + 1]) : 0.0;
     __syncthreads();
-    if (tid < a.ntiles) s_tiles[tid] = mass;
+    if (tid < a.ntiles) { s_tiles[tid] = fmax(mass, 0.0); s_tiles[a.ntiles + tid] = mass; }
   } else {
     for (int i = tid; i < tile1 - tile0; i += kDrawThreads)
-      publish(&a.tile_r[(int64_t)b * a.ntiles + tile0 + i], s_tiles[2 * i] + s_tiles[2 * i + 1]);
+      publish(&a.tile_r[(int64_t)b * a.ntiles + tile0 + i], tile_mass(s_tiles[2 * i], s_tiles[2 * i + 1]));
     stores_done();                                        // before this workgroup is counted
     __syncthreads();
     if (tid == 0) L->last = arrive(&a.resid_count[b], gridDim.x);
     __syncthreads();
     if (!L->last) return;
-    for (int t = tid; t < a.ntiles; t += kDrawThreads) s_tiles[t] = observe(&a.tile_r[(int64_t)b * a.ntiles + t]);
+    for (int t = tid; t < a.ntiles; t += kDrawThreads) s_tiles[t] = fmax(observe(&a.tile_r[(int64_t)b * a.ntiles + t]), 0.0);
   }
   __syncthreads();
 
@@ -324,19 +335,9 @@ __device__ inline void draw_final_token(const StepArgs& a, int b, int grp, int g
   __syncthreads();
   if (L->fallback) {                         // workgroup-uniform
     R.residual = false;
-    for (int t0 = 0; t0 < a.ntiles; t0 += kTurnTiles) {
-      const int tile = t0 + (wave >> 1), first = draw_first_id(t0, wave, lane);
-      double mass = 0.0;
-      if (tile < a.ntiles) {
-        TileRaw<kPerLane> raw;
-        load_tile<kPerLane>(R, a.V_t, first, 64, dv, raw);
-        mass = half_tile_mass(R, a.V_t, first, draw_first_id(t0, wave, 0), dv, raw);
-        if (lane == 0 && (wave & 1)) L->half[wave >> 1] = mass;
-      }
-      __syncthreads();
-      if (tile < a.ntiles && lane == 0 && !(wave & 1)) s_tiles[tile] = mass + L->half[wave >> 1];
-      __syncthreads();
-    }
+    for (int t = tid; t < a.ntiles; t += kDrawThreads)
+      s_tiles[t] = fabs(gridDim.x == 1 ? s_tiles[a.ntiles + t] : observe(&a.tile_r[(int64_t)b * a.ntiles + t]));
+    __syncthreads();
     if (wave == 0) pick_tile(false);
     __syncthreads();
   }

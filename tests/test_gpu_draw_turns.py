@@ -101,3 +101,28 @@ def test_masked_logits(temperature):
     gpu, ref, _ = _run_and_compare(case)
     drawn = ref["out_tokens"][ref["final_row"]]
     assert np.isfinite(case.target_logits[ref["final_row"], drawn]).all() and (ref["n_accept"] < ref["n_mapped"]).any()
+
+
+@pytest.mark.parametrize("B", [3, 120])                  # five workgroups of one turn, two of three turns
+def test_tiles_without_residual_mass(B):
+    """q' above p over a whole tile and over half of another: those have no residual mass, next to tiles that do (a draw from the
+    residual) and in sequences that have none anywhere (a draw from p)."""
+    ov, ot, Verifier, parity = _imports()
+    V_t, V_d = 40001, 1600
+    case = make_case(CaseSpec(name=f"no_mass_{B}", dtype="f32", d=8, V_t=V_t, V_d=V_d, k=[1] * B, temperature=[1.0] * B, n_direct=0,
+                              data_seed=96, philox_seed=14, logits_only=True))
+    case.direct_map[:] = -1
+    case.direct_map[1:1025] = np.arange(1024, 2048)
+    case.direct_map[1025:1537] = np.arange(5 * 1024, 5 * 1024 + 512)
+    case.target_logits[:] = 0
+    case.draft_logits[:] = 0
+    case.draft_ids[:] = 0                                # no image: the proposal is empty
+    for b in range(0, B, 3):                             # half of p and half of q' each on two ids of different tiles
+        case.target_logits[2 * b] = -2000.0
+        case.target_logits[2 * b, case.direct_map[[7, 1030]]] = 0
+        case.draft_logits[b] = -2000.0
+        case.draft_logits[b, [7, 1030]] = 0
+    gpu, ref, _ = _run_and_compare(case)
+    both = ot.OT_FLAG_UNMAPPABLE | ot.OT_FLAG_RESID_ZERO
+    assert gpu["flags"].tolist() == [both if b % 3 == 0 else ot.OT_FLAG_UNMAPPABLE for b in range(B)]
+    assert B < 10 or np.unique(gpu["out_tokens"][0::6]).size == 2          # both of them are drawn
