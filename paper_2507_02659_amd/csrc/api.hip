@@ -3,6 +3,7 @@
 // the method itself.
 #include <algorithm>
 #include <cstdarg>
+#include <cstdlib>
 #include <cstdio>
 #include <cstring>
 #include <new>
@@ -101,8 +102,10 @@ int ot_verify_init(const ot_verify_config* cfg, ot_ctx** out) {
   } catch (const std::bad_alloc&) {
     return fail(OT_ERR_NOMEM, "ot_verify_init: host allocation failed");
   }
+  size_t n_near = 0;
   for (size_t t = 0, at = pairs_at; t < (size_t)cfg->V_t; ++t) {
     if (tmap_h[t] == -1) continue;
+    if (at > pairs_at && std::abs(tmap_h[t] - tmap_h[at - 1]) <= 32) n_near += 1;
     tmap_h[at++] = (int32_t)t;
     tmap_h[at++] = tmap_h[t];
   }
@@ -155,6 +158,7 @@ int ot_verify_init(const ot_verify_config* cfg, ot_ctx** out) {
   if (e == hipSuccess) e = hipMemcpyAsync(c->tmap, tmap_h.data(), sizeof(int32_t) * tmap_h.size(), hipMemcpyHostToDevice, c->stream);
   c->pairs = reinterpret_cast<const int2*>(c->tmap + pairs_at);
   c->n_pairs = (int32_t)n_pairs;
+  c->local_pairs = 2 * n_near >= n_pairs;
   if (e == hipSuccess) {
     if (c->dtype == OT_BF16)
       e = launch_pack_w_bf16(static_cast<const uint16_t*>(cfg->W), c->d, c->V_t, c->Wp, c->Kp, c->Vp, c->stream);

@@ -12,15 +12,15 @@
 // wavefront forms the constants of p and q' at that position (LossRow) and, in group 0, the row's NLL and lambda, while
 // the others copy the draft row to LDS; then the workgroup sums q' (ln q' - ln p) over its terms in binary64 (optionally
 // writing q', Eq. 2, as fp32), publishes the sum and counts itself in at its row.  The last workgroup of a row adds the
-// groups' sums in ascending order and counts the row in; the last of all forms the totals, in a fixed order.  A row
+// groups' sums in a fixed order and counts the row in; the last of all forms the totals, in a fixed order.  A row
 // without a KL term is counted in by its group 0 alone.  Nothing waits for another workgroup.
 //
 // The terms are the mapped pairs (target id, draft id), listed once per context in ascending target id: a quarter of the
 // target ids where a 32000-id drafter meets a 128256-id target, and the logits are still read in order.  With every target
 // id visited the launch took 39 us at 144 rows, bound by its binary64 instructions.  Now it is bound by the chain of round
 // trips in a workgroup: 60 to 100 rows of 128256 ids are 32 to 52 MB, 5 to 8 us at the rate of a large copy.
-// Measured, us per call: 144 rows x 128256 ids 24.5, against 37.2 for four launches (constants 7.6, tiles of 1024 ids with
-// the gather from memory 31, sums per row 4.8, totals 4.0); 6 rows 12.6 / 20.3; 370 rows x 152064 ids 51 / 94.
+// Measured, us per call: 144 rows x 128256 ids 21.5, against 42.8 for four launches (in the kernel trace: constants 7.6, tiles
+// of 1024 ids with the gather from memory 30.9, sums per row 4.8, totals 4.0); 9 rows x 100000 ids 12.6 / 19.7.
 #include <algorithm>
 
 #include "device_math.h"
@@ -30,9 +30,7 @@
 namespace otv {
 namespace {
 
-constexpr int kThreads = kDrawThreads;
-constexpr int kWaves = kDrawWaves;
-constexpr int kPerTurn = 8;                   // ids per thread and turn, kThreads apart
+constexpr int kPerTurn = 8;                   // terms per thread and turn, a workgroup's threads apart
 
 struct LossRow {
   int32_t t_ng, t_pre;   // Eq. 2 overrides: target id of the n-gram / direct image of its first sub-token, or -1
@@ -109,6 +107,7 @@ __device__ inline LossRow make_loss_row(const LossArgs& a, int row, int kind, in
 }
 
 // Sum of x over the workgroup in a fixed order, valid in thread 0.
+template <int kWaves>
 __device__ inline double block_sum(double x, double* s_w, int wave, int lane) {
   x = wave_sum(x);
   if (lane == 0) s_w[wave] = x;
@@ -118,23 +117,40 @@ __device__ inline double block_sum(double x, double* s_w, int wave, int lane) {
   return total;
 }
 
-// The sums over all rows and the mean over the drafted tokens considered.
+// The sums over all rows and the mean over the drafted tokens considered.  Everything about a few rows is asked for before any
+// of it is looked at: one round trip to memory for four rows per thread.
+template <int kWaves>
 __device__ inline void loss_totals(const LossArgs& a, double (*s_term)[kWaves], int tid, int wave, int lane) {
+  constexpr int kAtOnce = 4, kThreads = 64 * kWaves;
   double term[4] = {0.0, 0.0, 0.0, 0.0};                // direct, n-gram, direct tokens, n-gram sub-tokens
-  for (int row = tid; row < a.M; row += kThreads) {
-    const int kind = observe(a.out.kind + row);
-    if (kind == 1) {
-      term[0] += observe(a.out.kl + row);
-      term[2] += 1.0;
-    } else if (kind == 2) {
-      const double x = a.ngram_term == OT_NGRAM_TERM_APPROX_KL ? observe(a.out.kl + row) : observe(a.out.nll + row);
-      term[1] += observe(a.out.weight + row) * x;
-      term[3] += (double)a.span_len[row];
+  double* other = a.ngram_term == OT_NGRAM_TERM_APPROX_KL ? a.out.kl : a.out.nll;
+  for (int row0 = tid; row0 < a.M; row0 += kAtOnce * kThreads) {
+    int kind[kAtOnce], len[kAtOnce];
+    double kl[kAtOnce], x[kAtOnce], weight[kAtOnce];
+#pragma unroll
+    for (int j = 0; j < kAtOnce; ++j) {
+      const int row = min(row0 + j * kThreads, a.M - 1);
+      kind[j] = observe(a.out.kind + row);
+      kl[j] = observe(a.out.kl + row);
+      x[j] = observe(other + row);
+      weight[j] = observe(a.out.weight + row);
+      len[j] = a.span_len[row];
+    }
+#pragma unroll
+    for (int j = 0; j < kAtOnce; ++j) {
+      if (row0 + j * kThreads >= a.M) break;
+      if (kind[j] == 1) {
+        term[0] += kl[j];
+        term[2] += 1.0;
+      } else if (kind[j] == 2) {
+        term[1] += weight[j] * x[j];
+        term[3] += (double)len[j];
+      }
     }
   }
   double t[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) t[i] = block_sum(term[i], s_term[i], wave, lane);
+  for (int i = 0; i < 4; ++i) t[i] = block_sum<kWaves>(term[i], s_term[i], wave, lane);
   if (tid == 0) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) a.out.totals[i] = t[i];
@@ -144,6 +160,7 @@ __device__ inline void loss_totals(const LossArgs& a, double (*s_term)[kWaves], 
 
 // Terms i = first + e * kThreads of n: mapped pairs in ascending target id, or every target id with its pre-image (past the
 // end the last one, masked later).
+template <int kThreads>
 __device__ inline void load_terms(const LossArgs& a, bool pairs, int n, int first, int2* id) {
   if (n == 0) {                                          // nothing is mapped
 #pragma unroll
@@ -160,16 +177,21 @@ __device__ inline void load_terms(const LossArgs& a, bool pairs, int n, int firs
   }
 }
 
-__global__ __launch_bounds__(kThreads) void loss_kernel(LossArgs a, int group_terms, int staged) {
+// Grid: row r's workgroups (`groups` of them) run on XCD r % 8 back to back, so that they meet in its L2, where a draft row that
+// is gathered from memory stays while they do.
+template <int kThreads>
+__global__ __launch_bounds__(kThreads, 4) void loss_kernel(LossArgs a, int groups, int group_terms, int staged) {
+  constexpr int kWaves = kThreads / 64;
   __shared__ LossRow s_row;
   __shared__ double s_term[4][kWaves];
   __shared__ int s_last;
-  const int row = blockIdx.y, grp = blockIdx.x, tid = threadIdx.x;
-  const int wave = uniform(tid >> 6), lane = tid & 63;
-  if (a.M == 0) {                                        // an empty batch: one workgroup
-    loss_totals(a, s_term, tid, wave, lane);
+  const int tid = threadIdx.x, wave = uniform(tid >> 6), lane = tid & 63;
+  const int slot = (int)blockIdx.x >> 3, row = slot / groups * 8 + ((int)blockIdx.x & 7), grp = slot % groups;
+  if (a.M == 0) {                                        // an empty batch
+    if (blockIdx.x == 0) loss_totals<kWaves>(a, s_term, tid, wave, lane);
     return;
   }
+  if (row >= a.M) return;                                // padding of the id space
   const bool pairs = a.out.qprime == nullptr;            // terms: the mapped pairs, or (q' is wanted everywhere) all ids
   const int n_terms = pairs ? a.n_pairs : a.V_t;
   const int i0 = grp * group_terms, i1 = min(i0 + group_terms, n_terms);
@@ -177,8 +199,8 @@ __global__ __launch_bounds__(kThreads) void loss_kernel(LossArgs a, int group_te
   const float* z = a.Z + (int64_t)row * a.ldz;
   int2 id[kPerTurn], id_next[kPerTurn] = {};             // (target id, draft id or -1)
   float zv[kPerTurn];
-  load_terms(a, pairs, n_terms, i0 + tid, id);
-  if (i0 + kPerTurn * kThreads < i1) load_terms(a, pairs, n_terms, i0 + tid + kPerTurn * kThreads, id_next);
+  load_terms<kThreads>(a, pairs, n_terms, i0 + tid, id);
+  if (i0 + kPerTurn * kThreads < i1) load_terms<kThreads>(a, pairs, n_terms, i0 + tid + kPerTurn * kThreads, id_next);
 #pragma unroll
   for (int e = 0; e < kPerTurn; ++e) zv[e] = z[id[e].x];
   const int s = a.span_start[row], L = a.span_len[row], t = a.mapped_ids[row];
@@ -212,7 +234,7 @@ __global__ __launch_bounds__(kThreads) void loss_kernel(LossArgs a, int group_te
   double kl = 0.0;
   if (visit) {
     int lds_at = -1;
-    if (staged) lds_at = stage_draft_row(zq, a.dtype, a.V_d, tid, 0);
+    if (staged) lds_at = stage_draft_row<kThreads>(zq, a.dtype, a.V_d, tid, 0);
     __syncthreads();
     const LossRow R = s_row;
     for (int at = i0 + tid; at - tid < i1; at += kPerTurn * kThreads) {
@@ -227,7 +249,7 @@ __global__ __launch_bounds__(kThreads) void loss_kernel(LossArgs a, int group_te
 #pragma unroll
         for (int e = 0; e < kPerTurn; ++e) z_next[e] = z[id_next[e].x];
       }
-      if (at - tid + 2 * kPerTurn * kThreads < i1) load_terms(a, pairs, n_terms, at + 2 * kPerTurn * kThreads, id_after);
+      if (at - tid + 2 * kPerTurn * kThreads < i1) load_terms<kThreads>(a, pairs, n_terms, at + 2 * kPerTurn * kThreads, id_after);
 #pragma unroll
       for (int e = 0; e < kPerTurn; ++e) {
         const int v = id[e].x;
@@ -247,35 +269,57 @@ __global__ __launch_bounds__(kThreads) void loss_kernel(LossArgs a, int group_te
     // the n-gram's target id, where it is no draft id's image and so in no pair
     if (pairs && grp == 0 && tid == 0 && R.t_ng >= 0 && a.tmap[R.t_ng] < 0 && R.pi > 0.0)
       kl += R.pi * (R.ln_pi - (((double)z[R.t_ng] - R.mx) * R.invT - R.lnS));
-    kl = need_kl ? block_sum(kl, s_term[0], wave, lane) : 0.0;
+    kl = need_kl ? block_sum<kWaves>(kl, s_term[0], wave, lane) : 0.0;
   }
-  if (tid == 0) {
-    bool row_done = true;
-    if (need_kl) {
-      double* part = a.part + (int64_t)row * gridDim.x;
-      publish(part + grp, kl);
-      row_done = arrive(a.count + 1 + row, gridDim.x);
-      kl = 0.0;
-      if (row_done)
-        for (int g = 0; g < (int)gridDim.x; ++g) kl += observe(part + g);
-    } else {
-      row_done = grp == 0;
+  if (wave == 0) {
+    bool row_done = need_kl || grp == 0;
+    if (need_kl && groups > 1) {
+      double* part = a.part + (int64_t)row * groups;
+      int last = 0;
+      if (lane == 0) {
+        publish(part + grp, kl);
+        last = arrive(a.count + 1 + row, groups);
+      }
+      row_done = uniform(last) != 0;
+      kl = row_done ? wave_sum(lane < groups ? observe(part + lane) : 0.0) : 0.0;   // a wavefront holds all groups
     }
-    s_last = 0;
-    if (row_done) {
-      publish(a.out.kl + row, kl);
-      s_last = arrive(a.count, a.M);
+    if (lane == 0) {
+      s_last = 0;
+      if (row_done) {
+        publish(a.out.kl + row, need_kl ? kl : 0.0);
+        s_last = arrive(a.count, a.M);
+      }
     }
   }
   __syncthreads();
-  if (s_last) loss_totals(a, s_term, tid, wave, lane);
+  if (s_last) loss_totals<kWaves>(a, s_term, tid, wave, lane);
 }
 
-// Groups of terms per row: one workgroup per compute unit over all rows (about half of them carry a term), but no fewer
-// terms in one than a turn takes.  Two per compute unit: 27.5 against 24.5 us at 144 rows, 45.6 against 42.0 with q'
-// written for 300 rows of 60000 ids.
-int loss_groups(int M, int n_terms, int n_cu) {
-  return std::max(1, std::min({kLossGroups, ceil_div(n_terms, kPerTurn * kThreads), ceil_div(n_cu, std::max(M, 1))}));
+// How a launch is split: threads per workgroup, the draft row in LDS or gathered from memory, groups of terms per row.  A
+// workgroup is a chain of about eight round trips, so a compute unit should hold several: 126 registers leave room for sixteen
+// wavefronts, the copies of the draft row for as many workgroups as fit into LDS: four of 256 threads up to 40 KB, two of 512
+// up to 78 KB, one of 1024 up to 150 KB.  Above that the logits are gathered, and where a row's logits lie in the order of its terms
+// (`local`: one vocabulary on both sides, or nearly) already from 78 KB on: neighbouring lanes then read the same line.  Gathered
+// at random, a row has to stay in the L2 of its XCD (4 MB) while its workgroups are at it: enough groups per row that the 128
+// workgroups which the XCD holds work on 2 MB of rows.  Otherwise as many groups as fill the chip, and no more than eight turns
+// in one where nothing was copied.
+// Measured, us per call (1024 threads, at most 16 groups | four launches | now): 144 rows x 128256 ids with 32000 draft ids
+// 24.3 | 42.8 | 21.5, 432 rows x 152064 53 | 100 | 45; 1024 rows x 5000 with 2000 37.5 | 25.7 | 17.9; 1200 x 32000 with 32000
+// 97 | 77 | 78.5; fp32, 1024 x 32000 with 32000 in order 87 | 65 | 66; fp32, 60000 draft ids at random, 432 rows 167 | 107 | 89, 1024
+// rows 477 | 276 | 282.  Still behind the four launches, whose constants were formed once a row: 1200 rows x 600 ids 43 | 20 | 23.
+struct LossPlan { int threads, staged, groups, group_terms; };
+LossPlan loss_plan(int M, int n_terms, int64_t row_bytes, bool local, int n_cu) {
+  LossPlan p;
+  p.staged = row_bytes <= (local ? 78 << 10 : (int64_t)kDrawLdsBytes);
+  p.threads = !p.staged || row_bytes <= 40 << 10 ? 256 : row_bytes <= 78 << 10 ? 512 : 1024;
+  const int turn = kPerTurn * p.threads;
+  int want = ceil_div((int64_t)(1024 / p.threads) * n_cu, std::max(M, 1));
+  if (!p.staged) want = std::max(want, ceil_div(n_terms, 8 * turn));
+  if (!p.staged && !local) want = std::max(want, (int)std::min<int64_t>(kLossGroups, 128 * row_bytes / (2 << 20)));
+  const int turns = std::max(1, ceil_div(n_terms, (int64_t)std::max(1, std::min({kLossGroups, ceil_div(n_terms, turn), want})) * turn));
+  p.group_terms = turns * turn;
+  p.groups = std::max(1, ceil_div(n_terms, p.group_terms));
+  return p;
 }
 
 }  // namespace
@@ -324,12 +368,13 @@ int ot_distill_loss(ot_ctx* ctx, const ot_step_in* in, const ot_step_out* step, 
 
   hipStream_t st = ctx->stream;
   const int n_terms = out->qprime ? a.V_t : a.n_pairs;
-  const int turns = std::max(1, ceil_div(n_terms, loss_groups(M, n_terms, ctx->n_cu) * kPerTurn * kThreads));
-  const int groups = std::max(1, ceil_div(n_terms, turns * kPerTurn * kThreads));
-  const size_t row_bytes = (size_t)a.V_d * (a.dtype == OT_BF16 ? 2 : 4) + 32;
-  const int staged = row_bytes <= kDrawLdsBytes;         // gathered from memory instead: 27 against 24.5 us at 144 rows
-  hipLaunchKernelGGL(loss_kernel, dim3(groups, std::max(M, 1)), dim3(kThreads), staged ? row_bytes : 16, st, a,
-                     turns * kPerTurn * kThreads, staged);
+  const int64_t row_bytes = (int64_t)a.V_d * (a.dtype == OT_BF16 ? 2 : 4) + 32;
+  const LossPlan p = loss_plan(M, n_terms, row_bytes, ctx->local_pairs, ctx->n_cu);
+  const dim3 grid((unsigned)(p.groups * ceil_div(std::max(M, 1), 8) * 8)), block(p.threads);
+  const size_t lds = p.staged ? row_bytes : 16;
+  if (p.threads == 1024) hipLaunchKernelGGL(loss_kernel<1024>, grid, block, lds, st, a, p.groups, p.group_terms, p.staged);
+  else if (p.threads == 512) hipLaunchKernelGGL(loss_kernel<512>, grid, block, lds, st, a, p.groups, p.group_terms, p.staged);
+  else hipLaunchKernelGGL(loss_kernel<256>, grid, block, lds, st, a, p.groups, p.group_terms, p.staged);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return ot_fail_hip(e, "ot_distill_loss: launch");
   return OT_OK;

@@ -24,6 +24,7 @@ struct ot_ctx {
   int32_t *dmap = nullptr, *tmap = nullptr;
   const int2* pairs = nullptr;        // [n_pairs] (target id, draft id) of the direct map in ascending target id, behind tmap
   int32_t n_pairs = 0;
+  bool local_pairs = false;           // neighbouring pairs are mostly neighbours among the draft ids as well
   float* Z = nullptr;
   float *tpart_max = nullptr, *dpart_max = nullptr, *row_max = nullptr, *drow_max = nullptr;
   double *tpart_sum = nullptr, *dpart_sum = nullptr, *row_sum = nullptr, *drow_sum = nullptr;

@@ -24,7 +24,7 @@ constexpr int kGemmTileGapUnits = 1032;
 constexpr int64_t packed_tile_units(int nks) { return (int64_t)nks * 256 + kGemmTileGapUnits; }
 // the same for the fp32 head: nkb 16-deep blocks of 4 x 64 float4
 constexpr int64_t packed_f32_tile_units(int nkb) { return (int64_t)nkb * 256 + kGemmTileGapUnits; }
-constexpr int kLossGroups = 16;      // workgroups per row of the distillation loss at most
+constexpr int kLossGroups = 64;      // workgroups per row of the distillation loss at most: a wavefront adds their sums
 
 inline int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 

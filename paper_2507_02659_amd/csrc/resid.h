@@ -191,6 +191,7 @@ __device__ inline int draw_first_id(int tile0, int wave, int lane) {
 // Copies the draft row to byte `at` of the dynamic LDS (all threads call it, a barrier follows): whole 16-byte chunks where
 // the row covers them, element by element at its ends, each byte at its own offset within a chunk.  Returns where the row
 // starts there.
+template <int kThreads>
 __device__ inline int stage_draft_row(const void* zq, int dtype, int V_d, int tid, int at) {
   const int esz = dtype == OT_BF16 ? 2 : 4;
   const char* row = static_cast<const char*>(zq);
@@ -200,16 +201,16 @@ __device__ inline int stage_draft_row(const void* zq, int dtype, int V_d, int ti
   const lds_chars s_row = draw_lds() + at;
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   constexpr int kAtOnce = 4;
-  for (int c0 = tid; c0 < chunks; c0 += kAtOnce * kDrawThreads) {
+  for (int c0 = tid; c0 < chunks; c0 += kAtOnce * kThreads) {
     u32x4 x[kAtOnce];
 #pragma unroll
     for (int j = 0; j < kAtOnce; ++j) {                    // any other chunk number loads the nearest of those
-      const int c = min(max(c0 + j * kDrawThreads, whole0), whole1 - 1);
+      const int c = min(max(c0 + j * kThreads, whole0), whole1 - 1);
       x[j] = whole0 < whole1 ? *reinterpret_cast<const u32x4*>(row + (c * 16 - head)) : u32x4{0, 0, 0, 0};
     }
 #pragma unroll
     for (int j = 0; j < kAtOnce; ++j) {
-      const int c = c0 + j * kDrawThreads, from = c * 16 - head;
+      const int c = c0 + j * kThreads, from = c * 16 - head;
       if (c >= whole0 && c < whole1) {
         *(__attribute__((address_space(3))) u32x4*)(s_row + c * 16) = x[j];
       } else if (c < chunks) {
@@ -263,7 +264,7 @@ __device__ inline void draw_final_token(const StepArgs& a, int b, int grp, int g
   FinalRow R = make_final_row(a, f);
   const int tile0 = grp * group_tiles, tile1 = min(tile0 + group_tiles, a.ntiles);
   if (row_at > 0 && R.residual && !R.greedy_draft) {     // workgroup-uniform
-    R.lds_at = stage_draft_row(R.zq, R.dtype, a.V_d, tid, 8 * row_at);
+    R.lds_at = stage_draft_row<kDrawThreads>(R.zq, R.dtype, a.V_d, tid, 8 * row_at);
     __syncthreads();
   }
 
