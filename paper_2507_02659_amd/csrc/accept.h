@@ -95,13 +95,16 @@ __device__ __forceinline__ void merge_chunk_row(const float* __restrict__ pmax, 
   wave_publish_row(r, sc, row, lane, s_mx, s_S, s_arg, at, to_workspace, g_mx, g_S, g_arg, invT, exact);
 }
 
-// Statistics of draft row q from the chunk partials of the statistics launch (ascending chunks): lane-local.
+// Statistics of draft row q from the chunk partials of the statistics launch (ascending chunks): lane-local.  kWide: the row may
+// have more than kChunksAtOnce chunks (compiled in where it has not, the binary64 exponential costs every step 0.3 us).
+constexpr int kChunksAtOnce = 4;                           // chunks asked for before any of them is looked at
+template <bool kWide>
 __device__ __forceinline__ void merge_draft_chunks(const StepArgs& a, int q, float Td, float* out_mx, double* out_S, int* out_arg,
                                           bool exact) {
   const int64_t o = (int64_t)q * a.nchd;
   const float sc = Td > 0.f ? kLog2eF / Td : kLog2eF;
   const double invTd = Td > 0.f ? 1.0 / (double)Td : 1.0;
-  constexpr int kAtOnce = 4;                               // chunks asked for before any of them is looked at
+  constexpr int kAtOnce = kChunksAtOnce;
   RunStat r;
   for (int c0 = 0; c0 < a.nchd; c0 += kAtOnce) {
     float m[kAtOnce];
@@ -118,10 +121,11 @@ __device__ __forceinline__ void merge_draft_chunks(const StepArgs& a, int q, flo
       if (c0 + j < a.nchd && m[j] > r.mx) { r.mx = m[j]; r.arg = arg[j]; }   // ascending chunks: a later equal maximum does not replace
     // in binary64 always: a factor per group of chunks, each with the error of a binary32 2^x, would add up in the sums of the
     // first chunks, which carry one such error already
-    if (before != -INFINITY && r.mx > before) r.sum *= rescale(before, r.mx, sc, invTd, true);
+    if (kWide && before != -INFINITY && r.mx > before) r.sum *= rescale(before, r.mx, sc, invTd, true);
 #pragma unroll
     for (int j = 0; j < kAtOnce; ++j)
       if (c0 + j < a.nchd && m[j] != -INFINITY) r.sum += sum[j] * rescale(m[j], r.mx, sc, invTd, exact);
+    if (!kWide) break;
   }
   *out_mx = r.mx; *out_S = r.sum; *out_arg = r.arg;
 }

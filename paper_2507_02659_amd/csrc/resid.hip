@@ -41,7 +41,8 @@ constexpr int64_t kRepeatedMergeBytes = 32 << 20;
 // LM head's epilogue and draft-row pieces.
 // kMany: more than kFusedMaxB sequences: row offsets from memory, partials merged in binary64 (as a runtime flag these two
 // cost a single sequence 0.7 of 13 us).
-template <bool kDraw, bool kChunks, bool kMany>
+// kWide: draft rows of more than kChunksAtOnce chunks (merge_draft_chunks).
+template <bool kDraw, bool kChunks, bool kMany, bool kWide = kMany>
 __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, RowOffsets ro, int group_tiles, int row_at) {
   const int b = blockIdx.y, grp = blockIdx.x, tid = threadIdx.x;
   const int wave = uniform(tid >> 6), lane = tid & 63;
@@ -79,7 +80,7 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, R
     s_d.hit[lane] = rec->hit[lane]; s_d.zq[lane] = rec->zq[lane]; s_d.dm[lane] = rec->dm[lane];
     if (lane < k) {
       float mxq; double Sq; int argq;
-      if (kChunks) merge_draft_chunks(a, q0 + lane, Td, &mxq, &Sq, &argq, kMany);
+      if (kChunks) merge_draft_chunks<kWide>(a, q0 + lane, Td, &mxq, &Sq, &argq, kMany);
       else merge_draft_pieces(a, q0 + lane, Td, &mxq, &Sq, &argq);
       s_d.qmx[lane] = mxq; s_d.qS[lane] = Sq; s_d.qarg[lane] = argq;
       if (lead) { a.drow_max[q0 + lane] = mxq; a.drow_sum[q0 + lane] = Sq; a.drow_arg[q0 + lane] = argq; }
@@ -156,6 +157,7 @@ hipError_t launch_final_draw(const StepArgs& a, const int32_t* row_off_host, int
   for (int b = 0; b <= kFusedMaxB; ++b) ro.v[b] = row_off_host[b <= a.B ? b : a.B];
   if (!a.hosted) {                                         // a few chunks per row: always one launch
     if (a.B > kFusedMaxB) hipLaunchKernelGGL((accept_draw_kernel<true, true, true>), grid, block, lds, stream, a, ro, group_tiles, row_at);
+    else if (a.nchd > kChunksAtOnce) hipLaunchKernelGGL((accept_draw_kernel<true, true, false, true>), grid, block, lds, stream, a, ro, group_tiles, row_at);
     else hipLaunchKernelGGL((accept_draw_kernel<true, true, false>), grid, block, lds, stream, a, ro, group_tiles, row_at);
     return hipGetLastError();
   }
