@@ -306,7 +306,7 @@ int ot_verify_workspace(ot_ctx* ctx, ot_workspace_view* view);
 #define OT_STAGE_LM_HEAD          0   /* z = h . W                                                            */
 #define OT_STAGE_SOFTMAX_STATS    1   /* softmax statistics of the target and draft rows; 0 when the LM-head
                                          launch computes them itself                                          */
-#define OT_STAGE_TRANSLATE_ACCEPT 2   /* nothing: translation and acceptance test run in the launch of the next stage */
+#define OT_STAGE_TRANSLATE_ACCEPT 2   /* 0: translation and acceptance test run in the launch of the next stage */
 #define OT_STAGE_RESIDUAL_DRAW    3   /* masses of max(0, p - q') (Eq. 2) at the final row, inverse-CDF draw  */
 #define OT_N_STAGES               4
 int ot_verify_profile(ot_ctx* ctx, int32_t enable);

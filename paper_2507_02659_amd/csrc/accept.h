@@ -33,7 +33,7 @@ __device__ __forceinline__ void wave_publish_row(const RunStat& r, float sc, int
 
 // Merges the LM head's partials of one target row (nfine of them, one per column tile): called by a whole wavefront.
 // A lane requests eight 16-byte partials at a time before it looks at any of them (one round trip to memory for up
-// to 512 tiles) and keeps a running maximum with the sum rescaled to it; the lanes are then merged by shuffles.  Sums
+// to 512 tiles) and keeps a running maximum with the sum rescaled to it; the lanes are then merged (wave_publish_row).  Sums
 // are rescaled and added in binary64, in a fixed order.  Lane 0 publishes the row's (max, sum, argmax) to LDS and to
 // the workspace.
 __device__ inline void merge_fused_row(const Partial* __restrict__ part, int nfine, int row, double invT, int lane,
@@ -131,11 +131,11 @@ __device__ __forceinline__ void merge_draft_chunks(const StepArgs& a, int q, flo
 }
 
 // The acceptance test of sequence b by one wavefront (lane = mapped position).  P is the lane's proposal (P.m, P.flags
-// wavefront-uniform), s_pmx / s_pS / s_parg the statistics of the sequence's target rows; z_tok, if `have_z`, is
-// z[row lane, t_lane] fetched by the caller.  With write_out the per-row and per-sequence outputs of the test are
+// wavefront-uniform), s_pmx / s_pS / s_parg the statistics of the sequence's target rows; z_tok is z[row lane, t_lane]
+// (lanes of the proposal).  With write_out the per-row and per-sequence outputs of the test are
 // written.  Returns the outcome record (valid in lane 0).
 __device__ inline FinalInfo accept_wave(const StepArgs& a, int b, int r0, int k, int q0, float T, float Td, double invT,
-                                        double invTd, uint64_t sid, const LaneProposal& P, bool have_z, float z_tok,
+                                        double invTd, uint64_t sid, const LaneProposal& P, float z_tok,
                                         const float* s_pmx, const double* s_pS, const int* s_parg, int lane,
                                         bool write_out) {
   FinalInfo fin;
@@ -165,8 +165,7 @@ __device__ inline FinalInfo accept_wave(const StepArgs& a, int b, int r0, int k,
   if (lane < m) {
     qp = exp(P.lq);
     if (T > 0.f) {
-      const double z = (double)(have_z ? z_tok : a.Z[(int64_t)(r0 + lane) * a.ldz + t_j]);
-      pt = exp((z - (double)mx) * invT) / S;
+      pt = exp(((double)z_tok - (double)mx) * invT) / S;
       if (qp > 0.0) ratio = fmin(1.0, pt / qp);
       else ratio = pt > 0.0 ? 1.0 : 0.0;
       ok = u24(w[0]) < ratio;

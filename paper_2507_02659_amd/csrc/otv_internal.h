@@ -12,7 +12,7 @@ namespace otv {
 // ------------------------------------------------------------------------------------------------ geometry
 constexpr int kStatThreads = 256;
 constexpr int kStatChunk = 8192;     // logits per workgroup of the softmax-statistics kernel (measured: 4096 and 16384 are slower)
-constexpr int kResidTile = 1024;     // vocabulary entries per workgroup of the residual kernel
+constexpr int kResidTile = 1024;     // target ids per tile of the final draw; a workgroup takes 8 to 512 consecutive tiles
 constexpr int kGemmColsPerWave = 64; // LM-head columns owned by one wavefront
 constexpr int kGemmKPad = 128;       // packed K extent is a multiple of this
 // Gap, in 16-byte units, between the packed weights of consecutive 64-column tiles.  Without it the tiles of a
@@ -47,7 +47,7 @@ constexpr int kCachePatchCap = 1024;  // slots that travel as a packed patch; mo
 
 // What the drafted ids of one sequence look up, none of which needs the target's logits: per draft position the longest
 // n-gram cache hit that starts there, the drafted id's own logit and its direct image.  Written by a workgroup of the
-// LM-head launch, read by the launch that follows it (which walks the window, Eq. 1, and tests acceptance).
+// LM-head or the statistics launch, read by the launch that follows it (which walks the window, Eq. 1, and tests acceptance).
 struct ProbeRecord {
   unsigned long long hit[64];   // (length << 60) | (slot << 32) | target, 0 = no hit
   float zq[64];                 // draft logit of the drafted id
@@ -57,7 +57,8 @@ struct ProbeRecord {
 };
 
 // ------------------------------------------------------------------------------------------------ per-step view
-// What the final-token kernels need to know about sequence b; written by the translate-and-accept kernel.
+// What the draw of the final token needs to know about sequence b: the outcome of its acceptance test (accept_wave), in LDS or,
+// where the test has a launch of its own, in memory.
 struct FinalInfo {
   int32_t mode;          // 0: nothing to draw (greedy, or bad id), 2: draw from p (free token), 3: draw from the residual
   int32_t row;           // global row of the final token (row_off[b] + n_b)
@@ -151,7 +152,7 @@ struct StepArgs {
   int64_t ldz;
   int32_t ncht, nchd;    // statistic chunks per target / draft row
   float* tpart_max; double* tpart_sum; int32_t* tpart_arg;   // [M, ncht]
-  FusedStats fused;      // fused.nfine > 0: the LM head left fine partials; the statistics kernel merges them per row
+  FusedStats fused;      // fused.nfine > 0: the LM head left partials, which accept_draw_kernel merges per row
   float* dpart_max; double* dpart_sum; int32_t* dpart_arg;   // [K, nchd]
   float* row_max; double* row_sum; int32_t* row_arg;         // [M]
   float* drow_max; double* drow_sum; int32_t* drow_arg;      // [K]
@@ -183,8 +184,8 @@ bool lmhead_bf16_hosts_draft_side(int M, int d, int Vp, int B, int K, int V_d, i
 int lmhead_bf16_draft_workers(int M, int d, int Vp, int B, int K, int n_cu);
 // `fused` may be nullptr or have part == nullptr (no statistics); otherwise fused->nfine must be
 // lmhead_bf16_fused_partials(M, d, Vp, n_cu) > 0 and fused->B <= kFusedMaxB.  With fused statistics and `draft_side` not
-// nullptr, the workgroups of the launch also compute the softmax statistics of the draft rows of *draft_side (one row
-// each, before their main loop) into its drow_* arrays.
+// nullptr, the launch also hosts the draft side of *draft_side: statistics of pieces of the draft rows into its dpiece, shared
+// out by its plan, and the drafted ids' lookups into its probe records.
 hipError_t launch_lmhead_bf16(const uint16_t* H, int M, int d, const uint16_t* Wp, int Kp, int Vp, float* Z, int V_t,
                               int64_t ldz, const uint16_t* zeros, const FusedStats* fused, const StepArgs* draft_side,
                               int n_cu, hipStream_t stream);

@@ -7,7 +7,7 @@
 // and the direct image of its first sub-token gets q_s(d_1) - pi.  When everything was accepted the draw is from p.
 //
 // Only the ONE row per sequence where the draw happens is touched.  A workgroup of 16 wavefronts takes a run of
-// consecutive tiles of kResidTile target ids of one sequence (draw_groups), eight at a time, two wavefronts per tile:
+// consecutive tiles of kResidTile target ids of one sequence (draw_group_tiles), eight at a time, two wavefronts per tile:
 //   every workgroup  forms the masses of max(0, p - q') of its tiles in binary64, publishes them and counts itself in;
 //   the workgroup that arrives last for its sequence  walks the tile masses in ascending order with a wavefront scan
 //                    to the tile that holds u * total, re-forms that tile with each thread owning 4 consecutive ids,

@@ -110,7 +110,7 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, R
   if (kDraw) load_tmap<kPerLane>(a.tmap, a.V_t, draw_first_id(grp * group_tiles, wave, lane), 64, dv);
   __syncthreads();
   if (wave == kTestWave) {
-    const FinalInfo fin = accept_wave(a, b, r0, k, q0, T, Td, invT, invTd, sid, P, true, z_tok, s_pmx, s_pS, s_parg, lane, lead);
+    const FinalInfo fin = accept_wave(a, b, r0, k, q0, T, Td, invT, invTd, sid, P, z_tok, s_pmx, s_pS, s_parg, lane, lead);
     if (lane == 0) s_fin = fin;
   }
   if (!kDraw) {
@@ -127,12 +127,14 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, R
 
 // Tiles per workgroup of the draw.  Eight (one turn) as long as that leaves no more than a workgroup per compute unit:
 // a small batch is bound by the chain of round trips in one workgroup, which every further turn would lengthen.  With
-// more, each workgroup takes as many turns as bring their number back to one per compute unit (a workgroup of 1024
-// threads fills one): its start, its share of the merge and its count at the end are then paid once for several turns,
+// more, each workgroup takes as many turns as bring their number back to one per compute unit (86 registers: five
+// wavefronts per SIMD, so that a workgroup of 16 fills one): its start, its share of the merge and its count at the end are then paid once for several turns,
 // and a turn's loads overlap the sums of the turn before.  At most 64 turns, so that the halves' scratch stays small.
 // Measured (kernel time, one turn per workgroup against this rule): 128 sequences x 128256 ids 109 + 10 us of a test
 // launch against 39 us in one launch (2 us a turn), 64 x 152064 (half greedy) 39 + 10 against 30, 300 x 32003 65 against
-// 30; 16 x 128256 and below stay at one turn.
+// 30; 16 x 128256 and below stay at one turn.  Right above one workgroup per compute unit (us per step from the logits, two
+// rows a sequence): 17 x 128256 27.1 against 22.4, 20: 28.9 / 22.8, 24: 31.4 / 24.2, 32: 33.8 / 26.2.  Up to 1.25, 1.5 and 2
+// workgroups per compute unit were slower at 64, 128 and 300 sequences as well (128: 60, 56 and 51 against 38 us).
 int draw_group_tiles(int ntiles, int B, int n_cu) {
   const int64_t groups = (int64_t)ceil_div(ntiles, kTurnTiles) * B;
   return kTurnTiles * std::min(64, std::max(1, ceil_div(groups, std::max(n_cu, 1))));
@@ -146,7 +148,9 @@ hipError_t launch_final_draw(const StepArgs& a, const int32_t* row_off_host, int
   const dim3 grid(ceil_div(a.ntiles, group_tiles), a.B), block(kDrawThreads);
   size_t lds = std::max((size_t)a.ntiles, 2 * (size_t)group_tiles) * sizeof(double);
   // From two turns on the workgroup keeps the draft row in LDS where it fits: a gather from memory moves a 128-byte line
-  // per id, about 2 us of a turn, the copy costs that once (128 sequences x 128256 ids: 51 us without, 39 with).
+  // per id, about 2 us of a turn, the copy costs that once (128 sequences x 128256 ids: 51 us without, 39 with).  Up to the largest
+// copies (us per step from the logits, 20 / 128 sequences): 50257 bf16 ids 26.0 / 60 against 26.4 / 76 gathered, 75000 26.6 / 62
+// against 28 / 89, 32000 fp32 ids 24.7 / 59 against 25.6 / 71.
   int row_at = 0;
   const size_t row_bytes = (size_t)a.V_d * (a.dtype == OT_BF16 ? 2 : 4) + 32;
   if (group_tiles > kTurnTiles && lds + 16 + row_bytes <= kDrawLdsBytes) {

@@ -269,7 +269,7 @@ __device__ __forceinline__ void wave_row_stats(const T* __restrict__ x, int V, f
 // hits_proposed, flags; mapped_ids, span_start, span_len, q_tok of the sequence's rows) and the use statistics of the
 // cache entries; where several workgroups walk the same sequence exactly one of them leads.
 __device__ inline void translate_walk(const StepArgs& a, int b, int r0, int k, int q0, float Td, double invTd, int lane,
-                                      DraftLds* L, LaneProposal* P, bool lead = true) {
+                                      DraftLds* L, LaneProposal* P, bool lead) {
   if (lane < k) {
     double lq;
     if (Td > 0.f) lq = ((double)L->zq[lane] - (double)L->qmx[lane]) * invTd - log(L->qS[lane]);
