@@ -13,7 +13,10 @@ pytestmark = pytest.mark.gpu
     ("bf16", 40001, 4001, 120),      # 3 turns, 2 groups; rows at every 2-byte alignment, last tile of 65 ids
     ("f32", 40000, 4003, 120),       # rows at every 4-byte alignment
     ("bf16", 8193, 3000, 300),       # 9 tiles in one group, the second turn holds a single tile of one id
-    ("bf16", 70000, 76000, 64),      # 152 KB per draft row: gathered from memory
+    ("bf16", 45000, 50257, 64),      # 100 KB per draft row in LDS
+    ("f32", 45000, 32003, 64),       # 128 KB
+    ("bf16", 70000, 76001, 64),      # 152 KB: next to the tiles' masses about the largest that is copied
+    ("bf16", 70000, 78000, 64),      # 156 KB: gathered from memory
     ("f32", 30000, 5, 300),          # a draft row shorter than two 16-byte chunks
 ])
 def test_several_turns_per_workgroup(dtype, V_t, V_d, B):
@@ -29,7 +32,7 @@ def test_several_turns_per_workgroup(dtype, V_t, V_d, B):
 
 
 def test_empty_residual_over_several_turns():
-    """Every residual underflows to zero mass: the last workgroup forms the masses of p itself (9 tiles, the last ragged)."""
+    """Every residual underflows to zero mass: the draw is from p (9 tiles in one workgroup, the last ragged)."""
     ov, ot, Verifier, parity = _imports()
     B, V_t, V_d = 300, 8200, 40
     case = make_case(CaseSpec(name="turns_zero", dtype="f32", d=8, V_t=V_t, V_d=V_d, k=[1] * B, temperature=[1.0] * B, n_direct=0,
