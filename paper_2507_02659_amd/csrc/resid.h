@@ -19,9 +19,9 @@
 //                    sequences of 128256 ids took 50 us, 29 now).
 // Nothing waits: a workgroup that is not last simply ends.  A workgroup that has all tiles of its sequence (a small
 // vocabulary, or many sequences) keeps the masses in LDS and counts nothing: three round trips to memory less.
-// What bounds a small batch is the chain of instructions and round trips in one workgroup (16 x 128256 ids: 17 us of
-// kernel, 21 before its gathers were freed and its scans and reductions moved from the LDS permute network to
-// data-parallel moves; one sequence of 32000 ids 12.5 against 16.2 us).
+// What bounds a small batch is the chain of instructions and round trips in one workgroup (the launch that tests and draws, in
+// the kernel trace: 16 x 128256 ids 17.9 us, 26.3 before its gathers were freed and its scans and reductions moved from the LDS
+// permute network to data-parallel moves; one sequence of 32000 ids 12.5 against 16.2 us).
 #pragma once
 
 #include "device_math.h"
@@ -72,26 +72,24 @@ struct FinalRow {
   }
 };
 
-// Largest float below x > 0.  The two floats of a scale are then both positive, and -inf times either is -inf: split at the
-// nearest float, the lower one is negative for about half of all temperatures (0.7, 0.9, ..), and a masked logit gave NaN.
-__device__ inline float float_below(double x) {
-  const float h = (float)x;
-  return (double)h >= x && h > 0.f ? __uint_as_float(__float_as_uint(h) - 1) : h;
-}
+// A scale x > 0 as two positive floats, its first 21 bits and the rest, so that -inf times either is -inf: split at the nearest
+// float, the lower one is negative for about half of all temperatures (0.7, 0.9, ..), and a masked logit gave NaN.
+__device__ inline float scale_hi(double x) { return (float)__hiloint2double(__double2hiint(x), 0); }
+__device__ inline float scale_lo(double x, float hi) { return fmaxf((float)(x - (double)hi), 1e-30f); }
 
 // The record is the same for every lane: all of it goes to scalar registers.
 __device__ inline FinalRow make_final_row(const StepArgs& a, const FinalInfo& f) {
   FinalRow R;
   R.z = a.Z + (int64_t)uniform(f.row) * a.ldz;
   const double sc = f.invT * 1.4426950408889634, scq = f.invTd * 1.4426950408889634;
-  const float sc_hi = float_below(sc), scq_hi = float_below(scq);
-  R.mx = uniform((float)f.mx); R.sc_hi = uniform(sc_hi); R.sc_lo = uniform((float)(sc - (double)sc_hi)); R.invS = uniform(f.invS);
+  const float sc_hi = scale_hi(sc), scq_hi = scale_hi(scq);
+  R.mx = uniform((float)f.mx); R.sc_hi = uniform(sc_hi); R.sc_lo = uniform(scale_lo(sc, sc_hi)); R.invS = uniform(f.invS);
   R.residual = uniform(f.mode) == 3;
   R.lds_at = -1;
   R.dtype = a.dtype;
   R.t_ng = uniform(f.t_ng); R.t_pre = uniform(f.t_pre); R.pi = uniform(f.pi); R.q_pre = uniform(f.q_pre);
   R.zq = static_cast<const char*>(a.draft_logits) + (size_t)uniform(f.drow) * a.V_d * (a.dtype == OT_BF16 ? 2 : 4);
-  R.mxq = uniform((float)f.mxq); R.scq_hi = uniform(scq_hi); R.scq_lo = uniform((float)(scq - (double)scq_hi));
+  R.mxq = uniform((float)f.mxq); R.scq_hi = uniform(scq_hi); R.scq_lo = uniform(scale_lo(scq, scq_hi));
   R.invSq = uniform(f.invSq); R.argq = uniform(f.argq);
   R.greedy_draft = uniform(f.greedy_draft) != 0;
   return R;
