@@ -264,7 +264,8 @@ static int step_impl(ot_ctx* ctx, ot_ngram_cache* cache, const ot_step_in* in, c
   // Without the LM head's help the statistics get a launch of their own, which also does the lookups, and one launch
   // follows it as above.
   if (e == hipSuccess && !a.hosted) e = launch_softmax_stats(a, st);
-  OT_MARK(2);                                // no launch, and so no event, of OT_STAGE_TRANSLATE_ACCEPT
+  OT_MARK(2);                                // OT_STAGE_TRANSLATE_ACCEPT launches nothing: its two events take their own cost off
+  OT_MARK(3);                                // the stages on either side, and it reads 0
   if (e == hipSuccess) e = launch_final_draw(a, in->row_off_host, ctx->n_cu, st);
   OT_MARK(4);
 #undef OT_MARK
@@ -306,7 +307,7 @@ int ot_verify_profile_read(ot_ctx* ctx, float* ms, int32_t* n_steps) {
     for (int s = 0; s < OT_N_STAGES; ++s) {
       if (s == OT_STAGE_TRANSLATE_ACCEPT) continue;
       float t = 0.f;
-      e = hipEventElapsedTime(&t, ev[s == OT_STAGE_RESIDUAL_DRAW ? OT_STAGE_TRANSLATE_ACCEPT : s], ev[s + 1]);
+      e = hipEventElapsedTime(&t, ev[s], ev[s + 1]);
       if (e != hipSuccess) return fail_hip(e, "hipEventElapsedTime");
       ms[s] += t;
     }
