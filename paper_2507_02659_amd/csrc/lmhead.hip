@@ -977,7 +977,8 @@ int lmhead_bf16_draft_workers(int M, int d, int Vp, int B, int K, int n_cu) {
 // With several M-blocks front workgroups take the draft side: hosted where the launch, with them in its rounds, is
 // estimated to end before a launch without them and the statistics pass.  They cost most where they push multiplying
 // workgroups into a round more: V_t = 128256, 320 rows (502 + 16 workgroups) 412 us hosted, 365 separate; 152064, 320 rows
-// 399 / 424; 1024 rows 1057 / 1104.
+// 399 / 424; 1024 rows 1057 / 1104; 20001 (d = 1024), 200 rows 39 / 47.  Over 216 shapes the choice costs 0.3 % on average against
+// the better one, 13 % at most (20001 columns with 200 draft rows of 20001, 54 / 61).
 bool lmhead_bf16_hosts_draft_side(int M, int d, int Vp, int B, int K, int V_d, int n_cu) {
   if (B < 1 || B > kFusedMaxB || K < 1) return false;
   const int workers = lmhead_bf16_draft_workers(M, d, Vp, B, K, n_cu);
@@ -988,11 +989,11 @@ bool lmhead_bf16_hosts_draft_side(int M, int d, int Vp, int B, int K, int V_d, i
   }
   const int n_front = workers / kWideWaves;
   const TallPlan plan = tall_plan(M, d, Vp, n_cu);
-  const double front_us = 2.0 * K * (double)V_d / (n_front * kFrontBytesPerUs) + ceil_div(B, 4 * n_front) * 15.0;
+  const double front_us = 2.0 * K * (double)V_d / (n_front * kFrontBytesPerUs) + ceil_div(B, 4 * n_front) * 10.0;
   if (n_front >= n_cu) return false;
   // The launch ends at the first moment by which n_front compute units that come free after front_us and the others have
   // had room for all workgroups, each kStatsUs longer for the row statistics; half of what stays idle counts, as above.
-  constexpr double kStatsUs = 5.0;
+  constexpr double kStatsUs = 4.5;
   const double t = plan.round_us + kStatsUs, n = plan.workgroups;
   const double rounds_alone = std::ceil(n / (n_cu - n_front) - 1e-9);          // the front's compute units never join
   double end = rounds_alone * t;
