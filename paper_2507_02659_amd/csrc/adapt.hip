@@ -6,9 +6,9 @@
 //                       log-probabilities in binary64; the running product is formed left to right (at most 63
 //                       factors) so that it has one fixed order, by every lane alike from lane reads, and lane i keeps
 //                       its own term; per-sequence loss partials go to the workspace.  With an arrival counter the last
-//                       workgroup adds them in a fixed order: a call is bound by its launches (64 sequences of up to 10 positions 7.4 us with
-//                       one, 10.2 with two).  The chain counts where windows are long: walked by one lane that also
-//                       stored every position, 16 sequences of 63 took 13.4 us, 8.0 now (10.6 with two launches).  Above 1024 sequences the sum is a launch of its own: the arrivals, one a
+//                       workgroup adds them in a fixed order: a call is bound by its launches (64 sequences of up to 10 positions 6.9 us with
+//                       one, 9.2 to 10.3 with two).  The chain counts where windows are long: walked by one lane that also
+//                       stored every position, 16 sequences of 63 took 13.1 us, 6.8 now (10.5 with two launches).  Above 1024 sequences the sum is a launch of its own: the arrivals, one a
 //                       workgroup at one word, take longer than that (3000 sequences 13.9 / 11.1 us, 512 7.7 / 10.2).
 //   adapt_total_kernel  the same sum as a launch of its own, for the entry point whose scratch overlapping calls may
 //                       share: they spoil each other's values there, and must not spoil a counter for later calls.
@@ -34,7 +34,7 @@ constexpr int kOneLaunchB = 1024;
 __device__ inline void adapt_total(const AdaptArgs& a, double (*s_w)[kWaves], int tid) {
   const int wave = tid >> 6, lane = tid & 63;
   double total = 0.0, count = 0.0;
-  constexpr int kAtOnce = 4;                             // sequences asked for before any of them is added
+  constexpr int kAtOnce = kOneLaunchB / kThreads;        // sequences asked for before any of them is added
   for (int b0 = tid; b0 < a.in.B; b0 += kAtOnce * kThreads) {
     double t[kAtOnce], c[kAtOnce];
 #pragma unroll
@@ -79,12 +79,20 @@ __global__ __launch_bounds__(kThreads) void adapt_rule_kernel(AdaptArgs a) {
       cost = (double)a.in.w_accept * l * (t + fmax(-x, 0.0)) + (double)a.in.w_reject * (1.0 - l) * (t + fmax(x, 0.0));
     }
   }
+  constexpr int kAtOnce = 8;                             // lane reads in front of the steps that wait for them
   const int n_all = uniform(n);
   double alive = 1.0, mine = 1.0, total = 0.0;           // mine: the product up to and including position i
-  for (int j = 0; j < n_all; ++j) {
-    alive *= lane_value(sig, j);
-    total += lane_value(cost, j);
-    if (i == j) mine = alive;
+  const double factor = i < n ? sig : 1.0;               // (past the window: factors of 1 and costs of 0)
+  for (int j0 = 0; j0 < n_all; j0 += kAtOnce) {
+    double f[kAtOnce], c[kAtOnce];
+#pragma unroll
+    for (int j = 0; j < kAtOnce; ++j) { f[j] = lane_value(factor, j0 + j); c[j] = lane_value(cost, j0 + j); }
+#pragma unroll
+    for (int j = 0; j < kAtOnce; ++j) {
+      alive *= f[j];
+      total += c[j];
+      if (i == j0 + j) mine = alive;
+    }
   }
   const bool summed = a.count && a.out.bce;              // by the last workgroup of this launch
   if (i == 0 && live) {
