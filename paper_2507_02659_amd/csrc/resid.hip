@@ -47,10 +47,9 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, R
   const int b = blockIdx.y, grp = blockIdx.x, tid = threadIdx.x;
   const int wave = uniform(tid >> 6), lane = tid & 63;
   __shared__ DrawLds s_draw;
-  __shared__ DraftLds s_d;
   __shared__ FinalInfo s_fin;
   __shared__ float s_pmx[64];
-  __shared__ double s_pS[64];
+  __shared__ double s_pinv[64];
   __shared__ int s_parg[64];
   int dv[kPerLane];
 
@@ -59,65 +58,84 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, R
   const float T = a.temperature[b];
   const float Td = a.draft_temperature ? a.draft_temperature[b] : T;
   const uint64_t sid = a.seq_id[b];
-  const double invT = T > 0.f ? 1.0 / (double)T : 1.0;
-  const double invTd = Td > 0.f ? 1.0 / (double)Td : 1.0;
   const bool lead = grp == 0;               // the group that writes the test's outputs and the row statistics
-  if (!(T > 0.f) && !lead) return;          // a greedy sequence draws nothing: its other groups have nothing to do
 
   // The LM-head launch left what the drafted ids look up (ProbeRecord) and the draft rows' statistics.  The last
-  // wavefront fetches them (one load of each array per lane), walks the window (Eq. 1) and asks for the logits of the
-  // proposed tokens, all on its own, while the other wavefronts merge the softmax partials of the target rows; the
-  // translation is thus repeated by every tile group of the sequence, and the lead group writes its outputs and the
-  // cache's use statistics.
+  // wavefront fetches them (one load of each array per lane), walks the window (Eq. 1), asks for the logits of the
+  // proposed tokens and forms q' while they are on their way, all on its own, while the other wavefronts merge the softmax
+  // partials of the target rows; the translation is thus repeated by every tile group of the sequence, and the lead group
+  // writes its outputs and the cache's use statistics.  That wavefront's chain of round trips and binary64 functions is what
+  // the others wait for: its loads leave before anything is known about the temperature, the walk comes before the functions,
+  // and q' is formed once as a product instead of through the logarithms of its factors (from the launch's start to the
+  // outcome 5.4 -> 3.8 us for one sequence of five drafted ids).
   const int q0 = r0 - b;
   constexpr int kTestWave = kDrawWaves - 1;   // runs the walk and the test
-  LaneProposal P;
-  P.t = -1; P.start = -1; P.L = 0; P.lq = 0.0; P.t_pre = -1; P.argq = -1; P.mxq = 0.f; P.Sq = 1.0; P.lq_first = 0.0;
-  P.m = 0; P.flags = 0;
+  Window W;
+  DraftLane D;
   float z_tok = 0.f;
+  bool bad = false, reached = false;
+  int pos = 0;
+  double u1 = 0.0;
+  uint32_t rnd[4] = {0, 0, 0, 0};             // of row `lane`: word 0 tests that mapped position, word 1 draws its final token
   if (wave == kTestWave) {
     const ProbeRecord* rec = a.probe + b;
-    s_d.hit[lane] = rec->hit[lane]; s_d.zq[lane] = rec->zq[lane]; s_d.dm[lane] = rec->dm[lane];
+    const unsigned long long hit = rec->hit[lane];
+    D.dm = rec->dm[lane];
+    bad = rec->bad != 0;                      // wavefront-uniform
+    D.zq = rec->zq[lane];
+    D.mxq = 0.f; D.Sq = 1.0; D.argq = -1; D.q = 0.0;
+    DraftPartials<kChunks> part;
+    if (lane < k) part.load(a, q0 + lane);
+    W = walk_window(k, lane, hit, D.dm);
+    reached = ((W.starts >> lane) & 1ull) != 0ull;
+    pos = __popcll(W.starts & bits_below(lane));
+    if (reached) z_tok = a.Z[(int64_t)(r0 + pos) * a.ldz + W.t];
     if (lane < k) {
-      float mxq; double Sq; int argq;
-      if (kChunks) merge_draft_chunks<kWide>(a, q0 + lane, Td, &mxq, &Sq, &argq, kMany);
-      else merge_draft_pieces(a, q0 + lane, Td, &mxq, &Sq, &argq);
-      s_d.qmx[lane] = mxq; s_d.qS[lane] = Sq; s_d.qarg[lane] = argq;
-      if (lead) { a.drow_max[q0 + lane] = mxq; a.drow_sum[q0 + lane] = Sq; a.drow_arg[q0 + lane] = argq; }
+      if constexpr (kChunks) merge_draft_chunks<kWide>(a, q0 + lane, Td, part, &D.mxq, &D.Sq, &D.argq, kMany);
+      else merge_draft_pieces(a, q0 + lane, Td, part, &D.mxq, &D.Sq, &D.argq);
+      if (lead) { a.drow_max[q0 + lane] = D.mxq; a.drow_sum[q0 + lane] = D.Sq; a.drow_arg[q0 + lane] = D.argq; }
+      if (Td > 0.f) D.q = exp(((double)D.zq - (double)D.mxq) * (1.0 / (double)Td)) / D.Sq;
+      else D.q = a.draft_ids[q0 + lane] == D.argq ? 1.0 : 0.0;
     }
-    const int bad = rec->bad;               // wavefront-uniform
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    if (bad) {
-      if (lead) translate_bad_sequence(a, b, r0, k, lane);
-      P.flags = OT_FLAG_BAD_ID;
-    } else {
-      translate_walk(a, b, r0, k, q0, Td, invTd, lane, &s_d, &P, lead);
-    }
-    if (!(P.flags & OT_FLAG_BAD_ID) && lane < P.m && T > 0.f) z_tok = a.Z[(int64_t)(r0 + lane) * a.ldz + P.t];
+    D.qp = segment_q(D.q, W);
+    if (T > 0.f) philox4x32_10((uint32_t)lane, a.step, (uint32_t)sid, (uint32_t)(sid >> 32), (uint32_t)a.seed, (uint32_t)(a.seed >> 32), rnd);
+    u1 = u24(__shfl(rnd[0], pos));
   }
+  const double invT = T > 0.f ? 1.0 / (double)T : 1.0;
+  const double invTd = Td > 0.f ? 1.0 / (double)Td : 1.0;
   for (int row = wave; row <= k; row += kDrawWaves) {
     if (kChunks)
-      merge_chunk_row(a.tpart_max, a.tpart_sum, a.tpart_arg, a.ncht, r0 + row, invT, lane, s_pmx, s_pS, s_parg, row, lead,
+      merge_chunk_row(a.tpart_max, a.tpart_sum, a.tpart_arg, a.ncht, r0 + row, invT, lane, s_pmx, s_pinv, s_parg, row, lead,
                       a.row_max, a.row_sum, a.row_arg, kMany);
     else
-      merge_fused_row(a.fused.part, a.fused.nfine, r0 + row, invT, lane, s_pmx, s_pS, s_parg, row, lead, a.row_max,
+      merge_fused_row(a.fused.part, a.fused.nfine, r0 + row, invT, lane, s_pmx, s_pinv, s_parg, row, lead, a.row_max,
                       a.row_sum, a.row_arg);
   }
+  if (!(T > 0.f) && !lead) return;            // a greedy sequence draws nothing: its other groups have nothing to do
   // The inverse map of this wavefront's ids is needed last (by the tile masses) and asked for here, behind the loads
   // that the test waits for: loads return in issue order, and asked for first it held those back by its own latency.
   if (kDraw) load_tmap<kPerLane>(a.tmap, a.V_t, draw_first_id(grp * group_tiles, wave, lane), 64, dv);
   __syncthreads();
+  Outcome O;
   if (wave == kTestWave) {
-    const FinalInfo fin = accept_wave(a, b, r0, k, q0, T, Td, invT, invTd, sid, P, z_tok, s_pmx, s_pS, s_parg, lane, lead);
+    FinalInfo fin{};                          // mode 0: nothing to draw
+    if (!bad) {
+      O = test_window(T, invT, W, D, reached, pos, z_tok, u1, s_pmx, s_pinv, s_parg);
+      fin = final_info(r0, q0, T, Td, invT, invTd, W, D, O, u24((uint32_t)__builtin_amdgcn_readlane((int)rnd[1], O.n)), s_pmx, s_pinv);
+    }
     if (lane == 0) s_fin = fin;
+    if (!kDraw && lane == 0) a.fin[b] = fin;
   }
-  if (!kDraw) {
-    if (tid == kTestWave * 64) a.fin[b] = s_fin;
-    return;
+  if (kDraw) __syncthreads();
+  if (wave == kTestWave && lead) {            // behind the barrier: nobody in this launch waits for these
+    if (bad) {
+      write_bad_sequence(a, b, r0, k, lane);
+    } else {
+      write_translation(a, b, r0, k, lane, W, reached, pos, D.qp);
+      write_outcome(a, b, r0, k, lane, T, W, O, reached, pos, s_parg);
+    }
   }
-  __syncthreads();
+  if (!kDraw) return;
   const FinalInfo f = s_fin;
   if (f.mode == 0) return;
   draw_final_token(a, b, grp, group_tiles, f, dv, &s_draw, row_at);

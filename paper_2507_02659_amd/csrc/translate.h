@@ -5,12 +5,11 @@
 //   * translation of the drafted window into the target vocabulary (Section "Cross-vocabulary N-gram Cache", Eq. 1):
 //     every window (start s, length L) of the drafted ids is probed in the n-gram table by its own thread; lane s of
 //     one wavefront prepares the segment that would start at s, and the window is then walked left to right as a chase
-//     through start + length: the longest cache hit at s yields one target token whose log q' is the sum of the L
-//     sub-token log-probabilities (the product of Eq. 1, kept in log space so that five or six factors of 1e-6 do not
-//     underflow), otherwise the direct image of d_s, and a draft id with neither ends the proposal.
+//     through start + length: the longest cache hit at s yields one target token whose q' is the product of the L
+//     sub-token probabilities, otherwise the direct image of d_s, and a draft id with neither ends the proposal.
 // The lookups of a sequence (drafted logits, direct images, table probes) need memory and can run early, next to the
-// LM head, which leaves them in a ProbeRecord; the walk itself is a few microseconds of one wavefront and runs where
-// the acceptance test does.  Its outcome is one LaneProposal per mapped position, held by lane j of that wavefront.
+// LM head, which leaves them in a ProbeRecord; the walk itself is a fraction of a microsecond of one wavefront and runs where
+// the acceptance test does.
 #pragma once
 
 #include "device_math.h"
@@ -20,31 +19,23 @@ namespace otv {
 
 constexpr float kLog2eF = 1.4426950408889634f;
 
-// LDS scratch of one sequence's translation (k <= 63 drafted positions).
+// LDS scratch of one sequence's lookups (k <= 63 drafted positions).
 struct DraftLds {
   unsigned long long hit[64];   // (length << 60) | (slot << 32) | target of the longest cache hit starting here, 0 = none
-  double logq[64];              // log q_i(d_i)
-  double qS[64];                // draft row statistics
-  float qmx[64];
   float zq[64];                 // draft logit of the drafted id
-  int32_t qarg[64];
   int32_t dm[64];               // direct image of the drafted id, or -1
   int32_t bad;                  // a drafted id was outside [0, V_d)
 };
 
-// What lane j of the walking wavefront knows about mapped position j after the translation.
-struct LaneProposal {
-  int t, start, L;              // target id (-1 beyond the proposal), first draft position, draft tokens covered
-  double lq;                    // log q'(t_j)
-  // the draft row a final draw at this position would use (Eq. 2): the row of the span's first sub-token, or for
-  // lane m the row of the draft id that could not be translated
-  int t_pre, argq;              // direct image of that row's drafted id (-1: none); argmax of the row
-  float mxq;                    // its maximum
-  double Sq;                    // its sum of exponentials
-  double lq_first;              // log q(d) of its drafted id
-  // wavefront-uniform
-  int m, flags;
+// A walked window.  Lane s of the walking wavefront holds the segment that would start at draft position s (target id or -1,
+// draft tokens covered, cache slot or -1); bit s of `starts` says that the walk reached it.  The j-th set bit is mapped
+// position j and is tested against row j of the sequence.  All but the segments is wavefront-uniform.
+struct Window {
+  int t, L, slot;
+  unsigned long long starts;
+  int m, end, flags;            // mapped positions; where the walk ended (k, or the draft id that could not be translated)
 };
+__device__ __forceinline__ unsigned long long bits_below(int i) { return (1ull << i) - 1ull; }   // i <= 63
 
 // Probe of one key held in registers (fully unrolled so that `ids` never has to live in scratch memory).
 // Returns the slot index of the entry, or -1.
@@ -264,91 +255,72 @@ __device__ __forceinline__ void wave_row_stats(const T* __restrict__ x, int V, f
 }
 
 // ---------------------------------------------------------------------------------------------- the walk
-// One wavefront (lane = threadIdx within it), after the barrier that publishes L: forms log q_i(d_i), walks the window
-// and returns mapped position `lane` in P.  With `lead` it also writes the translation's outputs (n_mapped,
-// hits_proposed, flags; mapped_ids, span_start, span_len, q_tok of the sequence's rows) and the use statistics of the
-// cache entries; where several workgroups walk the same sequence exactly one of them leads.
-__device__ inline void translate_walk(const StepArgs& a, int b, int r0, int k, int q0, float Td, double invTd, int lane,
-                                      DraftLds* L, LaneProposal* P, bool lead) {
-  if (lane < k) {
-    double lq;
-    if (Td > 0.f) lq = ((double)L->zq[lane] - (double)L->qmx[lane]) * invTd - log(L->qS[lane]);
-    else lq = (a.draft_ids[q0 + lane] == L->qarg[lane]) ? 0.0 : -INFINITY;
-    L->logq[lane] = lq;
-  }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-
-  // Lane s first prepares the segment that would start at draft position s (the longest cache hit there, else the
-  // direct image; log q' = sum of its sub-tokens' log-probabilities); the walk itself is then a chase through
-  // "start + length" with wavefront-uniform lane reads, a few cycles per token.
-  int seg_t = -1, seg_L = 1, seg_slot = -1;
-  double seg_lq = 0.0;
-  if (lane < k) {
-    const unsigned long long h = L->hit[lane];
-    if (h != 0ull) {
-      seg_L = (int)(h >> 60); seg_t = (int)(h & 0xFFFFFFFFull); seg_slot = (int)((h >> 32) & 0x0FFFFFFFull);
-    } else {
-      seg_t = L->dm[lane];
+// One wavefront walks the window of k drafted ids (Eq. 1) from what lane s looked up at draft position s: the longest cache hit
+// there and the direct image.  Where no window hits the cache that is a count of leading ones, otherwise a chase through
+// start + length with wavefront-uniform lane reads, a few cycles per token.
+__device__ __forceinline__ Window walk_window(int k, int lane, unsigned long long hit, int dm) {
+  Window w;
+  const bool found = lane < k && hit != 0ull;
+  w.t = lane < k ? (found ? (int)(hit & 0xFFFFFFFFull) : dm) : -1;
+  w.L = found ? (int)(hit >> 60) : 1;
+  w.slot = found ? (int)((hit >> 32) & 0x0FFFFFFFull) : -1;
+  w.flags = 0;
+  const unsigned long long can = __ballot(w.t >= 0);        // a hit or a direct image; not set from k on
+  if (__ballot(found) == 0ull) {
+    w.m = w.end = (int)__builtin_ctzll(~can);
+    w.starts = bits_below(w.m);
+  } else {
+    w.m = 0; w.end = 0; w.starts = 0ull;
+    while (w.end < k && ((can >> w.end) & 1ull)) {
+      w.starts |= 1ull << w.end;
+      w.end += __builtin_amdgcn_readlane(w.L, w.end);
+      ++w.m;
     }
-    for (int l = 0; l < seg_L; ++l) seg_lq += L->logq[lane + l];
   }
-  int m = 0, s_end = 0, flags = 0, start_j = -1;
-  while (s_end < k) {
-    const int at = __builtin_amdgcn_readfirstlane(s_end);
-    if (__builtin_amdgcn_readlane(seg_t, at) < 0) { flags |= OT_FLAG_UNMAPPABLE; break; }   // neither a hit nor a direct image
-    if (lane == m) start_j = at;
-    s_end = at + __builtin_amdgcn_readlane(seg_L, at);
-    ++m;
-  }
-  // lane j < m takes over the segment that starts at start_j
-  // (all lanes take part in the shuffles: a lane outside the active set would not supply its value)
-  const int src = start_j >= 0 ? start_j : 0;
-  const int got_t = __shfl(seg_t, src), got_L = __shfl(seg_L, src);
-  const double lq_j = __shfl(seg_lq, src);
-  const int slot_j = __shfl(seg_slot, src);
-  P->t = lane < m ? got_t : -1;
-  P->L = lane < m ? got_L : 0;
-  P->start = start_j;
-  P->lq = lane < m ? lq_j : 0.0;
-  P->m = m; P->flags = flags;
-  const int hits = __popcll(__ballot(lane < m && P->L > 1));
-  if (lead && lane < m && P->L > 1) {
-    // use statistics of the entry (Appendix, cache eviction): one more use, last used now
-    atomicAdd(&a.cache.uses[slot_j], 1u);
-    a.cache.last_used[slot_j] = a.cache.clock;
-    const uint32_t at = atomicAdd(a.cache.log_count, 1u);        // and the host hears of it through the log
-    if (at < (uint32_t)kCacheLogCap) a.cache.log[at] = make_uint2((uint32_t)slot_j + 1u, a.cache.clock);
-  }
-  // the draft row a final draw at this position would read
-  const int s_fin = lane < m ? start_j : ((lane == m && s_end < k) ? s_end : -1);
-  P->t_pre = -1; P->argq = -1; P->mxq = 0.f; P->Sq = 1.0; P->lq_first = 0.0;
-  if (s_fin >= 0) {
-    P->t_pre = L->dm[s_fin]; P->argq = L->qarg[s_fin]; P->mxq = L->qmx[s_fin]; P->Sq = L->qS[s_fin];
-    P->lq_first = L->logq[s_fin];
-    if (lane == m) P->start = s_fin;
-  }
-  if (lead && lane == 0) {
-    a.out.n_mapped[b] = m;
-    a.out.hits_proposed[b] = hits;
-    publish(&a.out.flags[b], flags);   // another workgroup may add a bit to it in the same launch (draw_final_token)
-  }
-  if (lead && lane <= k) {
-    a.out.mapped_ids[r0 + lane] = P->t;
-    a.out.span_start[r0 + lane] = lane < m ? start_j : -1;
-    a.out.span_len[r0 + lane] = P->L;
-    a.out.q_tok[r0 + lane] = lane < m ? (float)exp(P->lq) : 0.f;
-  }
+  if (w.end < k) w.flags |= OT_FLAG_UNMAPPABLE;
+  return w;
 }
 
-// Translation outputs of a sequence with a drafted id outside [0, V_d): it proposes nothing.
-__device__ inline void translate_bad_sequence(const StepArgs& a, int b, int r0, int k, int lane) {
-  if (lane <= k) {
+// q'(t) of the segment that starts at this lane from the lanes' q(d): the product over its draft tokens (Eq. 1).  Eight factors,
+// the longest key, stay far inside binary64's range unless one of them has left it already.
+__device__ __forceinline__ double segment_q(double q, const Window& w) {
+  double qp = q;
+  if (__ballot(w.L > 1) != 0ull) {
+    for (int l = 1; __ballot(w.L > l) != 0ull; ++l) {
+      const double next = __shfl_down(q, l);
+      if (l < w.L) qp *= next;
+    }
+  }
+  return qp;
+}
+
+// The translation's outputs (n_mapped, hits_proposed, flags; mapped_ids, span_start, span_len, q_tok of the sequence's rows) and
+// the use statistics of the cache entries, by one wavefront of the step per sequence.  pos: mapped position of a segment that
+// the walk reached.
+__device__ __forceinline__ void write_translation(const StepArgs& a, int b, int r0, int k, int lane, const Window& w, bool reached,
+                                                  int pos, double qp) {
+  const bool is_hit = reached && w.L > 1;
+  if (is_hit) {
+    // use statistics of the entry (Appendix, cache eviction): one more use, last used now
+    atomicAdd(&a.cache.uses[w.slot], 1u);
+    a.cache.last_used[w.slot] = a.cache.clock;
+    const uint32_t at = atomicAdd(a.cache.log_count, 1u);        // and the host hears of it through the log
+    if (at < (uint32_t)kCacheLogCap) a.cache.log[at] = make_uint2((uint32_t)w.slot + 1u, a.cache.clock);
+  }
+  const int hits = __popcll(__ballot(is_hit));
+  if (lane == 0) {
+    a.out.n_mapped[b] = w.m;
+    a.out.hits_proposed[b] = hits;
+    publish(&a.out.flags[b], w.flags);   // another workgroup may add a bit to it in the same launch (draw_final_token)
+  }
+  if (reached) {
+    a.out.mapped_ids[r0 + pos] = w.t; a.out.span_start[r0 + pos] = lane; a.out.span_len[r0 + pos] = w.L;
+    a.out.q_tok[r0 + pos] = (float)qp;
+  }
+  if (lane >= w.m && lane <= k) {
     a.out.mapped_ids[r0 + lane] = -1; a.out.span_start[r0 + lane] = -1; a.out.span_len[r0 + lane] = 0;
     a.out.q_tok[r0 + lane] = 0.f;
   }
-  if (lane == 0) { a.out.n_mapped[b] = 0; a.out.hits_proposed[b] = 0; a.out.flags[b] = OT_FLAG_BAD_ID; }
 }
 
 // Softmax statistics of elements [e0, e0 + n) of draft row q by one workgroup of kWaves wavefronts (all threads call it;
@@ -412,27 +384,6 @@ __device__ __forceinline__ void workgroup_draft_piece(const StepArgs& a, int q, 
     *out = r;
   }
   lds_barrier();
-}
-
-// Statistics of draft row q from its pieces (ascending order, the merge rule of the slices above): lane-local.
-__device__ __forceinline__ void merge_draft_pieces(const StepArgs& a, int q, float Td, float* out_mx, double* out_S,
-                                                   int* out_arg) {
-  const int j0 = 0, j1 = a.plan.pieces(q) - 1;
-  const DraftPiece* rec = a.dpiece + (int64_t)q * kDraftPieces;
-  DraftPiece pc[kDraftPieces];
-#pragma unroll
-  for (int j = 0; j < kDraftPieces; ++j) pc[j] = rec[min(j, j1 - j0)];     // all loads before any use
-  const float scale = Td > 0.f ? kLog2eF / Td : kLog2eF;
-  float bm = -INFINITY;
-  int ba = 0x7FFFFFFF;
-#pragma unroll
-  for (int j = 0; j < kDraftPieces; ++j)
-    if (j <= j1 - j0 && pc[j].mx > bm) { bm = pc[j].mx; ba = pc[j].arg; }
-  double total = 0.0;
-#pragma unroll
-  for (int j = 0; j < kDraftPieces; ++j)
-    if (j <= j1 - j0 && pc[j].mx != -INFINITY) total += pc[j].sum * (double)__builtin_amdgcn_exp2f((pc[j].mx - bm) * scale);
-  *out_mx = bm; *out_S = total; *out_arg = ba;
 }
 
 }  // namespace otv
