@@ -17,6 +17,9 @@ __device__ __forceinline__ double rescale(float x, float mx, float sc, double in
   return exact ? exp(((double)x - (double)mx) * invT) : (double)__builtin_amdgcn_exp2f((x - mx) * sc);
 }
 
+// The scale of a target row's exponents, log2(e) / T.
+__device__ __forceinline__ float row_scale(float T) { return T > 0.f ? (1.f / T) * kLog2eF : kLog2eF; }
+
 // Lanes of a wavefront hold running statistics r of parts of one row (exponent scale sc): merges them in a fixed order; lane 0
 // publishes the row's (max, 1 / sum, argmax) to LDS slot `at` and, if asked, (max, sum, argmax) to the workspace.
 __device__ __forceinline__ void wave_publish_row(const RunStat& r, float sc, int row, int lane, float* s_mx, double* s_inv,
@@ -35,24 +38,28 @@ __device__ __forceinline__ void wave_publish_row(const RunStat& r, float sc, int
 // A lane requests eight 16-byte partials at a time before it looks at any of them (one round trip to memory for up
 // to 512 tiles) and keeps a running maximum with the sum rescaled to it; the lanes are then merged (wave_publish_row).  Sums
 // are rescaled and added in binary64, in a fixed order.
-__device__ inline void merge_fused_row(const Partial* __restrict__ part, int nfine, int row, double invT, int lane,
+__device__ inline void merge_fused_row(const Partial* __restrict__ part, int nfine, int row, float T, int lane,
                                        float* s_mx, double* s_inv, int* s_arg, int at, bool to_workspace, float* g_mx,
                                        double* g_S, int32_t* g_arg) {
   const uint4* p = reinterpret_cast<const uint4*>(part + (int64_t)row * nfine);
-  const float sc = (float)invT * kLog2eF;
-  RunStat r;
-  for (int c0 = 0; c0 < nfine; c0 += 512) {
-    uint4 raw[8];
+  constexpr int kAtOnce = 8;
+  uint4 raw[kAtOnce];
+  auto load = [&](int c0) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int c = c0 + j * 64 + lane;
-      raw[j] = c < nfine ? p[c] : make_uint4(0xFF800000u, 0x7FFFFFFFu, 0u, 0u);     // (-inf, no column, 0.0)
-    }
+    for (int j = 0; j < kAtOnce; ++j) raw[j] = p[min(c0 + j * 64 + lane, nfine - 1)];
+  };
+  load(0);                                             // in front of everything that waits for the temperature
+  const float sc = row_scale(T);
+  RunStat r;
+  for (int c0 = 0; c0 < nfine; c0 += kAtOnce * 64) {
+    if (c0 > 0) load(c0);
     float bm = -INFINITY;
     int bi = 0x7FFFFFFF;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const float m = __uint_as_float(raw[j].x);
+    for (int j = 0; j < kAtOnce; ++j) {
+      if (c0 + j * 64 >= nfine) break;                 // wavefront-uniform
+      const float m = c0 + j * 64 + lane < nfine ? __uint_as_float(raw[j].x) : -INFINITY;
+      raw[j].x = __float_as_uint(m);
       const int ai = (int)raw[j].y;
       if (m > bm || (m == bm && ai < bi)) { bm = m; bi = ai; }
     }
@@ -62,10 +69,10 @@ __device__ inline void merge_fused_row(const Partial* __restrict__ part, int nfi
     }
     if (r.mx != -INFINITY) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const float m = __uint_as_float(raw[j].x);
-        const double sum = __hiloint2double((int)raw[j].w, (int)raw[j].z);
-        r.sum += sum * (double)__builtin_amdgcn_exp2f((m - r.mx) * sc);              // empty: 0 * exp2(-inf) = 0
+      for (int j = 0; j < kAtOnce; ++j) {
+        if (c0 + j * 64 >= nfine) break;
+        const double sum = c0 + j * 64 + lane < nfine ? __hiloint2double((int)raw[j].w, (int)raw[j].z) : 0.0;
+        r.sum += sum * (double)__builtin_amdgcn_exp2f((__uint_as_float(raw[j].x) - r.mx) * sc);
       }
     }
   }
@@ -75,11 +82,11 @@ __device__ inline void merge_fused_row(const Partial* __restrict__ part, int nfi
 // The same for the chunk partials of the statistics launch (three arrays, nch entries per row): lane c takes chunks
 // c, c + 64, ...  exact: as above; steps of many sequences, which no single chain of instructions bounds, ask for it.
 __device__ __forceinline__ void merge_chunk_row(const float* __restrict__ pmax, const double* __restrict__ psum,
-                                       const int32_t* __restrict__ parg, int nch, int row, double invT, int lane,
+                                       const int32_t* __restrict__ parg, int nch, int row, float T, double invT, int lane,
                                        float* s_mx, double* s_inv, int* s_arg, int at, bool to_workspace, float* g_mx,
                                        double* g_S, int32_t* g_arg, bool exact) {
   const int64_t o = (int64_t)row * nch;
-  const float sc = (float)invT * kLog2eF;
+  const float sc = row_scale(T);
   RunStat r;
   for (int c = lane; c < nch; c += 64) {
     const float m = pmax[o + c];
@@ -124,10 +131,9 @@ template <> struct DraftPartials<false> {
 // Statistics of draft row q from the chunk partials of the statistics launch (ascending chunks): lane-local.  kWide: the row may
 // have more than kChunksAtOnce chunks (compiled in where it has not, the binary64 exponential costs every step 0.3 us).
 template <bool kWide>
-__device__ __forceinline__ void merge_draft_chunks(const StepArgs& a, int q, float Td, DraftPartials<true>& p, float* out_mx, double* out_S,
+__device__ __forceinline__ void merge_draft_chunks(const StepArgs& a, int q, float Td, double invTd, DraftPartials<true>& p, float* out_mx, double* out_S,
                                           int* out_arg, bool exact) {
   const float sc = Td > 0.f ? kLog2eF / Td : kLog2eF;
-  const double invTd = Td > 0.f ? 1.0 / (double)Td : 1.0;
   constexpr int kAtOnce = kChunksAtOnce;
   RunStat r;
   for (int c0 = 0; c0 < a.nchd; c0 += kAtOnce) {
@@ -169,7 +175,7 @@ __device__ __forceinline__ void merge_draft_pieces(const StepArgs& a, int q, flo
 struct DraftLane {
   float zq, mxq;                // draft logit of the drafted id; the draft row's maximum, its lowest index, its sum
   int argq, dm;
-  double Sq, q, qp;             // q(d) of the drafted id; q'(t) of the segment
+  double Sq, invSq, q, qp;      // q(d) of the drafted id; q'(t) of the segment
 };
 
 // The outcome of the test.  n: first rejected mapped position, or m; `ratio` and `pt` of this lane's segment.
@@ -236,13 +242,23 @@ __device__ __forceinline__ void write_bad_sequence(const StepArgs& a, int b, int
   }
 }
 
+// log2(e) / T as two positive floats, its first 21 bits and the rest, so that -inf times either is -inf: split at the nearest
+// float, the lower one is negative for about half of all temperatures (0.7, 0.9, ..), and a masked logit gave NaN.
+struct Scale { float hi, lo; };
+__device__ __forceinline__ Scale split_scale(double invT) {
+  const double x = invT * 1.4426950408889634;
+  Scale s;
+  s.hi = (float)__hiloint2double(__double2hiint(x), 0);
+  s.lo = fmaxf((float)(x - (double)s.hi), 1e-30f);
+  return s;
+}
+
 // Where and from what the final token is drawn (wavefront-uniform).  u2: the uniform of row n.
-__device__ __forceinline__ FinalInfo final_info(int r0, int q0, float T, float Td, double invT, double invTd, const Window& w, const DraftLane& D,
+__device__ __forceinline__ FinalInfo final_info(int r0, int q0, float T, float Td, Scale sc, Scale scq, const Window& w, const DraftLane& D,
                                        const Outcome& o, double u2, const float* s_pmx, const double* s_pinv) {
-  FinalInfo fin;
-  fin.mode = 0; fin.row = r0 + o.n; fin.drow = 0; fin.t_ng = -1; fin.t_pre = -1; fin.argq = -1; fin.greedy_draft = 0;
-  fin.flags = w.flags; fin.pi = 0.0; fin.q_pre = 0.0; fin.u2 = u2;
-  fin.mx = (double)s_pmx[o.n]; fin.invT = invT; fin.invS = s_pinv[o.n]; fin.mxq = 0.0; fin.invTd = 1.0; fin.invSq = 1.0;
+  FinalInfo fin{};                                      // mode 0: nothing to draw
+  fin.row = r0 + o.n; fin.t_ng = -1; fin.t_pre = -1; fin.argq = -1; fin.flags = w.flags; fin.u2 = u2;
+  fin.mx = s_pmx[o.n]; fin.sc_hi = sc.hi; fin.sc_lo = sc.lo; fin.invS = s_pinv[o.n]; fin.scq_hi = scq.hi; fin.scq_lo = scq.lo;
   if (!(T > 0.f)) return fin;
   if (o.n == w.m && !(w.flags & OT_FLAG_UNMAPPABLE)) {
     fin.mode = 2;                                       // everything accepted: free token ~ p
@@ -251,9 +267,8 @@ __device__ __forceinline__ FinalInfo final_info(int r0, int q0, float T, float T
   fin.mode = 3;                                         // correction token ~ norm(max(0, p - q'))
   fin.drow = q0 + o.at;                                 // the rejected span's first draft row, or the untranslatable id's
   fin.greedy_draft = !(Td > 0.f);
-  fin.invTd = invTd;
-  fin.mxq = (double)__int_as_float(__builtin_amdgcn_readlane(__float_as_int(D.mxq), o.at));
-  fin.invSq = 1.0 / lane_value(D.Sq, o.at);
+  fin.mxq = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(D.mxq), o.at));
+  fin.invSq = lane_value(D.invSq, o.at);
   fin.argq = __builtin_amdgcn_readlane(D.argq, o.at);
   if (o.n < w.m && __builtin_amdgcn_readlane(w.L, o.at) > 1) {   // Eq. 2 overrides for the n-gram matched at this position
     fin.t_ng = __builtin_amdgcn_readlane(w.t, o.at);

@@ -121,7 +121,7 @@ int ot_verify_init(const ot_verify_config* cfg, ot_ctx** out) {
   c->Vp = ceil_div(cfg->V_t, 256) * 256;
   c->ncht = ceil_div(cfg->V_t, kStatChunk);
   c->nchd = ceil_div(cfg->V_d, kStatChunk);
-  c->ntiles = ceil_div(cfg->V_t, kResidTile);
+  c->max_units = ceil_div(cfg->V_t, kMinDrawUnit);
   hipError_t e = hipGetDevice(&c->device);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&c->n_cu, hipDeviceAttributeMultiprocessorCount, c->device);
   if (e != hipSuccess) { free_ctx(c); return fail_hip(e, "hipGetDevice"); }
@@ -145,14 +145,15 @@ int ot_verify_init(const ot_verify_config* cfg, ot_ctx** out) {
        dev_alloc(c, &c->dpiece, KQ * otv::kDraftPieces);
   ok = ok && dev_alloc(c, &c->loss_part, R * kLossGroups);
   ok = ok && dev_alloc(c, &c->adapt_part, 2 * Bm);
-  ok = ok && dev_alloc(c, &c->tile_r, Bm * c->ntiles);
-  const size_t n_counters = Bm + 1 + (R + 1);            // of the draw, of adaptive drafting, of the loss
-  ok = ok && dev_alloc(c, &c->resid_count, n_counters);
+  ok = ok && dev_alloc(c, &c->unit_mass, Bm * c->max_units);
+  const size_t n_counters = 1 + (R + 1);                 // of adaptive drafting, of the loss
+  ok = ok && dev_alloc(c, &c->counters, n_counters);
   if (!ok) { free_ctx(c); return fail(OT_ERR_NOMEM, "ot_verify_init: device allocation failed"); }
 
   if (c->zeros) e = hipMemsetAsync(c->zeros, 0, 64, c->stream);
-  if (e == hipSuccess) e = hipMemsetAsync(c->resid_count, 0, sizeof(int32_t) * n_counters, c->stream);
-  c->adapt_count = c->resid_count + Bm;
+  if (e == hipSuccess) e = hipMemsetAsync(c->counters, 0, sizeof(int32_t) * n_counters, c->stream);
+  if (e == hipSuccess) e = hipMemsetAsync(c->unit_mass, 0xFF, sizeof(double) * Bm * c->max_units, c->stream);
+  c->adapt_count = c->counters;
   c->loss_count = c->adapt_count + 1;
   if (e == hipSuccess) e = hipMemcpyAsync(c->dmap, cfg->direct_map, sizeof(int32_t) * c->V_d, hipMemcpyHostToDevice, c->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(c->tmap, tmap_h.data(), sizeof(int32_t) * tmap_h.size(), hipMemcpyHostToDevice, c->stream);
@@ -212,7 +213,7 @@ static int step_impl(ot_ctx* ctx, ot_ngram_cache* cache, const ot_step_in* in, c
   }
   a.Z = from_logits ? ext_logits : ctx->Z;
   a.ldz = ctx->V_t;
-  a.ncht = ctx->ncht; a.nchd = ctx->nchd; a.ntiles = ctx->ntiles;
+  a.ncht = ctx->ncht; a.nchd = ctx->nchd;
   a.tpart_max = ctx->tpart_max; a.tpart_sum = ctx->tpart_sum; a.tpart_arg = ctx->tpart_arg;
   a.dpart_max = ctx->dpart_max; a.dpart_sum = ctx->dpart_sum; a.dpart_arg = ctx->dpart_arg;
   a.row_max = ctx->row_max; a.row_sum = ctx->row_sum; a.row_arg = ctx->row_arg;
@@ -220,7 +221,7 @@ static int step_impl(ot_ctx* ctx, ot_ngram_cache* cache, const ot_step_in* in, c
   a.fin = ctx->fin;
   a.probe = ctx->probe;
   a.dpiece = ctx->dpiece;
-  a.tile_r = ctx->tile_r; a.resid_count = ctx->resid_count;
+  a.unit_mass = ctx->unit_mass; a.max_units = ctx->max_units;
   a.out = *o;
 
   hipStream_t st = ctx->stream;

@@ -37,8 +37,9 @@ __device__ inline double lane_value(double x, int l) {
 // of __shfl_xor would pay one after the other.
 template <int kCtrl, int kRowMask = 0xF>
 __device__ inline double dpp_f64(double x) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), kCtrl, kRowMask, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), kCtrl, kRowMask, 0xF, false);
+  constexpr bool kAllRows = kRowMask == 0xF;             // then lanes without a partner are zeroed by the move itself
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), kCtrl, kRowMask, 0xF, kAllRows);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), kCtrl, kRowMask, 0xF, kAllRows);
   return __hiloint2double(hi, lo);                       // rows outside the mask receive +0.0
 }
 __device__ inline double wave_sum(double x) {

@@ -14,7 +14,7 @@ int ot_static_scratch_prepare();
 
 struct ot_ctx {
   int32_t d = 0, V_t = 0, V_d = 0, max_batch = 0, max_k = 0, dtype = 0, max_ngram_len = 0, draft_side = 0;
-  int32_t max_rows = 0, max_K = 0, Kp = 0, Vp = 0, ncht = 0, nchd = 0, ntiles = 0;
+  int32_t max_rows = 0, max_K = 0, Kp = 0, Vp = 0, ncht = 0, nchd = 0, max_units = 0;
   hipStream_t stream = nullptr;
   int device = 0;
   std::vector<void*> allocs;
@@ -33,10 +33,10 @@ struct ot_ctx {
   int n_cu = 0;                       // compute units of the device
   otv::DraftPiece* dpiece = nullptr;  // [max_K, kDraftPieces] pieces of the draft rows' statistics, as the probe records
   otv::ProbeRecord* probe = nullptr;  // [max_batch] lookups of the drafted ids, between the LM-head launch and the next
-  double* tile_r = nullptr;
-  int32_t* resid_count = nullptr;     // [max_batch] arrival counters of the residual launch, zero between launches
+  double* unit_mass = nullptr;        // [max_batch, max_units] masses of the draw, all bits set between launches
   otv::FinalInfo* fin = nullptr;
   double* loss_part = nullptr;        // [max_rows, kLossGroups] KL sums of a row's groups
+  int32_t* counters = nullptr;        // the arrival counters below, in one allocation
   int32_t* loss_count = nullptr;      // [max_rows + 1] arrival counters of the loss launch, 0 between launches
   int32_t* adapt_count = nullptr;     // arrival counter of the adaptive-drafting launch, 0 between launches
   double* adapt_part = nullptr;       // [max_batch, 2] per-sequence partials of the acceptance head's loss

@@ -12,7 +12,7 @@ namespace otv {
 // ------------------------------------------------------------------------------------------------ geometry
 constexpr int kStatThreads = 256;
 constexpr int kStatChunk = 8192;     // logits per workgroup of the softmax-statistics kernel (measured: 4096 and 16384 are slower)
-constexpr int kResidTile = 1024;     // target ids per tile of the final draw; a workgroup takes 8 to 512 consecutive tiles
+constexpr int kMinDrawUnit = 128;    // target ids per unit of the final draw at least: as many masses per sequence
 constexpr int kGemmColsPerWave = 64; // LM-head columns owned by one wavefront
 constexpr int kGemmKPad = 128;       // packed K extent is a multiple of this
 // Gap, in 16-byte units, between the packed weights of consecutive 64-column tiles.  Without it the tiles of a
@@ -71,8 +71,9 @@ struct FinalInfo {
   double pi;             // product of the n-gram's sub-token probabilities
   double q_pre;          // q(d_1) - pi
   double u2;             // uniform of the draw
-  // p(v) = exp((z_v - mx) * invT) * invS at the final row; q_s(d) = exp((zq_d - mxq) * invTd) * invSq at draft row drow
-  double mx, invT, invS, mxq, invTd, invSq;
+  // p(v) = 2^((z_v - mx) * (sc_hi + sc_lo)) * invS at the final row; q_s(d) the same of zq_d at draft row drow
+  double invS, invSq;
+  float mx, sc_hi, sc_lo, mxq, scq_hi, scq_lo;
 };
 
 // Softmax partial of one row over one column tile: maximum, its lowest column, sum of exp((z - mx) / T).
@@ -163,9 +164,8 @@ struct StepArgs {
                          // and the probe records: one launch follows it, which translates, tests and draws;
                          // 0: the statistics launch left chunk partials (tpart_*, dpart_*) and the probe records for it
   FinalInfo* fin;        // [B]
-  int32_t ntiles;        // residual tiles per row
-  double* tile_r;        // [B, ntiles]
-  int32_t* resid_count;  // [B] tile workgroups of the residual launch that have delivered their mass; 0 between launches
+  int32_t max_units;     // masses per sequence in
+  double* unit_mass;     // [B, max_units] of the draw: what its workgroups hand to each other; all bits set between launches
   // outputs (device)
   ot_step_out out;
 };

@@ -6,22 +6,24 @@
 // pre-image), except that the n-gram matched at this position gets the product pi of its sub-token probabilities
 // and the direct image of its first sub-token gets q_s(d_1) - pi.  When everything was accepted the draw is from p.
 //
-// Only the ONE row per sequence where the draw happens is touched.  A workgroup of 16 wavefronts takes a run of
-// consecutive tiles of kResidTile target ids of one sequence (draw_group_tiles), eight at a time, two wavefronts per tile:
-//   every workgroup  forms the masses of max(0, p - q') of its tiles in binary64, publishes them and counts itself in;
-//   the workgroup that arrives last for its sequence  walks the tile masses in ascending order with a wavefront scan
-//                    to the tile that holds u * total, re-forms that tile with each thread owning 4 consecutive ids,
-//                    scans the running sum in ascending id order and emits the first id whose running sum exceeds the
-//                    target (inverse CDF).  Which workgroup that is varies from run to run; what it computes does not.
-//                    When the residual is empty (reachable only through underflow) it walks the masses of p, the
-//                    fallback distribution, instead: every workgroup leaves that of a tile without residual mass in its
-//                    place, negative (nothing to do in the common case; formed by the last workgroup alone, 32 such
-//                    sequences of 128256 ids took 50 us, 29 now).
-// Nothing waits: a workgroup that is not last simply ends.  A workgroup that has all tiles of its sequence (a small
-// vocabulary, or many sequences) keeps the masses in LDS and counts nothing: three round trips to memory less.
-// What bounds a small batch is the chain of instructions and round trips in one workgroup (the launch that tests and draws, in
-// the kernel trace: 16 x 128256 ids 17.9 us, 26.3 before its gathers were freed and its scans and reductions moved from the LDS
-// permute network to data-parallel moves; one sequence of 32000 ids 12.5 against 16.2 us).
+// Only the ONE row per sequence where the draw happens is touched.  A workgroup of 16 wavefronts takes a run of consecutive
+// units of 64 * kPer target ids of one sequence (draw_split), a unit per wavefront and turn:
+//   every workgroup  forms the masses of max(0, p - q') of its units in binary64 and publishes them; when they have reached
+//                    memory it looks at the masses of all units of its sequence, and ends if one is still missing;
+//   the workgroup that finds them all  (the one whose masses arrive last does; more than one may, and they do the same)
+//                    scans the masses to the unit that holds u * total, re-forms that unit with one id per thread, scans
+//                    the running sum in ascending id order and emits the first id whose running sum exceeds the target
+//                    (inverse CDF).  When the residual is empty (reachable only through underflow) it takes the masses of
+//                    p, the fallback distribution, instead: every wavefront leaves that of a unit without residual mass in
+//                    its place, negative (nothing to do in the common case).
+// Nothing waits for another workgroup.  A mass that is missing reads as kNoMass, which the finder puts back for the next launch
+// once it has its copy; a workgroup that looks while that happens ends, since the finder goes on.  (Counted in at one word
+// per sequence instead, sixteen arrivals took 0.9 to 2.3 us next to each other and a look at the masses followed all the same.)
+// A workgroup that has all units of its sequence (a small vocabulary, or many sequences) keeps the masses in LDS.
+// What bounds a small batch is the chain of instructions and round trips in one workgroup, at the clock that the LM head leaves
+// behind (2.4 GHz after 6 rows x 32000 ids, 1.25 after 144 x 128256): few instructions count for more than few bytes.  From its
+// start to its end the launch that tests and draws takes 8.3 us there at 6 rows x 32000 ids and 17.9 at 144 x 128256; with tiles
+// of 1024 ids, a counter per sequence and four ids per thread at the end it took 10.8 and 22.3 (12.1 and 24 with the test as it was).
 #pragma once
 
 #include "device_math.h"
@@ -31,11 +33,6 @@ namespace otv {
 
 constexpr int kDrawWaves = 16;                       // wavefronts per workgroup
 constexpr int kDrawThreads = kDrawWaves * 64;
-constexpr int kTurnTiles = kDrawWaves / 2;           // tiles a workgroup sums at a time: two wavefronts share one
-constexpr int kPerLane = kResidTile / 128;           // ids per lane while two wavefronts sum one tile
-constexpr int kPickThreads = 256;
-constexpr int kPer = kResidTile / kPickThreads;      // consecutive ids per thread while the chosen tile is scanned
-static_assert(kPer == 4, "the fixed summation trees below are written for 4 ids per thread");
 
 // p(v) and q'(v) of Eq. 2 at the final row of one sequence.
 struct FinalRow {
@@ -72,42 +69,42 @@ struct FinalRow {
   }
 };
 
-// A scale x > 0 as two positive floats, its first 21 bits and the rest, so that -inf times either is -inf: split at the nearest
-// float, the lower one is negative for about half of all temperatures (0.7, 0.9, ..), and a masked logit gave NaN.
-__device__ inline float scale_hi(double x) { return (float)__hiloint2double(__double2hiint(x), 0); }
-__device__ inline float scale_lo(double x, float hi) { return fmaxf((float)(x - (double)hi), 1e-30f); }
-
 // The record is the same for every lane: all of it goes to scalar registers.
 __device__ inline FinalRow make_final_row(const StepArgs& a, const FinalInfo& f) {
   FinalRow R;
   R.z = a.Z + (int64_t)uniform(f.row) * a.ldz;
-  const double sc = f.invT * 1.4426950408889634, scq = f.invTd * 1.4426950408889634;
-  const float sc_hi = scale_hi(sc), scq_hi = scale_hi(scq);
-  R.mx = uniform((float)f.mx); R.sc_hi = uniform(sc_hi); R.sc_lo = uniform(scale_lo(sc, sc_hi)); R.invS = uniform(f.invS);
+  R.mx = uniform(f.mx); R.sc_hi = uniform(f.sc_hi); R.sc_lo = uniform(f.sc_lo); R.invS = uniform(f.invS);
   R.residual = uniform(f.mode) == 3;
   R.lds_at = -1;
   R.dtype = a.dtype;
   R.t_ng = uniform(f.t_ng); R.t_pre = uniform(f.t_pre); R.pi = uniform(f.pi); R.q_pre = uniform(f.q_pre);
   R.zq = static_cast<const char*>(a.draft_logits) + (size_t)uniform(f.drow) * a.V_d * (a.dtype == OT_BF16 ? 2 : 4);
-  R.mxq = uniform((float)f.mxq); R.scq_hi = uniform(scq_hi); R.scq_lo = uniform(scale_lo(scq, scq_hi));
+  R.mxq = uniform(f.mxq); R.scq_hi = uniform(f.scq_hi); R.scq_lo = uniform(f.scq_lo);
   R.invSq = uniform(f.invSq); R.argq = uniform(f.argq);
   R.greedy_draft = uniform(f.greedy_draft) != 0;
   return R;
 }
 
 // Inverse direct map of N ids v = first + e * stride (independent of which row is drawn from: issued early).  Ids past
-// the vocabulary read the last entry and are masked afterwards: no branch around the loads.
+// the vocabulary read the last entry and are masked afterwards: no branch around the loads.  all_exist (wavefront-uniform): there
+// are none, and the loads share one address.
 template <int N>
-__device__ inline void load_tmap(const int32_t* __restrict__ tmap, int V_t, int first, int stride, int* dv) {
+__device__ inline void load_tmap(const int32_t* __restrict__ tmap, int V_t, int first, int stride, bool all_exist, int* dv) {
+  if (all_exist) {
+    const int32_t* p = tmap + first;
 #pragma unroll
-  for (int e = 0; e < N; ++e) dv[e] = tmap[min(first + e * stride, V_t - 1)];
+    for (int e = 0; e < N; ++e) dv[e] = p[e * stride];
+  } else {
+#pragma unroll
+    for (int e = 0; e < N; ++e) dv[e] = tmap[min(first + e * stride, V_t - 1)];
+  }
 }
 
 // Stand-in logit of an id that does not exist or has no pre-image: finite, so that the two-float scaling below never
 // meets inf * 0, and so far below any maximum that its exponential is exactly 0.
 constexpr float kFarBelow = -1e30f;
 
-// The dynamic LDS of the draw kernels: the tiles' masses, then (where a workgroup takes several turns) the draft row.
+// The dynamic LDS of the draw kernels: the units' masses, then (where a workgroup takes several turns) the draft row.
 typedef __attribute__((address_space(3))) char* lds_chars;
 extern __shared__ __attribute__((aligned(16))) double s_draw_dynamic[];
 __device__ inline lds_chars draw_lds() { return (lds_chars)(void __attribute__((address_space(3)))*)s_draw_dynamic; }
@@ -141,9 +138,15 @@ template <int N> struct TileRaw { float z[N]; uint32_t xq[N]; };
 // logit) and nothing is converted between two loads.  With the conversion inside a conditional block per id every
 // gather was waited for by itself, eight round trips of about 1 us in a row.
 template <int N>
-__device__ inline void load_tile(const FinalRow& R, int V_t, int first, int stride, const int* dv, TileRaw<N>& raw) {
+__device__ inline void load_tile(const FinalRow& R, int V_t, int first, int stride, bool all_exist, const int* dv, TileRaw<N>& raw) {
+  if (all_exist) {
+    const float* z = R.z + first;
 #pragma unroll
-  for (int e = 0; e < N; ++e) raw.z[e] = R.z[min(first + e * stride, V_t - 1)];
+    for (int e = 0; e < N; ++e) raw.z[e] = z[e * stride];
+  } else {
+#pragma unroll
+    for (int e = 0; e < N; ++e) raw.z[e] = R.z[min(first + e * stride, V_t - 1)];
+  }
   if (!R.residual || R.greedy_draft) {                   // wavefront-uniform
 #pragma unroll
     for (int e = 0; e < N; ++e) raw.xq[e] = 0u;
@@ -158,10 +161,13 @@ __device__ inline void load_tile(const FinalRow& R, int V_t, int first, int stri
 template <int N>
 __device__ inline void tile_values(const FinalRow& R, int V_t, int first, int stride, int lo, int hi, const int* dv,
                                    const TileRaw<N>& raw, double* r) {
-  const bool all_exist = hi <= V_t;
+  if (hi <= V_t) {
 #pragma unroll
-  for (int e = 0; e < N; ++e)                                     // beyond V_t: 2^(-huge) = 0
-    r[e] = R.p_of(all_exist || first + e * stride < V_t ? raw.z[e] : kFarBelow);
+    for (int e = 0; e < N; ++e) r[e] = R.p_of(raw.z[e]);
+  } else {
+#pragma unroll
+    for (int e = 0; e < N; ++e) r[e] = R.p_of(first + e * stride < V_t ? raw.z[e] : kFarBelow);   // beyond V_t: 2^(-huge) = 0
+  }
   if (!R.residual) return;
   const uint32_t shift = R.dtype == OT_BF16 ? 16u : 0u;
   float xq[N];
@@ -179,11 +185,6 @@ __device__ inline void tile_values(const FinalRow& R, int V_t, int first, int st
       r[e] = v < V_t ? fmax(0.0, r[e] - R.qprime(v, dv[e], xq[e])) : 0.0;
     }
   }
-}
-
-// first id a lane sums among the eight tiles that start at `tile0`
-__device__ inline int draw_first_id(int tile0, int wave, int lane) {
-  return (tile0 + (wave >> 1)) * kResidTile + (wave & 1) * (kResidTile / 2) + lane;
 }
 
 // Copies the draft row to byte `at` of the dynamic LDS (all threads call it, a barrier follows): whole 16-byte chunks where
@@ -223,23 +224,22 @@ __device__ inline int stage_draft_row(const void* zq, int dtype, int V_d, int ti
 }
 
 struct DrawLds {
-  double w[kPickThreads / 64];
-  double base, target;
-  int first[kPickThreads / 64], lastnz[kPickThreads / 64];
-  int pick, fallback, last;
+  double w[16];                 // sums of the chosen unit's wavefronts
+  int missing;
 };
 
 constexpr size_t kDrawLdsBytes = 150 << 10;    // dynamic LDS of a workgroup with a copy of the draft row at most (160 KB a compute unit)
 
-// Mass of the 512 ids from `lo` on (this lane: first + e * 64), in every lane: of the residual or, where that is zero, minus
-// that of p.
-__device__ inline double half_tile_mass(const FinalRow& R, int V_t, int first, int lo, const int* dv, const TileRaw<kPerLane>& raw) {
-  double r[kPerLane];
+// Mass of the unit of 64 * kPer ids from `lo` on (this lane: lo + lane + e * 64), in every lane: of the residual or, where that
+// is zero, minus that of p.
+template <int kPer>
+__device__ inline double unit_mass(const FinalRow& R, int V_t, int lo, int lane, const int* dv, const TileRaw<kPer>& raw) {
+  double r[kPer];
   auto sum = [&](const FinalRow& S) {
-    tile_values<kPerLane>(S, V_t, first, 64, lo, lo + kResidTile / 2, dv, raw, r);
-    double x = 0.0;
+    tile_values<kPer>(S, V_t, lo + lane, 64, lo, lo + 64 * kPer, dv, raw, r);
+    double x = r[0] + r[1];
 #pragma unroll
-    for (int e = 0; e < kPerLane; e += 4) x += (r[e] + r[e + 1]) + (r[e + 2] + r[e + 3]);
+    for (int e = 2; e < kPer; e += 2) x += r[e] + r[e + 1];
     return wave_sum(x);
   };
   const double mass = sum(R);
@@ -248,142 +248,159 @@ __device__ inline double half_tile_mass(const FinalRow& R, int V_t, int first, i
   P.residual = false;
   return -sum(P);
 }
-// The same of a tile from its halves.
-__device__ inline double tile_mass(double a, double b) { return a <= 0.0 && b <= 0.0 ? a + b : fmax(a, 0.0) + fmax(b, 0.0); }
 
-// Workgroup `grp` of sequence b takes tiles [grp * group_tiles, (grp + 1) * group_tiles), group_tiles a multiple of
-// kTurnTiles (all kDrawThreads threads call this; f is the sequence's outcome record with f.mode != 0; dv holds tmap of
-// the ids draw_first_id(grp * group_tiles, wave, lane) + e * 64, e < kPerLane).  The dynamic LDS holds
-// max(ntiles, 2 * group_tiles) doubles (twice ntiles where one workgroup has all tiles) and, if row_at > 0, from double row_at on room for the draft row and 32 bytes.
-__device__ inline void draw_final_token(const StepArgs& a, int b, int grp, int group_tiles, const FinalInfo& f, int* dv,
+// In the workspace for a unit whose mass is not there (bits of a NaN that no arithmetic gives).
+constexpr unsigned long long kNoMassBits = ~0ull;
+__device__ inline bool no_mass(double x) { return (unsigned long long)__double_as_longlong(x) == kNoMassBits; }
+
+// A mass as stored (the residual's or, negative, that of p) as one of the distribution that is drawn from.
+__device__ inline double drawn_mass(double x, bool of_p) { return of_p ? fabs(x) : fmax(x, 0.0); }
+
+// What the scan of the masses chooses: the unit, the mass in front of it, and the target mass u * total.
+struct UnitPick { int unit; double base, target; bool empty; };
+
+// By one wavefront, from the masses of n_units units in LDS and the sums of 64 of them each (one turn of the loops up to 4096
+// units).  The total and the crossing come from the same sums; where rounding pushes the target past the end the last unit with
+// mass is taken.
+__device__ inline UnitPick pick_unit(const double* s_mass, const double* s_sums, int n_units, double u2, int lane, bool of_p) {
+  const int n_chunks = (n_units + 63) / 64;
+  UnitPick p;
+  auto chunk = [&](int c) { const double x = s_sums[min(c, n_chunks - 1)]; return c < n_chunks ? x : 0.0; };
+  double total = 0.0, x = 0.0, incl = 0.0;
+  for (int c0 = 0; c0 < n_chunks; c0 += 64) {
+    x = chunk(c0 + lane);
+    incl = wave_scan(x) + total;
+    total = lane_value(incl, 63);
+  }
+  p.empty = !(total > 0.0);
+  p.target = u2 * total;
+  p.base = 0.0;
+  int c = 0;
+  double before = 0.0;
+  for (int c0 = 0; c0 < n_chunks; c0 += 64) {
+    if (n_chunks > 64) {                                   // (otherwise the sums are still there)
+      x = chunk(c0 + lane);
+      incl = wave_scan(x) + before;
+    }
+    const unsigned long long past = __ballot(incl > p.target), some = past ? past : __ballot(x > 0.0);
+    if (some) {
+      const int l = past ? (int)__builtin_ctzll(past) : 63 - (int)__builtin_clzll(some);
+      c = c0 + l;
+      p.base = l > 0 ? lane_value(incl, l - 1) : before;
+      if (past) break;
+    }
+    before = lane_value(incl, 63);
+  }
+  const double m = c * 64 + lane < n_units ? drawn_mass(s_mass[c * 64 + lane], of_p) : 0.0;
+  const double run = wave_scan(m);
+  const unsigned long long past = __ballot(m > 0.0 && p.base + run > p.target), some = __ballot(m > 0.0);
+  const int i = past ? (int)__builtin_ctzll(past) : some ? 63 - (int)__builtin_clzll(some) : 0;
+  p.unit = c * 64 + i;
+  if (i > 0) p.base += lane_value(run, i - 1);
+  return p;
+}
+
+// Workgroup `grp` of sequence b takes units [grp * group_units, (grp + 1) * group_units) of n_units, group_units a multiple of
+// kDrawWaves (all kDrawThreads threads call this; f is the sequence's outcome record with f.mode != 0; dv holds tmap of the ids
+// (grp * group_units + wave) * 64 * kPer + lane + e * 64, e < kPer).  The dynamic LDS holds 65 doubles for every 64 units begun
+// (draw_lds_doubles) and, if row_at > 0, from double row_at on room for the draft row and 32 bytes.
+__host__ __device__ inline int draw_lds_doubles(int n_units) { return (n_units + 63) / 64 * 65; }
+template <int kPer>
+__device__ inline void draw_final_token(const StepArgs& a, int b, int grp, int n_units, int group_units, const FinalInfo& f, int* dv,
                                         DrawLds* L, int row_at) {
-  double* s_tiles = s_draw_dynamic;
+  constexpr int kUnit = 64 * kPer;
   const int tid = threadIdx.x, wave = uniform((int)(threadIdx.x >> 6)), lane = tid & 63;
+  const int n_chunks = (n_units + 63) / 64;
+  double *s_mass = s_draw_dynamic, *s_sums = s_mass + n_chunks * 64;   // the masses; the sums of 64 each
   FinalRow R = make_final_row(a, f);
-  const int tile0 = grp * group_tiles, tile1 = min(tile0 + group_tiles, a.ntiles);
+  const int unit0 = grp * group_units, unit1 = min(unit0 + group_units, n_units);
+  const bool alone = gridDim.x == 1;
+  double* masses = a.unit_mass + (int64_t)b * a.max_units;
+  if (tid == 0) L->missing = 0;
   if (row_at > 0 && R.residual && !R.greedy_draft) {     // workgroup-uniform
     R.lds_at = stage_draft_row<kDrawThreads>(R.zq, R.dtype, a.V_d, tid, 8 * row_at);
     __syncthreads();
   }
 
-  // ---- masses of this workgroup's tiles: wavefronts 2i and 2i+1 take the two halves of a tile (coalesced: consecutive
-  // lanes on consecutive ids) and leave them in LDS; after the last turn one thread per tile adds the halves and publishes
-  for (int t0 = tile0; t0 < tile1; t0 += kTurnTiles) {
-    const int tile = t0 + (wave >> 1), first = draw_first_id(t0, wave, lane);
-    if (tile >= tile1) break;
-    TileRaw<kPerLane> raw;
-    load_tile<kPerLane>(R, a.V_t, first, 64, dv, raw);
-    int dv_next[kPerLane] = {};                          // asked for behind what this turn waits for
-    if (t0 + kTurnTiles < tile1) load_tmap<kPerLane>(a.tmap, a.V_t, first + kTurnTiles * kResidTile, 64, dv_next);
-    const double mass = half_tile_mass(R, a.V_t, first, draw_first_id(t0, wave, 0), dv, raw);
-    if (lane == 0) s_tiles[2 * (tile - tile0) + (wave & 1)] = mass;
-#pragma unroll
-    for (int e = 0; e < kPerLane; ++e) dv[e] = dv_next[e];
-  }
-  __syncthreads();
-  if (gridDim.x == 1) {                                  // all tiles are this workgroup's (at most kDrawThreads): they stay in LDS
-    const double mass = tid < a.ntiles ? tile_mass(s_tiles[2 * tid], s_tiles[2 * tid + 1]) : 0.0;
-    __syncthreads();
-    if (tid < a.ntiles) { s_tiles[tid] = fmax(mass, 0.0); s_tiles[a.ntiles + tid] = mass; }
-  } else {
-    for (int i = tid; i < tile1 - tile0; i += kDrawThreads)
-      publish(&a.tile_r[(int64_t)b * a.ntiles + tile0 + i], tile_mass(s_tiles[2 * i], s_tiles[2 * i + 1]));
-    stores_done();                                        // before this workgroup is counted
-    __syncthreads();
-    if (tid == 0) L->last = arrive(&a.resid_count[b], gridDim.x);
-    __syncthreads();
-    if (!L->last) return;
-    for (int t = tid; t < a.ntiles; t += kDrawThreads) s_tiles[t] = fmax(observe(&a.tile_r[(int64_t)b * a.ntiles + t]), 0.0);
-  }
-  __syncthreads();
-
-  // ---- the last workgroup of the sequence: inverse CDF over the tile masses, then inside the tile that holds the draw
-  // Wavefront 0: running mass over the tiles in ascending order, in place (a wavefront scan of 64 tiles at a time plus a
-  // carry), and the tile where it crosses u * total.  The total and the crossing both come from these same sums.
-  auto pick_tile = [&](bool may_fall_back) {
-    double* m = s_tiles;
-    double carry = 0.0;
-    for (int t0 = 0; t0 < a.ntiles; t0 += 64) {
-      const int t = t0 + lane;
-      const double incl = wave_scan(t < a.ntiles ? m[t] : 0.0) + carry;
-      if (t < a.ntiles) m[t] = incl;
-      carry = __shfl(incl, 63);
-    }
-    const double total = carry;
-    const int fallback = may_fall_back && !(total > 0.0);    // residual of zero mass: draw from p
-    const double target = f.u2 * total;
-    int pick = -1;
-    for (int t0 = 0; t0 < a.ntiles && pick < 0; t0 += 64) {
-      const int t = t0 + lane;
-      const unsigned long long hit = __ballot(t < a.ntiles && m[t] > target);
-      if (hit) pick = t0 + (int)__ffsll((long long)hit) - 1;
-    }
-    if (pick < 0) {                          // rounding pushed the target past the end: take the last tile that adds mass
-      pick = 0;
-      for (int t = 1; t < a.ntiles; ++t) if (m[t] > m[t - 1]) pick = t;
-    }
-    const double base = pick > 0 ? m[pick - 1] : 0.0;
+  // ---- masses of this workgroup's units, a wavefront on each (coalesced: consecutive lanes on consecutive ids)
+  for (int unit = unit0 + wave; unit < unit1; unit += kDrawWaves) {
+    const int lo = unit * kUnit;
+    TileRaw<kPer> raw;
+    load_tile<kPer>(R, a.V_t, lo + lane, 64, lo + kUnit <= a.V_t, dv, raw);
+    int dv_next[kPer] = {};                              // asked for behind what this turn waits for
+    const int lo_next = lo + kDrawWaves * kUnit;
+    if (unit + kDrawWaves < unit1) load_tmap<kPer>(a.tmap, a.V_t, lo_next + lane, 64, lo_next + kUnit <= a.V_t, dv_next);
+    const double mass = unit_mass<kPer>(R, a.V_t, lo, lane, dv, raw);
     if (lane == 0) {
-      // The word is not read back: the leading workgroup stored it in this launch, on an XCD with its own L2.  That store was
-      // written through before the workgroup was counted in, so this one comes after it.
-      if (fallback) publish(&a.out.flags[b], f.flags | OT_FLAG_RESID_ZERO);
-      L->pick = pick; L->base = base; L->target = target; L->fallback = fallback;
+      if (alone) s_mass[unit] = mass;
+      else publish(masses + unit, mass);
+    }
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) dv[e] = dv_next[e];
+  }
+  if (!alone) stores_done();                              // of this wavefront; behind the barrier, of all of them
+  __syncthreads();
+  auto sum_chunks = [&](bool of_p, bool from_memory) {
+    for (int c = wave; c < n_chunks; c += kDrawWaves) {
+      const int t = c * 64 + lane;
+      double x = 0.0;
+      if (from_memory) {
+        x = observe(masses + min(t, n_units - 1));
+        if (no_mass(x)) L->missing = 1;
+        s_mass[t] = x;
+      } else {
+        x = s_mass[t];
+      }
+      x = wave_sum(t < n_units ? drawn_mass(x, of_p) : 0.0);
+      if (lane == 0) s_sums[c] = x;
     }
   };
-  if (wave == 0) pick_tile(true);
+  sum_chunks(false, !alone);
   __syncthreads();
-  if (L->fallback) {                         // workgroup-uniform
-    R.residual = false;
-    for (int t = tid; t < a.ntiles; t += kDrawThreads)
-      s_tiles[t] = fabs(gridDim.x == 1 ? s_tiles[a.ntiles + t] : observe(&a.tile_r[(int64_t)b * a.ntiles + t]));
-    __syncthreads();
-    if (wave == 0) pick_tile(false);
-    __syncthreads();
+  if (!alone) {
+    if (L->missing) return;
+    for (int t = tid; t < n_units; t += kDrawThreads) publish(masses + t, __longlong_as_double((long long)kNoMassBits));
   }
-  const double target = L->target;
-  const bool picker = wave < kPickThreads / 64;
-  const int pick = uniform(L->pick);
-  const int v0 = pick * kResidTile + tid * kPer;         // a picking thread owns kPer consecutive ids: ascending running sum
-  double r[kPer] = {0.0, 0.0, 0.0, 0.0};
-  double excl = 0.0;
-  if (picker) {
-    int dvp[kPer];
-    TileRaw<kPer> raw;
-    load_tmap<kPer>(a.tmap, a.V_t, v0, 1, dvp);
-    load_tile<kPer>(R, a.V_t, v0, 1, dvp, raw);
-    tile_values<kPer>(R, a.V_t, v0, 1, pick * kResidTile, (pick + 1) * kResidTile, dvp, raw, r);
-    const double incl = wave_scan(((r[0] + r[1]) + r[2]) + r[3]);
-    excl = __shfl_up(incl, 1);
-    if (lane == 0) excl = 0.0;
+
+  // ---- inverse CDF over the masses (every wavefront for itself), then inside the unit that holds the draw: kPer wavefronts
+  // take 64 ids each
+  UnitPick P = pick_unit(s_mass, s_sums, n_units, f.u2, lane, false);
+  if (P.empty) {                                          // residual of zero mass: draw from p
+    R.residual = false;
+    __syncthreads();
+    sum_chunks(true, false);
+    __syncthreads();
+    P = pick_unit(s_mass, s_sums, n_units, f.u2, lane, true);
+    P.empty = true;
+  }
+  double r = 0.0, incl = 0.0;
+  const int lo = uniform(P.unit) * kUnit + wave * 64;
+  if (wave < kPer) {
+    const bool all_exist = lo + 64 <= a.V_t;
+    int dvp;
+    TileRaw<1> raw;
+    load_tmap<1>(a.tmap, a.V_t, lo + lane, 0, all_exist, &dvp);
+    load_tile<1>(R, a.V_t, lo + lane, 0, all_exist, &dvp, raw);
+    tile_values<1>(R, a.V_t, lo + lane, 0, lo, lo + 64, &dvp, raw, &r);
+    incl = wave_scan(r);
     if (lane == 63) L->w[wave] = incl;
   }
   __syncthreads();
-  if (picker) {
-    double before = L->base;
-    for (int w = 0; w < wave; ++w) before += L->w[w];
-    double c = before + excl;
-    int first = 0x7FFFFFFF, last = -1;
-#pragma unroll
-    for (int e = 0; e < kPer; ++e) {
-      c += r[e];
-      if (r[e] > 0.0) {
-        last = v0 + e;
-        if (first == 0x7FFFFFFF && c > target) first = v0 + e;
+  if (wave < kPer) {
+    // lane w: what the first w + 1 wavefronts hold.  The wavefront in whose ids the running sum passes the target writes: the same
+    // sums in every wavefront, so it is one of them (rounding past the end: the last with mass)
+    const double sums = wave_scan(lane < kPer ? L->w[lane] : 0.0);
+    const unsigned long long past = __ballot(lane < kPer && P.base + sums > P.target), some = __ballot(lane < kPer && L->w[lane] > 0.0);
+    const int at = past ? (int)__builtin_ctzll(past) : some ? 63 - (int)__builtin_clzll(some) : 0;
+    if (wave == at) {
+      const double before = P.base + (wave > 0 ? lane_value(sums, wave - 1) : 0.0);
+      const unsigned long long past1 = __ballot(r > 0.0 && before + incl > P.target), some1 = __ballot(r > 0.0);
+      const int i = past1 ? (int)__builtin_ctzll(past1) : some1 ? 63 - (int)__builtin_clzll(some1) : -1;
+      if (lane == 0) {
+        a.out.out_tokens[f.row] = i >= 0 ? lo + i : -1;
+        a.out.flags[b] = f.flags | (P.empty ? OT_FLAG_RESID_ZERO : 0);
       }
     }
-    // ids ascend with the lanes: the lowest lane that crossed, the highest that holds mass.  (By ballots: LDS atomics of a
-    // whole wavefront on one word are unrolled lane by lane, which took 3 to 4 us here.)
-    const unsigned long long crossed = __ballot(first != 0x7FFFFFFF), mass = __ballot(last >= 0);
-    const int w_first = crossed ? __builtin_amdgcn_readlane(first, (int)__ffsll((long long)crossed) - 1) : -1;
-    const int w_last = mass ? __builtin_amdgcn_readlane(last, 63 - (int)__clzll((long long)mass)) : -1;
-    if (lane == 0) { L->first[wave] = w_first; L->lastnz[wave] = w_last; }
-  }
-  __syncthreads();
-  if (tid == 0) {
-    int token = -1;
-    for (int w = 0; w < kPickThreads / 64 && token < 0; ++w) token = L->first[w];
-    for (int w = kPickThreads / 64 - 1; w >= 0 && token < 0; --w) token = L->lastnz[w];
-    a.out.out_tokens[f.row] = token;
   }
 }
 

@@ -1,5 +1,5 @@
 // The launches that draw the final token of every sequence (Algorithm 1: correction token from the residual of Eq. 2,
-// or free token from p), grid = (groups of tiles of kResidTile target ids) x (sequences).
+// or free token from p), grid = (groups of units of target ids) x (sequences).
 //   final_draw_kernel   the outcome records of the acceptance test are in memory (written by the launch before).
 //   accept_draw_kernel  follows the launch that did the draft side and the softmax partials, the LM head's or the
 //                       statistics launch: every workgroup first repeats the translation and the acceptance test of its
@@ -18,16 +18,25 @@
 namespace otv {
 namespace {
 
-// row_at: where the draft row's copy starts in the dynamic LDS, in doubles (0: no copy)
-__global__ __launch_bounds__(kDrawThreads) void final_draw_kernel(StepArgs a, int group_tiles, int row_at) {
+// How the draw is split, see draw_split.  row_at: where the draft row's copy starts in the dynamic LDS, in doubles (0: no copy)
+struct DrawSplit { int n_units, group_units, row_at; };
+
+template <int kPer>
+__device__ inline int draw_first_id(const DrawSplit& s, int grp, int wave) {
+  return (grp * s.group_units + wave) * (64 * kPer);
+}
+
+template <int kPer>
+__global__ __launch_bounds__(kDrawThreads) void final_draw_kernel(StepArgs a, DrawSplit s) {
   const int b = blockIdx.y, grp = blockIdx.x, tid = threadIdx.x;
   const int wave = uniform(tid >> 6), lane = tid & 63;
   __shared__ DrawLds s_draw;
-  int dv[kPerLane];
-  load_tmap<kPerLane>(a.tmap, a.V_t, draw_first_id(grp * group_tiles, wave, lane), 64, dv);   // overlaps the next load
+  int dv[kPer];
+  const int first = draw_first_id<kPer>(s, grp, wave);
+  load_tmap<kPer>(a.tmap, a.V_t, first + lane, 64, first + 64 * kPer <= a.V_t, dv);   // overlaps the next load
   const FinalInfo f = a.fin[b];
   if (f.mode == 0) return;                  // greedy or flagged sequence: nothing to draw
-  draw_final_token(a, b, grp, group_tiles, f, dv, &s_draw, row_at);
+  draw_final_token<kPer>(a, b, grp, s.n_units, s.group_units, f, dv, &s_draw, s.row_at);
 }
 
 // Row offsets of up to kFusedMaxB sequences as a kernel argument (the host has them): the workgroup knows its rows without
@@ -36,14 +45,14 @@ struct RowOffsets { int32_t v[kFusedMaxB + 1]; };
 constexpr int64_t kRepeatedMergeBytes = 32 << 20;
 
 // kDraw = false: grid = (1) x (sequences); the workgroup only runs the test and leaves the outcome record in memory for
-// a final_draw_kernel launch (used when repeating the test in every tile group would cost more than a launch).
+// a final_draw_kernel launch (used when repeating the test in every group of units would cost more than a launch).
 // kChunks: the partials come from the statistics launch (chunk partials in three arrays per side) instead of the
 // LM head's epilogue and draft-row pieces.
 // kMany: more than kFusedMaxB sequences: row offsets from memory, partials merged in binary64 (as a runtime flag these two
 // cost a single sequence 0.7 of 13 us).
 // kWide: draft rows of more than kChunksAtOnce chunks (merge_draft_chunks).
-template <bool kDraw, bool kChunks, bool kMany, bool kWide = kMany>
-__global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, RowOffsets ro, int group_tiles, int row_at) {
+template <int kPer, bool kDraw, bool kChunks, bool kMany = false, bool kWide = kMany>
+__global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, RowOffsets ro, DrawSplit split) {
   const int b = blockIdx.y, grp = blockIdx.x, tid = threadIdx.x;
   const int wave = uniform(tid >> 6), lane = tid & 63;
   __shared__ DrawLds s_draw;
@@ -51,7 +60,7 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, R
   __shared__ float s_pmx[64];
   __shared__ double s_pinv[64];
   __shared__ int s_parg[64];
-  int dv[kPerLane];
+  int dv[kPer];
 
   const int r0 = kMany ? a.row_off[b] : ro.v[b];
   const int k = (kMany ? a.row_off[b + 1] : ro.v[b + 1]) - r0 - 1;
@@ -63,11 +72,11 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, R
   // The LM-head launch left what the drafted ids look up (ProbeRecord) and the draft rows' statistics.  The last
   // wavefront fetches them (one load of each array per lane), walks the window (Eq. 1), asks for the logits of the
   // proposed tokens and forms q' while they are on their way, all on its own, while the other wavefronts merge the softmax
-  // partials of the target rows; the translation is thus repeated by every tile group of the sequence, and the lead group
+  // partials of the target rows; the translation is thus repeated by every group of the sequence, and the lead group
   // writes its outputs and the cache's use statistics.  That wavefront's chain of round trips and binary64 functions is what
   // the others wait for: its loads leave before anything is known about the temperature, the walk comes before the functions,
   // and q' is formed once as a product instead of through the logarithms of its factors (from the launch's start to the
-  // outcome 5.4 -> 3.8 us for one sequence of five drafted ids).
+  // outcome 5.4 -> 2.7 us for one sequence of five drafted ids).
   const int q0 = r0 - b;
   constexpr int kTestWave = kDrawWaves - 1;   // runs the walk and the test
   Window W;
@@ -76,52 +85,58 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, R
   bool bad = false, reached = false;
   int pos = 0;
   double u1 = 0.0;
+  double invT = 1.0;
   uint32_t rnd[4] = {0, 0, 0, 0};             // of row `lane`: word 0 tests that mapped position, word 1 draws its final token
+  Scale sc{}, scq{};
   if (wave == kTestWave) {
     const ProbeRecord* rec = a.probe + b;
     const unsigned long long hit = rec->hit[lane];
     D.dm = rec->dm[lane];
     bad = rec->bad != 0;                      // wavefront-uniform
     D.zq = rec->zq[lane];
-    D.mxq = 0.f; D.Sq = 1.0; D.argq = -1; D.q = 0.0;
+    D.mxq = 0.f; D.Sq = 1.0; D.argq = -1;
     DraftPartials<kChunks> part;
     if (lane < k) part.load(a, q0 + lane);
+    if (T > 0.f) philox4x32_10((uint32_t)lane, a.step, (uint32_t)sid, (uint32_t)(sid >> 32), (uint32_t)a.seed, (uint32_t)(a.seed >> 32), rnd);
+    invT = T > 0.f ? 1.0 / (double)T : 1.0;
+    const double invTd = Td > 0.f ? 1.0 / (double)Td : 1.0;
+    sc = split_scale(invT); scq = split_scale(invTd);
     W = walk_window(k, lane, hit, D.dm);
     reached = ((W.starts >> lane) & 1ull) != 0ull;
     pos = __popcll(W.starts & bits_below(lane));
     if (reached) z_tok = a.Z[(int64_t)(r0 + pos) * a.ldz + W.t];
+    u1 = u24(__shfl(rnd[0], pos));
     if (lane < k) {
-      if constexpr (kChunks) merge_draft_chunks<kWide>(a, q0 + lane, Td, part, &D.mxq, &D.Sq, &D.argq, kMany);
+      if constexpr (kChunks) merge_draft_chunks<kWide>(a, q0 + lane, Td, invTd, part, &D.mxq, &D.Sq, &D.argq, kMany);
       else merge_draft_pieces(a, q0 + lane, Td, part, &D.mxq, &D.Sq, &D.argq);
       if (lead) { a.drow_max[q0 + lane] = D.mxq; a.drow_sum[q0 + lane] = D.Sq; a.drow_arg[q0 + lane] = D.argq; }
-      if (Td > 0.f) D.q = exp(((double)D.zq - (double)D.mxq) * (1.0 / (double)Td)) / D.Sq;
-      else D.q = a.draft_ids[q0 + lane] == D.argq ? 1.0 : 0.0;
     }
+    D.invSq = 1.0 / D.Sq;
+    D.q = Td > 0.f ? exp(((double)D.zq - (double)D.mxq) * invTd) * D.invSq : 0.0;
+    if (!(Td > 0.f) && lane < k) D.q = a.draft_ids[q0 + lane] == D.argq ? 1.0 : 0.0;
     D.qp = segment_q(D.q, W);
-    if (T > 0.f) philox4x32_10((uint32_t)lane, a.step, (uint32_t)sid, (uint32_t)(sid >> 32), (uint32_t)a.seed, (uint32_t)(a.seed >> 32), rnd);
-    u1 = u24(__shfl(rnd[0], pos));
   }
-  const double invT = T > 0.f ? 1.0 / (double)T : 1.0;
-  const double invTd = Td > 0.f ? 1.0 / (double)Td : 1.0;
+  if (kMany && wave != kTestWave) invT = T > 0.f ? 1.0 / (double)T : 1.0;
   for (int row = wave; row <= k; row += kDrawWaves) {
     if (kChunks)
-      merge_chunk_row(a.tpart_max, a.tpart_sum, a.tpart_arg, a.ncht, r0 + row, invT, lane, s_pmx, s_pinv, s_parg, row, lead,
+      merge_chunk_row(a.tpart_max, a.tpart_sum, a.tpart_arg, a.ncht, r0 + row, T, invT, lane, s_pmx, s_pinv, s_parg, row, lead,
                       a.row_max, a.row_sum, a.row_arg, kMany);
     else
-      merge_fused_row(a.fused.part, a.fused.nfine, r0 + row, invT, lane, s_pmx, s_pinv, s_parg, row, lead, a.row_max,
+      merge_fused_row(a.fused.part, a.fused.nfine, r0 + row, T, lane, s_pmx, s_pinv, s_parg, row, lead, a.row_max,
                       a.row_sum, a.row_arg);
   }
   if (!(T > 0.f) && !lead) return;            // a greedy sequence draws nothing: its other groups have nothing to do
-  // The inverse map of this wavefront's ids is needed last (by the tile masses) and asked for here, behind the loads
+  // The inverse map of this wavefront's ids is needed last (by the masses) and asked for here, behind the loads
   // that the test waits for: loads return in issue order, and asked for first it held those back by its own latency.
-  if (kDraw) load_tmap<kPerLane>(a.tmap, a.V_t, draw_first_id(grp * group_tiles, wave, lane), 64, dv);
+  const int first = draw_first_id<kPer>(split, grp, wave);
+  if (kDraw) load_tmap<kPer>(a.tmap, a.V_t, first + lane, 64, first + 64 * kPer <= a.V_t, dv);
   __syncthreads();
   Outcome O;
   if (wave == kTestWave) {
     FinalInfo fin{};                          // mode 0: nothing to draw
     if (!bad) {
       O = test_window(T, invT, W, D, reached, pos, z_tok, u1, s_pmx, s_pinv, s_parg);
-      fin = final_info(r0, q0, T, Td, invT, invTd, W, D, O, u24((uint32_t)__builtin_amdgcn_readlane((int)rnd[1], O.n)), s_pmx, s_pinv);
+      fin = final_info(r0, q0, T, Td, sc, scq, W, D, O, u24((uint32_t)__builtin_amdgcn_readlane((int)rnd[1], O.n)), s_pmx, s_pinv);
     }
     if (lane == 0) s_fin = fin;
     if (!kDraw && lane == 0) a.fin[b] = fin;
@@ -131,69 +146,85 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, R
     if (bad) {
       write_bad_sequence(a, b, r0, k, lane);
     } else {
-      write_translation(a, b, r0, k, lane, W, reached, pos, D.qp);
+      write_translation(a, b, r0, k, lane, W, reached, pos, D.qp, !(T > 0.f));
       write_outcome(a, b, r0, k, lane, T, W, O, reached, pos, s_parg);
     }
   }
   if (!kDraw) return;
   const FinalInfo f = s_fin;
   if (f.mode == 0) return;
-  draw_final_token(a, b, grp, group_tiles, f, dv, &s_draw, row_at);
+  draw_final_token<kPer>(a, b, grp, split.n_units, split.group_units, f, dv, &s_draw, split.row_at);
 }
 
-}  // namespace
-
-// Tiles per workgroup of the draw.  Eight (one turn) as long as that leaves no more than a workgroup per compute unit:
-// a small batch is bound by the chain of round trips in one workgroup, which every further turn would lengthen.  With
-// more, each workgroup takes as many turns as bring their number back to one per compute unit (86 registers: five
-// wavefronts per SIMD, so that a workgroup of 16 fills one): its start, its share of the merge and its count at the end are then paid once for several turns,
-// and a turn's loads overlap the sums of the turn before.  At most 64 turns, so that the halves' scratch stays small.
-// Measured (kernel time, one turn per workgroup against this rule): 128 sequences x 128256 ids 109 + 10 us of a test
-// launch against 39 us in one launch (2 us a turn), 64 x 152064 (half greedy) 39 + 10 against 30, 300 x 32003 65 against
-// 30; 16 x 128256 and below stay at one turn.  Right above one workgroup per compute unit (us per step from the logits, two
-// rows a sequence): 17 x 128256 27.1 against 22.4, 20: 28.9 / 22.8, 24: 31.4 / 24.2, 32: 33.8 / 26.2.  Up to 1.25, 1.5 and 2
-// workgroups per compute unit were slower at 64, 128 and 300 sequences as well (128: 60, 56 and 51 against 38 us).
-int draw_group_tiles(int ntiles, int B, int n_cu) {
-  const int64_t groups = (int64_t)ceil_div(ntiles, kTurnTiles) * B;
-  return kTurnTiles * std::min(64, std::max(1, ceil_div(groups, std::max(n_cu, 1))));
+// Units of the draw and their share per workgroup.  While no more than a workgroup per compute unit is needed for one turn each,
+// a wavefront takes as few ids as that allows: 128 (up to 512 units), else 256, else 512 (1024 above two million target ids).  A
+// small batch is bound by the chain of instructions and round trips in one workgroup, which fewer ids per lane shorten.  With
+// more groups than compute units each workgroup takes as many turns as bring their number back to one per compute unit (84
+// registers: five wavefronts per SIMD, so that a workgroup of 16 fills one): its start, its share of the merge and its look at the
+// masses are then paid once for several turns, and a turn's loads overlap the sums of the turn before.
+// Measured, us per step, 128 / 256 / 512 ids a wavefront: 6 rows x 32000 ids 53.9 / 54.1 / 55.2, 12 rows x 64000 (d = 1024) 39.4 /
+// 40.1 / 42.6, 24 x 152064 -- / 180.8 / 182.0, 80 x 32000 66.7 / 66.2 / 68.1, 6 x 152064 (d = 1024) -- / 69.2 / 70.7.
+template <int kPer> DrawSplit draw_split(int V_t, int B, int n_cu) {
+  DrawSplit s;
+  s.n_units = ceil_div(V_t, 64 * kPer);
+  const int64_t groups = (int64_t)ceil_div(s.n_units, kDrawWaves) * B;
+  s.group_units = kDrawWaves * std::max(1, ceil_div(groups, std::max(n_cu, 1)));
+  s.row_at = 0;
+  return s;
 }
 
 // hosted: the LM-head launch left its softmax partials, the draft rows' pieces and the probe records; otherwise the
 // statistics launch left its chunk partials and the probe records.  row_off_host holds the B + 1 row offsets.
-hipError_t launch_final_draw(const StepArgs& a, const int32_t* row_off_host, int n_cu, hipStream_t stream) {
-  if (a.B == 0) return hipSuccess;
-  const int group_tiles = draw_group_tiles(a.ntiles, a.B, n_cu);
-  const dim3 grid(ceil_div(a.ntiles, group_tiles), a.B), block(kDrawThreads);
-  size_t lds = std::max((size_t)a.ntiles, 2 * (size_t)group_tiles) * sizeof(double);
+template <int kPer>
+hipError_t launch_draw(const StepArgs& a, const int32_t* row_off_host, const DrawSplit& split, hipStream_t stream) {
+  DrawSplit s = split;
+  const dim3 grid(ceil_div(s.n_units, s.group_units), a.B), block(kDrawThreads);
+  size_t lds = (size_t)(draw_lds_doubles(s.n_units) + 1) / 2 * 2 * sizeof(double);
   // From two turns on the workgroup keeps the draft row in LDS where it fits: a gather from memory moves a 128-byte line
   // per id, about 2 us of a turn, the copy costs that once (128 sequences x 128256 ids: 51 us without, 39 with).  Up to the largest
-// copies (us per step from the logits, 20 / 128 sequences): 50257 bf16 ids 26.0 / 60 against 26.4 / 76 gathered, 75000 26.6 / 62
-// against 28 / 89, 32000 fp32 ids 24.7 / 59 against 25.6 / 71.
-  int row_at = 0;
+  // copies (us per step from the logits, 20 / 128 sequences): 50257 bf16 ids 26.0 / 60 against 26.4 / 76 gathered, 75000 26.6 / 62
+  // against 28 / 89, 32000 fp32 ids 24.7 / 59 against 25.6 / 71.
   const size_t row_bytes = (size_t)a.V_d * (a.dtype == OT_BF16 ? 2 : 4) + 32;
-  if (group_tiles > kTurnTiles && lds + 16 + row_bytes <= kDrawLdsBytes) {
-    row_at = (int)((lds + 15) / 16) * 2;
-    lds = (size_t)row_at * sizeof(double) + row_bytes;
+  if (s.group_units > kDrawWaves && lds + row_bytes <= kDrawLdsBytes) {
+    s.row_at = (int)(lds / sizeof(double));
+    lds += row_bytes;
   }
   RowOffsets ro;
   for (int b = 0; b <= kFusedMaxB; ++b) ro.v[b] = row_off_host[b <= a.B ? b : a.B];
   if (!a.hosted) {                                         // a few chunks per row: always one launch
-    if (a.B > kFusedMaxB) hipLaunchKernelGGL((accept_draw_kernel<true, true, true>), grid, block, lds, stream, a, ro, group_tiles, row_at);
-    else if (a.nchd > kChunksAtOnce) hipLaunchKernelGGL((accept_draw_kernel<true, true, false, true>), grid, block, lds, stream, a, ro, group_tiles, row_at);
-    else hipLaunchKernelGGL((accept_draw_kernel<true, true, false>), grid, block, lds, stream, a, ro, group_tiles, row_at);
+    if (a.B > kFusedMaxB) {
+      if constexpr (kPer >= 8) hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, true>), grid, block, lds, stream, a, ro, s);
+      else return hipErrorInvalidValue;
+    } else if (a.nchd > kChunksAtOnce) {
+      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, true>), grid, block, lds, stream, a, ro, s);
+    } else {
+      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true>), grid, block, lds, stream, a, ro, s);
+    }
     return hipGetLastError();
   }
   if (a.B > kFusedMaxB) return hipErrorInvalidValue;
-  // Every tile group of a sequence repeats the merge of its rows' partials: M x nfine x 16 bytes per group.  Up to
+  // Every group of units of a sequence repeats the merge of its rows' partials: M x nfine x 16 bytes per group.  Up to
   // about the traffic that costs as much as a launch this is one launch; beyond it the test gets a launch of its own.
   const int64_t repeated = (int64_t)a.M * a.fused.nfine * (int64_t)sizeof(Partial) * grid.x;
   if (repeated <= kRepeatedMergeBytes) {
-    hipLaunchKernelGGL((accept_draw_kernel<true, false, false>), grid, block, lds, stream, a, ro, group_tiles, row_at);
+    hipLaunchKernelGGL((accept_draw_kernel<kPer, true, false>), grid, block, lds, stream, a, ro, s);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL((accept_draw_kernel<false, false, false>), dim3(1, a.B), block, 0, stream, a, ro, group_tiles, row_at);
-  hipLaunchKernelGGL(final_draw_kernel, grid, block, lds, stream, a, group_tiles, row_at);
+  hipLaunchKernelGGL((accept_draw_kernel<8, false, false>), dim3(1, a.B), block, 0, stream, a, ro, s);
+  hipLaunchKernelGGL(final_draw_kernel<kPer>, grid, block, lds, stream, a, s);
   return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_final_draw(const StepArgs& a, const int32_t* row_off_host, int n_cu, hipStream_t stream) {
+  if (a.B == 0) return hipSuccess;
+  const DrawSplit two = draw_split<2>(a.V_t, a.B, n_cu), four = draw_split<4>(a.V_t, a.B, n_cu);
+  if (two.group_units == kDrawWaves && two.n_units <= 512 && a.B <= kFusedMaxB) return launch_draw<2>(a, row_off_host, two, stream);
+  if (four.group_units == kDrawWaves && a.B <= kFusedMaxB) return launch_draw<4>(a, row_off_host, four, stream);
+  const DrawSplit eight = draw_split<8>(a.V_t, a.B, n_cu);
+  if (eight.n_units <= 4096) return launch_draw<8>(a, row_off_host, eight, stream);
+  return launch_draw<16>(a, row_off_host, draw_split<16>(a.V_t, a.B, n_cu), stream);
 }
 
 }  // namespace otv

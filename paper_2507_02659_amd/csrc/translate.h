@@ -296,9 +296,9 @@ __device__ __forceinline__ double segment_q(double q, const Window& w) {
 
 // The translation's outputs (n_mapped, hits_proposed, flags; mapped_ids, span_start, span_len, q_tok of the sequence's rows) and
 // the use statistics of the cache entries, by one wavefront of the step per sequence.  pos: mapped position of a segment that
-// the walk reached.
+// the walk reached.  with_flags: nothing is drawn (otherwise the draw, which may add a flag, writes them).
 __device__ __forceinline__ void write_translation(const StepArgs& a, int b, int r0, int k, int lane, const Window& w, bool reached,
-                                                  int pos, double qp) {
+                                                  int pos, double qp, bool with_flags) {
   const bool is_hit = reached && w.L > 1;
   if (is_hit) {
     // use statistics of the entry (Appendix, cache eviction): one more use, last used now
@@ -311,7 +311,7 @@ __device__ __forceinline__ void write_translation(const StepArgs& a, int b, int 
   if (lane == 0) {
     a.out.n_mapped[b] = w.m;
     a.out.hits_proposed[b] = hits;
-    publish(&a.out.flags[b], w.flags);   // another workgroup may add a bit to it in the same launch (draw_final_token)
+    if (with_flags) a.out.flags[b] = w.flags;
   }
   if (reached) {
     a.out.mapped_ids[r0 + pos] = w.t; a.out.span_start[r0 + pos] = lane; a.out.span_len[r0 + pos] = w.L;
