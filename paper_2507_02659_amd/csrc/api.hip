@@ -134,9 +134,10 @@ int ot_verify_init(const ot_verify_config* cfg, ot_ctx** out) {
   ok = ok && dev_alloc(c, &c->dmap, (size_t)c->V_d) && dev_alloc(c, &c->tmap, tmap_h.size());
   ok = ok && dev_alloc(c, &c->Z, R * (size_t)c->V_t);
   ok = ok && dev_alloc(c, &c->tpart_max, R * c->ncht) && dev_alloc(c, &c->tpart_sum, R * c->ncht) && dev_alloc(c, &c->tpart_arg, R * c->ncht);
-  if (c->dtype == OT_BF16) {
-    const size_t nf = (size_t)(c->Vp / 128);              // the narrowest workgroups
-    ok = ok && dev_alloc(c, &c->fpart, R * nf);
+  {
+    // a partial per row and 64 columns of the fp32 head and of up to 16 rows, else per row and 128 columns at most
+    const size_t per_64 = (size_t)(c->Vp / 64), per_128 = (size_t)(c->Vp / 128);
+    ok = ok && dev_alloc(c, &c->fpart, c->dtype == OT_BF16 ? std::max(R * per_128, std::min<size_t>(R, 16) * per_64) : R * per_64);
   }
   ok = ok && dev_alloc(c, &c->dpart_max, KQ * c->nchd) && dev_alloc(c, &c->dpart_sum, KQ * c->nchd) && dev_alloc(c, &c->dpart_arg, KQ * c->nchd);
   ok = ok && dev_alloc(c, &c->row_max, R) && dev_alloc(c, &c->row_sum, R) && dev_alloc(c, &c->row_arg, R);
@@ -240,26 +241,28 @@ static int step_impl(ot_ctx* ctx, ot_ngram_cache* cache, const ot_step_in* in, c
 #define OT_MARK(i) do { if (ev && e == hipSuccess) e = hipEventRecord(ev[i], st); } while (0)
   OT_MARK(0);
   if (e == hipSuccess && !from_logits) {
-    if (ctx->dtype == OT_BF16) {
-      // Where its kernel supports it, the LM-head launch leaves per-tile softmax partials of the target rows (no second
-      // pass over the logits) and hosts the draft side of the step (the draft rows' statistics in pieces, the drafted
-      // ids' lookups): what follows it is then one launch that merges both, walks the windows, tests and draws.
-      const bool supported = lmhead_bf16_draft_workers(M, ctx->d, ctx->Vp, in->B, K, ctx->n_cu) > 0 && K >= 1 && in->B <= kFusedMaxB;
-      const bool host_it = supported && (ctx->draft_side == OT_DRAFT_SIDE_IN_LM_HEAD ||
-                                         (ctx->draft_side == OT_DRAFT_SIDE_AUTO &&
-                                          lmhead_bf16_hosts_draft_side(M, ctx->d, ctx->Vp, in->B, K, ctx->V_d, ctx->n_cu)));
-      const int nfine = host_it ? lmhead_bf16_fused_partials(M, ctx->d, ctx->Vp, ctx->n_cu) : 0;
-      if (nfine > 0) {
-        a.fused.row_off = in->row_off; a.fused.temperature = in->temperature; a.fused.B = in->B; a.fused.nfine = nfine;
-        a.fused.part = ctx->fpart;
-        a.hosted = 1;
-        a.plan = make_piece_plan(lmhead_bf16_draft_workers(M, ctx->d, ctx->Vp, in->B, K, ctx->n_cu), K);
-      }
-      e = launch_lmhead_bf16(static_cast<const uint16_t*>(in->hidden), M, ctx->d, ctx->Wp, ctx->Kp, ctx->Vp, ctx->Z,
-                             ctx->V_t, a.ldz, ctx->zeros, &a.fused, a.hosted ? &a : nullptr, ctx->n_cu, st);
+    // Where its kernel supports it, the LM-head launch leaves per-tile softmax partials of the target rows (no second
+    // pass over the logits) and hosts the draft side of the step (the draft rows' statistics in pieces, the drafted
+    // ids' lookups): what follows it is then one launch that merges both, walks the windows, tests and draws.
+    const bool bf16 = ctx->dtype == OT_BF16;
+    const int workers = in->B > kFusedMaxB || K < 1 ? 0 : bf16 ? lmhead_bf16_draft_workers(M, ctx->d, ctx->Vp, in->B, K, ctx->n_cu)
+                                                               : lmhead_f32_draft_workers(M, ctx->V_t, in->B, K, ctx->n_cu);
+    if (workers > 0 && (ctx->draft_side == OT_DRAFT_SIDE_IN_LM_HEAD ||
+                        (ctx->draft_side == OT_DRAFT_SIDE_AUTO &&
+                         (bf16 ? lmhead_bf16_hosts_draft_side(M, ctx->d, ctx->Vp, in->B, K, ctx->V_d, ctx->n_cu)
+                               : lmhead_f32_hosts_draft_side(M, ctx->d, ctx->V_t, in->B, K, ctx->V_d, ctx->n_cu))))) {
+      a.fused.row_off = in->row_off; a.fused.temperature = in->temperature; a.fused.B = in->B; a.fused.part = ctx->fpart;
+      a.fused.nfine = bf16 ? lmhead_bf16_fused_partials(M, ctx->d, ctx->Vp, ctx->n_cu) : ceil_div(ctx->V_t, 64);
+      a.hosted = 1;
+      a.plan = make_piece_plan(workers, K);
     }
+    const StepArgs* draft_side = a.hosted ? &a : nullptr;
+    if (bf16)
+      e = launch_lmhead_bf16(static_cast<const uint16_t*>(in->hidden), M, ctx->d, ctx->Wp, ctx->Kp, ctx->Vp, ctx->Z,
+                             ctx->V_t, a.ldz, ctx->zeros, &a.fused, draft_side, ctx->n_cu, st);
     else
-      e = launch_lmhead_f32(static_cast<const float*>(in->hidden), M, ctx->d, ctx->Wf, ctx->Z, ctx->V_t, a.ldz, st);
+      e = launch_lmhead_f32(static_cast<const float*>(in->hidden), M, ctx->d, ctx->Wf, ctx->Z, ctx->V_t, a.ldz, &a.fused,
+                            draft_side, st);
   }
   OT_MARK(1);
   // Without the LM head's help the statistics get a launch of their own, which also does the lookups, and one launch

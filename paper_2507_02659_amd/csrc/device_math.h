@@ -42,11 +42,15 @@ __device__ inline double dpp_f64(double x) {
   const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), kCtrl, kRowMask, 0xF, kAllRows);
   return __hiloint2double(hi, lo);                       // rows outside the mask receive +0.0
 }
-__device__ inline double wave_sum(double x) {
+__device__ inline double row16_sum(double x) {
   x += dpp_f64<0xB1>(x);             // neighbours 1 apart
   x += dpp_f64<0x4E>(x);             // 2 apart
   x += dpp_f64<0x141>(x);            // mirrored halves of eight lanes
   x += dpp_f64<0x140>(x);            // mirrored row of sixteen: every lane holds its row's sum
+  return x;
+}
+__device__ inline double wave_sum(double x) {
+  x = row16_sum(x);
   x += dpp_f64<0x142, 0xA>(x);       // lane 15 of row 0 into row 1, of row 2 into row 3
   x += dpp_f64<0x143, 0xC>(x);       // lane 31 into rows 2 and 3: lane 63 holds the total
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), 63), __builtin_amdgcn_readlane(__double2loint(x), 63));
@@ -66,14 +70,22 @@ template <int kCtrl, int kRowMask = 0xF>
 __device__ inline int dpp_self(int x) { return __builtin_amdgcn_update_dpp(x, x, kCtrl, kRowMask, 0xF, false); }
 template <int kCtrl, int kRowMask = 0xF>
 __device__ inline float dpp_self(float x) { return __int_as_float(dpp_self<kCtrl, kRowMask>(__float_as_int(x))); }
-__device__ inline float wave_max(float x) {
+__device__ inline float row16_max(float x) {
   x = fmaxf(x, dpp_self<0xB1>(x)); x = fmaxf(x, dpp_self<0x4E>(x)); x = fmaxf(x, dpp_self<0x141>(x));
-  x = fmaxf(x, dpp_self<0x140>(x)); x = fmaxf(x, dpp_self<0x142, 0xA>(x)); x = fmaxf(x, dpp_self<0x143, 0xC>(x));
+  return fmaxf(x, dpp_self<0x140>(x));
+}
+__device__ inline int row16_min(int x) {
+  x = min(x, dpp_self<0xB1>(x)); x = min(x, dpp_self<0x4E>(x)); x = min(x, dpp_self<0x141>(x));
+  return min(x, dpp_self<0x140>(x));
+}
+__device__ inline float wave_max(float x) {
+  x = row16_max(x);
+  x = fmaxf(x, dpp_self<0x142, 0xA>(x)); x = fmaxf(x, dpp_self<0x143, 0xC>(x));
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
 }
 __device__ inline int wave_min(int x) {
-  x = min(x, dpp_self<0xB1>(x)); x = min(x, dpp_self<0x4E>(x)); x = min(x, dpp_self<0x141>(x));
-  x = min(x, dpp_self<0x140>(x)); x = min(x, dpp_self<0x142, 0xA>(x)); x = min(x, dpp_self<0x143, 0xC>(x));
+  x = row16_min(x);
+  x = min(x, dpp_self<0x142, 0xA>(x)); x = min(x, dpp_self<0x143, 0xC>(x));
   return __builtin_amdgcn_readlane(x, 63);
 }
 

@@ -624,78 +624,117 @@ __global__ __launch_bounds__(WPG * 64) void lmhead_bf16_wide_kernel(const uint16
 }
 
 // ---------------------------------------------------------------------------------------------------------------
-// Skinny kernel: M <= 16 rows (one MFMA row tile).  A workgroup owns 64 columns and splits the hidden dimension
+typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));   // rows may start at any float
+
+// A row's four logits from column n on.
+__device__ __forceinline__ void store_logits(float* __restrict__ dst, int n, int V_t, const f32x4& z) {
+  if (n + 4 <= V_t) {
+    *reinterpret_cast<f32x4_u*>(dst) = z;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (n + e < V_t) dst[e] = z[e];
+  }
+}
+
+// Exponent scales of an M-block's rows, for the statistics of their logits: thread b holds sequence b's rows and temperature
+// (asked for in front of the first weights, at most 255 sequences) and fills in those of the block.
+struct BlockScales {
+  int lo = 0, hi = 0;
+  float T = 0.f;
+  __device__ __forceinline__ void load(const FusedStats& fs, int tid) {
+    if (fs.part && tid < fs.B) { lo = fs.row_off[tid]; hi = fs.row_off[tid + 1]; T = fs.temperature[tid]; }
+  }
+  __device__ __forceinline__ void fill(float* s_scale, int row0, int n_rows) const {
+    for (int r = max(lo - row0, 0); r < min(hi - row0, n_rows); ++r) s_scale[r] = T > 0.f ? kLog2eF / T : kLog2eF;
+  }
+};
+
+// Skinny kernel: M <= 16 rows (one MFMA row tile).  A workgroup takes 64 columns at a time and splits the hidden dimension
 // over its 8 wavefronts, so that even a 32000-column head yields thousands of wavefronts streaming W; the hidden
 // fragments are tiny and read straight from global memory (L2 resident).  The 8 partial tiles are summed through
-// LDS in a fixed order.
+// LDS in a fixed order; a row's 64 logits end up in 16 lanes, which also form their softmax partial.
+// The draft side of the step runs in workgroups of its own in front (n_front of them, see front_draft_side).  Two workgroups fit on
+// a compute unit (94 registers, three fetches deep; 144 with four deep and branches around the refills, where 500 + 16 workgroups
+// were a third round: 44.4 us for 6 rows x 32000 columns, 40.1 now and without the draft side).  Several tiles per workgroup, so
+// that there are fewer partials, empty its pipeline at every tile: 190 to 211 us for 152064 columns instead of 166.
 template <int PF>
-__global__ __launch_bounds__(512) void lmhead_bf16_skinny_kernel(const uint16_t* __restrict__ H, int M, int d,
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void lmhead_bf16_skinny_kernel(const uint16_t* __restrict__ H, int M, int d,
                                                                  const uint4* __restrict__ Wp, int nks,
-                                                                 float* __restrict__ Z, int V_t, int64_t ldz) {
+                                                                 float* __restrict__ Z, int V_t, int64_t ldz,
+                                                                 const uint16_t* __restrict__ zeros, FusedStats fs, int n_front, StepArgs ds) {
   constexpr int kWaves = 8;
-  __shared__ __attribute__((aligned(16))) float sRed[kWaves][4][64][4];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int wt = blockIdx.x;
+  constexpr int kRow = 17;                          // float4 per padded row of the reduction scratch
+  __shared__ f32x4 sRed[kWaves][16 * kRow];
+  __shared__ float sScale[16];
+  const int tid = threadIdx.x, wave = uniform(tid >> 6), lane = tid & 63;
+  const int wg = (int)blockIdx.x - n_front;
+  static_assert(sizeof(sRed) >= kFrontLdsBytes, "scratch of the draft side");
+  if (wg < 0) {
+    front_draft_side<uint16_t, kWaves>(ds, blockIdx.x, tid, sRed);
+    return;
+  }
+  const int wt = wg;
   const int ks0 = (int)(((int64_t)nks * wave) / kWaves), ks1 = (int)(((int64_t)nks * (wave + 1)) / kWaves);
-  const uint4* wp = Wp + (int64_t)wt * packed_tile_units(nks) + lane;
-  const int h_row = lane & 15, h_col = 8 * (lane >> 4);
-  const bool h_ok = h_row < M;
-  const uint16_t* hp = H + (int64_t)(h_ok ? h_row : 0) * d + h_col;
+  const int h_col = 8 * (lane >> 4);
+  const uint32_t h_at = (uint32_t)(min(lane & 15, M - 1) * d + h_col);   // rows past M are never stored: any valid row will do
+  BlockScales scales;
+  scales.load(fs, tid);
 
+  const uint4* wp = Wp + (int64_t)wt * packed_tile_units(nks);
   f32x4 acc[4];
 #pragma unroll
   for (int nw = 0; nw < 4; ++nw) acc[nw] = f32x4{0.f, 0.f, 0.f, 0.f};
-  uint4 bq[PF][4], hq[PF];
+  u32x4 bq[PF][4];
+  uint4 hq[PF];
   auto fetch = [&](int slot, int ks) {
+    const uint4* w = wp + (int64_t)ks * 256;
 #pragma unroll
-    for (int nw = 0; nw < 4; ++nw) {               // read once by the whole launch: nontemporal (see the wide kernel)
-      const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(wp + ((int64_t)ks * 4 + nw) * 64));
-      bq[slot][nw] = make_uint4(v.x, v.y, v.z, v.w);
-    }
-    hq[slot] = make_uint4(0, 0, 0, 0);
-    if (h_ok && ks * 32 + h_col < d) hq[slot] = *reinterpret_cast<const uint4*>(hp + ks * 32);
+    for (int nw = 0; nw < 4; ++nw)                 // read once by the whole launch: nontemporal (see the wide kernel)
+      bq[slot][nw] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(w + nw * 64 + lane));
+    // the padded tail of the hidden dimension must read as zero
+    hq[slot] = *reinterpret_cast<const uint4*>(ks * 32 + h_col < d ? H + ks * 32 + h_at : zeros);
+  };
+  auto multiply = [&](int slot) {
+    const bf16x8 hf = __builtin_bit_cast(bf16x8, hq[slot]);
+#pragma unroll
+    for (int nw = 0; nw < 4; ++nw)
+      acc[nw] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, bq[slot][nw]), hf, acc[nw], 0, 0, 0);
   };
 #pragma unroll
-  for (int s = 0; s < PF; ++s) {
+  for (int s = 0; s < PF; ++s)
     if (ks0 + s < ks1) fetch(s, ks0 + s);
-  }
-  for (int base = ks0; base < ks1; base += PF) {
+  int base = ks0;
+  for (; base + 2 * PF <= ks1; base += PF) {       // every refill in range: no branch inside
 #pragma unroll
     for (int s = 0; s < PF; ++s) {
-      const int ks = base + s;
-      if (ks < ks1) {
-        uint4 bw[4];
-#pragma unroll
-        for (int nw = 0; nw < 4; ++nw) bw[nw] = bq[s][nw];
-        const bf16x8 hf = __builtin_bit_cast(bf16x8, hq[s]);
-        if (ks + PF < ks1) fetch(s, ks + PF);
-#pragma unroll
-        for (int nw = 0; nw < 4; ++nw)
-          acc[nw] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, bw[nw]), hf, acc[nw], 0, 0, 0);
-      }
+      multiply(s);
+      fetch(s, base + s + PF);
     }
   }
 #pragma unroll
-  for (int nw = 0; nw < 4; ++nw)
-    *reinterpret_cast<float4*>(&sRed[wave][nw][lane][0]) = make_float4(acc[nw][0], acc[nw][1], acc[nw][2], acc[nw][3]);
+  for (int s = 0; s < 2 * PF - 1; ++s) {
+    if (base + s < ks1) {
+      multiply(s % PF);
+      if (s < PF - 1 && base + s + PF < ks1) fetch(s % PF, base + s + PF);
+    }
+  }
+  // acc[nw][e] = partial Z[lane%16][64*wt + 16*nw + 4*(lane/16) + e]
+#pragma unroll
+  for (int nw = 0; nw < 4; ++nw) sRed[wave][(lane & 15) * kRow + nw * 4 + (lane >> 4)] = acc[nw];
+  scales.fill(sScale, 0, 16);
   __syncthreads();
-  if (tid < 256) {
-    const int nw = tid >> 6, l = tid & 63;
-    float4 sum = *reinterpret_cast<const float4*>(&sRed[0][nw][l][0]);
+  if (wave >= 4) return;
+  const int m = tid >> 4, c = tid & 15;              // row and float4 column of the summed tile
+  f32x4 sum = sRed[0][m * kRow + c];
 #pragma unroll
-    for (int w = 1; w < kWaves; ++w) {
-      const float4 x = *reinterpret_cast<const float4*>(&sRed[w][nw][l][0]);
-      sum.x += x.x; sum.y += x.y; sum.z += x.z; sum.w += x.w;
-    }
-    const int m = l & 15;
-    const int n = wt * 64 + nw * 16 + 4 * (l >> 4);
-    if (m < M) {
-      float* dst = Z + (int64_t)m * ldz + n;
-      const float v[4] = {sum.x, sum.y, sum.z, sum.w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (n + e < V_t) dst[e] = v[e];
-    }
+  for (int w = 1; w < kWaves; ++w) sum += sRed[w][m * kRow + c];
+  const int n = wt * 64 + 4 * c;
+  if (m < M) store_logits(Z + (int64_t)m * ldz + n, n, V_t, sum);
+  if (fs.part) {
+    const float z[4] = {sum[0], sum[1], sum[2], sum[3]};
+    const Partial p = partial_of_64(z, n, V_t, sScale[m < M ? m : 0]);
+    if (m < M && c == 0) fs.part[(int64_t)m * fs.nfine + wt] = p;
   }
 }
 
@@ -710,11 +749,11 @@ __global__ __launch_bounds__(512) void lmhead_bf16_skinny_kernel(const uint16_t*
 // A workgroup owns 64 columns and up to 48 rows and splits the hidden dimension over its wavefronts, whose partial tiles
 // are summed through LDS in a fixed order: a head of 1024 columns is 16 workgroups of 8 wavefronts, one of 32000 is 500
 // per row block.  The row blocks of a column tile run on the same XCD back to back and meet in its L2.
-// Measured (64 rows, d = 1024, V_t = 32000 / 5 rows, d = 256, V_t = 1024): 47 / 4.3 us, against 575 / 68 us of a kernel
+// The launch also leaves softmax partials and takes the draft side (a workgroup per job, or packed into few: f32_row_front),
+// which spares the statistics launch: 57.2 -> 54.8 us per step at 64 rows, 17.4 -> 14.2 at 5.
+// Measured (64 rows, d = 1024, V_t = 32000 / 5 rows, d = 256, V_t = 1024): 46 / 4.2 us, with the draft side 49.6 / 5.4, against 575 / 68 us of a kernel
 // whose threads owned one column each over all of the hidden dimension (1000 and 4 workgroups of serial chains); error
 // against 64 bits 4.7e-7 and 1.1e-7, with one long chain per logit 2e-6 and 6e-7.
-typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));   // rows may start at any float
-
 __global__ __launch_bounds__(256) void pack_w_f32_kernel(const float* __restrict__ W, int d, int V_t,
                                                          float4* __restrict__ Wp, int nkb, int64_t n_units) {
   const int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -734,13 +773,25 @@ __global__ __launch_bounds__(256) void pack_w_f32_kernel(const float* __restrict
 template <int MT, int WAVES, int PF>
 __global__ __launch_bounds__(WAVES * 64) void lmhead_f32_kernel(const float* __restrict__ H, int M, int d,
                                                                 const f32x4* __restrict__ Wp, int nkb, int n_wtiles,
-                                                                float* __restrict__ Z, int V_t, int64_t ldz, int m_blocks) {
+                                                                float* __restrict__ Z, int V_t, int64_t ldz, int m_blocks,
+                                                                FusedStats fs, int n_front, StepArgs ds) {
   constexpr int kRow = 17;                              // float4 per padded row of the reduction scratch
   __shared__ f32x4 sRed[WAVES][MT * 16 * kRow];
+  __shared__ float sScale[MT * 16];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int slot = (int)blockIdx.x >> 3;
-  const int wt = (slot / m_blocks) * 8 + ((int)blockIdx.x & 7), row0 = (slot % m_blocks) * (MT * 16);
+  static_assert(sizeof(sRed) >= kFrontLdsBytes, "scratch of the draft side");
+  static_assert(WAVES * 64 >= kFusedMaxB, "a thread per sequence");
+  const int wg = (int)blockIdx.x - n_front;             // n_front is a multiple of 8: the XCDs below are those of the block ids
+  if (wg < 0) {
+    if (ds.plan.base == kDraftPieces) front_draft_side<float, WAVES>(ds, blockIdx.x, tid, sRed);
+    else front_draft_rows<float, WAVES>(ds, blockIdx.x, n_front, tid, sRed);
+    return;
+  }
+  const int slot = wg >> 3;
+  const int wt = (slot / m_blocks) * 8 + (wg & 7), row0 = (slot % m_blocks) * (MT * 16);
   if (wt >= n_wtiles) return;                           // padding of the id space
+  BlockScales scales;
+  scales.load(fs, tid);
   const int whole = d / 16;                             // blocks without a ragged end, split over the wavefronts
   const int kb0 = (int)(((int64_t)whole * wave) / WAVES), kb1 = (int)(((int64_t)whole * (wave + 1)) / WAVES);
   const f32x4* wp = Wp + (int64_t)wt * packed_f32_tile_units(nkb) + lane;
@@ -807,6 +858,7 @@ __global__ __launch_bounds__(WAVES * 64) void lmhead_f32_kernel(const float* __r
 #pragma unroll
     for (int e = 0; e < 4; ++e)
       sRed[wave][(mt * 16 + (lane & 15)) * kRow + 4 * g + e] = f32x4{acc[mt][0][e], acc[mt][1][e], acc[mt][2][e], acc[mt][3][e]};
+  scales.fill(sScale, row0, MT * 16);
   __syncthreads();
   for (int i = tid; i < MT * 256; i += WAVES * 64) {
     const int r = i >> 4, c = i & 15;
@@ -814,25 +866,37 @@ __global__ __launch_bounds__(WAVES * 64) void lmhead_f32_kernel(const float* __r
 #pragma unroll
     for (int w = 1; w < WAVES; ++w) sum += sRed[w][r * kRow + c];
     const int m = row0 + r, n = wt * 64 + 4 * c;
-    if (m < M) {
-      float* dst = Z + (int64_t)m * ldz + n;
-      if (n + 4 <= V_t) {
-        *reinterpret_cast<f32x4_u*>(dst) = sum;
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (n + e < V_t) dst[e] = sum[e];
-      }
+    if (m < M) store_logits(Z + (int64_t)m * ldz + n, n, V_t, sum);
+    if (fs.part) {
+      const float z[4] = {sum[0], sum[1], sum[2], sum[3]};
+      const Partial p = partial_of_64(z, n, V_t, sScale[m < M ? r : 0]);
+      if (m < M && c == 0) fs.part[(int64_t)m * fs.nfine + wt] = p;
     }
   }
 }
 
+// Front workgroups of the kernels that give each draft-side job one: a sequence's lookups, a piece of a draft row.
+int front_jobs(const StepArgs& a) { return a.B + a.plan.jobs(a.K); }
+bool front_plan_fits(const StepArgs& a) {
+  return a.K >= 1 && a.B >= 1 && a.plan.base >= 1 && a.plan.more >= 0 && a.plan.more <= a.K &&
+         a.plan.base + (a.plan.more > 0) <= kDraftPieces &&
+         (int64_t)a.plan.more * (a.plan.base + 1) + (int64_t)(a.K - a.plan.more) * a.plan.base == a.plan.workers;
+}
+
+// Front workgroups of an fp32 launch that takes the draft side by whole rows: few, because its multiplying workgroups fill the
+// chip (64 rows, d = 1024, V_t = 32000: 1000 workgroups, four to a compute unit).  There a workgroup for each of 16 sequences'
+// lookups and 48 rows' pieces put some of those back by a round: 50.8 us instead of 46.2.
+int f32_row_front(int B, int K) { return std::min(32, ceil_div(std::max(B, ceil_div(K, 4)), 8) * 8); }
+
 template <int MT, int WAVES, int PF>
-hipError_t launch_f32(const float* H, int M, int d, const float* Wp, float* Z, int V_t, int64_t ldz, hipStream_t stream) {
+hipError_t launch_f32(const float* H, int M, int d, const float* Wp, float* Z, int V_t, int64_t ldz, const FusedStats& fs,
+                      const StepArgs* draft_side, hipStream_t stream) {
   const int nkb = ceil_div(d, 16), n_wtiles = ceil_div(V_t, 64), m_blocks = ceil_div(M, MT * 16);
-  hipLaunchKernelGGL((lmhead_f32_kernel<MT, WAVES, PF>), dim3((unsigned)(ceil_div(n_wtiles, 8) * 8 * m_blocks)),
+  const int n_front = !draft_side ? 0 : draft_side->plan.base == kDraftPieces ? ceil_div(front_jobs(*draft_side), 8) * 8
+                                                                              : f32_row_front(draft_side->B, draft_side->K);
+  hipLaunchKernelGGL((lmhead_f32_kernel<MT, WAVES, PF>), dim3((unsigned)(n_front + ceil_div(n_wtiles, 8) * 8 * m_blocks)),
                      dim3(WAVES * 64), 0, stream, H, M, d, reinterpret_cast<const f32x4*>(Wp), nkb, n_wtiles, Z, V_t, ldz,
-                     m_blocks);
+                     m_blocks, fs, n_front, draft_side ? *draft_side : StepArgs{});
   return hipGetLastError();
 }
 
@@ -954,7 +1018,7 @@ int lmhead_bf16_tile_cols(int M, int d, int Vp, int n_cu) {
 }
 
 int lmhead_bf16_fused_partials(int M, int d, int Vp, int n_cu) {
-  if (M <= 16) return 0;             // the skinny kernel does not fuse
+  if (M <= 16) return Vp / kGemmColsPerWave;
   return ceil_div(Vp, lmhead_bf16_tile_cols(M, d, Vp, n_cu));
 }
 
@@ -963,8 +1027,18 @@ int lmhead_bf16_fused_partials(int M, int d, int Vp, int n_cu) {
 // partials and hosts nothing.
 int lmhead_bf16_draft_workers(int M, int d, int Vp, int B, int K, int n_cu) {
   const int nfine = lmhead_bf16_fused_partials(M, d, Vp, n_cu);
-  if (nfine == 0) return 0;
+  if (M <= 16) return kDraftPieces * K;      // workgroups of their own
   return M > kSingleBlockRows ? lmhead_bf16_front_workgroups(M, B) * kWideWaves : nfine;
+}
+
+// Partials per row of up to 16 rows beyond which these are merged by a statistics launch over the logits instead: every workgroup
+// of the draw merges its sequence's rows, 512 partials a round trip.  6 rows: 500 partials (32000 columns) 49.1 us per step against
+// 53.4 with a statistics launch; 2376 (152064 columns) 179.7 against 178.3, the launch that merges takes 13.4 us instead of 7.9.
+constexpr int kMaxMergedPartials = 1024;
+// Whether the pieces of draft rows of row_bytes each, a workgroup on each, end before a launch of head_us does, or no later than a
+// statistics launch behind it would: a workgroup that only reads draws 8 KB per us next to the weight streams.
+static bool front_pieces_end_in_time(double row_bytes, double head_us) {
+  return row_bytes / kDraftPieces / kFrontBytesPerUs <= head_us + 5.0;
 }
 
 // Whether the LM-head launch should host the draft side (the draft rows' statistics, the drafted ids' lookups, and the
@@ -983,6 +1057,7 @@ bool lmhead_bf16_hosts_draft_side(int M, int d, int Vp, int B, int K, int V_d, i
   if (B < 1 || B > kFusedMaxB || K < 1) return false;
   const int workers = lmhead_bf16_draft_workers(M, d, Vp, B, K, n_cu);
   if (workers == 0) return false;
+  if (M <= 16) return Vp / kGemmColsPerWave <= kMaxMergedPartials && front_pieces_end_in_time(2.0 * V_d, lmhead_launch_us(M, d, Vp));
   if (M <= kSingleBlockRows) {
     if (lmhead_bf16_tile_cols(M, d, Vp, n_cu) < 256) return false;
     return 2 * K <= workers || 4.0 * M * Vp / 5.0e6 >= 9.0 * ceil_div(K, workers);
@@ -1021,8 +1096,12 @@ hipError_t launch_lmhead_bf16(const uint16_t* H, int M, int d, const uint16_t* W
   }
   if (tiles <= 1) {
     const int nks = Kp / 32, n_wtiles = Vp / kGemmColsPerWave;
-    hipLaunchKernelGGL((lmhead_bf16_skinny_kernel<4>), dim3(n_wtiles), dim3(512), 0, stream, H, M, d,
-                       reinterpret_cast<const uint4*>(Wp), nks, Z, V_t, ldz);
+    const bool hosts = draft_side && fs.part;
+    if (hosts && !front_plan_fits(*draft_side)) return hipErrorInvalidValue;
+    const int n_front = hosts ? front_jobs(*draft_side) : 0;
+    hipLaunchKernelGGL((lmhead_bf16_skinny_kernel<3>), dim3(n_front + n_wtiles), dim3(512), 0, stream, H, M, d,
+                       reinterpret_cast<const uint4*>(Wp), nks, Z, V_t, ldz, zeros, fs, n_front,
+                       hosts ? *draft_side : StepArgs{});
     return hipGetLastError();
   }
   if (M <= kSingleBlockRows) {
@@ -1075,13 +1154,37 @@ hipError_t launch_pack_w_f32(const float* W, int d, int V_t, float* Wp, hipStrea
 // of L2 but put more wavefronts on a compute unit, and this product needs them to cover its loads: 64 rows as two blocks
 // of two tiles 47 us, as one of four 50 us (d = 1024, V_t = 32000).  A single row tile splits the hidden dimension over
 // eight wavefronts (more bytes in flight, small heads fill more of the chip), the others over four (eight: 51 us).
-hipError_t launch_lmhead_f32(const float* H, int M, int d, const float* Wp, float* Z, int V_t, int64_t ldz,
-                             hipStream_t stream) {
-  if (M == 0) return hipSuccess;
+static int f32_block_tiles(int M) {
   const int tiles = ceil_div(M, 16);
-  if (tiles == 1) return launch_f32<1, 8, 4>(H, M, d, Wp, Z, V_t, ldz, stream);
-  if (ceil_div(tiles, 3) * 3 < ceil_div(tiles, 2) * 2) return launch_f32<3, 4, 2>(H, M, d, Wp, Z, V_t, ldz, stream);
-  return launch_f32<2, 4, 2>(H, M, d, Wp, Z, V_t, ldz, stream);
+  return tiles == 1 ? 1 : ceil_div(tiles, 3) * 3 < ceil_div(tiles, 2) * 2 ? 3 : 2;
+}
+hipError_t launch_lmhead_f32(const float* H, int M, int d, const float* Wp, float* Z, int V_t, int64_t ldz,
+                             const FusedStats* fused, const StepArgs* draft_side, hipStream_t stream) {
+  if (M == 0) return hipSuccess;
+  FusedStats fs{};
+  if (fused && fused->part) {
+    if (fused->nfine != ceil_div(V_t, 64) || fused->B < 1 || fused->B > kFusedMaxB) return hipErrorInvalidValue;
+    fs = *fused;
+  }
+  if (!fs.part) draft_side = nullptr;
+  if (draft_side && !front_plan_fits(*draft_side)) return hipErrorInvalidValue;
+  const int tiles = f32_block_tiles(M);
+  if (tiles == 1) return launch_f32<1, 8, 4>(H, M, d, Wp, Z, V_t, ldz, fs, draft_side, stream);
+  if (tiles == 3) return launch_f32<3, 4, 2>(H, M, d, Wp, Z, V_t, ldz, fs, draft_side, stream);
+  return launch_f32<2, 4, 2>(H, M, d, Wp, Z, V_t, ldz, fs, draft_side, stream);
+}
+
+// A launch that leaves room on the chip gives every piece of a draft row a workgroup of its own, a larger one takes whole rows.
+int lmhead_f32_draft_workers(int M, int V_t, int B, int K, int n_cu) {
+  const int multiplying = ceil_div(ceil_div(V_t, 64), 8) * 8 * ceil_div(M, 16 * f32_block_tiles(M));
+  return multiplying + B + kDraftPieces * K <= 2 * n_cu ? kDraftPieces * K : K;
+}
+bool lmhead_f32_hosts_draft_side(int M, int d, int V_t, int B, int K, int V_d, int n_cu) {
+  if (B < 1 || B > kFusedMaxB || K < 1) return false;
+  const double head_us = std::max(4.0 * d * (double)V_t / 6.0e6, 2.0 * M * d * (double)V_t / 1.0e8);
+  if (lmhead_f32_draft_workers(M, V_t, B, K, n_cu) > K) return front_pieces_end_in_time(4.0 * V_d, head_us);
+  const int front = f32_row_front(B, K);
+  return ceil_div(B, front) * 5.0 + ceil_div(K, 4 * front) * (4.0 * V_d / 3.0e3) <= head_us;
 }
 
 }  // namespace otv

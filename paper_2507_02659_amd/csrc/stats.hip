@@ -176,15 +176,7 @@ __global__ __launch_bounds__(kStatThreads) void softmax_stats_kernel(StepArgs a)
   const bool by_ballot = a.B <= kBallotSequences;
   if (wg < 0) {
     __shared__ DraftLds s_d;
-    const int b = blockIdx.x, tid = threadIdx.x;
-    const int r0 = a.row_off[b], k = a.row_off[b + 1] - r0 - 1;
-    draft_lds_reset(&s_d, tid);
-    __syncthreads();
-    fetch_ids_and_probe(a, r0 - b, k, tid, kStatThreads, &s_d);
-    __syncthreads();
-    ProbeRecord* rec = a.probe + b;
-    if (tid < 64) { rec->hit[tid] = s_d.hit[tid]; rec->zq[tid] = s_d.zq[tid]; rec->dm[tid] = s_d.dm[tid]; }
-    if (tid == 0) rec->bad = s_d.bad;
+    lookup_sequence(a, blockIdx.x, threadIdx.x, kStatThreads, &s_d);
     return;
   }
   if (wg < n_target) {

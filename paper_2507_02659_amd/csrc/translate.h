@@ -112,6 +112,18 @@ __device__ __forceinline__ void fetch_ids_and_probe(const StepArgs& a, int q0, i
   }
 }
 
+// The lookups of sequence b by a workgroup of n threads (all call it): its ProbeRecord.
+__device__ __forceinline__ void lookup_sequence(const StepArgs& a, int b, int tid, int n, DraftLds* L) {
+  const int r0 = a.row_off[b], k = a.row_off[b + 1] - r0 - 1;
+  draft_lds_reset(L, tid);
+  __syncthreads();
+  fetch_ids_and_probe(a, r0 - b, k, tid, n, L);
+  __syncthreads();
+  ProbeRecord* rec = a.probe + b;
+  if (tid < 64) { rec->hit[tid] = L->hit[tid]; rec->zq[tid] = L->zq[tid]; rec->dm[tid] = L->dm[tid]; }
+  if (tid == 0) rec->bad = L->bad;
+}
+
 // ---------------------------------------------------------------------------------------------- draft row statistics
 // 16-byte vectors of a logit row, kept as loaded until they are used (a bf16 vector unpacks to 8 floats).
 template <typename T> struct RowVec;
@@ -339,18 +351,18 @@ __device__ __forceinline__ const TD* piece_wave_slice(const StepArgs& a, int q, 
 }
 
 // requests the first batch of this wavefront's slice, for a later workgroup_draft_piece<.., true> of the same piece
-template <typename TD, int kWaves>
+template <typename TD, int kWaves, int kBatch = kPieceBatch>
 __device__ __forceinline__ void workgroup_draft_piece_request(const StepArgs& a, int q, int e0, int n, int tid,
-                                                              RowFirstBatch<TD, kPieceBatch>& first) {
+                                                              RowFirstBatch<TD, kBatch>& first) {
   int lo, n_own;
   const TD* x = piece_wave_slice<TD, kWaves>(a, q, e0, n, tid >> 6, &lo, &n_own);
-  row_first_batch_load<TD, kPieceBatch>(x, n_own, tid & 63, first);
+  row_first_batch_load<TD, kBatch>(x, n_own, tid & 63, first);
 }
 
-template <typename TD, int kWaves, bool kFirst = false>
+template <typename TD, int kWaves, bool kFirst = false, int kBatch = kPieceBatch>
 __device__ __forceinline__ void workgroup_draft_piece(const StepArgs& a, int q, int e0, int n, float Td, int tid,
                                                       float* s_mx, int32_t* s_arg, double* s_S, DraftPiece* out,
-                                                      const RowFirstBatch<TD, kPieceBatch>* first = nullptr) {
+                                                      const RowFirstBatch<TD, kBatch>* first = nullptr) {
   const int wave = tid >> 6, lane = tid & 63;
   int lo, n_own;
   const TD* x = piece_wave_slice<TD, kWaves>(a, q, e0, n, wave, &lo, &n_own);
@@ -359,7 +371,7 @@ __device__ __forceinline__ void workgroup_draft_piece(const StepArgs& a, int q, 
   int arg = 0x7FFFFFFF;
   double S = 0.0;
   if (n_own > 0) {
-    wave_row_stats<TD, kPieceBatch, kFirst>(x, n_own, scale, lane, &mx, &arg, &S, first);
+    wave_row_stats<TD, kBatch, kFirst>(x, n_own, scale, lane, &mx, &arg, &S, first);
     arg += e0 + lo;
   }
   // The two barriers order LDS accesses only (all LDS operations of this wavefront done, then meet): the fence of
@@ -384,6 +396,72 @@ __device__ __forceinline__ void workgroup_draft_piece(const StepArgs& a, int q, 
     *out = r;
   }
   lds_barrier();
+}
+
+// Draft-side job `job` of a launch with a workgroup for each of them in front of those that multiply: the lookups of sequence
+// `job`, then one piece of a draft row each (a.plan with as many workers as pieces).  lds: kFrontLdsBytes.
+constexpr size_t kFrontLdsBytes = sizeof(DraftLds) > 512 ? sizeof(DraftLds) : 512;
+template <typename TD, int kWaves>
+__device__ __forceinline__ void front_draft_side(const StepArgs& a, int job, int tid, void* lds) {
+  if (job < a.B) {
+    lookup_sequence(a, job, tid, kWaves * 64, static_cast<DraftLds*>(lds));
+    return;
+  }
+  if (job - a.B >= a.plan.jobs(a.K)) return;            // padding
+  int q, i, e0, n;
+  a.plan.locate(job - a.B, &q, &i);
+  PiecePlan::span(a.V_d, a.plan.pieces(q), i, &e0, &n);
+  constexpr int kBatch = 4;                             // as many as leave the multiplying workgroups' registers alone
+  RowFirstBatch<TD, kBatch> first;
+  workgroup_draft_piece_request<TD, kWaves, kBatch>(a, q, e0, n, tid, first);
+  const float* temps = a.draft_temperature ? a.draft_temperature : a.temperature;
+  const float Td = temps[find_sequence(a.row_off, a.B, q, 1, tid & 63)];
+  static_assert(kWaves * (sizeof(double) + 2 * sizeof(float)) <= kFrontLdsBytes, "the slices' statistics fit");
+  double* s_S = static_cast<double*>(lds);
+  float* s_mx = reinterpret_cast<float*>(s_S + kWaves);
+  workgroup_draft_piece<TD, kWaves, true, kBatch>(a, q, e0, n, Td, tid, s_mx, reinterpret_cast<int32_t*>(s_mx + kWaves), s_S,
+                                          a.dpiece + (int64_t)q * kDraftPieces + i, &first);
+}
+
+// The same by few workgroups: front workgroup j of n takes the lookups of sequences j, j + n, .., then every wavefront of it whole
+// draft rows (a.plan with one piece per row).
+template <typename TD, int kWaves>
+__device__ __forceinline__ void front_draft_rows(const StepArgs& a, int j, int n, int tid, void* lds) {
+  for (int b = j; b < a.B; b += n) {
+    lookup_sequence(a, b, tid, kWaves * 64, static_cast<DraftLds*>(lds));
+    __syncthreads();
+  }
+  const float* temps = a.draft_temperature ? a.draft_temperature : a.temperature;
+  const int lane = tid & 63;
+  for (int q = j * kWaves + uniform(tid >> 6); q < a.K; q += n * kWaves) {
+    const float Td = temps[find_sequence(a.row_off, a.B, q, 1, lane)];
+    DraftPiece r;
+    wave_row_stats<TD, kPieceBatch>(static_cast<const TD*>(a.draft_logits) + (int64_t)q * a.V_d, a.V_d, Td > 0.f ? kLog2eF / Td : kLog2eF,
+                                    lane, &r.mx, &r.arg, &r.sum);
+    if (lane == 0) a.dpiece[(int64_t)q * kDraftPieces] = r;
+  }
+}
+
+// Softmax partial of 64 columns of a target row, held by a row of 16 consecutive lanes, four columns from n on each: in all of
+// these lanes.  sc: exponent scale of the row.  Four exponentials are added in binary32, the rest in binary64.
+__device__ __forceinline__ Partial partial_of_64(const float* z, int n, int V_t, float sc) {
+  float v[4], best = -INFINITY;
+  int arg = 0x7FFFFFFF;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    v[e] = n + e < V_t ? z[e] : -INFINITY;
+    if (v[e] > best) { best = v[e]; arg = n + e; }         // ascending columns: the first maximum is kept
+  }
+  Partial p;
+  p.mx = row16_max(best);
+  p.arg = row16_min(best == p.mx ? arg : 0x7FFFFFFF);
+  float s = 0.f;
+  if (p.mx != -INFINITY) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s += __builtin_amdgcn_exp2f((v[e] - p.mx) * sc);   // masked: exp2(-inf) = 0
+  }
+  p.sum = row16_sum((double)s);
+  return p;
 }
 
 }  // namespace otv
