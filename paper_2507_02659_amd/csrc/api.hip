@@ -247,16 +247,16 @@ static int step_impl(ot_ctx* ctx, ot_ngram_cache* cache, const ot_step_in* in, c
     const bool bf16 = ctx->dtype == OT_BF16;
     const int workers = in->B > kFusedMaxB || K < 1 ? 0 : bf16 ? lmhead_bf16_draft_workers(M, ctx->d, ctx->Vp, in->B, K, ctx->n_cu)
                                                                : lmhead_f32_draft_workers(M, ctx->V_t, in->B, K, ctx->n_cu);
-    if (workers > 0 && (ctx->draft_side == OT_DRAFT_SIDE_IN_LM_HEAD ||
-                        (ctx->draft_side == OT_DRAFT_SIDE_AUTO &&
-                         (bf16 ? lmhead_bf16_hosts_draft_side(M, ctx->d, ctx->Vp, in->B, K, ctx->V_d, ctx->n_cu)
-                               : lmhead_f32_hosts_draft_side(M, ctx->d, ctx->V_t, in->B, K, ctx->V_d, ctx->n_cu))))) {
+    if (workers > 0 && ctx->draft_side == OT_DRAFT_SIDE_IN_LM_HEAD) a.hosted = kHostsAll;
+    if (workers > 0 && ctx->draft_side == OT_DRAFT_SIDE_AUTO)
+      a.hosted = bf16 ? lmhead_bf16_hosts(M, ctx->d, ctx->Vp, in->B, K, ctx->V_d, ctx->n_cu)
+                      : lmhead_f32_hosts_draft_side(M, ctx->d, ctx->V_t, in->B, K, ctx->V_d, ctx->n_cu) ? kHostsAll : kHostsNothing;
+    if (a.hosted != kHostsNothing) {
       a.fused.row_off = in->row_off; a.fused.temperature = in->temperature; a.fused.B = in->B; a.fused.part = ctx->fpart;
       a.fused.nfine = bf16 ? lmhead_bf16_fused_partials(M, ctx->d, ctx->Vp, ctx->n_cu) : ceil_div(ctx->V_t, 64);
-      a.hosted = 1;
       a.plan = make_piece_plan(workers, K);
     }
-    const StepArgs* draft_side = a.hosted ? &a : nullptr;
+    const StepArgs* draft_side = a.hosted == kHostsAll ? &a : nullptr;
     if (bf16)
       e = launch_lmhead_bf16(static_cast<const uint16_t*>(in->hidden), M, ctx->d, ctx->Wp, ctx->Kp, ctx->Vp, ctx->Z,
                              ctx->V_t, a.ldz, ctx->zeros, &a.fused, draft_side, ctx->n_cu, st);
@@ -265,9 +265,9 @@ static int step_impl(ot_ctx* ctx, ot_ngram_cache* cache, const ot_step_in* in, c
                             draft_side, st);
   }
   OT_MARK(1);
-  // Without the LM head's help the statistics get a launch of their own, which also does the lookups, and one launch
-  // follows it as above.
-  if (e == hipSuccess && !a.hosted) e = launch_softmax_stats(a, st);
+  // What the LM head did not take gets a launch of its own: the statistics of both sides' rows or, where it left the partials, of
+  // the draft rows, and the lookups.  One launch follows it as above.
+  if (e == hipSuccess && a.hosted != kHostsAll) e = launch_softmax_stats(a, st);
   OT_MARK(2);                                // OT_STAGE_TRANSLATE_ACCEPT launches nothing: its two events take their own cost off
   OT_MARK(3);                                // the stages on either side, and it reads 0
   if (e == hipSuccess) e = launch_final_draw(a, in->row_off_host, ctx->n_cu, st);

@@ -1049,23 +1049,30 @@ static bool front_pieces_end_in_time(double row_bytes, double head_us) {
 // hosted / separate: V_t = 128256, 128 rows 82 / 92 (d = 1024); V_t = 48000, 96 rows 98 / 101, 128 rows (whole draft rows)
 // 117 / 108; V_t = 60000, 168 rows 102 / 87 (d = 2048); V_t = 32000, 80 rows 74 / 72; V_t = 8000, 80 rows 64 / 58.
 // With several M-blocks front workgroups take the draft side: hosted where the launch, with them in its rounds, is
-// estimated to end before a launch without them and the statistics pass.  They cost most where they push multiplying
+// estimated to end before a launch without them and the statistics pass, over the draft rows alone if the launch still leaves the
+// target rows' partials (a launch more than hosted, and the estimate's 7 us a round and 8 beside are what fits the shapes below).
+// Measured, all hosted or, where noted, separate / partials only: 1024 rows x 128256 1039 us / 1003 (57 MB of draft rows), 320 rows
+// 366 / 351, 400 (d = 1024) 188 / 172, 240 x 60000 (d = 1024) separate 67.3 / 67.2; not taken: 424 x 152064 483 / 493, 1000 x 100000
+// with 9000 draft ids (d = 600) 253 / 267, 320 x 32000 (d = 3584) separate 94.6 / 95.1.
+// They cost most where they push multiplying
 // workgroups into a round more: V_t = 128256, 320 rows (502 + 16 workgroups) 412 us hosted, 365 separate; 152064, 320 rows
 // 399 / 424; 1024 rows 1057 / 1104; 20001 (d = 1024), 200 rows 39 / 47.  Over 216 shapes the choice costs 0.3 % on average against
 // the better one, 13 % at most (20001 columns with 200 draft rows of 20001, 54 / 61).
-bool lmhead_bf16_hosts_draft_side(int M, int d, int Vp, int B, int K, int V_d, int n_cu) {
-  if (B < 1 || B > kFusedMaxB || K < 1) return false;
+int lmhead_bf16_hosts(int M, int d, int Vp, int B, int K, int V_d, int n_cu) {
+  if (B < 1 || B > kFusedMaxB || K < 1) return kHostsNothing;
   const int workers = lmhead_bf16_draft_workers(M, d, Vp, B, K, n_cu);
-  if (workers == 0) return false;
-  if (M <= 16) return Vp / kGemmColsPerWave <= kMaxMergedPartials && front_pieces_end_in_time(2.0 * V_d, lmhead_launch_us(M, d, Vp));
+  if (workers == 0) return kHostsNothing;
+  if (M <= 16)
+    return Vp / kGemmColsPerWave <= kMaxMergedPartials && front_pieces_end_in_time(2.0 * V_d, lmhead_launch_us(M, d, Vp)) ? kHostsAll
+                                                                                                                         : kHostsNothing;
   if (M <= kSingleBlockRows) {
-    if (lmhead_bf16_tile_cols(M, d, Vp, n_cu) < 256) return false;
-    return 2 * K <= workers || 4.0 * M * Vp / 5.0e6 >= 9.0 * ceil_div(K, workers);
+    if (lmhead_bf16_tile_cols(M, d, Vp, n_cu) < 256) return kHostsNothing;
+    return 2 * K <= workers || 4.0 * M * Vp / 5.0e6 >= 9.0 * ceil_div(K, workers) ? kHostsAll : kHostsNothing;
   }
   const int n_front = workers / kWideWaves;
   const TallPlan plan = tall_plan(M, d, Vp, n_cu);
   const double front_us = 2.0 * K * (double)V_d / (n_front * kFrontBytesPerUs) + ceil_div(B, 4 * n_front) * 10.0;
-  if (n_front >= n_cu) return false;
+  if (n_front >= n_cu) return kHostsNothing;
   // The launch ends at the first moment by which n_front compute units that come free after front_us and the others have
   // had room for all workgroups, each kStatsUs longer for the row statistics; half of what stays idle counts, as above.
   constexpr double kStatsUs = 4.5;
@@ -1079,8 +1086,10 @@ bool lmhead_bf16_hosts_draft_side(int M, int d, int Vp, int B, int K, int V_d, i
   for (double at = t; at < end; at += t)
     if ((n_cu - n_front) * std::round(at / t) + n_front * std::floor(std::max(0.0, at - front_us) / t) >= n) end = at;
   const double hosted = std::max(front_us, 0.5 * (end + (n * t + n_front * front_us) / n_cu));
-  const double separate = plan.rounds * plan.round_us + 4.0 + (4.0 * M * Vp + 2.0 * K * (double)V_d) / 5.0e6;
-  return hosted < separate;
+  const double draft_us = 2.0 * K * (double)V_d / 5.0e6;
+  const double separate = plan.rounds * plan.round_us + 4.0 + 4.0 * M * Vp / 5.0e6 + draft_us;
+  const double partials = plan.rounds * (plan.round_us + 7.0) + 8.0 + draft_us;
+  return hosted < std::min(separate, partials) ? kHostsAll : partials < separate ? kHostsPartials : kHostsNothing;
 }
 
 hipError_t launch_lmhead_bf16(const uint16_t* H, int M, int d, const uint16_t* Wp, int Kp, int Vp, float* Z, int V_t,

@@ -132,6 +132,9 @@ inline PiecePlan make_piece_plan(int workers, int K) {
   return p;
 }
 
+// What of a step's statistics the LM-head launch takes.
+enum { kHostsNothing = 0, kHostsAll = 1, kHostsPartials = 2 };
+
 struct StepArgs {
   // problem
   int32_t B, M, K, d, V_t, V_d, dtype, max_ngram_len;
@@ -160,9 +163,10 @@ struct StepArgs {
   DraftPiece* dpiece;    // [K, kDraftPieces] statistics of the pieces of the draft rows, left by the LM-head launch
   PiecePlan plan;        // how the LM-head launch shared out the draft rows
   ProbeRecord* probe;    // [B] what the drafted ids of each sequence look up (see ProbeRecord), left by the LM-head launch
-  int32_t hosted;        // the LM-head launch left the target rows' softmax partials (`fused`), the draft rows' pieces
+  int32_t hosted;        // kHostsAll: the LM-head launch left the target rows' softmax partials (`fused`), the draft rows' pieces
                          // and the probe records: one launch follows it, which translates, tests and draws;
-                         // 0: the statistics launch left chunk partials (tpart_*, dpart_*) and the probe records for it
+                         // kHostsPartials: it left `fused`, and the statistics launch the draft rows' chunk partials (dpart_*) and
+                         // the probe records; kHostsNothing: the statistics launch left chunk partials of both (tpart_*, dpart_*)
   FinalInfo* fin;        // [B]
   int32_t max_units;     // masses per sequence in
   double* unit_mass;     // [B, max_units] of the draw: what its workgroups hand to each other; all bits set between launches
@@ -177,9 +181,9 @@ hipError_t launch_pack_w_bf16(const uint16_t* W, int d, int V_t, uint16_t* Wp, i
 // kernel without the fused statistics.
 // (n_cu = compute units of the device: the column width of a workgroup is chosen so that the launch takes few rounds.)
 int lmhead_bf16_fused_partials(int M, int d, int Vp, int n_cu);
-// Whether a step of this shape lets the LM-head launch host the draft side and emit the partials (else the step runs
-// the statistics and the translation as launches of their own).
-bool lmhead_bf16_hosts_draft_side(int M, int d, int Vp, int B, int K, int V_d, int n_cu);
+// What the LM-head launch of a step of this shape takes (kHosts..): partials and the draft side, the partials only, or nothing (the
+// statistics launch takes the rest).
+int lmhead_bf16_hosts(int M, int d, int Vp, int B, int K, int V_d, int n_cu);
 // workgroups of launch_lmhead_bf16 that share the draft rows (0: that shape leaves no partials and hosts nothing)
 int lmhead_bf16_draft_workers(int M, int d, int Vp, int B, int K, int n_cu);
 // `fused` may be nullptr or have part == nullptr (no statistics); otherwise fused->nfine must be

@@ -47,11 +47,11 @@ constexpr int64_t kRepeatedMergeBytes = 32 << 20;
 // kDraw = false: grid = (1) x (sequences); the workgroup only runs the test and leaves the outcome record in memory for
 // a final_draw_kernel launch (used when repeating the test in every group of units would cost more than a launch).
 // kChunks: the partials come from the statistics launch (chunk partials in three arrays per side) instead of the
-// LM head's epilogue and draft-row pieces.
+// LM head's epilogue and draft-row pieces; kFused as well: only the draft rows' do.
 // kMany: more than kFusedMaxB sequences: row offsets from memory, partials merged in binary64 (as a runtime flag these two
 // cost a single sequence 0.7 of 13 us).
 // kWide: draft rows of more than kChunksAtOnce chunks (merge_draft_chunks).
-template <int kPer, bool kDraw, bool kChunks, bool kMany = false, bool kWide = kMany>
+template <int kPer, bool kDraw, bool kChunks, bool kMany = false, bool kWide = kMany, bool kFused = !kChunks>
 __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, RowOffsets ro, DrawSplit split) {
   const int b = blockIdx.y, grp = blockIdx.x, tid = threadIdx.x;
   const int wave = uniform(tid >> 6), lane = tid & 63;
@@ -118,7 +118,7 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, R
   }
   if (kMany && wave != kTestWave) invT = T > 0.f ? 1.0 / (double)T : 1.0;
   for (int row = wave; row <= k; row += kDrawWaves) {
-    if (kChunks)
+    if (!kFused)
       merge_chunk_row(a.tpart_max, a.tpart_sum, a.tpart_arg, a.ncht, r0 + row, T, invT, lane, s_pmx, s_pinv, s_parg, row, lead,
                       a.row_max, a.row_sum, a.row_arg, kMany);
     else
@@ -173,8 +173,7 @@ template <int kPer> DrawSplit draw_split(int V_t, int B, int n_cu) {
   return s;
 }
 
-// hosted: the LM-head launch left its softmax partials, the draft rows' pieces and the probe records; otherwise the
-// statistics launch left its chunk partials and the probe records.  row_off_host holds the B + 1 row offsets.
+// What was left by which launch: see StepArgs::hosted.  row_off_host holds the B + 1 row offsets.
 template <int kPer>
 hipError_t launch_draw(const StepArgs& a, const int32_t* row_off_host, const DrawSplit& split, hipStream_t stream) {
   DrawSplit s = split;
@@ -191,7 +190,7 @@ hipError_t launch_draw(const StepArgs& a, const int32_t* row_off_host, const Dra
   }
   RowOffsets ro;
   for (int b = 0; b <= kFusedMaxB; ++b) ro.v[b] = row_off_host[b <= a.B ? b : a.B];
-  if (!a.hosted) {                                         // a few chunks per row: always one launch
+  if (a.hosted == kHostsNothing) {                         // a few chunks per row: always one launch
     if (a.B > kFusedMaxB) {
       if constexpr (kPer >= 8) hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, true>), grid, block, lds, stream, a, ro, s);
       else return hipErrorInvalidValue;
@@ -207,10 +206,12 @@ hipError_t launch_draw(const StepArgs& a, const int32_t* row_off_host, const Dra
   // about the traffic that costs as much as a launch this is one launch; beyond it the test gets a launch of its own.
   const int64_t repeated = (int64_t)a.M * a.fused.nfine * (int64_t)sizeof(Partial) * grid.x;
   if (repeated <= kRepeatedMergeBytes) {
-    hipLaunchKernelGGL((accept_draw_kernel<kPer, true, false>), grid, block, lds, stream, a, ro, s);
+    if (a.hosted == kHostsAll) hipLaunchKernelGGL((accept_draw_kernel<kPer, true, false>), grid, block, lds, stream, a, ro, s);
+    else hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, true, true>), grid, block, lds, stream, a, ro, s);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL((accept_draw_kernel<8, false, false>), dim3(1, a.B), block, 0, stream, a, ro, s);
+  if (a.hosted == kHostsAll) hipLaunchKernelGGL((accept_draw_kernel<8, false, false>), dim3(1, a.B), block, 0, stream, a, ro, s);
+  else hipLaunchKernelGGL((accept_draw_kernel<8, false, true, false, true, true>), dim3(1, a.B), block, 0, stream, a, ro, s);
   hipLaunchKernelGGL(final_draw_kernel<kPer>, grid, block, lds, stream, a, s);
   return hipGetLastError();
 }

@@ -171,7 +171,7 @@ __global__ __launch_bounds__(kStatThreads) void softmax_stats_kernel(StepArgs a)
   // run underneath the stream of the others.  Then n_target workgroups take target chunks, the rest draft chunks.
   const int n_lookup = a.B;
   const int wg = (int)blockIdx.x - n_lookup;
-  const int n_target = a.M * a.ncht;
+  const int n_target = a.hosted == kHostsNothing ? a.M * a.ncht : 0;   // else the LM head left the target rows' partials
   const int lane = threadIdx.x & 63;
   const bool by_ballot = a.B <= kBallotSequences;
   if (wg < 0) {
@@ -210,7 +210,7 @@ __global__ __launch_bounds__(kStatThreads) void softmax_stats_kernel(StepArgs a)
 
 hipError_t launch_softmax_stats(const StepArgs& a, hipStream_t stream) {
   if (a.B == 0) return hipSuccess;
-  const dim3 grid(a.M * a.ncht + a.K * a.nchd + a.B), block(kStatThreads);
+  const dim3 grid((a.hosted == kHostsNothing ? a.M * a.ncht : 0) + a.K * a.nchd + a.B), block(kStatThreads);
   if (a.dtype == OT_BF16) hipLaunchKernelGGL(softmax_stats_kernel<uint16_t>, grid, block, 0, stream, a);
   else hipLaunchKernelGGL(softmax_stats_kernel<float>, grid, block, 0, stream, a);
   return hipGetLastError();
