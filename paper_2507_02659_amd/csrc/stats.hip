@@ -98,8 +98,6 @@ __device__ __forceinline__ void chunk_stats(const T* __restrict__ x_row, int V, 
   const int shift = (int)(reinterpret_cast<uintptr_t>(x) / sizeof(T)) & (kVec - 1);
 
   float v[kPerThread];
-  float best = -INFINITY;
-  int best_i = 0x7FFFFFFF;
   typename Loader<T>::Raw raw[kLoads];
 #pragma unroll
   for (int i = 0; i < kLoads; ++i) {
@@ -119,48 +117,53 @@ __device__ __forceinline__ void chunk_stats(const T* __restrict__ x_row, int V, 
       for (int e = 0; e < kVec; ++e) v[i * kVec + e] = (at + e >= 0 && at + e < n) ? Loader<T>::one(x + at + e) : -INFINITY;
     }
   }
+  float best = over;
 #pragma unroll
-  for (int i = 0; i < kLoads; ++i) {
-    const int at = (i * kStatThreads + tid) * kVec - shift;
-#pragma unroll
-    for (int e = 0; e < kVec; ++e) {
-      if (v[i * kVec + e] > best) { best = v[i * kVec + e]; best_i = at + e; }   // ascending index: first maximum kept
-    }
-  }
-  if (over > best) { best = over; best_i = at_over; }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    float ob = __shfl_xor(best, off);
-    int oi = __shfl_xor(best_i, off);
-    if (ob > best || (ob == best && oi < best_i)) { best = ob; best_i = oi; }
-  }
+  for (int i = 0; i < kPerThread; ++i) best = fmaxf(best, v[i]);
+  best = wave_max(best);
   __shared__ float s_max[kStatThreads / 64];
   __shared__ int s_idx[kStatThreads / 64];
   __shared__ double s_sum[kStatThreads / 64];
-  const int wave = tid >> 6, lane = tid & 63;
-  if (lane == 0) { s_max[wave] = best; s_idx[wave] = best_i; }
+  const int wave = uniform(tid >> 6), lane = tid & 63;
+  const float own = best;
+  if (lane == 0) s_max[wave] = best;
   __syncthreads();
-  best = s_max[0]; best_i = s_idx[0];
+  best = s_max[0];
 #pragma unroll
-  for (int w = 1; w < kStatThreads / 64; ++w) {
-    if (s_max[w] > best || (s_max[w] == best && s_idx[w] < best_i)) { best = s_max[w]; best_i = s_idx[w]; }
+  for (int w = 1; w < kStatThreads / 64; ++w) best = fmaxf(best, s_max[w]);
+  // its lowest index: only a wavefront that holds it looks
+  int best_i = 0x7FFFFFFF;
+  if (uniform(own) == uniform(best) && uniform(best) != -INFINITY) {
+#pragma unroll
+    for (int i = kLoads - 1; i >= 0; --i)
+#pragma unroll
+      for (int e = kVec - 1; e >= 0; --e)
+        if (v[i * kVec + e] == best) best_i = (i * kStatThreads + tid) * kVec - shift + e;
+    if (over == best) best_i = min(best_i, at_over);
+    best_i = wave_min(best_i);
   }
-  // exponentials relative to the chunk maximum; masked slots hold -inf and contribute exp2(-inf) = 0
-  float acc = __builtin_amdgcn_exp2f((over - best) * scale);
+  // exponentials relative to the chunk maximum (of a chunk without finite logits: to 0); masked slots hold -inf and contribute
+  // exp2(-inf) = 0
+  const float top = best == -INFINITY ? 0.f : best;
+  float acc = __builtin_amdgcn_exp2f((over - top) * scale);
 #pragma unroll
-  for (int i = 0; i < kPerThread; ++i) acc += __builtin_amdgcn_exp2f((v[i] - best) * scale);
-  double sum = (double)acc;
+  for (int i = 0; i < kPerThread; i += 4) {
+    float t[4];
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
-  if (lane == 0) s_sum[wave] = sum;
+    for (int e = 0; e < 4; ++e) t[e] = __builtin_amdgcn_exp2f((v[i + e] - top) * scale);
+    acc += (t[0] + t[1]) + (t[2] + t[3]);
+  }
+  const double sum = wave_sum((double)acc);
+  if (lane == 0) { s_idx[wave] = best_i; s_sum[wave] = sum; }
   __syncthreads();
   if (tid == 0) {
     double total = s_sum[0];
+    int arg = s_idx[0];
 #pragma unroll
-    for (int w = 1; w < kStatThreads / 64; ++w) total += s_sum[w];
+    for (int w = 1; w < kStatThreads / 64; ++w) { total += s_sum[w]; arg = min(arg, s_idx[w]); }
     pmax[slot] = best;
     psum[slot] = total;
-    parg[slot] = base + best_i;
+    parg[slot] = arg == 0x7FFFFFFF ? arg : base + arg;
   }
 }
 
