@@ -20,8 +20,8 @@
 //   * A workgroup owns 128 to 640 columns, so that the launch fits into few, full rounds of one workgroup per compute
 //     unit (what a workgroup does outside its main loop is time its compute unit does not stream).
 //   * The launch can host the draft side of the step, the work that needs no target logits (see draft-side jobs in
-//     the kernel): with one M-block inside the multiplying workgroups, behind their first loads; with several in a
-//     few workgroups at the front of the launch.
+//     the kernel): with one M-block inside the multiplying workgroups, behind their first loads; with several, or with up
+//     to 16 rows, in workgroups at the front of the launch.  With several M-blocks it may also leave the partials alone.
 //   * All waits on the load counter are written by hand, by number (loads complete in issue order), and workgroup
 //     barriers carry no fence: with direct-to-LDS loads in flight every wait the compiler adds itself is a full
 //     drain of the counter, which would empty the weight pipeline at every slice.

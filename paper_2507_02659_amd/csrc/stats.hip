@@ -2,8 +2,8 @@
 //
 // These three numbers are all the step needs of p = softmax(z/T) and q = softmax(zq/T_d) (Notation paragraph):
 // a probability is re-formed on demand as exp((z_v - max)/T) / sum, so no probability row is ever written to
-// memory.  One launch covers the M target rows (fp32 logits from the LM head) and the K draft rows (storage
-// dtype): one workgroup reduces one chunk of kStatChunk logits of one row.  The chunk is read once into registers
+// memory.  One launch covers the M target rows (fp32 logits from the LM head; none where that left their partials) and the K draft
+// rows (storage dtype): one workgroup reduces one chunk of kStatChunk logits of one row.  The chunk is read once into registers
 // (16-byte loads, consecutive lanes on consecutive vectors), reduced to its maximum through wavefront shuffles and
 // LDS, and only then exponentiated, so every logit is read from HBM exactly once.  The per-chunk partials are
 // merged in a fixed order by the consumer.  The launch also carries one workgroup per sequence that
