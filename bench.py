@@ -176,7 +176,7 @@ def main():
     achieved = gemm_bytes / gemm_s / 1e9 if gemm_s > 0 else 0.0
     # what follows the LM head: with fused statistics one launch (merge of the partials + acceptance + draw), else
     # statistics, translation + acceptance, draw
-    fused = esz == 2 and M > 16 and case.B <= 255 and not from_logits
+    fused = esz == 2 and case.B <= 255 and not from_logits and (M > 16 or V_t <= 65536)
     tail_us = ms_per_step * 1e3 - stage_us["lm_head"]
     extra = {
         "stage_us": {k: round(x, 2) for k, x in stage_us.items()},
@@ -185,7 +185,7 @@ def main():
         "lm_head_tflops": round(2.0 * M * d * V_t / gemm_s / 1e12, 1) if gemm_s > 0 else None,
         "lm_head_frac_mfma_peak": round(2.0 * M * d * V_t / gemm_s / 1e12 / MFMA_BF16_PEAK_TFLOPS, 4) if gemm_s > 0 else None,
         "rows_per_s": round(M * args.steps / elapsed, 1),
-        "step_hbm_bytes": gemm_bytes + esz * K * V_d + (16 * M * ((V_t + 255) // 256) if fused else 4 * M * V_t)
+        "step_hbm_bytes": gemm_bytes + esz * K * V_d + (16 * M * (-(-V_t // (256 if M > 16 else 64))) if fused else 4 * M * V_t)
                           + case.B * (4 * V_t + esz * V_d + 4 * V_t),
     }
     if len(ring) > 1:

@@ -57,7 +57,7 @@ struct ProbeRecord {
 };
 
 // ------------------------------------------------------------------------------------------------ per-step view
-// What the draw of the final token needs to know about sequence b: the outcome of its acceptance test (accept_wave), in LDS or,
+// What the draw of the final token needs to know about sequence b: the outcome of its acceptance test (test_window), in LDS or,
 // where the test has a launch of its own, in memory.
 struct FinalInfo {
   int32_t mode;          // 0: nothing to draw (greedy, or bad id), 2: draw from p (free token), 3: draw from the residual
