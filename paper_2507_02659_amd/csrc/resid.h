@@ -261,7 +261,8 @@ struct UnitPick { int unit; double base, target; bool empty; };
 
 // By one wavefront, from the masses of n_units units in LDS and the sums of 64 of them each (one turn of the loops up to 4096
 // units).  The total and the crossing come from the same sums; where rounding pushes the target past the end the last unit with
-// mass is taken.
+// mass is taken.  What is taken has mass of its own at every level: every lane of a scan adds in another order, so that a running
+// sum can pass the target at an entry of zero, by a unit in the last place.
 __device__ inline UnitPick pick_unit(const double* s_mass, const double* s_sums, int n_units, double u2, int lane, bool of_p) {
   const int n_chunks = (n_units + 63) / 64;
   UnitPick p;
@@ -282,7 +283,7 @@ __device__ inline UnitPick pick_unit(const double* s_mass, const double* s_sums,
       x = chunk(c0 + lane);
       incl = wave_scan(x) + before;
     }
-    const unsigned long long past = __ballot(incl > p.target), some = past ? past : __ballot(x > 0.0);
+    const unsigned long long past = __ballot(x > 0.0 && incl > p.target), some = past ? past : __ballot(x > 0.0);
     if (some) {
       const int l = past ? (int)__builtin_ctzll(past) : 63 - (int)__builtin_clzll(some);
       c = c0 + l;
@@ -389,8 +390,8 @@ __device__ inline void draw_final_token(const StepArgs& a, int b, int grp, int n
   if (wave < kPer) {
     // lane w: what the first w + 1 wavefronts hold.  The wavefront in whose ids the running sum passes the target writes: the same
     // sums in every wavefront, so it is one of them (rounding past the end: the last with mass)
-    const double sums = wave_scan(lane < kPer ? L->w[lane] : 0.0);
-    const unsigned long long past = __ballot(lane < kPer && P.base + sums > P.target), some = __ballot(lane < kPer && L->w[lane] > 0.0);
+    const double own = lane < kPer ? L->w[lane] : 0.0, sums = wave_scan(own);
+    const unsigned long long past = __ballot(own > 0.0 && P.base + sums > P.target), some = __ballot(own > 0.0);
     const int at = past ? (int)__builtin_ctzll(past) : some ? 63 - (int)__builtin_clzll(some) : 0;
     if (wave == at) {
       const double before = P.base + (wave > 0 ? lane_value(sums, wave - 1) : 0.0);
