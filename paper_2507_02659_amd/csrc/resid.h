@@ -7,7 +7,8 @@
 // and the direct image of its first sub-token gets q_s(d_1) - pi.  When everything was accepted the draw is from p.
 //
 // Only the ONE row per sequence where the draw happens is touched.  A workgroup of 16 wavefronts takes a run of consecutive
-// units of 64 * kPer target ids of one sequence (draw_split), a unit per wavefront and turn:
+// units of one sequence, a unit per wavefront and turn, of 64 * kPer target ids each (of a vast vocabulary a number of such blocks,
+// draw_split):
 //   every workgroup  forms the masses of max(0, p - q') of its units in binary64 and publishes them; when they have reached
 //                    memory it looks at the masses of all units of its sequence, and ends if one is still missing;
 //   the workgroup that finds them all  (the one whose masses arrive last does; more than one may, and they do the same)
@@ -259,57 +260,57 @@ __device__ inline double drawn_mass(double x, bool of_p) { return of_p ? fabs(x)
 // What the scan of the masses chooses: the unit, the mass in front of it, and the target mass u * total.
 struct UnitPick { int unit; double base, target; bool empty; };
 
-// By one wavefront, from the masses of n_units units in LDS and the sums of 64 of them each (one turn of the loops up to 4096
-// units).  The total and the crossing come from the same sums; where rounding pushes the target past the end the last unit with
-// mass is taken.  What is taken has mass of its own at every level: every lane of a scan adds in another order, so that a running
-// sum can pass the target at an entry of zero, by a unit in the last place.
-__device__ inline UnitPick pick_unit(const double* s_mass, const double* s_sums, int n_units, double u2, int lane, bool of_p) {
+// Mass of a unit of several blocks from those of two parts of it: minus that of p where neither holds residual mass.
+__device__ inline double joined_mass(double a, double b) { return a <= 0.0 && b <= 0.0 ? a + b : fmax(a, 0.0) + fmax(b, 0.0); }
+
+// By one wavefront, from the masses of n_units units (at most 4096) in LDS and the sums of 64 of them each.  The total and the
+// crossing come from the same sums; where rounding pushes the target past the end the last unit with mass is taken.  What is taken
+// has mass of its own at every level: every lane of a scan adds in another order, so that a running sum can pass the target at an
+// entry of zero, by a unit in the last place.
+// kInside: among the blocks of a unit that was taken, `from` (its base and the target), instead.
+template <bool kInside = false>
+__device__ inline UnitPick pick_unit(const double* s_mass, const double* s_sums, int n_units, double u2, int lane, bool of_p,
+                                     const UnitPick& from = UnitPick{0, 0.0, 0.0, false}) {
   const int n_chunks = (n_units + 63) / 64;
   UnitPick p;
-  auto chunk = [&](int c) { const double x = s_sums[min(c, n_chunks - 1)]; return c < n_chunks ? x : 0.0; };
-  double total = 0.0, x = 0.0, incl = 0.0;
-  for (int c0 = 0; c0 < n_chunks; c0 += 64) {
-    x = chunk(c0 + lane);
-    incl = wave_scan(x) + total;
-    total = lane_value(incl, 63);
-  }
+  const double sum = s_sums[min(lane, n_chunks - 1)], x = lane < n_chunks ? sum : 0.0;
+  const double incl = wave_scan(x) + from.base, total = lane_value(incl, 63);
   p.empty = !(total > 0.0);
-  p.target = u2 * total;
-  p.base = 0.0;
+  p.target = kInside ? from.target : u2 * total;
+  p.base = from.base;
   int c = 0;
-  double before = 0.0;
-  for (int c0 = 0; c0 < n_chunks; c0 += 64) {
-    if (n_chunks > 64) {                                   // (otherwise the sums are still there)
-      x = chunk(c0 + lane);
-      incl = wave_scan(x) + before;
-    }
-    const unsigned long long past = __ballot(x > 0.0 && incl > p.target), some = past ? past : __ballot(x > 0.0);
-    if (some) {
-      const int l = past ? (int)__builtin_ctzll(past) : 63 - (int)__builtin_clzll(some);
-      c = c0 + l;
-      p.base = l > 0 ? lane_value(incl, l - 1) : before;
-      if (past) break;
-    }
-    before = lane_value(incl, 63);
+  const unsigned long long past = __ballot(x > 0.0 && incl > p.target), some = past ? past : __ballot(x > 0.0);
+  if (some) {
+    c = past ? (int)__builtin_ctzll(past) : 63 - (int)__builtin_clzll(some);
+    if (c > 0) p.base = lane_value(incl, c - 1);
   }
   const double m = c * 64 + lane < n_units ? drawn_mass(s_mass[c * 64 + lane], of_p) : 0.0;
   const double run = wave_scan(m);
-  const unsigned long long past = __ballot(m > 0.0 && p.base + run > p.target), some = __ballot(m > 0.0);
-  const int i = past ? (int)__builtin_ctzll(past) : some ? 63 - (int)__builtin_clzll(some) : 0;
+  const unsigned long long past1 = __ballot(m > 0.0 && p.base + run > p.target), some1 = __ballot(m > 0.0);
+  const int i = past1 ? (int)__builtin_ctzll(past1) : some1 ? 63 - (int)__builtin_clzll(some1) : 0;
   p.unit = c * 64 + i;
   if (i > 0) p.base += lane_value(run, i - 1);
   return p;
 }
 
+// How the draw is split, see draw_split.  A unit is `blocks` (1 unless kBlocks) times 64 * kPer ids, at most 1024 blocks; row_at:
+// where the draft row's copy starts in the dynamic LDS, in doubles (0: no copy).
+struct DrawSplit { int n_units, group_units, row_at, blocks; };
+template <int kPer, bool kBlocks>
+__device__ inline int draw_first_id(const DrawSplit& s, int grp, int wave) {
+  return (grp * s.group_units + wave) * (64 * kPer) * (kBlocks ? s.blocks : 1);
+}
+
 // Workgroup `grp` of sequence b takes units [grp * group_units, (grp + 1) * group_units) of n_units, group_units a multiple of
 // kDrawWaves (all kDrawThreads threads call this; f is the sequence's outcome record with f.mode != 0; dv holds tmap of the ids
-// (grp * group_units + wave) * 64 * kPer + lane + e * 64, e < kPer).  The dynamic LDS holds 65 doubles for every 64 units begun
-// (draw_lds_doubles) and, if row_at > 0, from double row_at on room for the draft row and 32 bytes.
+// draw_first_id + lane + e * 64, e < kPer).  The dynamic LDS holds 65 doubles for every 64 units begun (draw_lds_doubles) and, if
+// row_at > 0, from double row_at on room for the draft row and 32 bytes.
 __host__ __device__ inline int draw_lds_doubles(int n_units) { return (n_units + 63) / 64 * 65; }
-template <int kPer>
-__device__ inline void draw_final_token(const StepArgs& a, int b, int grp, int n_units, int group_units, const FinalInfo& f, int* dv,
-                                        DrawLds* L, int row_at) {
-  constexpr int kUnit = 64 * kPer;
+template <int kPer, bool kBlocks>
+__device__ inline void draw_final_token(const StepArgs& a, int b, int grp, const DrawSplit& split, const FinalInfo& f, int* dv,
+                                        DrawLds* L) {
+  constexpr int kUnit = 64 * kPer;                        // ids of a block
+  const int n_units = split.n_units, group_units = split.group_units, row_at = split.row_at, blocks = kBlocks ? split.blocks : 1;
   const int tid = threadIdx.x, wave = uniform((int)(threadIdx.x >> 6)), lane = tid & 63;
   const int n_chunks = (n_units + 63) / 64;
   double *s_mass = s_draw_dynamic, *s_sums = s_mass + n_chunks * 64;   // the masses; the sums of 64 each
@@ -325,19 +326,26 @@ __device__ inline void draw_final_token(const StepArgs& a, int b, int grp, int n
 
   // ---- masses of this workgroup's units, a wavefront on each (coalesced: consecutive lanes on consecutive ids)
   for (int unit = unit0 + wave; unit < unit1; unit += kDrawWaves) {
-    const int lo = unit * kUnit;
-    TileRaw<kPer> raw;
-    load_tile<kPer>(R, a.V_t, lo + lane, 64, lo + kUnit <= a.V_t, dv, raw);
-    int dv_next[kPer] = {};                              // asked for behind what this turn waits for
-    const int lo_next = lo + kDrawWaves * kUnit;
-    if (unit + kDrawWaves < unit1) load_tmap<kPer>(a.tmap, a.V_t, lo_next + lane, 64, lo_next + kUnit <= a.V_t, dv_next);
-    const double mass = unit_mass<kPer>(R, a.V_t, lo, lane, dv, raw);
-    if (lane == 0) {
-      if (alone) s_mass[unit] = mass;
-      else publish(masses + unit, mass);
-    }
+    double mass = 0.0;
+    int blk = 0;
+    do {
+      const int lo = (unit * blocks + blk) * kUnit;
+      TileRaw<kPer> raw;
+      load_tile<kPer>(R, a.V_t, lo + lane, 64, lo + kUnit <= a.V_t, dv, raw);
+      int dv_next[kPer] = {};                            // asked for behind what this turn waits for
+      const bool inside = kBlocks && blk + 1 < blocks;
+      const int lo_next = inside ? lo + kUnit : (unit + kDrawWaves) * blocks * kUnit;
+      if (inside || unit + kDrawWaves < unit1)
+        load_tmap<kPer>(a.tmap, a.V_t, lo_next + lane, 64, lo_next + kUnit <= a.V_t, dv_next);
+      const double m = unit_mass<kPer>(R, a.V_t, lo, lane, dv, raw);
+      mass = kBlocks ? joined_mass(mass, m) : m;
+      if (!inside && lane == 0) {
+        if (alone) s_mass[unit] = mass;
+        else publish(masses + unit, mass);
+      }
 #pragma unroll
-    for (int e = 0; e < kPer; ++e) dv[e] = dv_next[e];
+      for (int e = 0; e < kPer; ++e) dv[e] = dv_next[e];
+    } while (kBlocks && ++blk < blocks);
   }
   if (!alone) stores_done();                              // of this wavefront; behind the barrier, of all of them
   __syncthreads();
@@ -373,6 +381,27 @@ __device__ inline void draw_final_token(const StepArgs& a, int b, int grp, int n
     __syncthreads();
     P = pick_unit(s_mass, s_sums, n_units, f.u2, lane, true);
     P.empty = true;
+  }
+  if constexpr (kBlocks) {                                // the same among the unit's blocks, whose masses take the place of the units'
+    __syncthreads();
+    for (int blk = wave; blk < blocks; blk += kDrawWaves) {
+      const int lo = (uniform(P.unit) * blocks + blk) * kUnit;
+      const bool all_exist = lo + kUnit <= a.V_t;
+      TileRaw<kPer> raw;
+      load_tmap<kPer>(a.tmap, a.V_t, lo + lane, 64, all_exist, dv);
+      load_tile<kPer>(R, a.V_t, lo + lane, 64, all_exist, dv, raw);
+      const double m = unit_mass<kPer>(R, a.V_t, lo, lane, dv, raw);
+      if (lane == 0) s_mass[blk] = m;
+    }
+    __syncthreads();
+    for (int c = wave; c * 64 < blocks; c += kDrawWaves) {
+      const double x = wave_sum(c * 64 + lane < blocks ? drawn_mass(s_mass[c * 64 + lane], false) : 0.0);
+      if (lane == 0) s_sums[c] = x;
+    }
+    __syncthreads();
+    const UnitPick Q = pick_unit<true>(s_mass, s_sums, blocks, 0.0, lane, false, P);
+    P.unit = P.unit * blocks + Q.unit;
+    P.base = Q.base;
   }
   double r = 0.0, incl = 0.0;
   const int lo = uniform(P.unit) * kUnit + wave * 64;

@@ -18,25 +18,17 @@
 namespace otv {
 namespace {
 
-// How the draw is split, see draw_split.  row_at: where the draft row's copy starts in the dynamic LDS, in doubles (0: no copy)
-struct DrawSplit { int n_units, group_units, row_at; };
-
-template <int kPer>
-__device__ inline int draw_first_id(const DrawSplit& s, int grp, int wave) {
-  return (grp * s.group_units + wave) * (64 * kPer);
-}
-
-template <int kPer>
+template <int kPer, bool kBlocks>
 __global__ __launch_bounds__(kDrawThreads) void final_draw_kernel(StepArgs a, DrawSplit s) {
   const int b = blockIdx.y, grp = blockIdx.x, tid = threadIdx.x;
   const int wave = uniform(tid >> 6), lane = tid & 63;
   __shared__ DrawLds s_draw;
   int dv[kPer];
-  const int first = draw_first_id<kPer>(s, grp, wave);
+  const int first = draw_first_id<kPer, kBlocks>(s, grp, wave);
   load_tmap<kPer>(a.tmap, a.V_t, first + lane, 64, first + 64 * kPer <= a.V_t, dv);   // overlaps the next load
   const FinalInfo f = a.fin[b];
   if (f.mode == 0) return;                  // greedy or flagged sequence: nothing to draw
-  draw_final_token<kPer>(a, b, grp, s.n_units, s.group_units, f, dv, &s_draw, s.row_at);
+  draw_final_token<kPer, kBlocks>(a, b, grp, s, f, dv, &s_draw);
 }
 
 // Row offsets of up to kFusedMaxB sequences as a kernel argument (the host has them): the workgroup knows its rows without
@@ -51,7 +43,8 @@ constexpr int64_t kRepeatedMergeBytes = 32 << 20;
 // kMany: more than kFusedMaxB sequences: row offsets from memory, partials merged in binary64 (as a runtime flag these two
 // cost a single sequence 0.7 of 13 us).
 // kWide: draft rows of more than kChunksAtOnce chunks (merge_draft_chunks).
-template <int kPer, bool kDraw, bool kChunks, bool kMany = false, bool kWide = kMany, bool kFused = !kChunks>
+// kBlocks: units of several blocks (draw_split).
+template <int kPer, bool kDraw, bool kChunks, bool kMany = false, bool kWide = kMany, bool kFused = !kChunks, bool kBlocks = false>
 __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, RowOffsets ro, DrawSplit split) {
   const int b = blockIdx.y, grp = blockIdx.x, tid = threadIdx.x;
   const int wave = uniform(tid >> 6), lane = tid & 63;
@@ -128,7 +121,7 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, R
   if (!(T > 0.f) && !lead) return;            // a greedy sequence draws nothing: its other groups have nothing to do
   // The inverse map of this wavefront's ids is needed last (by the masses) and asked for here, behind the loads
   // that the test waits for: loads return in issue order, and asked for first it held those back by its own latency.
-  const int first = draw_first_id<kPer>(split, grp, wave);
+  const int first = draw_first_id<kPer, kBlocks>(split, grp, wave);
   if (kDraw) load_tmap<kPer>(a.tmap, a.V_t, first + lane, 64, first + 64 * kPer <= a.V_t, dv);
   __syncthreads();
   Outcome O;
@@ -153,20 +146,27 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, R
   if (!kDraw) return;
   const FinalInfo f = s_fin;
   if (f.mode == 0) return;
-  draw_final_token<kPer>(a, b, grp, split.n_units, split.group_units, f, dv, &s_draw, split.row_at);
+  draw_final_token<kPer, kBlocks>(a, b, grp, split, f, dv, &s_draw);
 }
 
 // Units of the draw and their share per workgroup.  While no more than a workgroup per compute unit is needed for one turn each,
-// a wavefront takes as few ids as that allows: 128 (up to 512 units), else 256, else 512 (1024 above two million target ids).  A
+// a wavefront takes as few ids as that allows: 128 (up to 512 units), else 256, else 512.  A
 // small batch is bound by the chain of instructions and round trips in one workgroup, which fewer ids per lane shorten.  With
 // more groups than compute units each workgroup takes as many turns as bring their number back to one per compute unit (84
 // registers: five wavefronts per SIMD, so that a workgroup of 16 fills one): its start, its share of the merge and its look at the
 // masses are then paid once for several turns, and a turn's loads overlap the sums of the turn before.
 // Measured, us per step, 128 / 256 / 512 ids a wavefront: 6 rows x 32000 ids 53.9 / 54.1 / 55.2, 12 rows x 64000 (d = 1024) 39.4 /
 // 40.1 / 42.6, 24 x 152064 -- / 180.8 / 182.0, 80 x 32000 66.7 / 66.2 / 68.1, 6 x 152064 (d = 1024) -- / 69.2 / 70.7.
+// Above 4096 units of 512 ids a unit is as many blocks of 512 as leave no more than that, and a sequence's masses 33 KB of LDS at
+// any vocabulary (a mass for every 1024 ids filled LDS at 20 million).  Against units of 1024 ids with 16 a lane, which spilled 20
+// registers, us per step from the logits: 16 sequences of 2.2 million ids 116 -> 103, of 9 million 401 -> 344, one of 4.2 million
+// 27.3 -> 28.1.
+constexpr int kMaxUnits = 4096;
 template <int kPer> DrawSplit draw_split(int V_t, int B, int n_cu) {
   DrawSplit s;
   s.n_units = ceil_div(V_t, 64 * kPer);
+  s.blocks = kPer == 8 ? ceil_div(s.n_units, kMaxUnits) : 1;
+  s.n_units = ceil_div(s.n_units, s.blocks);
   const int64_t groups = (int64_t)ceil_div(s.n_units, kDrawWaves) * B;
   s.group_units = kDrawWaves * std::max(1, ceil_div(groups, std::max(n_cu, 1)));
   s.row_at = 0;
@@ -174,7 +174,7 @@ template <int kPer> DrawSplit draw_split(int V_t, int B, int n_cu) {
 }
 
 // What was left by which launch: see StepArgs::hosted.  row_off_host holds the B + 1 row offsets.
-template <int kPer>
+template <int kPer, bool kBlocks = false>
 hipError_t launch_draw(const StepArgs& a, const int32_t* row_off_host, const DrawSplit& split, hipStream_t stream) {
   DrawSplit s = split;
   const dim3 grid(ceil_div(s.n_units, s.group_units), a.B), block(kDrawThreads);
@@ -192,12 +192,12 @@ hipError_t launch_draw(const StepArgs& a, const int32_t* row_off_host, const Dra
   for (int b = 0; b <= kFusedMaxB; ++b) ro.v[b] = row_off_host[b <= a.B ? b : a.B];
   if (a.hosted == kHostsNothing) {                         // a few chunks per row: always one launch
     if (a.B > kFusedMaxB) {
-      if constexpr (kPer >= 8) hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, true>), grid, block, lds, stream, a, ro, s);
+      if constexpr (kPer == 8) hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, true, true, false, kBlocks>), grid, block, lds, stream, a, ro, s);
       else return hipErrorInvalidValue;
     } else if (a.nchd > kChunksAtOnce) {
-      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, true>), grid, block, lds, stream, a, ro, s);
+      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, true, false, kBlocks>), grid, block, lds, stream, a, ro, s);
     } else {
-      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true>), grid, block, lds, stream, a, ro, s);
+      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, false, false, kBlocks>), grid, block, lds, stream, a, ro, s);
     }
     return hipGetLastError();
   }
@@ -206,13 +206,13 @@ hipError_t launch_draw(const StepArgs& a, const int32_t* row_off_host, const Dra
   // about the traffic that costs as much as a launch this is one launch; beyond it the test gets a launch of its own.
   const int64_t repeated = (int64_t)a.M * a.fused.nfine * (int64_t)sizeof(Partial) * grid.x;
   if (repeated <= kRepeatedMergeBytes) {
-    if (a.hosted == kHostsAll) hipLaunchKernelGGL((accept_draw_kernel<kPer, true, false>), grid, block, lds, stream, a, ro, s);
-    else hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, true, true>), grid, block, lds, stream, a, ro, s);
+    if (a.hosted == kHostsAll) hipLaunchKernelGGL((accept_draw_kernel<kPer, true, false, false, false, true, kBlocks>), grid, block, lds, stream, a, ro, s);
+    else hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, true, true, kBlocks>), grid, block, lds, stream, a, ro, s);
     return hipGetLastError();
   }
   if (a.hosted == kHostsAll) hipLaunchKernelGGL((accept_draw_kernel<8, false, false>), dim3(1, a.B), block, 0, stream, a, ro, s);
   else hipLaunchKernelGGL((accept_draw_kernel<8, false, true, false, true, true>), dim3(1, a.B), block, 0, stream, a, ro, s);
-  hipLaunchKernelGGL(final_draw_kernel<kPer>, grid, block, lds, stream, a, s);
+  hipLaunchKernelGGL((final_draw_kernel<kPer, kBlocks>), grid, block, lds, stream, a, s);
   return hipGetLastError();
 }
 
@@ -224,8 +224,8 @@ hipError_t launch_final_draw(const StepArgs& a, const int32_t* row_off_host, int
   if (two.group_units == kDrawWaves && two.n_units <= 512 && a.B <= kFusedMaxB) return launch_draw<2>(a, row_off_host, two, stream);
   if (four.group_units == kDrawWaves && a.B <= kFusedMaxB) return launch_draw<4>(a, row_off_host, four, stream);
   const DrawSplit eight = draw_split<8>(a.V_t, a.B, n_cu);
-  if (eight.n_units <= 4096) return launch_draw<8>(a, row_off_host, eight, stream);
-  return launch_draw<16>(a, row_off_host, draw_split<16>(a.V_t, a.B, n_cu), stream);
+  if (eight.blocks == 1) return launch_draw<8>(a, row_off_host, eight, stream);
+  return launch_draw<8, true>(a, row_off_host, eight, stream);
 }
 
 }  // namespace otv

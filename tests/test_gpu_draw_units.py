@@ -1,5 +1,5 @@
-"""The final draw at the edges of its units: 128, 256, 512 or 1024 target ids per wavefront, one or several workgroups per
-sequence, more masses than one wavefront scans at once.  Against the oracle; every case runs twice on one context, so that the
+"""The final draw at the edges of its units: 128, 256 or 512 target ids per wavefront or several blocks of 512, one or several
+workgroups per sequence, more masses than one wavefront scans at once.  Against the oracle; every case runs twice on one context, so that the
 second launch finds what the first put back."""
 import numpy as np
 import pytest
@@ -20,8 +20,8 @@ pytestmark = pytest.mark.gpu
     ("bf16", 33025, 3001, 24),      # 130 of 256, one id in the last
     ("bf16", 65600, 3001, 40),      # 129 of 512, two turns: the second of every sequence has one unit of 64 ids
     ("f32", 300000, 2000, 2),       # 1172 of 256: 19 sums of 64 masses
-    ("f32", 2097153, 2000, 1),      # above 4096 units of 512: 1024 ids each
-    ("f32", 4194400, 2000, 1),      # 4097 of those: the sums of 64 masses no longer fit a wavefront
+    ("f32", 2097153, 2000, 1),      # above 4096 units of 512: two blocks each, 2049 units
+    ("f32", 4194400, 2000, 1),      # 8193 blocks of 512: three each
 ])
 def test_units_of_the_draw(dtype, V_t, V_d, B):
     ov, ot, Verifier, parity = _imports()
