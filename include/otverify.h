@@ -300,6 +300,13 @@ typedef struct ot_workspace_view {
 } ot_workspace_view;
 int ot_verify_workspace(ot_ctx* ctx, ot_workspace_view* view);
 
+/* How ot_verify_step runs a step of B sequences with M rows in total on this context: what its LM-head launch takes, and the
+ * number of its kernel launches, LM head included.  Nothing is enqueued.  OT_ERR_SHAPE for a step that would not be accepted.  */
+#define OT_STRUCTURE_SEPARATE  0   /* the logits alone: the statistics of both sides' rows and the lookups get a launch     */
+#define OT_STRUCTURE_HOSTED    1   /* also the target rows' softmax partials and the whole draft side                       */
+#define OT_STRUCTURE_PARTIALS  2   /* also the target rows' softmax partials; the draft side gets a launch                  */
+int ot_verify_structure(ot_ctx* ctx, int32_t B, int32_t M, int32_t* structure, int32_t* n_launches);
+
 /* Kernel timing.  While enabled, every step records HIP events between its kernels on the context's stream.
  * ot_verify_profile_read synchronises the stream, adds the elapsed milliseconds of the steps run since the
  * last read into ms[0 .. OT_N_STAGES) (overwriting it), stores the number of steps in *n_steps and resets.    */

@@ -26,13 +26,15 @@ STAGE_NAMES = ("lm_head", "softmax_stats", "translate_accept", "residual_draw")
 
 OT_EVICT_NONE, OT_EVICT_LRU, OT_EVICT_LFU = 0, 1, 2
 OT_DRAFT_SIDE_AUTO, OT_DRAFT_SIDE_IN_LM_HEAD, OT_DRAFT_SIDE_SEPARATE = 0, 1, 2
+OT_STRUCTURE_SEPARATE, OT_STRUCTURE_HOSTED, OT_STRUCTURE_PARTIALS = 0, 1, 2
 OT_LAMBDA_FIXED, OT_LAMBDA_TARGET_PROB = 0, 1
 OT_NGRAM_TERM_NLL, OT_NGRAM_TERM_APPROX_KL = 0, 1
 
 EXPORTS = (
     "ot_verify_init", "ot_verify_destroy", "ot_ngram_cache_build", "ot_ngram_cache_create", "ot_ngram_cache_insert",
     "ot_ngram_cache_size", "ot_ngram_cache_export", "ot_ngram_cache_import", "ot_ngram_cache_destroy", "ot_verify_step",
-    "ot_verify_step_from_logits", "ot_distill_loss", "ot_adaptive_drafting", "ot_adaptive_drafting_static", "ot_verify_workspace", "ot_verify_profile",
+    "ot_verify_step_from_logits", "ot_distill_loss", "ot_adaptive_drafting", "ot_adaptive_drafting_static", "ot_verify_workspace", "ot_verify_structure",
+    "ot_verify_profile",
     "ot_verify_profile_read", "ot_last_error", "ot_version",
 )
 
@@ -143,6 +145,8 @@ def load_library() -> C.CDLL:
     lib.ot_adaptive_drafting_static.restype = C.c_int
     lib.ot_verify_workspace.argtypes = [C.c_void_p, C.POINTER(ot_workspace_view)]
     lib.ot_verify_workspace.restype = C.c_int
+    lib.ot_verify_structure.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.POINTER(C.c_int32), C.POINTER(C.c_int32)]
+    lib.ot_verify_structure.restype = C.c_int
     lib.ot_verify_profile.argtypes = [C.c_void_p, C.c_int32]
     lib.ot_verify_profile.restype = C.c_int
     lib.ot_verify_profile_read.argtypes = [C.c_void_p, C.POINTER(C.c_float), C.POINTER(C.c_int32)]
@@ -306,6 +310,13 @@ def ot_verify_workspace(ctx) -> ot_workspace_view:
     v = ot_workspace_view()
     _check(load_library().ot_verify_workspace(ctx, C.byref(v)))
     return v
+
+
+def ot_verify_structure(ctx, B: int, M: int):
+    """Returns (OT_STRUCTURE_*, number of kernel launches) of a step of B sequences with M rows in total."""
+    s, n = C.c_int32(), C.c_int32()
+    _check(load_library().ot_verify_structure(ctx, B, M, C.byref(s), C.byref(n)))
+    return s.value, n.value
 
 
 def ot_verify_profile(ctx, enable: bool):

@@ -179,6 +179,25 @@ void ot_verify_destroy(ot_ctx* ctx) {
   free_ctx(ctx);
 }
 
+// What the LM-head launch of a step of B sequences and M rows takes (kHosts..), and how the draft rows are shared out in it.
+// Where its kernel supports it, it leaves per-tile softmax partials of the target rows (no second pass over the logits) and hosts
+// the draft side of the step (the draft rows' statistics in pieces, the drafted ids' lookups): what follows it is then one launch
+// that merges both, walks the windows, tests and draws.
+struct HeadPlan { int hosted, workers, nfine; };
+static HeadPlan head_plan(const ot_ctx* ctx, int B, int M) {
+  const int K = M - B, n_cu = ctx->n_cu;
+  const bool bf16 = ctx->dtype == OT_BF16;
+  HeadPlan p{kHostsNothing, 0, 0};
+  if (B > kFusedMaxB || K < 1 || ctx->draft_side == OT_DRAFT_SIDE_SEPARATE) return p;
+  if (ctx->draft_side == OT_DRAFT_SIDE_IN_LM_HEAD) p.hosted = kHostsAll;
+  else if (bf16) p.hosted = lmhead_bf16_hosts(M, ctx->d, ctx->Vp, B, K, ctx->V_d, n_cu);
+  else p.hosted = lmhead_f32_hosts_draft_side(M, ctx->d, ctx->V_t, B, K, ctx->V_d, n_cu) ? kHostsAll : kHostsNothing;
+  if (p.hosted == kHostsNothing) return p;
+  p.workers = bf16 ? lmhead_bf16_draft_workers(M, ctx->d, ctx->Vp, B, K, n_cu) : lmhead_f32_draft_workers(M, ctx->V_t, B, K, n_cu);
+  p.nfine = bf16 ? lmhead_bf16_fused_partials(M, ctx->d, ctx->Vp, n_cu) : ceil_div(ctx->V_t, 64);
+  return p;
+}
+
 static int step_impl(ot_ctx* ctx, ot_ngram_cache* cache, const ot_step_in* in, const float* ext_logits,
                      bool from_logits, ot_step_out* o) {
   if (!ctx || !in || !o) return fail(OT_ERR_NULL, "ot_verify_step: ctx, in and out must not be NULL");
@@ -241,23 +260,15 @@ static int step_impl(ot_ctx* ctx, ot_ngram_cache* cache, const ot_step_in* in, c
 #define OT_MARK(i) do { if (ev && e == hipSuccess) e = hipEventRecord(ev[i], st); } while (0)
   OT_MARK(0);
   if (e == hipSuccess && !from_logits) {
-    // Where its kernel supports it, the LM-head launch leaves per-tile softmax partials of the target rows (no second
-    // pass over the logits) and hosts the draft side of the step (the draft rows' statistics in pieces, the drafted
-    // ids' lookups): what follows it is then one launch that merges both, walks the windows, tests and draws.
-    const bool bf16 = ctx->dtype == OT_BF16;
-    const int workers = in->B > kFusedMaxB || K < 1 ? 0 : bf16 ? lmhead_bf16_draft_workers(M, ctx->d, ctx->Vp, in->B, K, ctx->n_cu)
-                                                               : lmhead_f32_draft_workers(M, ctx->V_t, in->B, K, ctx->n_cu);
-    if (workers > 0 && ctx->draft_side == OT_DRAFT_SIDE_IN_LM_HEAD) a.hosted = kHostsAll;
-    if (workers > 0 && ctx->draft_side == OT_DRAFT_SIDE_AUTO)
-      a.hosted = bf16 ? lmhead_bf16_hosts(M, ctx->d, ctx->Vp, in->B, K, ctx->V_d, ctx->n_cu)
-                      : lmhead_f32_hosts_draft_side(M, ctx->d, ctx->V_t, in->B, K, ctx->V_d, ctx->n_cu) ? kHostsAll : kHostsNothing;
+    const HeadPlan plan = head_plan(ctx, in->B, M);
+    a.hosted = plan.hosted;
     if (a.hosted != kHostsNothing) {
       a.fused.row_off = in->row_off; a.fused.temperature = in->temperature; a.fused.B = in->B; a.fused.part = ctx->fpart;
-      a.fused.nfine = bf16 ? lmhead_bf16_fused_partials(M, ctx->d, ctx->Vp, ctx->n_cu) : ceil_div(ctx->V_t, 64);
-      a.plan = make_piece_plan(workers, K);
+      a.fused.nfine = plan.nfine;
+      a.plan = make_piece_plan(plan.workers, K);
     }
     const StepArgs* draft_side = a.hosted == kHostsAll ? &a : nullptr;
-    if (bf16)
+    if (ctx->dtype == OT_BF16)
       e = launch_lmhead_bf16(static_cast<const uint16_t*>(in->hidden), M, ctx->d, ctx->Wp, ctx->Kp, ctx->Vp, ctx->Z,
                              ctx->V_t, a.ldz, ctx->zeros, &a.fused, draft_side, ctx->n_cu, st);
     else
@@ -292,6 +303,17 @@ int ot_verify_workspace(ot_ctx* ctx, ot_workspace_view* v) {
   v->logits = ctx->Z; v->ld_logits = ctx->V_t;
   v->row_max = ctx->row_max; v->row_sumexp = ctx->row_sum; v->row_argmax = ctx->row_arg;
   v->draft_row_max = ctx->drow_max; v->draft_row_sumexp = ctx->drow_sum; v->draft_row_argmax = ctx->drow_arg;
+  return OT_OK;
+}
+
+int ot_verify_structure(ot_ctx* ctx, int32_t B, int32_t M, int32_t* structure, int32_t* n_launches) {
+  if (!ctx || !structure || !n_launches) return fail(OT_ERR_NULL, "ot_verify_structure: NULL argument");
+  if (B < 1 || B > ctx->max_batch || M < B || M > B * (ctx->max_k + 1))
+    return fail(OT_ERR_SHAPE, "ot_verify_structure: B = %d, M = %d exceed the context (max_batch = %d, max_k = %d)", B, M, ctx->max_batch,
+                ctx->max_k);
+  const HeadPlan plan = head_plan(ctx, B, M);
+  *structure = plan.hosted;
+  *n_launches = (plan.hosted == kHostsAll ? 1 : 2) + final_draw_launches(plan.hosted, plan.nfine, M, ctx->V_t, B, ctx->n_cu);
   return OT_OK;
 }
 

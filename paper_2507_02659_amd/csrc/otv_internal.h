@@ -133,7 +133,7 @@ inline PiecePlan make_piece_plan(int workers, int K) {
 }
 
 // What of a step's statistics the LM-head launch takes.
-enum { kHostsNothing = 0, kHostsAll = 1, kHostsPartials = 2 };
+enum { kHostsNothing = OT_STRUCTURE_SEPARATE, kHostsAll = OT_STRUCTURE_HOSTED, kHostsPartials = OT_STRUCTURE_PARTIALS };
 
 struct StepArgs {
   // problem
@@ -202,5 +202,7 @@ bool lmhead_f32_hosts_draft_side(int M, int d, int V_t, int B, int K, int V_d, i
 hipError_t launch_softmax_stats(const StepArgs& a, hipStream_t stream);
 // translation and acceptance test (when the LM-head launch hosted the draft side) and the draw of the final tokens
 hipError_t launch_final_draw(const StepArgs& a, const int32_t* row_off_host, int n_cu, hipStream_t stream);
+// launches that takes: 1, or 2 where the test has one of its own (nfine: partials per target row, if the LM head left them)
+int final_draw_launches(int hosted, int nfine, int M, int V_t, int B, int n_cu);
 
 }  // namespace otv

@@ -173,6 +173,22 @@ template <int kPer> DrawSplit draw_split(int V_t, int B, int n_cu) {
   return s;
 }
 
+// ids per lane and their split
+struct DrawPlan { int per; DrawSplit split; };
+DrawPlan draw_plan(int V_t, int B, int n_cu) {
+  const DrawSplit two = draw_split<2>(V_t, B, n_cu), four = draw_split<4>(V_t, B, n_cu);
+  if (two.group_units == kDrawWaves && two.n_units <= 512 && B <= kFusedMaxB) return {2, two};
+  if (four.group_units == kDrawWaves && B <= kFusedMaxB) return {4, four};
+  return {8, draw_split<8>(V_t, B, n_cu)};
+}
+
+// Every group of units of a sequence repeats the merge of its rows' partials: M x nfine x 16 bytes per group.  Up to
+// about the traffic that costs as much as a launch this is one launch; beyond it the test gets a launch of its own.  (A few chunks
+// of the statistics launch per row: always one.)
+bool test_has_its_launch(int hosted, int nfine, int M, const DrawSplit& s) {
+  return hosted != kHostsNothing && (int64_t)M * nfine * (int64_t)sizeof(Partial) * ceil_div(s.n_units, s.group_units) > kRepeatedMergeBytes;
+}
+
 // What was left by which launch: see StepArgs::hosted.  row_off_host holds the B + 1 row offsets.
 template <int kPer, bool kBlocks = false>
 hipError_t launch_draw(const StepArgs& a, const int32_t* row_off_host, const DrawSplit& split, hipStream_t stream) {
@@ -190,7 +206,7 @@ hipError_t launch_draw(const StepArgs& a, const int32_t* row_off_host, const Dra
   }
   RowOffsets ro;
   for (int b = 0; b <= kFusedMaxB; ++b) ro.v[b] = row_off_host[b <= a.B ? b : a.B];
-  if (a.hosted == kHostsNothing) {                         // a few chunks per row: always one launch
+  if (a.hosted == kHostsNothing) {
     if (a.B > kFusedMaxB) {
       if constexpr (kPer == 8) hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, true, true, false, kBlocks>), grid, block, lds, stream, a, ro, s);
       else return hipErrorInvalidValue;
@@ -202,10 +218,7 @@ hipError_t launch_draw(const StepArgs& a, const int32_t* row_off_host, const Dra
     return hipGetLastError();
   }
   if (a.B > kFusedMaxB) return hipErrorInvalidValue;
-  // Every group of units of a sequence repeats the merge of its rows' partials: M x nfine x 16 bytes per group.  Up to
-  // about the traffic that costs as much as a launch this is one launch; beyond it the test gets a launch of its own.
-  const int64_t repeated = (int64_t)a.M * a.fused.nfine * (int64_t)sizeof(Partial) * grid.x;
-  if (repeated <= kRepeatedMergeBytes) {
+  if (!test_has_its_launch(a.hosted, a.fused.nfine, a.M, s)) {
     if (a.hosted == kHostsAll) hipLaunchKernelGGL((accept_draw_kernel<kPer, true, false, false, false, true, kBlocks>), grid, block, lds, stream, a, ro, s);
     else hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, true, true, kBlocks>), grid, block, lds, stream, a, ro, s);
     return hipGetLastError();
@@ -220,12 +233,15 @@ hipError_t launch_draw(const StepArgs& a, const int32_t* row_off_host, const Dra
 
 hipError_t launch_final_draw(const StepArgs& a, const int32_t* row_off_host, int n_cu, hipStream_t stream) {
   if (a.B == 0) return hipSuccess;
-  const DrawSplit two = draw_split<2>(a.V_t, a.B, n_cu), four = draw_split<4>(a.V_t, a.B, n_cu);
-  if (two.group_units == kDrawWaves && two.n_units <= 512 && a.B <= kFusedMaxB) return launch_draw<2>(a, row_off_host, two, stream);
-  if (four.group_units == kDrawWaves && a.B <= kFusedMaxB) return launch_draw<4>(a, row_off_host, four, stream);
-  const DrawSplit eight = draw_split<8>(a.V_t, a.B, n_cu);
-  if (eight.blocks == 1) return launch_draw<8>(a, row_off_host, eight, stream);
-  return launch_draw<8, true>(a, row_off_host, eight, stream);
+  const DrawPlan plan = draw_plan(a.V_t, a.B, n_cu);
+  if (plan.per == 2) return launch_draw<2>(a, row_off_host, plan.split, stream);
+  if (plan.per == 4) return launch_draw<4>(a, row_off_host, plan.split, stream);
+  if (plan.split.blocks == 1) return launch_draw<8>(a, row_off_host, plan.split, stream);
+  return launch_draw<8, true>(a, row_off_host, plan.split, stream);
+}
+
+int final_draw_launches(int hosted, int nfine, int M, int V_t, int B, int n_cu) {
+  return test_has_its_launch(hosted, nfine, M, draw_plan(V_t, B, n_cu).split) ? 2 : 1;
 }
 
 }  // namespace otv

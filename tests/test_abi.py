@@ -88,6 +88,7 @@ def test_init_argument_errors_need_no_gpu():
     assert lib.ot_verify_step(None, None, None, None) == ot.OT_ERR_NULL
     assert lib.ot_verify_workspace(None, None) == ot.OT_ERR_NULL
     assert lib.ot_verify_profile(None, 1) == ot.OT_ERR_NULL
+    assert lib.ot_verify_structure(None, 1, 1, None, None) == ot.OT_ERR_NULL
     lib.ot_verify_destroy(None)
     lib.ot_ngram_cache_destroy(None)
 
@@ -162,6 +163,11 @@ def test_step_and_cache_errors():
                           ot.make_step_out({}))
         empty = ot.ot_ngram_cache_build(v.ctx, [0], [], [])
         ot.ot_ngram_cache_destroy(empty)
+        assert ot.ot_verify_structure(v.ctx, 2, 7) == (ot.OT_STRUCTURE_HOSTED, 2)
+        for B, M in ((0, 1), (3, 7), (2, 1), (2, 9)):
+            with pytest.raises(ot.OtError) as e:
+                ot.ot_verify_structure(v.ctx, B, M)
+            assert e.value.code == ot.OT_ERR_SHAPE
         v.step(inp)
         res = v.results(inp)
         assert np.all(res["n_emit"] >= 1)

@@ -36,6 +36,9 @@ def test_partials_and_draft_side(dtype, d, V_t, V_d, ks):
         _say(f"small head {dtype} M={case.M} d={d} V_t={V_t} V_d={V_d} draft_side={side}")
         v = Verifier.for_case(case, draft_side=side)
         try:
+            structure = ot.ot_verify_structure(v.ctx, case.B, case.M)[0]
+            if side != ot.OT_DRAFT_SIDE_AUTO:
+                assert structure == (ot.OT_STRUCTURE_HOSTED if side == ot.OT_DRAFT_SIDE_IN_LM_HEAD else ot.OT_STRUCTURE_SEPARATE)
             got = v.run_case(case)
             ws = v.workspace(case.M, case.K, with_logits=True)
         finally:

@@ -11,14 +11,14 @@ from workloads import CaseSpec, make_case
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("d,V_t,V_d,ks", [
-    (64, 40001, 12001, [7, 8, 9] * 20),                 # 540 rows, two chunks a draft row; odd rows
-    (64, 40001, 24577, [0, 3, 1, 3] * 60),              # 660 rows, four chunks
-    (64, 50001, 33001, [10] * 64),                      # five chunks
-    (16, 50001, 24001, [1, 2] * 127 + [40]),            # 255 sequences, the most
-    (16, 100001, 8001, [61] * 9),                       # test and draw in launches of their own
+@pytest.mark.parametrize("d,V_t,V_d,ks,launches", [
+    (64, 40001, 12001, [7, 8, 9] * 20, 3),              # 540 rows, two chunks a draft row; odd rows
+    (64, 40001, 24577, [0, 3, 1, 3] * 60, 3),           # 660 rows, four chunks
+    (64, 50001, 33001, [10] * 64, 3),                   # five chunks
+    (16, 50001, 24001, [1, 2] * 127 + [40], 3),         # 255 sequences, the most
+    (16, 100001, 8001, [61] * 9, 4),                    # test and draw in launches of their own
 ])
-def test_partials_from_the_head_draft_side_behind_it(d, V_t, V_d, ks):
+def test_partials_from_the_head_draft_side_behind_it(d, V_t, V_d, ks, launches):
     ov, ot, Verifier, parity = _imports()
     B = len(ks)
     temps, dtemps = [[1.0, 0.5, 0.0, 2.0][i % 4] for i in range(B)], [[0.8, 1.0, 1.3, 0.0][i % 4] for i in range(B)]
@@ -32,6 +32,7 @@ def test_partials_from_the_head_draft_side_behind_it(d, V_t, V_d, ks):
     _say(f"partials only M={case.M} d={d} V_t={V_t} V_d={V_d}")
     v = Verifier.for_case(case)
     try:
+        assert ot.ot_verify_structure(v.ctx, case.B, case.M) == (ot.OT_STRUCTURE_PARTIALS, launches)
         got = v.run_case(case)
         ws = v.workspace(case.M, case.K, with_logits=True)
     finally:
