@@ -770,19 +770,20 @@ __global__ __launch_bounds__(256) void pack_w_f32_kernel(const float* __restrict
   Wp[(int64_t)wt * packed_f32_tile_units(nkb) + ((int64_t)kb * 4 + s) * 64 + lane] = make_float4(w[0], w[1], w[2], w[3]);
 }
 
-template <int MT, int WAVES, int PF>
+// kStats: partials and the draft side; a launch without them runs the kernel that does not hold their code.
+template <int MT, int WAVES, int PF, bool kStats>
 __global__ __launch_bounds__(WAVES * 64) void lmhead_f32_kernel(const float* __restrict__ H, int M, int d,
                                                                 const f32x4* __restrict__ Wp, int nkb, int n_wtiles,
                                                                 float* __restrict__ Z, int V_t, int64_t ldz, int m_blocks,
                                                                 FusedStats fs, int n_front, StepArgs ds) {
   constexpr int kRow = 17;                              // float4 per padded row of the reduction scratch
   __shared__ f32x4 sRed[WAVES][MT * 16 * kRow];
-  __shared__ float sScale[MT * 16];
+  __shared__ float sScale[kStats ? MT * 16 : 1];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   static_assert(sizeof(sRed) >= kFrontLdsBytes, "scratch of the draft side");
   static_assert(WAVES * 64 >= kFusedMaxB, "a thread per sequence");
-  const int wg = (int)blockIdx.x - n_front;             // n_front is a multiple of 8: the XCDs below are those of the block ids
-  if (wg < 0) {
+  const int wg = (int)blockIdx.x - (kStats ? n_front : 0);   // n_front is a multiple of 8: the XCDs below are those of the block ids
+  if (kStats && wg < 0) {
     if (ds.plan.base == kDraftPieces) front_draft_side<float, WAVES>(ds, blockIdx.x, tid, sRed);
     else front_draft_rows<float, WAVES>(ds, blockIdx.x, n_front, tid, sRed);
     return;
@@ -791,7 +792,7 @@ __global__ __launch_bounds__(WAVES * 64) void lmhead_f32_kernel(const float* __r
   const int wt = (slot / m_blocks) * 8 + (wg & 7), row0 = (slot % m_blocks) * (MT * 16);
   if (wt >= n_wtiles) return;                           // padding of the id space
   BlockScales scales;
-  scales.load(fs, tid);
+  if constexpr (kStats) scales.load(fs, tid);
   const int whole = d / 16;                             // blocks without a ragged end, split over the wavefronts
   const int kb0 = (int)(((int64_t)whole * wave) / WAVES), kb1 = (int)(((int64_t)whole * (wave + 1)) / WAVES);
   const f32x4* wp = Wp + (int64_t)wt * packed_f32_tile_units(nkb) + lane;
@@ -858,7 +859,7 @@ __global__ __launch_bounds__(WAVES * 64) void lmhead_f32_kernel(const float* __r
 #pragma unroll
     for (int e = 0; e < 4; ++e)
       sRed[wave][(mt * 16 + (lane & 15)) * kRow + 4 * g + e] = f32x4{acc[mt][0][e], acc[mt][1][e], acc[mt][2][e], acc[mt][3][e]};
-  scales.fill(sScale, row0, MT * 16);
+  if constexpr (kStats) scales.fill(sScale, row0, MT * 16);
   __syncthreads();
   for (int i = tid; i < MT * 256; i += WAVES * 64) {
     const int r = i >> 4, c = i & 15;
@@ -867,7 +868,7 @@ __global__ __launch_bounds__(WAVES * 64) void lmhead_f32_kernel(const float* __r
     for (int w = 1; w < WAVES; ++w) sum += sRed[w][r * kRow + c];
     const int m = row0 + r, n = wt * 64 + 4 * c;
     if (m < M) store_logits(Z + (int64_t)m * ldz + n, n, V_t, sum);
-    if (fs.part) {
+    if constexpr (kStats) {
       const float z[4] = {sum[0], sum[1], sum[2], sum[3]};
       const Partial p = partial_of_64(z, n, V_t, sScale[m < M ? r : 0]);
       if (m < M && c == 0) fs.part[(int64_t)m * fs.nfine + wt] = p;
@@ -894,9 +895,14 @@ hipError_t launch_f32(const float* H, int M, int d, const float* Wp, float* Z, i
   const int nkb = ceil_div(d, 16), n_wtiles = ceil_div(V_t, 64), m_blocks = ceil_div(M, MT * 16);
   const int n_front = !draft_side ? 0 : draft_side->plan.base == kDraftPieces ? ceil_div(front_jobs(*draft_side), 8) * 8
                                                                               : f32_row_front(draft_side->B, draft_side->K);
-  hipLaunchKernelGGL((lmhead_f32_kernel<MT, WAVES, PF>), dim3((unsigned)(n_front + ceil_div(n_wtiles, 8) * 8 * m_blocks)),
-                     dim3(WAVES * 64), 0, stream, H, M, d, reinterpret_cast<const f32x4*>(Wp), nkb, n_wtiles, Z, V_t, ldz,
-                     m_blocks, fs, n_front, draft_side ? *draft_side : StepArgs{});
+  const dim3 grid((unsigned)(n_front + ceil_div(n_wtiles, 8) * 8 * m_blocks)), block(WAVES * 64);
+  const f32x4* wp = reinterpret_cast<const f32x4*>(Wp);
+  if (fs.part)
+    hipLaunchKernelGGL((lmhead_f32_kernel<MT, WAVES, PF, true>), grid, block, 0, stream, H, M, d, wp, nkb, n_wtiles, Z, V_t, ldz,
+                       m_blocks, fs, n_front, draft_side ? *draft_side : StepArgs{});
+  else
+    hipLaunchKernelGGL((lmhead_f32_kernel<MT, WAVES, PF, false>), grid, block, 0, stream, H, M, d, wp, nkb, n_wtiles, Z, V_t, ldz,
+                       m_blocks, fs, 0, StepArgs{});
   return hipGetLastError();
 }
 
@@ -1183,17 +1189,34 @@ hipError_t launch_lmhead_f32(const float* H, int M, int d, const float* Wp, floa
   return launch_f32<2, 4, 2>(H, M, d, Wp, Z, V_t, ldz, fs, draft_side, stream);
 }
 
+static int f32_multiplying_workgroups(int M, int V_t) {
+  return ceil_div(ceil_div(V_t, 64), 8) * 8 * ceil_div(M, 16 * f32_block_tiles(M));
+}
 // A launch that leaves room on the chip gives every piece of a draft row a workgroup of its own, a larger one takes whole rows.
 int lmhead_f32_draft_workers(int M, int V_t, int B, int K, int n_cu) {
-  const int multiplying = ceil_div(ceil_div(V_t, 64), 8) * 8 * ceil_div(M, 16 * f32_block_tiles(M));
-  return multiplying + B + kDraftPieces * K <= 2 * n_cu ? kDraftPieces * K : K;
+  return f32_multiplying_workgroups(M, V_t) + B + kDraftPieces * K <= 2 * n_cu ? kDraftPieces * K : K;
 }
+// Whether the fp32 launch should leave partials and take the draft side.  That spares the statistics launch (6 us and a pass over both
+// sides' logits).  It costs the multiplying workgroups their epilogue and the launch behind it the merge of a partial per row and 64
+// columns; where wavefronts of front workgroups take whole draft rows, the launch lasts as long as they do: one draws 3.5 KB per us, and
+// a fifth of that while the weights stream.  A front that pushes multiplying workgroups into one round more costs 0.15 of a round.
+// Measured at 1002 shapes (d = 64 to 1024, 1024 to 152064 columns, 2 to 510 rows, draft rows of 1000 to 32000 ids): the choice costs
+// 0.2 % on average against the better one, 10 % at most (256 rows x 152064, d = 256, 192 draft rows of 32000 ids).  With a draft row
+// priced at 3 KB per us next to any head it was 2 % and 35 %.  us per step, hosted / separate: 5 rows x 100000 (d = 1024), draft rows
+// of 32000 ids 123 / 91, of 1000 92 / 92; 16 rows x 152064 (2376 partials a row) 138 / 137, x 32000 32.3 / 36.0; 64 rows x 32000
+// with draft rows of 8000 54.9 / 58.3.
 bool lmhead_f32_hosts_draft_side(int M, int d, int V_t, int B, int K, int V_d, int n_cu) {
   if (B < 1 || B > kFusedMaxB || K < 1) return false;
-  const double head_us = std::max(4.0 * d * (double)V_t / 6.0e6, 2.0 * M * d * (double)V_t / 1.0e8);
+  const double product_us = 2.0 * M * d * (double)V_t / 1.0e8, head_us = std::max(4.0 * d * (double)V_t / 6.0e6, product_us);
   if (lmhead_f32_draft_workers(M, V_t, B, K, n_cu) > K) return front_pieces_end_in_time(4.0 * V_d, head_us);
-  const int front = f32_row_front(B, K);
-  return ceil_div(B, front) * 5.0 + ceil_div(K, 4 * front) * (4.0 * V_d / 3.0e3) <= head_us;
+  const int front = f32_row_front(B, K), block_tiles = f32_block_tiles(M);
+  const double front_us = ceil_div(B, front) * 1.0 + ceil_div(K, 4 * front) * (4.0 * V_d / 3.5e3) + 0.8 * head_us;
+  const int at_once = n_cu * (block_tiles == 1 ? 2 : block_tiles == 2 ? 4 : 3);      // workgroups that fit the chip
+  const int multiplying = f32_multiplying_workgroups(M, V_t), rounds = ceil_div(multiplying, at_once);
+  const double added_us = 0.0035 * ceil_div(V_t, 64) + 0.5e-6 * M * (double)V_t + 0.06 * product_us +
+                          (ceil_div(multiplying + front, at_once) > rounds ? 0.15 * product_us / rounds : 0.0);
+  const double statistics_us = 6.0 + (4.0 * M * (double)V_t + 4.0 * K * (double)V_d) / 5.0e6;
+  return std::max(head_us + added_us, front_us) < head_us + statistics_us;
 }
 
 }  // namespace otv
