@@ -1029,8 +1029,7 @@ int lmhead_bf16_fused_partials(int M, int d, int Vp, int n_cu) {
 }
 
 // Workgroups of launch_lmhead_bf16 that share the draft rows when the launch hosts the draft side: the multiplying
-// ones with a single M-block (their number: one per tile of columns), the front ones otherwise.  0: the shape leaves no
-// partials and hosts nothing.
+// ones with a single M-block (their number: one per tile of columns), workgroups of their own or front ones otherwise.
 int lmhead_bf16_draft_workers(int M, int d, int Vp, int B, int K, int n_cu) {
   const int nfine = lmhead_bf16_fused_partials(M, d, Vp, n_cu);
   if (M <= 16) return kDraftPieces * K;      // workgroups of their own
@@ -1054,20 +1053,19 @@ static bool front_pieces_end_in_time(double row_bytes, double head_us) {
 // Heads of 128-column workgroups are never hosted: their logits are few and their epilogues many.  Measured, us per step
 // hosted / separate: V_t = 128256, 128 rows 82 / 92 (d = 1024); V_t = 48000, 96 rows 98 / 101, 128 rows (whole draft rows)
 // 117 / 108; V_t = 60000, 168 rows 102 / 87 (d = 2048); V_t = 32000, 80 rows 74 / 72; V_t = 8000, 80 rows 64 / 58.
-// With several M-blocks front workgroups take the draft side: hosted where the launch, with them in its rounds, is
-// estimated to end before a launch without them and the statistics pass, over the draft rows alone if the launch still leaves the
-// target rows' partials (a launch more than hosted, and the estimate's 7 us a round and 8 beside are what fits the shapes below).
-// Measured, all hosted or, where noted, separate / partials only: 1024 rows x 128256 1039 us / 1003 (57 MB of draft rows), 320 rows
-// 366 / 351, 400 (d = 1024) 188 / 172, 240 x 60000 (d = 1024) separate 67.3 / 67.2; not taken: 424 x 152064 483 / 493, 1000 x 100000
-// with 9000 draft ids (d = 600) 253 / 267, 320 x 32000 (d = 3584) separate 94.6 / 95.1.
-// They cost most where they push multiplying
-// workgroups into a round more: V_t = 128256, 320 rows (502 + 16 workgroups) 412 us hosted, 365 separate; 152064, 320 rows
-// 399 / 424; 1024 rows 1057 / 1104; 20001 (d = 1024), 200 rows 39 / 47.  Over 216 shapes the choice costs 0.3 % on average against
-// the better one, 13 % at most (20001 columns with 200 draft rows of 20001, 54 / 61).
+// With several M-blocks front workgroups take the draft side: hosted where the launch, with them in its rounds, is estimated to end
+// before a launch without them and the statistics pass, over the draft rows alone if the launch still leaves the target rows'
+// partials.  The row statistics cost a round of multiplying workgroups kStatsUs in either structure; the partials alone cost a launch
+// more (8 us with its draft rows' chunks merged).  Both are fitted to 240 shapes (d = 1024 and 4096, 8000 to 152064 columns, 192 to 1024
+// rows, draft rows of 8000 and 32000 ids), each timed in all three structures: the choice costs 0.5 % on average against the best, 15 %
+// at most (400 rows x 20001, d = 1024, draft rows of 8000: separate 53.9, hosted 46.6); without the partials alone the best choice of
+// the other two costs 1.9 %.  us per step, hosted / separate / partials alone: 1024 rows x 128256 1039 / -- / 1003, 512 rows x 128256
+// (d = 1024) 245 / 218 / 193, 240 rows 129 / 116 / 114, 320 rows x 50000 (d = 1024) 59.7 / 67.7 / 64.5, 192 rows x 8000 (d = 1024) 41.7 / 26.0 /
+// 28.5.  Front workgroups cost most where they push multiplying ones into a round more: V_t = 128256, 320 rows (502 + 16 workgroups) 412
+// us hosted, 365 separate.
 int lmhead_bf16_hosts(int M, int d, int Vp, int B, int K, int V_d, int n_cu) {
   if (B < 1 || B > kFusedMaxB || K < 1) return kHostsNothing;
   const int workers = lmhead_bf16_draft_workers(M, d, Vp, B, K, n_cu);
-  if (workers == 0) return kHostsNothing;
   if (M <= 16)
     return Vp / kGemmColsPerWave <= kMaxMergedPartials && front_pieces_end_in_time(2.0 * V_d, lmhead_launch_us(M, d, Vp)) ? kHostsAll
                                                                                                                          : kHostsNothing;
@@ -1081,7 +1079,7 @@ int lmhead_bf16_hosts(int M, int d, int Vp, int B, int K, int V_d, int n_cu) {
   if (n_front >= n_cu) return kHostsNothing;
   // The launch ends at the first moment by which n_front compute units that come free after front_us and the others have
   // had room for all workgroups, each kStatsUs longer for the row statistics; half of what stays idle counts, as above.
-  constexpr double kStatsUs = 4.5;
+  constexpr double kStatsUs = 7.0;
   const double t = plan.round_us + kStatsUs, n = plan.workgroups;
   const double rounds_alone = std::ceil(n / (n_cu - n_front) - 1e-9);          // the front's compute units never join
   double end = rounds_alone * t;
@@ -1094,7 +1092,7 @@ int lmhead_bf16_hosts(int M, int d, int Vp, int B, int K, int V_d, int n_cu) {
   const double hosted = std::max(front_us, 0.5 * (end + (n * t + n_front * front_us) / n_cu));
   const double draft_us = 2.0 * K * (double)V_d / 5.0e6;
   const double separate = plan.rounds * plan.round_us + 4.0 + 4.0 * M * Vp / 5.0e6 + draft_us;
-  const double partials = plan.rounds * (plan.round_us + 7.0) + 8.0 + draft_us;
+  const double partials = plan.rounds * (plan.round_us + kStatsUs) + 8.0 + draft_us;
   return hosted < std::min(separate, partials) ? kHostsAll : partials < separate ? kHostsPartials : kHostsNothing;
 }
 
@@ -1105,7 +1103,7 @@ hipError_t launch_lmhead_bf16(const uint16_t* H, int M, int d, const uint16_t* W
   const int tiles = ceil_div(M, 16);
   FusedStats fs{};
   if (fused && fused->part) {
-    if (fused->nfine != lmhead_bf16_fused_partials(M, d, Vp, n_cu) || fused->nfine == 0 || fused->B < 1 || fused->B > kFusedMaxB)
+    if (fused->nfine != lmhead_bf16_fused_partials(M, d, Vp, n_cu) || fused->B < 1 || fused->B > kFusedMaxB)
       return hipErrorInvalidValue;
     fs = *fused;
   }

@@ -177,17 +177,16 @@ struct StepArgs {
 // ------------------------------------------------------------------------------------------------ launchers
 // Each returns the hipError_t of its launch.  All work goes to `stream`.
 hipError_t launch_pack_w_bf16(const uint16_t* W, int d, int V_t, uint16_t* Wp, int Kp, int Vp, hipStream_t stream);
-// Partials per row that launch_lmhead_bf16 emits for M rows of a Vp-column (padded) head; 0: that shape runs a
-// kernel without the fused statistics.
+// Partials per row that launch_lmhead_bf16 emits for M rows of a Vp-column (padded) head, where it is asked for them.
 // (n_cu = compute units of the device: the column width of a workgroup is chosen so that the launch takes few rounds.)
 int lmhead_bf16_fused_partials(int M, int d, int Vp, int n_cu);
 // What the LM-head launch of a step of this shape takes (kHosts..): partials and the draft side, the partials only, or nothing (the
 // statistics launch takes the rest).
 int lmhead_bf16_hosts(int M, int d, int Vp, int B, int K, int V_d, int n_cu);
-// workgroups of launch_lmhead_bf16 that share the draft rows (0: that shape leaves no partials and hosts nothing)
+// workers of launch_lmhead_bf16 that share the draft rows
 int lmhead_bf16_draft_workers(int M, int d, int Vp, int B, int K, int n_cu);
 // `fused` may be nullptr or have part == nullptr (no statistics); otherwise fused->nfine must be
-// lmhead_bf16_fused_partials(M, d, Vp, n_cu) > 0 and fused->B <= kFusedMaxB.  With fused statistics and `draft_side` not
+// lmhead_bf16_fused_partials(M, d, Vp, n_cu) and fused->B <= kFusedMaxB.  With fused statistics and `draft_side` not
 // nullptr, the launch also hosts the draft side of *draft_side: statistics of pieces of the draft rows into its dpiece, shared
 // out by its plan, and the drafted ids' lookups into its probe records.
 hipError_t launch_lmhead_bf16(const uint16_t* H, int M, int d, const uint16_t* Wp, int Kp, int Vp, float* Z, int V_t,
