@@ -59,8 +59,8 @@ def read_traffic_note(path):
 
 
 def measure_cliffs(torch, Verifier):
-    """Step time at the capacity edges the header documents: B = 255 / 256 (fused launch against separate passes) at a
-    mid-size bf16 head, and the one-thread-per-logit fp32 head."""
+    """Step time at a capacity edge the header documents, B = 255 / 256 (the most sequences that a hosted step takes) at a mid-size
+    bf16 head, and that of an fp32 head."""
     from workloads import CaseSpec, make_case
     out = {}
     for name, B, dtype in (("bf16_B255", 255, "bf16"), ("bf16_B256", 256, "bf16"), ("f32_B16", 16, "f32")):
@@ -174,9 +174,9 @@ def main():
     gemm_bytes = lm_head_bytes(M, d, V_t) if esz == 2 else 4 * d * V_t + 4 * M * d + 4 * M * V_t
     gemm_s = stage_us["lm_head"] * 1e-6
     achieved = gemm_bytes / gemm_s / 1e9 if gemm_s > 0 else 0.0
-    # what follows the LM head: with fused statistics one launch (merge of the partials + acceptance + draw), else
-    # statistics, translation + acceptance, draw
-    fused = esz == 2 and case.B <= 255 and not from_logits and (M > 16 or V_t <= 65536)
+    # what the LM-head launch leaves to others (the library says): all statistics, the draft side alone, or nothing
+    structure, launches = ot.ot_verify_structure(v.ctx, case.B, M)
+    fused = structure != ot.OT_STRUCTURE_SEPARATE and not from_logits
     tail_us = ms_per_step * 1e3 - stage_us["lm_head"]
     extra = {
         "stage_us": {k: round(x, 2) for k, x in stage_us.items()},
@@ -185,12 +185,15 @@ def main():
         "lm_head_tflops": round(2.0 * M * d * V_t / gemm_s / 1e12, 1) if gemm_s > 0 else None,
         "lm_head_frac_mfma_peak": round(2.0 * M * d * V_t / gemm_s / 1e12 / MFMA_BF16_PEAK_TFLOPS, 4) if gemm_s > 0 else None,
         "rows_per_s": round(M * args.steps / elapsed, 1),
-        "step_hbm_bytes": gemm_bytes + esz * K * V_d + (16 * M * (-(-V_t // (256 if M > 16 else 64))) if fused else 4 * M * V_t)
+        "step_hbm_bytes": gemm_bytes + esz * K * V_d + (16 * M * (-(-V_t // (256 if esz == 2 and M > 16 else 64))) if fused else 4 * M * V_t)
                           + case.B * (4 * V_t + esz * V_d + 4 * V_t),
     }
     if len(ring) > 1:
         extra["cold_weights"] = f"steps rotate over {len(ring)} contexts with private copies of the LM head"
-    extra["row_statistics"] = "lm_head epilogue, draft side in the same launch" if fused else "separate pass over the logits"
+    if not from_logits:
+        extra["launches_per_step"] = launches
+    extra["row_statistics"] = ("separate pass over the logits" if not fused else "lm_head epilogue, draft side in the same launch"
+                               if structure == ot.OT_STRUCTURE_HOSTED else "lm_head epilogue, draft side in a launch of its own")
 
     # The softmax pass on its own (the metric's "% HBM BW (softmax)"): the same batch through
     # ot_verify_step_from_logits with the logits the LM head just produced, so that the statistics kernel reads all

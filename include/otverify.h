@@ -67,21 +67,22 @@ typedef struct ot_ngram_cache ot_ngram_cache; /* owns the device hash table of o
 
 /* ---- ot_verify_init ----------------------------------------------------------------------------------- */
 /* The draft rows' softmax statistics and what the drafted ids look up for the translation (Eq. 1: the drafted logit,
- * the direct image, the n-gram cache probes) need nothing from the LM head.  Where the bf16 LM-head kernel supports it
- * (more than 16 rows, at most 255 sequences) the LM-head launch itself can do that work: with up to 176 rows, where the
- * launch is bound by the weight stream, every multiplying workgroup takes a piece of a draft row while its first loads
- * are in flight; with more rows a few workgroups at the front of the launch take all of it.  The launch then also
- * leaves the target rows' softmax partials, and one launch follows it (window walk, acceptance test, final draw)
- * instead of two. */
-/* Capacity edges (all shapes inside max_batch / max_k are served; what changes is the launch structure):
- *   - 16 rows or fewer, more than 255 sequences, OT_F32, or a step entered through ot_verify_step_from_logits: the draft
- *     side always runs after the LM head (the softmax statistics of all rows and the lookups as a launch of their own,
- *     then the launch that walks, tests and draws: one launch more, a few microseconds and a pass over the logits);
- *   - OT_DRAFT_SIDE_AUTO also chooses that where hosting is estimated to cost more: heads of up to about 32768 columns,
- *     more than half a draft row per multiplying workgroup next to few logits (up to 176 rows), or front workgroups
- *     that lengthen the launch (above).                                                                        */
-#define OT_DRAFT_SIDE_AUTO        0   /* decide per step from its shape (estimate of both durations)               */
-#define OT_DRAFT_SIDE_IN_LM_HEAD  1   /* inside the LM-head launch whenever the kernel supports the shape          */
+ * the direct image, the n-gram cache probes) need nothing from the LM head.  A step of at most 255 sequences and at least
+ * one drafted id runs in one of three launch structures (ot_verify_structure tells which):
+ *   - hosted, two launches: the LM-head launch does that work as well.  OT_BF16 with 17 to 176 rows, where the launch is
+ *     bound by the weight stream: every multiplying workgroup takes a piece of a draft row while its first loads are in
+ *     flight.  Up to 16 rows, more than 176 rows, and OT_F32: workgroups at the front of the launch take all of it.  The
+ *     launch also leaves the target rows' softmax partials, and one launch follows it (window walk, acceptance test, final
+ *     draw; two, the test apart, where many rows have many partials);
+ *   - partials alone, three launches (OT_BF16, more than 176 rows): the LM-head launch leaves the target rows' partials, a
+ *     launch of its own does the draft side;
+ *   - separate, three launches: the softmax statistics of all rows and the lookups have a launch of their own behind the LM
+ *     head (a few microseconds and a pass over the logits).  More than 255 sequences, steps without a drafted id and
+ *     those entered through ot_verify_step_from_logits (two launches, no LM head) always run like this.
+ * OT_DRAFT_SIDE_AUTO takes the structure that is estimated to end first.  It never hosts in OT_BF16 heads of up to about
+ * 32768 columns with 17 to 176 rows, nor in heads of more than 65536 columns with up to 16.                       */
+#define OT_DRAFT_SIDE_AUTO        0   /* decide per step from its shape (estimate of the durations)                */
+#define OT_DRAFT_SIDE_IN_LM_HEAD  1   /* hosted wherever there are drafted ids and at most 255 sequences           */
 #define OT_DRAFT_SIDE_SEPARATE    2   /* always as launches of their own after the LM head                         */
 
 typedef struct ot_verify_config {
@@ -311,7 +312,8 @@ int ot_verify_structure(ot_ctx* ctx, int32_t B, int32_t M, int32_t* structure, i
  * ot_verify_profile_read synchronises the stream, adds the elapsed milliseconds of the steps run since the
  * last read into ms[0 .. OT_N_STAGES) (overwriting it), stores the number of steps in *n_steps and resets.    */
 #define OT_STAGE_LM_HEAD          0   /* z = h . W                                                            */
-#define OT_STAGE_SOFTMAX_STATS    1   /* softmax statistics of the target and draft rows; 0 when the LM-head
+#define OT_STAGE_SOFTMAX_STATS    1   /* softmax statistics of the target and draft rows (of the draft rows, if
+                                         the LM head left the partials of the others); 0 when the LM-head
                                          launch computes them itself                                          */
 #define OT_STAGE_TRANSLATE_ACCEPT 2   /* 0: translation and acceptance test run in the launch of the next stage */
 #define OT_STAGE_RESIDUAL_DRAW    3   /* masses of max(0, p - q') (Eq. 2) at the final row, inverse-CDF draw  */

@@ -184,7 +184,7 @@ struct Outcome {
   double pt, ratio;
 };
 
-// s_pmx / s_pS / s_pinv / s_parg: the statistics of the sequence's target rows; z_tok: z[row pos, t] of a reached segment; u1 its
+// s_pmx / s_pinv / s_parg: maximum, 1 / sum and argmax of the sequence's target rows; z_tok: z[row pos, t] of a reached segment; u1 its
 // uniform.
 __device__ __forceinline__ Outcome test_window(float T, double invT, const Window& w, const DraftLane& D, bool reached, int pos, float z_tok,
                                       double u1, const float* s_pmx, const double* s_pinv, const int* s_parg) {

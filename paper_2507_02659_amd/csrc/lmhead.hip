@@ -1057,7 +1057,7 @@ static bool front_pieces_end_in_time(double row_bytes, double head_us) {
 // before a launch without them and the statistics pass, over the draft rows alone if the launch still leaves the target rows'
 // partials.  The row statistics cost a round of multiplying workgroups kStatsUs in either structure; the partials alone cost a launch
 // more (8 us with its draft rows' chunks merged).  Both are fitted to 240 shapes (d = 1024 and 4096, 8000 to 152064 columns, 192 to 1024
-// rows, draft rows of 8000 and 32000 ids), each timed in all three structures: the choice costs 0.5 % on average against the best, 15 %
+// rows, draft rows of 8000 and 32000 ids), each timed in all three structures: the choice costs 0.4 % on average against the best, 15 %
 // at most (400 rows x 20001, d = 1024, draft rows of 8000: separate 53.9, hosted 46.6); without the partials alone the best choice of
 // the other two costs 1.9 %.  us per step, hosted / separate / partials alone: 1024 rows x 128256 1039 / -- / 1003, 512 rows x 128256
 // (d = 1024) 245 / 218 / 193, 240 rows 129 / 116 / 114, 320 rows x 50000 (d = 1024) 59.7 / 67.7 / 64.5, 192 rows x 8000 (d = 1024) 41.7 / 26.0 /

@@ -29,10 +29,11 @@ struct ot_ctx {
   float *tpart_max = nullptr, *dpart_max = nullptr, *row_max = nullptr, *drow_max = nullptr;
   double *tpart_sum = nullptr, *dpart_sum = nullptr, *row_sum = nullptr, *drow_sum = nullptr;
   int32_t *tpart_arg = nullptr, *dpart_arg = nullptr, *row_arg = nullptr, *drow_arg = nullptr;
-  otv::Partial* fpart = nullptr;      // [max_rows, Vp/128] softmax partials from the LM-head epilogue (bf16)
+  otv::Partial* fpart = nullptr;      // softmax partials from the LM-head epilogue: per row one for 64 columns (fp32, and up to 16 rows of
+                                      // bf16) or for 128 to 640
   int n_cu = 0;                       // compute units of the device
   otv::DraftPiece* dpiece = nullptr;  // [max_K, kDraftPieces] pieces of the draft rows' statistics, as the probe records
-  otv::ProbeRecord* probe = nullptr;  // [max_batch] lookups of the drafted ids, between the LM-head launch and the next
+  otv::ProbeRecord* probe = nullptr;  // [max_batch] lookups of the drafted ids, from the LM-head or the statistics launch
   double* unit_mass = nullptr;        // [max_batch, max_units] masses of the draw, all bits set between launches
   otv::FinalInfo* fin = nullptr;
   double* loss_part = nullptr;        // [max_rows, kLossGroups] KL sums of a row's groups

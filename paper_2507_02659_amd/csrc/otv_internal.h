@@ -162,7 +162,7 @@ struct StepArgs {
   float* drow_max; double* drow_sum; int32_t* drow_arg;      // [K]
   DraftPiece* dpiece;    // [K, kDraftPieces] statistics of the pieces of the draft rows, left by the LM-head launch
   PiecePlan plan;        // how the LM-head launch shared out the draft rows
-  ProbeRecord* probe;    // [B] what the drafted ids of each sequence look up (see ProbeRecord), left by the LM-head launch
+  ProbeRecord* probe;    // [B] what the drafted ids of each sequence look up (see ProbeRecord)
   int32_t hosted;        // kHostsAll: the LM-head launch left the target rows' softmax partials (`fused`), the draft rows' pieces
                          // and the probe records: one launch follows it, which translates, tests and draws;
                          // kHostsPartials: it left `fused`, and the statistics launch the draft rows' chunk partials (dpart_*) and
@@ -199,7 +199,7 @@ hipError_t launch_lmhead_f32(const float* H, int M, int d, const float* Wp, floa
 int lmhead_f32_draft_workers(int M, int V_t, int B, int K, int n_cu);
 bool lmhead_f32_hosts_draft_side(int M, int d, int V_t, int B, int K, int V_d, int n_cu);
 hipError_t launch_softmax_stats(const StepArgs& a, hipStream_t stream);
-// translation and acceptance test (when the LM-head launch hosted the draft side) and the draw of the final tokens
+// translation, acceptance test and the draw of the final tokens
 hipError_t launch_final_draw(const StepArgs& a, const int32_t* row_off_host, int n_cu, hipStream_t stream);
 // launches that takes: 1, or 2 where the test has one of its own (nfine: partials per target row, if the LM head left them)
 int final_draw_launches(int hosted, int nfine, int M, int V_t, int B, int n_cu);

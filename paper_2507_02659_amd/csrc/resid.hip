@@ -6,8 +6,8 @@
 //                       sequence (one wavefront merges the partials of the draft rows and walks the window from the
 //                       probe record while the others merge the target rows' partials, one wavefront per row; then that
 //                       wavefront runs the test: a few microseconds of work on data that sits in L2, cheaper than a
-//                       launch of its own: 300 sequences x 32003 ids 42 us, against 10.5 + 30.6 and a launch), then
-//                       takes part in the draw.  The workgroups of a sequence reach the same outcome; only group 0
+//                       launch of its own: with the draw of that time 300 sequences x 32003 ids took 42 us against
+//                       10.5 + 30.6 and a launch; it takes 33 now), then takes part in the draw.  The workgroups of a sequence reach the same outcome; only group 0
 //                       writes the outputs of the translation and the test, the draft rows' merged statistics and
 //                       the cache's use statistics.
 #include <algorithm>
@@ -152,8 +152,8 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, R
 // Units of the draw and their share per workgroup.  While no more than a workgroup per compute unit is needed for one turn each,
 // a wavefront takes as few ids as that allows: 128 (up to 512 units), else 256, else 512.  A
 // small batch is bound by the chain of instructions and round trips in one workgroup, which fewer ids per lane shorten.  With
-// more groups than compute units each workgroup takes as many turns as bring their number back to one per compute unit (84
-// registers: five wavefronts per SIMD, so that a workgroup of 16 fills one): its start, its share of the merge and its look at the
+// more groups than compute units each workgroup takes as many turns as bring their number back to one per compute unit (80 to 95
+// registers: five or six wavefronts per SIMD, of which a workgroup takes four, so that a second does not fit): its start, its share of the merge and its look at the
 // masses are then paid once for several turns, and a turn's loads overlap the sums of the turn before.
 // Measured, us per step, 128 / 256 / 512 ids a wavefront: 6 rows x 32000 ids 53.9 / 54.1 / 55.2, 12 rows x 64000 (d = 1024) 39.4 /
 // 40.1 / 42.6, 24 x 152064 -- / 180.8 / 182.0, 80 x 32000 66.7 / 66.2 / 68.1, 6 x 152064 (d = 1024) -- / 69.2 / 70.7.

@@ -293,8 +293,9 @@ __device__ __forceinline__ Window walk_window(int k, int lane, unsigned long lon
   return w;
 }
 
-// q'(t) of the segment that starts at this lane from the lanes' q(d): the product over its draft tokens (Eq. 1).  Eight factors,
-// the longest key, stay far inside binary64's range unless one of them has left it already.
+// q'(t) of the segment that starts at this lane from the lanes' q(d): the product over its draft tokens (Eq. 1).  Below about 1e-308
+// it is 0, as the exponential of the summed logarithms would be (eight factors of 1e-45 are enough at a low draft temperature): a
+// token with p > 0 is accepted then.
 __device__ __forceinline__ double segment_q(double q, const Window& w) {
   double qp = q;
   if (__ballot(w.L > 1) != 0ull) {
