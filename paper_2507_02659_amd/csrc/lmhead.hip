@@ -1196,23 +1196,27 @@ int lmhead_f32_draft_workers(int M, int V_t, int B, int K, int n_cu) {
 }
 // Whether the fp32 launch should leave partials and take the draft side.  That spares the statistics launch (6 us and a pass over both
 // sides' logits).  It costs the multiplying workgroups their epilogue and the launch behind it the merge of a partial per row and 64
-// columns; where wavefronts of front workgroups take whole draft rows, the launch lasts as long as they do: one draws 3.5 KB per us, and
-// a fifth of that while the weights stream.  A front that pushes multiplying workgroups into one round more costs 0.15 of a round.
-// Measured at 1002 shapes (d = 64 to 1024, 1024 to 152064 columns, 2 to 510 rows, draft rows of 1000 to 32000 ids): the choice costs
-// 0.2 % on average against the better one, 10 % at most (256 rows x 152064, d = 256, 192 draft rows of 32000 ids).  With a draft row
-// priced at 3 KB per us next to any head it was 2 % and 35 %.  us per step, hosted / separate: 5 rows x 100000 (d = 1024), draft rows
-// of 32000 ids 123 / 91, of 1000 92 / 92; 16 rows x 152064 (2376 partials a row) 138 / 137, x 32000 32.3 / 36.0; 64 rows x 32000
+// columns (and a launch where the test gets one of its own); where wavefronts of front workgroups take whole draft rows, the launch
+// lasts as long as they do: one draws 3.5 KB per us, 1.6 with more than two rows in turn, and a fifth of that while the weights stream
+// (1020 rows x 65536, d = 64, seven rows of 8000 ids each, 282 us hosted, 211 separate).  A front that pushes
+// multiplying workgroups into one round more costs 0.15 of a round.
+// Measured at 1296 shapes (d = 64 to 1024, 1024 to 152064 columns, 2 to 1530 rows, draft rows of 1000 to 32000 ids): the choice costs
+// 0.2 % on average against the better one, 10 % at most (16 rows x 100000, d = 256, draft rows of 8000 ids, 36.0 / 32.7).  With a draft
+// row priced at 3 KB per us next to any head it was 3 % and 63 %.  us per step, hosted / separate: 5 rows x 100000 (d = 1024), draft
+// rows of 32000 ids 123 / 91, of 1000 92 / 92; 16 rows x 152064 (2376 partials a row) 138 / 137, x 32000 32.3 / 36.0; 64 rows x 32000
 // with draft rows of 8000 54.9 / 58.3.
 bool lmhead_f32_hosts_draft_side(int M, int d, int V_t, int B, int K, int V_d, int n_cu) {
   if (B < 1 || B > kFusedMaxB || K < 1) return false;
   const double product_us = 2.0 * M * d * (double)V_t / 1.0e8, head_us = std::max(4.0 * d * (double)V_t / 6.0e6, product_us);
   if (lmhead_f32_draft_workers(M, V_t, B, K, n_cu) > K) return front_pieces_end_in_time(4.0 * V_d, head_us);
   const int front = f32_row_front(B, K), block_tiles = f32_block_tiles(M);
-  const double front_us = ceil_div(B, front) * 1.0 + ceil_div(K, 4 * front) * (4.0 * V_d / 3.5e3) + 0.8 * head_us;
+  const int rows_each = ceil_div(K, 4 * front);
+  const double front_us = ceil_div(B, front) * 1.0 + rows_each * (4.0 * V_d / (rows_each <= 2 ? 3.5e3 : 1.6e3)) + 0.8 * head_us;
   const int at_once = n_cu * (block_tiles == 1 ? 2 : block_tiles == 2 ? 4 : 3);      // workgroups that fit the chip
   const int multiplying = f32_multiplying_workgroups(M, V_t), rounds = ceil_div(multiplying, at_once);
   const double added_us = 0.0035 * ceil_div(V_t, 64) + 0.5e-6 * M * (double)V_t + 0.06 * product_us +
-                          (ceil_div(multiplying + front, at_once) > rounds ? 0.15 * product_us / rounds : 0.0);
+                          (ceil_div(multiplying + front, at_once) > rounds ? 0.15 * product_us / rounds : 0.0) +
+                          (final_draw_launches(kHostsAll, ceil_div(V_t, 64), M, V_t, B, n_cu) > 1 ? 15.0 : 0.0);
   const double statistics_us = 6.0 + (4.0 * M * (double)V_t + 4.0 * K * (double)V_d) / 5.0e6;
   return std::max(head_us + added_us, front_us) < head_us + statistics_us;
 }

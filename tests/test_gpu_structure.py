@@ -27,6 +27,8 @@ def _structure(dtype, d, V_t, V_d, B, M):
     (1024, 100000, 32000, 8, 32, False),     # 139 / 113
     (256, 152064, 32000, 16, 64, False),     # 97 / 81
     (64, 32000, 32000, 16, 64, False),       # 57 / 26
+    (64, 65536, 8000, 170, 1020, False),     # 282 / 211: seven draft rows in turn
+    (64, 65536, 1000, 64, 384, True),        # 75 / 79
 ])
 def test_fp32_head(d, V_t, V_d, B, M, hosted):
     ot = _imports()[1]
