@@ -7,9 +7,9 @@
 //                       probe record while the others merge the target rows' partials, one wavefront per row; then that
 //                       wavefront runs the test: a few microseconds of work on data that sits in L2, cheaper than a
 //                       launch of its own: with the draw of that time 300 sequences x 32003 ids took 42 us against
-//                       10.5 + 30.6 and a launch; it takes 33 now), then takes part in the draw.  The workgroups of a sequence reach the same outcome; only group 0
-//                       writes the outputs of the translation and the test, the draft rows' merged statistics and
-//                       the cache's use statistics.
+//                       10.5 + 30.6 and a launch; it takes 33 now), then takes part in the draw.  The workgroups of
+//                       a sequence reach the same outcome; only group 0 writes the outputs of the translation and the
+//                       test, the draft rows' merged statistics and the cache's use statistics.
 #include <algorithm>
 
 #include "accept.h"
@@ -153,8 +153,9 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, R
 // a wavefront takes as few ids as that allows: 128 (up to 512 units), else 256, else 512.  A
 // small batch is bound by the chain of instructions and round trips in one workgroup, which fewer ids per lane shorten.  With
 // more groups than compute units each workgroup takes as many turns as bring their number back to one per compute unit (80 to 95
-// registers: five or six wavefronts per SIMD, of which a workgroup takes four, so that a second does not fit): its start, its share of the merge and its look at the
-// masses are then paid once for several turns, and a turn's loads overlap the sums of the turn before.
+// registers: five or six wavefronts per SIMD, of which a workgroup takes four, so that a second does not fit): its start, its share
+// of the merge and its look at the masses are then paid once for several turns, and a turn's loads overlap the sums of the turn
+// before.
 // Measured, us per step, 128 / 256 / 512 ids a wavefront: 6 rows x 32000 ids 53.9 / 54.1 / 55.2, 12 rows x 64000 (d = 1024) 39.4 /
 // 40.1 / 42.6, 24 x 152064 -- / 180.8 / 182.0, 80 x 32000 66.7 / 66.2 / 68.1, 6 x 152064 (d = 1024) -- / 69.2 / 70.7.
 // Above 4096 units of 512 ids a unit is as many blocks of 512 as leave no more than that, and a sequence's masses 33 KB of LDS at
@@ -208,8 +209,10 @@ hipError_t launch_draw(const StepArgs& a, const int32_t* row_off_host, const Dra
   for (int b = 0; b <= kFusedMaxB; ++b) ro.v[b] = row_off_host[b <= a.B ? b : a.B];
   if (a.hosted == kHostsNothing) {
     if (a.B > kFusedMaxB) {
-      if constexpr (kPer == 8) hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, true, true, false, kBlocks>), grid, block, lds, stream, a, ro, s);
-      else return hipErrorInvalidValue;
+      if constexpr (kPer == 8)
+        hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, true, true, false, kBlocks>), grid, block, lds, stream, a, ro, s);
+      else
+        return hipErrorInvalidValue;
     } else if (a.nchd > kChunksAtOnce) {
       hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, true, false, kBlocks>), grid, block, lds, stream, a, ro, s);
     } else {
@@ -219,8 +222,10 @@ hipError_t launch_draw(const StepArgs& a, const int32_t* row_off_host, const Dra
   }
   if (a.B > kFusedMaxB) return hipErrorInvalidValue;
   if (!test_has_its_launch(a.hosted, a.fused.nfine, a.M, s)) {
-    if (a.hosted == kHostsAll) hipLaunchKernelGGL((accept_draw_kernel<kPer, true, false, false, false, true, kBlocks>), grid, block, lds, stream, a, ro, s);
-    else hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, true, true, kBlocks>), grid, block, lds, stream, a, ro, s);
+    if (a.hosted == kHostsAll)
+      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, false, false, false, true, kBlocks>), grid, block, lds, stream, a, ro, s);
+    else
+      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, true, true, kBlocks>), grid, block, lds, stream, a, ro, s);
     return hipGetLastError();
   }
   if (a.hosted == kHostsAll) hipLaunchKernelGGL((accept_draw_kernel<8, false, false>), dim3(1, a.B), block, 0, stream, a, ro, s);
