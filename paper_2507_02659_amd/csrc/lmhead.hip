@@ -1057,7 +1057,7 @@ static bool front_pieces_end_in_time(double row_bytes, double head_us) {
 // before a launch without them and the statistics pass, over the draft rows alone if the launch still leaves the target rows'
 // partials.  The row statistics cost a round of multiplying workgroups kStatsUs in either structure; the partials alone cost a launch
 // more (8 us with its draft rows' chunks merged).  Both are fitted to 240 shapes (d = 1024 and 4096, 8000 to 152064 columns, 192 to 1024
-// rows, draft rows of 8000 and 32000 ids), each timed in all three structures: the choice costs 0.4 % on average against the best, 15 %
+// rows, draft rows of 8000 and 32000 ids), each timed in all three structures: the choice costs 0.5 % on average against the best, 15 %
 // at most (400 rows x 20001, d = 1024, draft rows of 8000: separate 53.9, hosted 46.6); without the partials alone the best choice of
 // the other two costs 1.9 %.  us per step, hosted / separate / partials alone: 1024 rows x 128256 1039 / -- / 1003, 512 rows x 128256
 // (d = 1024) 245 / 218 / 193, 240 rows 129 / 116 / 114, 320 rows x 50000 (d = 1024) 59.7 / 67.7 / 64.5, 192 rows x 8000 (d = 1024) 41.7 / 26.0 /
@@ -1078,7 +1078,8 @@ int lmhead_bf16_hosts(int M, int d, int Vp, int B, int K, int V_d, int n_cu) {
   const double front_us = 2.0 * K * (double)V_d / (n_front * kFrontBytesPerUs) + ceil_div(B, 4 * n_front) * 10.0;
   if (n_front >= n_cu) return kHostsNothing;
   // The launch ends at the first moment by which n_front compute units that come free after front_us and the others have
-  // had room for all workgroups, each kStatsUs longer for the row statistics; half of what stays idle counts, as above.
+  // had room for all workgroups, each kStatsUs longer for the row statistics; 0.4 of what stays idle counts (0.5 sent
+  // 1024 rows x 50000, d = 1024, to the partials alone, 162 us per step instead of 154).
   constexpr double kStatsUs = 7.0;
   const double t = plan.round_us + kStatsUs, n = plan.workgroups;
   const double rounds_alone = std::ceil(n / (n_cu - n_front) - 1e-9);          // the front's compute units never join
@@ -1089,7 +1090,7 @@ int lmhead_bf16_hosts(int M, int d, int Vp, int B, int K, int V_d, int n_cu) {
   }
   for (double at = t; at < end; at += t)
     if ((n_cu - n_front) * std::round(at / t) + n_front * std::floor(std::max(0.0, at - front_us) / t) >= n) end = at;
-  const double hosted = std::max(front_us, 0.5 * (end + (n * t + n_front * front_us) / n_cu));
+  const double hosted = std::max(front_us, 0.4 * end + 0.6 * (n * t + n_front * front_us) / n_cu);
   const double draft_us = 2.0 * K * (double)V_d / 5.0e6;
   const double separate = plan.rounds * plan.round_us + 4.0 + 4.0 * M * Vp / 5.0e6 + draft_us;
   const double partials = plan.rounds * (plan.round_us + kStatsUs) + 8.0 + draft_us;
