@@ -193,7 +193,7 @@ static HeadPlan head_plan(const ot_ctx* ctx, int B, int M) {
   else if (bf16) p.hosted = lmhead_bf16_hosts(M, ctx->d, ctx->Vp, B, K, ctx->V_d, n_cu);
   else p.hosted = lmhead_f32_hosts_draft_side(M, ctx->d, ctx->V_t, B, K, ctx->V_d, n_cu) ? kHostsAll : kHostsNothing;
   if (p.hosted == kHostsNothing) return p;
-  p.workers = bf16 ? lmhead_bf16_draft_workers(M, ctx->d, ctx->Vp, B, K, n_cu) : lmhead_f32_draft_workers(M, ctx->V_t, B, K, n_cu);
+  p.workers = bf16 ? lmhead_bf16_draft_workers(M, ctx->d, ctx->Vp, B, K, n_cu) : lmhead_f32_draft_workers(M, ctx->d, ctx->V_t, B, K, n_cu);
   p.nfine = bf16 ? lmhead_bf16_fused_partials(M, ctx->d, ctx->Vp, n_cu) : ceil_div(ctx->V_t, 64);
   return p;
 }
@@ -273,7 +273,7 @@ static int step_impl(ot_ctx* ctx, ot_ngram_cache* cache, const ot_step_in* in, c
                              ctx->V_t, a.ldz, ctx->zeros, &a.fused, draft_side, ctx->n_cu, st);
     else
       e = launch_lmhead_f32(static_cast<const float*>(in->hidden), M, ctx->d, ctx->Wf, ctx->Z, ctx->V_t, a.ldz, &a.fused,
-                            draft_side, st);
+                            draft_side, ctx->n_cu, st);
   }
   OT_MARK(1);
   // What the LM head did not take gets a launch of its own: the statistics of both sides' rows or, where it left the partials, of

@@ -739,7 +739,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void l
 }
 
 // ---------------------------------------------------------------------------------------------------------------
-// fp32 head, on v_mfma_f32_16x16x4_f32 (binary32 products and sums, twice the rate of the vector units' fused
+// fp32 head of up to 16 rows or a short hidden dimension, on v_mfma_f32_16x16x4_f32 (binary32 products and sums, twice the rate of the vector units' fused
 // multiply-adds).  Bound by the matrix cores from about 48 rows on (147 TFLOP/s is what a large fp32 product reaches on
 // this card), by the weight stream below.  W is re-tiled once at init so that a wavefront's loads are contiguous:
 // unit(wt, kb, s, lane), one float4, holds W[16*kb + 4*(lane/16) + s][64*wt + 4*(lane%16) + 0..3], zero outside [d, V_t].
@@ -780,7 +780,7 @@ __global__ __launch_bounds__(WAVES * 64) void lmhead_f32_kernel(const float* __r
   __shared__ f32x4 sRed[WAVES][MT * 16 * kRow];
   __shared__ float sScale[kStats ? MT * 16 : 1];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  static_assert(sizeof(sRed) >= kFrontLdsBytes, "scratch of the draft side");
+  static_assert(sizeof(sRed) >= kFrontLdsBytes && sizeof(sRed) >= WAVES * sizeof(DraftLds), "scratch of the draft side");
   static_assert(WAVES * 64 >= kFusedMaxB, "a thread per sequence");
   const int wg = (int)blockIdx.x - (kStats ? n_front : 0);   // n_front is a multiple of 8: the XCDs below are those of the block ids
   if (kStats && wg < 0) {
@@ -876,6 +876,227 @@ __global__ __launch_bounds__(WAVES * 64) void lmhead_f32_kernel(const float* __r
   }
 }
 
+// ---------------------------------------------------------------------------------------------------------------
+// fp32 head of more than 16 rows and a longer hidden dimension (f32_plan), on the bf16 matrix instruction, which is sixteen times as
+// fast as the binary32 one.  A binary32 value is the sum of three bf16 values, its leading eight significant bits, the next eight
+// and the rest, exactly; of the nine products of two such triples the six largest are formed (each exact, added up in binary32),
+// what is left out is below 2^-23 of a product.  Fewer roundings than with the binary32 instruction, one per 32 products instead of
+// one per 4: error against 64 bits at d = 1024 2.4e-7 of the logits' norm, 2.9e-7 there.
+// Same packed weights and the same split over four wavefronts as above; a step is two blocks of 16 hidden indices.  Bound by the
+// loads: of 36 us at 64 rows x 32000 columns (d = 1024; 45.8 with the binary32 instruction) 25 are left without the hidden rows' traffic (one L2
+// read of all rows per 64 columns), the splits and half of the products, 30 with the traffic alone.  Tried instead: the hidden rows'
+// thirds shared through LDS, wavefronts by columns and halves of the hidden dimension: 43 us, a barrier per 64 hidden indices and
+// longer chains of sums (3.4e-7).
+struct Thirds { bf16x8 part[3]; };
+__device__ __forceinline__ Thirds split_thirds(const float (&x)[8], float& largest) {
+  uint32_t w[3][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) largest = fmaxf(fmaxf(__builtin_fabsf(x[2 * i]), __builtin_fabsf(x[2 * i + 1])), largest);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    uint32_t a = __float_as_uint(x[2 * i]), b = __float_as_uint(x[2 * i + 1]);
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      w[t][i] = __builtin_amdgcn_perm(b, a, 0x07060302u);          // the upper halves of both
+      if (t < 2) {
+        a = __float_as_uint(__uint_as_float(a) - __uint_as_float(a & 0xFFFF0000u));
+        b = __float_as_uint(__uint_as_float(b) - __uint_as_float(b & 0xFFFF0000u));
+      }
+    }
+  }
+  Thirds r;
+#pragma unroll
+  for (int t = 0; t < 3; ++t) r.part[t] = __builtin_bit_cast(bf16x8, make_uint4(w[t][0], w[t][1], w[t][2], w[t][3]));
+  return r;
+}
+
+template <int MT, bool kStats>
+__global__ __launch_bounds__(256, MT == 2 ? 3 : 2) void lmhead_f32_thirds_kernel(const float* __restrict__ H, int M, int d,
+                                                                   const f32x4* __restrict__ Wp, int nkb, int n_wtiles,
+                                                                   float* __restrict__ Z, int V_t, int64_t ldz, int m_blocks,
+                                                                   FusedStats fs, int n_front, StepArgs ds) {
+  constexpr int kWaves = 4;
+  constexpr int kRow = 17;                              // float4 per padded row of the reduction scratch
+  __shared__ f32x4 sRed[kWaves][MT * 16 * kRow];
+  __shared__ float sScale[kStats ? MT * 16 : 1];
+  __shared__ int sBad[kWaves];
+  const int tid = threadIdx.x, wave = uniform(tid >> 6), lane = tid & 63;
+  static_assert(sizeof(sRed) >= kFrontLdsBytes && sizeof(sRed) >= kWaves * sizeof(DraftLds), "scratch of the draft side");
+  static_assert(kWaves * 64 >= kFusedMaxB, "a thread per sequence");
+  const int wg = (int)blockIdx.x - (kStats ? n_front : 0);   // n_front is a multiple of 8: the XCDs below are those of the block ids
+  if (kStats && wg < 0) {
+    if (ds.plan.base == kDraftPieces) front_draft_side<float, kWaves>(ds, blockIdx.x, tid, sRed);
+    else front_draft_rows<float, kWaves, MT == 2 ? 8 : 16>(ds, blockIdx.x, n_front, tid, sRed);
+    return;
+  }
+  const int slot = wg >> 3;
+  const int wt = (slot / m_blocks) * 8 + (wg & 7), row0 = (slot % m_blocks) * (MT * 16);
+  if (wt >= n_wtiles) return;                           // padding of the id space
+  BlockScales scales;
+  if constexpr (kStats) scales.load(fs, tid);
+  // steps of two 16-deep blocks without a ragged end, split over the wavefronts; the last one takes what is left over
+  const int pairs = d / 32;
+  const int p0 = pairs * wave / kWaves, p1 = pairs * (wave + 1) / kWaves;
+  const f32x4* wp = Wp + (int64_t)wt * packed_f32_tile_units(nkb) + lane;
+  const int g = lane >> 4;
+  const float* hp[MT];                                  // rows past M are never stored: any valid row will do
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) hp[mt] = H + (int64_t)min(row0 + mt * 16 + (lane & 15), M - 1) * d + 4 * g;
+
+  f32x4 acc[MT][4];
+  f32x4 wq[2][8], hq[MT][2];
+  float largest = 0.f;                                  // absolute value of an operand
+  auto clear = [&]() {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int nw = 0; nw < 4; ++nw) acc[mt][nw] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  auto fetch_w = [&](int st, int p) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const f32x4* src = wp + ((int64_t)p * 8 + i) * 64;
+      wq[st][i] = m_blocks == 1 ? __builtin_nontemporal_load(src) : *src;   // read once by the whole launch: nontemporal
+    }
+  };
+  auto fetch_h = [&](int p) {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) hq[mt][j] = *reinterpret_cast<const f32x4_u*>(hp[mt] + p * 32 + j * 16);
+  };
+  // What is left of the hidden dimension behind the whole steps (fewer than 32): reads as zero past its end.
+  auto fetch_rest = [&]() {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) wq[0][i] = wp[(int64_t)min(pairs * 8 + i, nkb * 4 - 1) * 64];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int k = pairs * 32 + j * 16 + 4 * g + e;
+          const float x = hp[mt][min(k, d - 1) - 4 * g];
+          hq[mt][j][e] = k < d ? x : 0.f;
+        }
+  };
+  // One step out of weight slot st, which is refilled for step next_w once its values are split, the hidden values for next_h.
+  auto step = [&](auto refill, int st, int next_w, int next_h) {
+    constexpr bool kRefill = decltype(refill)::value;
+    Thirds h[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      float x[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) x[i] = hq[mt][i / 4][i % 4];
+      h[mt] = split_thirds(x, largest);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (kRefill) fetch_h(next_h);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int nw = 0; nw < 4; ++nw) {
+      float x[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) x[i] = wq[st][i][nw];
+      const Thirds w = split_thirds(x, largest);
+      constexpr int kW[6] = {2, 0, 1, 1, 0, 0}, kH[6] = {0, 2, 1, 0, 1, 0};   // the small products first
+#pragma unroll
+      for (int i = 0; i < 6; ++i)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+          acc[mt][nw] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.part[kW[i]], h[mt].part[kH[i]], acc[mt][nw], 0, 0, 0);
+    }
+    if (kRefill) fetch_w(st, next_w);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  clear();
+  if (p0 < p1) {
+    // a refill past this wavefront's last step asks for that again: no branch inside
+    fetch_w(0, p0);
+    fetch_h(p0);
+    fetch_w(1, min(p0 + 1, p1 - 1));
+    for (int p = p0;; p += 2) {
+      step(std::true_type(), 0, min(p + 2, p1 - 1), min(p + 1, p1 - 1));
+      if (p + 1 >= p1) break;
+      step(std::true_type(), 1, min(p + 3, p1 - 1), min(p + 2, p1 - 1));
+      if (p + 2 >= p1) break;
+    }
+  }
+  const bool rest = wave == kWaves - 1 && pairs * 2 < nkb;
+  if (rest) {
+    fetch_rest();
+    step(std::false_type(), 0, 0, 0);
+  }
+  // An infinite or NaN operand does not survive the split (inf - inf), and 0 times an infinite part is no longer the product.  A
+  // denormal part counts as 0 in the multiplication: below 2^-126 of an operand, less than 2^-66 of a product with one below 2^60.
+  // A workgroup that ends up with a logit that is not finite, or met an operand of 2^60 or more, forms its tile again on the binary32
+  // matrix instruction.
+  auto sound = [&]() {
+    bool ok = largest < 0x1p60f;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int nw = 0; nw < 4; ++nw)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ok = ok && __builtin_fabsf(acc[mt][nw][e]) < INFINITY;
+    return __ballot(!ok) == 0ull;
+  };
+  // acc[mt][nw][e] = partial Z[row0 + 16*mt + lane%16][64*wt + 4*(4*(lane/16) + e) + nw]
+  auto park = [&]() {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        sRed[wave][(mt * 16 + (lane & 15)) * kRow + 4 * g + e] = f32x4{acc[mt][0][e], acc[mt][1][e], acc[mt][2][e], acc[mt][3][e]};
+  };
+  park();
+  const bool ok = sound();
+  if (lane == 0) sBad[wave] = !ok;
+  if constexpr (kStats) scales.fill(sScale, row0, MT * 16);
+  __syncthreads();
+  if (sBad[0] | sBad[1] | sBad[2] | sBad[3]) {          // workgroup-uniform
+    clear();
+    auto multiply_f32 = [&]() {
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+          for (int nw = 0; nw < 4; ++nw)
+            acc[mt][nw] = __builtin_amdgcn_mfma_f32_16x16x4f32(wq[0][i][nw], hq[mt][i / 4][i % 4], acc[mt][nw], 0, 0, 0);
+    };
+    for (int p = p0; p < p1; ++p) {
+      fetch_w(0, p);
+      fetch_h(p);
+      multiply_f32();
+    }
+    if (rest) {
+      fetch_rest();
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (pairs * 8 + i >= nkb * 4) wq[0][i] = f32x4{0.f, 0.f, 0.f, 0.f};   // no such block: its stand-in may be infinite
+      multiply_f32();
+    }
+    __syncthreads();
+    park();
+    __syncthreads();
+  }
+  for (int i = tid; i < MT * 256; i += kWaves * 64) {
+    const int r = i >> 4, c = i & 15;
+    f32x4 sum = sRed[0][r * kRow + c];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) sum += sRed[w][r * kRow + c];
+    const int m = row0 + r, n = wt * 64 + 4 * c;
+    if (m < M) store_logits(Z + (int64_t)m * ldz + n, n, V_t, sum);
+    if constexpr (kStats) {
+      const float z[4] = {sum[0], sum[1], sum[2], sum[3]};
+      const Partial p = partial_of_64(z, n, V_t, sScale[m < M ? r : 0]);
+      if (m < M && c == 0) fs.part[(int64_t)m * fs.nfine + wt] = p;
+    }
+  }
+}
+
 // Front workgroups of the kernels that give each draft-side job one: a sequence's lookups, a piece of a draft row.
 int front_jobs(const StepArgs& a) { return a.B + a.plan.jobs(a.K); }
 bool front_plan_fits(const StepArgs& a) {
@@ -884,17 +1105,68 @@ bool front_plan_fits(const StepArgs& a) {
          (int64_t)a.plan.more * (a.plan.base + 1) + (int64_t)(a.K - a.plan.more) * a.plan.base == a.plan.workers;
 }
 
+// How more than 16 rows of an fp32 head run: row tiles per block, and the kernel.
+// Below 384 hidden indices a wavefront of the thirds kernel has less than three steps, and the other one is faster or even (24 to 64 rows
+// x 32000 columns, d = 256: 2 to 6 %, d = 64: 4 to 17 %); from there on the thirds are, by 9 % over 84 shapes at d = 384, 15 % over 378
+// at d = 512 and 1024, 34 % at 256 rows x 32000 columns.  The other one takes two row tiles, or three where that pads less (48 rows,
+// 144 rows); smaller blocks read the weights again out of L2 but put more wavefronts on a compute unit, which cover its loads.  The
+// thirds kernel takes the block whose workgroups cost the fullest compute unit least, 2 + 2.5 per row tile each (us at d = 1024, measured
+// at 24 to 256 rows x 1000 to 100000 columns: a step takes 19 us more than their sum): small heads fill the chip with small blocks, large
+// ones split the weights less often.  64 rows x 8000 / 32000 columns, us per step with blocks of 2 / 3 / 4 tiles 25.8 / 29.0 / 31.1 and
+// 47.3 / 56.8 / 46.1, 80 rows x 32000 59.3 / 56.9 / 67.3.
+struct F32Plan { int tiles; bool thirds; int workgroups, at_once; };   // workgroups that multiply; that the chip holds at once
+F32Plan f32_plan(int M, int d, int V_t, int n_cu) {
+  const int tiles = ceil_div(M, 16), n_wtiles = ceil_div(V_t, 64);
+  F32Plan p{1, false, 0, 2 * n_cu};
+  if (tiles > 1 && d < 384) {
+    p.tiles = ceil_div(tiles, 3) * 3 < ceil_div(tiles, 2) * 2 ? 3 : 2;
+    p.at_once = n_cu * (p.tiles == 2 ? 4 : 3);
+  } else if (tiles > 1) {
+    p.thirds = true;
+    double least = INFINITY;
+    for (int mt = 2; mt <= 4; ++mt) {
+      const double cost = ceil_div((int64_t)n_wtiles * ceil_div(tiles, mt), std::max(n_cu, 1)) * (2.0 + 2.5 * mt);
+      if (cost < least) { least = cost; p.tiles = mt; }
+    }
+    p.at_once = n_cu * (p.tiles == 2 ? 3 : 2);
+  }
+  p.workgroups = ceil_div(n_wtiles, 8) * 8 * ceil_div(tiles, p.tiles);
+  return p;
+}
+
 // Front workgroups of an fp32 launch that takes the draft side by whole rows: few, because its multiplying workgroups fill the
-// chip (64 rows, d = 1024, V_t = 32000: 1000 workgroups, four to a compute unit).  There a workgroup for each of 16 sequences'
-// lookups and 48 rows' pieces put some of those back by a round: 50.8 us instead of 46.2.
-int f32_row_front(int B, int K) { return std::min(32, ceil_div(std::max(B, ceil_div(K, 4)), 8) * 8); }
+// chip, and no more than its last round has room for.  (64 rows, d = 1024, V_t = 32000: 1000 workgroups, four to a compute unit; a
+// workgroup for each of 16 sequences' lookups and 48 rows' pieces put some of those back by a round: 50.8 us instead of 46.2.)
+int f32_row_front(const F32Plan& p, int B, int K) {
+  const int want = std::min(32, ceil_div(std::max(B, ceil_div(K, 4)), 8) * 8);
+  if (!p.thirds) return want;
+  const int room = (ceil_div(p.workgroups, std::max(p.at_once, 1)) * p.at_once - p.workgroups) / 8 * 8;
+  return room >= 8 ? std::min(want, room) : want;
+}
+
+template <int MT>
+hipError_t launch_f32_thirds(const float* H, int M, int d, const float* Wp, float* Z, int V_t, int64_t ldz, const FusedStats& fs,
+                             const StepArgs* draft_side, const F32Plan& plan, hipStream_t stream) {
+  const int nkb = ceil_div(d, 16), n_wtiles = ceil_div(V_t, 64), m_blocks = ceil_div(M, MT * 16);
+  const int n_front = !draft_side ? 0 : draft_side->plan.base == kDraftPieces ? ceil_div(front_jobs(*draft_side), 8) * 8
+                                                                              : f32_row_front(plan, draft_side->B, draft_side->K);
+  const dim3 grid((unsigned)(n_front + ceil_div(n_wtiles, 8) * 8 * m_blocks)), block(256);
+  const f32x4* wp = reinterpret_cast<const f32x4*>(Wp);
+  if (fs.part)
+    hipLaunchKernelGGL((lmhead_f32_thirds_kernel<MT, true>), grid, block, 0, stream, H, M, d, wp, nkb, n_wtiles, Z, V_t, ldz,
+                       m_blocks, fs, n_front, draft_side ? *draft_side : StepArgs{});
+  else
+    hipLaunchKernelGGL((lmhead_f32_thirds_kernel<MT, false>), grid, block, 0, stream, H, M, d, wp, nkb, n_wtiles, Z, V_t, ldz,
+                       m_blocks, fs, 0, StepArgs{});
+  return hipGetLastError();
+}
 
 template <int MT, int WAVES, int PF>
 hipError_t launch_f32(const float* H, int M, int d, const float* Wp, float* Z, int V_t, int64_t ldz, const FusedStats& fs,
-                      const StepArgs* draft_side, hipStream_t stream) {
+                      const StepArgs* draft_side, const F32Plan& plan, hipStream_t stream) {
   const int nkb = ceil_div(d, 16), n_wtiles = ceil_div(V_t, 64), m_blocks = ceil_div(M, MT * 16);
   const int n_front = !draft_side ? 0 : draft_side->plan.base == kDraftPieces ? ceil_div(front_jobs(*draft_side), 8) * 8
-                                                                              : f32_row_front(draft_side->B, draft_side->K);
+                                                                              : f32_row_front(plan, draft_side->B, draft_side->K);
   const dim3 grid((unsigned)(n_front + ceil_div(n_wtiles, 8) * 8 * m_blocks)), block(WAVES * 64);
   const f32x4* wp = reinterpret_cast<const f32x4*>(Wp);
   if (fs.part)
@@ -1164,16 +1436,8 @@ hipError_t launch_pack_w_f32(const float* W, int d, int V_t, float* Wp, hipStrea
   return hipGetLastError();
 }
 
-// Row tiles per block: two, or three where that pads less (48 rows, 144 rows).  Smaller blocks read the weights again out
-// of L2 but put more wavefronts on a compute unit, and this product needs them to cover its loads: 64 rows as two blocks
-// of two tiles 47 us, as one of four 50 us (d = 1024, V_t = 32000).  A single row tile splits the hidden dimension over
-// eight wavefronts (more bytes in flight, small heads fill more of the chip), the others over four (eight: 51 us).
-static int f32_block_tiles(int M) {
-  const int tiles = ceil_div(M, 16);
-  return tiles == 1 ? 1 : ceil_div(tiles, 3) * 3 < ceil_div(tiles, 2) * 2 ? 3 : 2;
-}
 hipError_t launch_lmhead_f32(const float* H, int M, int d, const float* Wp, float* Z, int V_t, int64_t ldz,
-                             const FusedStats* fused, const StepArgs* draft_side, hipStream_t stream) {
+                             const FusedStats* fused, const StepArgs* draft_side, int n_cu, hipStream_t stream) {
   if (M == 0) return hipSuccess;
   FusedStats fs{};
   if (fused && fused->part) {
@@ -1182,18 +1446,24 @@ hipError_t launch_lmhead_f32(const float* H, int M, int d, const float* Wp, floa
   }
   if (!fs.part) draft_side = nullptr;
   if (draft_side && !front_plan_fits(*draft_side)) return hipErrorInvalidValue;
-  const int tiles = f32_block_tiles(M);
-  if (tiles == 1) return launch_f32<1, 8, 4>(H, M, d, Wp, Z, V_t, ldz, fs, draft_side, stream);
-  if (tiles == 3) return launch_f32<3, 4, 2>(H, M, d, Wp, Z, V_t, ldz, fs, draft_side, stream);
-  return launch_f32<2, 4, 2>(H, M, d, Wp, Z, V_t, ldz, fs, draft_side, stream);
+  const F32Plan plan = f32_plan(M, d, V_t, n_cu);
+  if (plan.thirds) {
+    if (plan.tiles == 4) return launch_f32_thirds<4>(H, M, d, Wp, Z, V_t, ldz, fs, draft_side, plan, stream);
+    if (plan.tiles == 3) return launch_f32_thirds<3>(H, M, d, Wp, Z, V_t, ldz, fs, draft_side, plan, stream);
+    return launch_f32_thirds<2>(H, M, d, Wp, Z, V_t, ldz, fs, draft_side, plan, stream);
+  }
+  if (plan.tiles == 1) return launch_f32<1, 8, 4>(H, M, d, Wp, Z, V_t, ldz, fs, draft_side, plan, stream);
+  if (plan.tiles == 3) return launch_f32<3, 4, 2>(H, M, d, Wp, Z, V_t, ldz, fs, draft_side, plan, stream);
+  return launch_f32<2, 4, 2>(H, M, d, Wp, Z, V_t, ldz, fs, draft_side, plan, stream);
 }
 
-static int f32_multiplying_workgroups(int M, int V_t) {
-  return ceil_div(ceil_div(V_t, 64), 8) * 8 * ceil_div(M, 16 * f32_block_tiles(M));
-}
-// A launch that leaves room on the chip gives every piece of a draft row a workgroup of its own, a larger one takes whole rows.
-int lmhead_f32_draft_workers(int M, int V_t, int B, int K, int n_cu) {
-  return f32_multiplying_workgroups(M, V_t) + B + kDraftPieces * K <= 2 * n_cu ? kDraftPieces * K : K;
+// A launch that leaves room on the chip gives every piece of a draft row a workgroup of its own, a larger one takes whole rows, or
+// halves where that leaves the busiest wavefront less (48 rows by 32 wavefronts).
+int lmhead_f32_draft_workers(int M, int d, int V_t, int B, int K, int n_cu) {
+  const F32Plan plan = f32_plan(M, d, V_t, n_cu);
+  if (plan.workgroups + B + kDraftPieces * K <= 2 * n_cu) return kDraftPieces * K;
+  const int wavefronts = 4 * f32_row_front(plan, B, K);
+  return plan.thirds && ceil_div(2 * K, wavefronts) < 2 * ceil_div(K, wavefronts) ? 2 * K : K;
 }
 // Whether the fp32 launch should leave partials and take the draft side.  That spares the statistics launch (6 us and a pass over both
 // sides' logits).  It costs the multiplying workgroups their epilogue and the launch behind it the merge of a partial per row and 64
@@ -1201,20 +1471,22 @@ int lmhead_f32_draft_workers(int M, int V_t, int B, int K, int n_cu) {
 // lasts as long as they do: one draws 3.5 KB per us, 1.6 with more than two rows in turn, and a fifth of that while the weights stream
 // (1020 rows x 65536, d = 64, seven rows of 8000 ids each, 282 us hosted, 211 separate).  A front that pushes
 // multiplying workgroups into one round more costs 0.15 of a round.
-// Measured at 1296 shapes (d = 64 to 1024, 1024 to 152064 columns, 2 to 1530 rows, draft rows of 1000 to 32000 ids): the choice costs
+// Measured at 1296 shapes (d = 64 to 1024, 1024 to 152064 columns, 2 to 1530 rows, draft rows of 1000 to 32000 ids), before the thirds
+// kernel and with the front's loads asked for one after the other: the choice costs
 // 0.2 % on average against the better one, 10 % at most (16 rows x 100000, d = 256, draft rows of 8000 ids, 36.0 / 32.7).  With a draft
-// row priced at 3 KB per us next to any head it was 3 % and 63 %.  us per step, hosted / separate: 5 rows x 100000 (d = 1024), draft
+// row priced at 3 KB per us next to any head it was 3 % and 63 %; with the thirds kernel, at 378 shapes, 0.6 % and 12 %.  us per step, hosted / separate: 5 rows x 100000 (d = 1024), draft
 // rows of 32000 ids 123 / 91, of 1000 92 / 92; 16 rows x 152064 (2376 partials a row) 138 / 137, x 32000 32.3 / 36.0; 64 rows x 32000
 // with draft rows of 8000 54.9 / 58.3.
 bool lmhead_f32_hosts_draft_side(int M, int d, int V_t, int B, int K, int V_d, int n_cu) {
   if (B < 1 || B > kFusedMaxB || K < 1) return false;
   const double product_us = 2.0 * M * d * (double)V_t / 1.0e8, head_us = std::max(4.0 * d * (double)V_t / 6.0e6, product_us);
-  if (lmhead_f32_draft_workers(M, V_t, B, K, n_cu) > K) return front_pieces_end_in_time(4.0 * V_d, head_us);
-  const int front = f32_row_front(B, K), block_tiles = f32_block_tiles(M);
-  const int rows_each = ceil_div(K, 4 * front);
-  const double front_us = ceil_div(B, front) * 1.0 + rows_each * (4.0 * V_d / (rows_each <= 2 ? 3.5e3 : 1.6e3)) + 0.8 * head_us;
-  const int at_once = n_cu * (block_tiles == 1 ? 2 : block_tiles == 2 ? 4 : 3);      // workgroups that fit the chip
-  const int multiplying = f32_multiplying_workgroups(M, V_t), rounds = ceil_div(multiplying, at_once);
+  const int workers = lmhead_f32_draft_workers(M, d, V_t, B, K, n_cu);
+  if (workers == kDraftPieces * K) return front_pieces_end_in_time(4.0 * V_d, head_us);
+  const F32Plan plan = f32_plan(M, d, V_t, n_cu);
+  const int front = f32_row_front(plan, B, K);
+  const double rows_each = ceil_div(workers, 4 * front) * (double)K / workers;
+  const double front_us = ceil_div(B, front) * 1.0 + rows_each * (4.0 * V_d / (rows_each <= (plan.thirds ? 3 : 2) ? 3.5e3 : 1.6e3)) + 0.8 * head_us;
+  const int at_once = plan.at_once, multiplying = plan.workgroups, rounds = ceil_div(multiplying, at_once);
   const double added_us = 0.0035 * ceil_div(V_t, 64) + 0.5e-6 * M * (double)V_t + 0.06 * product_us +
                           (ceil_div(multiplying + front, at_once) > rounds ? 0.15 * product_us / rounds : 0.0) +
                           (final_draw_launches(kHostsAll, ceil_div(V_t, 64), M, V_t, B, n_cu) > 1 ? 15.0 : 0.0);

@@ -195,8 +195,8 @@ hipError_t launch_lmhead_bf16(const uint16_t* H, int M, int d, const uint16_t* W
 hipError_t launch_pack_w_f32(const float* W, int d, int V_t, float* Wp, hipStream_t stream);
 // `fused` and `draft_side` as above (one partial per row and 64 columns; plan.workers = lmhead_f32_draft_workers(..))
 hipError_t launch_lmhead_f32(const float* H, int M, int d, const float* Wp, float* Z, int V_t, int64_t ldz,
-                             const FusedStats* fused, const StepArgs* draft_side, hipStream_t stream);
-int lmhead_f32_draft_workers(int M, int V_t, int B, int K, int n_cu);
+                             const FusedStats* fused, const StepArgs* draft_side, int n_cu, hipStream_t stream);
+int lmhead_f32_draft_workers(int M, int d, int V_t, int B, int K, int n_cu);
 bool lmhead_f32_hosts_draft_side(int M, int d, int V_t, int B, int K, int V_d, int n_cu);
 hipError_t launch_softmax_stats(const StepArgs& a, hipStream_t stream);
 // translation, acceptance test and the draw of the final tokens

@@ -124,6 +124,26 @@ __device__ __forceinline__ void lookup_sequence(const StepArgs& a, int b, int ti
   if (tid == 0) rec->bad = L->bad;
 }
 
+// The same by one wavefront on its own (L: its part of LDS).  Its LDS operations are done in order; the compiler is kept from moving
+// them across the hand-overs.
+__device__ __forceinline__ void wave_lookup_sequence(const StepArgs& a, int b, int lane, DraftLds* L) {
+  const int r0 = a.row_off[b], k = a.row_off[b + 1] - r0 - 1;
+  auto hand_over = []() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0), vmcnt and expcnt unconstrained
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("" ::: "memory");
+  };
+  draft_lds_reset(L, lane);
+  hand_over();
+  fetch_ids_and_probe(a, r0 - b, k, lane, 64, L);
+  hand_over();
+  ProbeRecord* rec = a.probe + b;
+  rec->hit[lane] = L->hit[lane]; rec->zq[lane] = L->zq[lane]; rec->dm[lane] = L->dm[lane];
+  if (lane == 0) rec->bad = L->bad;
+  hand_over();
+}
+
 // ---------------------------------------------------------------------------------------------- draft row statistics
 // 16-byte vectors of a logit row, kept as loaded until they are used (a bf16 vector unpacks to 8 floats).
 template <typename T> struct RowVec;
@@ -424,22 +444,59 @@ __device__ __forceinline__ void front_draft_side(const StepArgs& a, int job, int
                                           a.dpiece + (int64_t)q * kDraftPieces + i, &first);
 }
 
-// The same by few workgroups: front workgroup j of n takes the lookups of sequences j, j + n, .., then every wavefront of it whole
-// draft rows (a.plan with one piece per row).
-template <typename TD, int kWaves>
+// The same by few workgroups: front workgroup j of n takes the lookups of sequences, then every wavefront of it whole draft rows, or
+// halves (a.plan with one or two pieces per row).  Next to the other workgroups' streams a dependent load takes microseconds, so
+// that the chains of loads decide how long this lasts: a piece's first batch is asked for a piece ahead (the first one in front
+// of the lookups), and the sequences' row offsets and temperatures are held across the lanes (at most kFusedMaxB of them).
+template <typename TD, int kWaves, int kBatch = kPieceBatch>
 __device__ __forceinline__ void front_draft_rows(const StepArgs& a, int j, int n, int tid, void* lds) {
-  for (int b = j; b < a.B; b += n) {
-    lookup_sequence(a, b, tid, kWaves * 64, static_cast<DraftLds*>(lds));
-    __syncthreads();
-  }
+  const int lane = tid & 63, wave = uniform(tid >> 6), pieces = a.plan.base, jobs = a.K * pieces;
   const float* temps = a.draft_temperature ? a.draft_temperature : a.temperature;
-  const int lane = tid & 63;
-  for (int q = j * kWaves + uniform(tid >> 6); q < a.K; q += n * kWaves) {
-    const float Td = temps[find_sequence(a.row_off, a.B, q, 1, lane)];
-    DraftPiece r;
-    wave_row_stats<TD, kPieceBatch>(static_cast<const TD*>(a.draft_logits) + (int64_t)q * a.V_d, a.V_d, Td > 0.f ? kLog2eF / Td : kLog2eF,
-                                    lane, &r.mx, &r.arg, &r.sum);
-    if (lane == 0) a.dpiece[(int64_t)q * kDraftPieces] = r;
+  constexpr int kSeqRegs = (kFusedMaxB + 64) / 64;
+  int seq_before[kSeqRegs];
+  float seq_temp[kSeqRegs];
+#pragma unroll
+  for (int i = 0; i < kSeqRegs; ++i) {
+    const int b = min(64 * i + lane, a.B - 1);
+    seq_before[i] = a.row_off[b] - b;
+    seq_temp[i] = temps[b];
+  }
+  auto piece = [&](int job, int* e0, int* len) {
+    PiecePlan::span(a.V_d, pieces, job % pieces, e0, len);
+    return static_cast<const TD*>(a.draft_logits) + (int64_t)(job / pieces) * a.V_d + *e0;
+  };
+  int job = n * kWaves - 1 - (j * kWaves + wave);       // from the last wavefront on: the first ones have the lookups
+  int e0, len;
+  RowFirstBatch<TD, kBatch> first, next;
+  const TD* x = piece(min(job, jobs - 1), &e0, &len);
+  row_first_batch_load<TD, kBatch>(x, len, lane, first);
+  DraftLds* L = static_cast<DraftLds*>(lds);
+  if (a.B <= n) {
+    if (j < a.B) lookup_sequence(a, j, tid, kWaves * 64, L);
+  } else {                                              // several sequences each: side by side, a wavefront on each
+    for (int b = j * kWaves + wave; b < a.B; b += n * kWaves) wave_lookup_sequence(a, b, lane, L + wave);
+  }
+  for (; job < jobs; job += n * kWaves) {
+    int e0_next, len_next;                              // past the end: the last piece again, looked at by nobody
+    const TD* x_next = piece(min(job + n * kWaves, jobs - 1), &e0_next, &len_next);
+    row_first_batch_load<TD, kBatch>(x_next, len_next, lane, next);
+    const int q = job / pieces;
+    int owner = -1;
+    float Td = 1.f;
+#pragma unroll
+    for (int i = 0; i < kSeqRegs; ++i) owner += __popcll(__ballot(64 * i + lane < a.B && seq_before[i] <= q));
+#pragma unroll
+    for (int i = 0; i < kSeqRegs; ++i) {
+      const float t = __shfl(seq_temp[i], owner & 63);
+      if ((owner >> 6) == i) Td = t;
+    }
+    DraftPiece r; r.mx = -INFINITY; r.arg = 0x7FFFFFFF; r.sum = 0.0;
+    if (len > 0) {
+      wave_row_stats<TD, kBatch, true>(x, len, Td > 0.f ? kLog2eF / Td : kLog2eF, lane, &r.mx, &r.arg, &r.sum, &first);
+      if (r.mx != -INFINITY) r.arg += e0;
+    }
+    if (lane == 0) a.dpiece[(int64_t)q * kDraftPieces + job % pieces] = r;
+    x = x_next; e0 = e0_next; len = len_next; first = next;
   }
 }
 

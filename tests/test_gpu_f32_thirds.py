@@ -1,0 +1,93 @@
+"""The fp32 head on bf16 thirds (more than 16 rows, 384 hidden indices or more): edges of its blocks of 32, 48 and 64 rows, of its steps of
+32 hidden indices and their split over four wavefronts; operands that do not survive the split; the draft side by few front workgroups."""
+import numpy as np
+import pytest
+
+import test_gpu_hosted_small_heads as hosted
+from test_gpu_parity import _imports, _say
+from workloads import CaseSpec, make_case
+
+pytestmark = pytest.mark.gpu
+
+
+def _logits(case):
+    ov, ot, Verifier, parity = _imports()
+    v = Verifier.for_case(case)
+    try:
+        v.step(v.upload(case))
+        return v.workspace(case.M, case.K, with_logits=True)["logits"]
+    finally:
+        v.close()
+
+
+def _case(M, d, V_t):
+    ks = [min(50, M - r) - 1 for r in range(0, M, 50)]
+    return make_case(CaseSpec(name=f"thirds_{M}x{d}x{V_t}", dtype="f32", d=d, V_t=V_t, V_d=48, k=ks, temperature=[1.0] * len(ks), n_direct=32,
+                              data_seed=M * 7 + d, philox_seed=1))
+
+
+@pytest.mark.parametrize("M,d,V_t", [(17, 512, 65), (32, 513, 129), (48, 543, 16001), (49, 528, 200), (64, 560, 16385), (80, 1023, 8001),
+                                     (129, 545, 320), (260, 640, 2050), (33, 385, 3001)])
+def test_logits(M, d, V_t):
+    case = _case(M, d, V_t)
+    # values over many binades: every third of an operand takes part
+    rng = np.random.default_rng(M + d)
+    case.hidden *= np.exp2(rng.integers(-12, 13, size=case.hidden.shape)).astype(np.float32)
+    _say(f"thirds M={M} d={d} V_t={V_t}")
+    got = _logits(case)
+    H, W = case.hidden.astype(np.float64), case.W.astype(np.float64)
+    # d roundings of 2^-24 of partial sums that walk up to sqrt(sum (h w)^2), eight standard deviations; the products that are left
+    # out, three below 2^-24 of a product each, all of one sign
+    bound = 8 * 2.0 ** -24 * np.sqrt(d) * np.sqrt((H * H) @ (W * W)) + 3 * 2.0 ** -24 * (np.abs(H) @ np.abs(W))
+    assert np.all(np.abs(got - H @ W) <= bound + 1e-30)
+
+
+@pytest.mark.parametrize("d", [512, 530])
+def test_operands_that_are_not_finite(d):
+    M, V_t = 50, 400
+    case = _case(M, d, V_t)
+    case.W[:, :] = np.where(case.W == 0, 0.01, case.W)
+    case.hidden[:, :] = np.where(case.hidden == 0, 0.5, case.hidden)
+    case.hidden[3, 7] = np.inf                # a whole row of infinities
+    case.hidden[20, d - 1] = -np.inf
+    case.hidden[33, 100] = np.nan
+    case.W[5, 70] = np.inf                    # a column
+    case.W[6, 200] = np.nan
+    case.hidden[40, 9], case.W[9, 300] = 2e38, 1e30   # a product beyond binary32
+    _say(f"thirds, operands that are not finite, d={d}")
+    got = _logits(case)
+    with np.errstate(all="ignore"):
+        H, W = case.hidden.astype(np.float64), case.W.astype(np.float64)
+        want = np.empty((M, V_t))
+        for v in range(V_t):
+            p = H * W[:, v]
+            want[:, v] = np.where(np.abs(p) > 3.4028235e38, np.sign(p) * np.inf, p).sum(axis=1)
+    want[np.abs(want) > 3.4028235e38] *= np.inf
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    assert np.array_equal(np.isposinf(got), np.isposinf(want)) and np.array_equal(np.isneginf(got), np.isneginf(want))
+    ok = np.isfinite(want)
+    with np.errstate(all="ignore"):
+        bound = 8 * 2.0 ** -24 * np.sqrt(d) * np.sqrt((H * H) @ (W * W)) + 3 * 2.0 ** -24 * (np.abs(H) @ np.abs(W))
+    assert np.all(np.abs(got[ok] - want[ok]) <= bound[ok] + 1e-30)
+
+
+@pytest.mark.parametrize("up_hidden", [True, False])
+def test_operands_whose_lower_thirds_are_denormal(up_hidden):
+    case = _case(40, 600, 300)
+    up, down = (case.hidden, case.W) if up_hidden else (case.W, case.hidden)
+    up *= np.float32(2.0 ** 110)
+    down *= np.float32(2.0 ** -116)           # thirds of 2^-116 - 16 and less, down to denormals themselves
+    _say(f"thirds, denormal parts, up_hidden={up_hidden}")
+    got = _logits(case)
+    H, W = case.hidden.astype(np.float64), case.W.astype(np.float64)
+    bound = 8 * 2.0 ** -24 * np.sqrt(600) * np.sqrt((H * H) @ (W * W)) + 3 * 2.0 ** -24 * (np.abs(H) @ np.abs(W))
+    assert np.all(np.abs(got - H @ W) <= bound)
+
+
+@pytest.mark.parametrize("V_t,V_d,ks", [
+    (32001, 9001, [3] * 16),                  # blocks of 64 rows, halves of draft rows, two sequences a front workgroup
+    (32001, 40, [0, 1, 2] * 30),              # 90 sequences: lookups by wavefronts; halves shorter than a batch
+    (24577, 4099, [23]),                      # blocks of 32 rows, one sequence, whole rows of several batches
+])
+def test_draft_side_of_few_front_workgroups(V_t, V_d, ks):
+    hosted.test_partials_and_draft_side("f32", 400, V_t, V_d, ks)
