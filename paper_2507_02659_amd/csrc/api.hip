@@ -313,7 +313,7 @@ int ot_verify_structure(ot_ctx* ctx, int32_t B, int32_t M, int32_t* structure, i
                 ctx->max_k);
   const HeadPlan plan = head_plan(ctx, B, M);
   *structure = plan.hosted;
-  *n_launches = (plan.hosted == kHostsAll ? 1 : 2) + final_draw_launches(plan.hosted, plan.nfine, M, ctx->V_t, B, ctx->n_cu);
+  *n_launches = (plan.hosted == kHostsAll ? 1 : 2) + final_draw_launches(plan.hosted, plan.nfine, M, ctx->V_t, ctx->V_d, B, ctx->n_cu);
   return OT_OK;
 }
 

@@ -1489,7 +1489,7 @@ bool lmhead_f32_hosts_draft_side(int M, int d, int V_t, int B, int K, int V_d, i
   const int at_once = plan.at_once, multiplying = plan.workgroups, rounds = ceil_div(multiplying, at_once);
   const double added_us = 0.0035 * ceil_div(V_t, 64) + 0.5e-6 * M * (double)V_t + 0.06 * product_us +
                           (ceil_div(multiplying + front, at_once) > rounds ? 0.15 * product_us / rounds : 0.0) +
-                          (final_draw_launches(kHostsAll, ceil_div(V_t, 64), M, V_t, B, n_cu) > 1 ? 15.0 : 0.0);
+                          (final_draw_launches(kHostsAll, ceil_div(V_t, 64), M, V_t, V_d, B, n_cu) > 1 ? 15.0 : 0.0);
   const double statistics_us = 6.0 + (4.0 * M * (double)V_t + 4.0 * K * (double)V_d) / 5.0e6;
   return std::max(head_us + added_us, front_us) < head_us + statistics_us;
 }

@@ -202,6 +202,6 @@ hipError_t launch_softmax_stats(const StepArgs& a, hipStream_t stream);
 // translation, acceptance test and the draw of the final tokens
 hipError_t launch_final_draw(const StepArgs& a, const int32_t* row_off_host, int n_cu, hipStream_t stream);
 // launches that takes: 1, or 2 where the test has one of its own (nfine: partials per target row, if the LM head left them)
-int final_draw_launches(int hosted, int nfine, int M, int V_t, int B, int n_cu);
+int final_draw_launches(int hosted, int nfine, int M, int V_t, int V_d, int B, int n_cu);
 
 }  // namespace otv

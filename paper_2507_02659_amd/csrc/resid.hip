@@ -18,8 +18,8 @@
 namespace otv {
 namespace {
 
-template <int kPer, bool kBlocks>
-__global__ __launch_bounds__(kDrawThreads) void final_draw_kernel(StepArgs a, DrawSplit s) {
+template <int kPer, bool kBlocks, int kWaves>
+__global__ __launch_bounds__(kWaves * 64) void final_draw_kernel(StepArgs a, DrawSplit s) {
   const int b = blockIdx.y, grp = blockIdx.x, tid = threadIdx.x;
   const int wave = uniform(tid >> 6), lane = tid & 63;
   __shared__ DrawLds s_draw;
@@ -28,7 +28,7 @@ __global__ __launch_bounds__(kDrawThreads) void final_draw_kernel(StepArgs a, Dr
   load_tmap<kPer>(a.tmap, a.V_t, first + lane, 64, first + 64 * kPer <= a.V_t, dv);   // overlaps the next load
   const FinalInfo f = a.fin[b];
   if (f.mode == 0) return;                  // greedy or flagged sequence: nothing to draw
-  draw_final_token<kPer, kBlocks>(a, b, grp, s, f, dv, &s_draw);
+  draw_final_token<kPer, kBlocks, kWaves>(a, b, grp, s, f, dv, &s_draw);
 }
 
 // Row offsets of up to kFusedMaxB sequences as a kernel argument (the host has them): the workgroup knows its rows without
@@ -44,8 +44,9 @@ constexpr int64_t kRepeatedMergeBytes = 32 << 20;
 // cost a single sequence 0.7 of 13 us).
 // kWide: draft rows of more than kChunksAtOnce chunks (merge_draft_chunks).
 // kBlocks: units of several blocks (draw_split).
-template <int kPer, bool kDraw, bool kChunks, bool kMany = false, bool kWide = kMany, bool kFused = !kChunks, bool kBlocks = false>
-__global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, RowOffsets ro, DrawSplit split) {
+template <int kPer, bool kDraw, bool kChunks, bool kMany = false, bool kWide = kMany, bool kFused = !kChunks, bool kBlocks = false,
+          int kWaves = kDrawWaves>
+__global__ __launch_bounds__(kWaves * 64) void accept_draw_kernel(StepArgs a, RowOffsets ro, DrawSplit split) {
   const int b = blockIdx.y, grp = blockIdx.x, tid = threadIdx.x;
   const int wave = uniform(tid >> 6), lane = tid & 63;
   __shared__ DrawLds s_draw;
@@ -71,7 +72,7 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, R
   // and q' is formed once as a product instead of through the logarithms of its factors (from the launch's start to the
   // outcome 5.4 -> 2.7 us for one sequence of five drafted ids).
   const int q0 = r0 - b;
-  constexpr int kTestWave = kDrawWaves - 1;   // runs the walk and the test
+  constexpr int kTestWave = kWaves - 1;   // runs the walk and the test
   Window W;
   DraftLane D;
   float z_tok = 0.f;
@@ -110,7 +111,7 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, R
     D.qp = segment_q(D.q, W);
   }
   if (kMany && wave != kTestWave) invT = T > 0.f ? 1.0 / (double)T : 1.0;
-  for (int row = wave; row <= k; row += kDrawWaves) {
+  for (int row = wave; row <= k; row += kWaves) {
     if (!kFused)
       merge_chunk_row(a.tpart_max, a.tpart_sum, a.tpart_arg, a.ncht, r0 + row, T, invT, lane, s_pmx, s_pinv, s_parg, row, lead,
                       a.row_max, a.row_sum, a.row_arg, kMany);
@@ -146,16 +147,22 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, R
   if (!kDraw) return;
   const FinalInfo f = s_fin;
   if (f.mode == 0) return;
-  draw_final_token<kPer, kBlocks>(a, b, grp, split, f, dv, &s_draw);
+  draw_final_token<kPer, kBlocks, kWaves>(a, b, grp, split, f, dv, &s_draw);
 }
 
 // Units of the draw and their share per workgroup.  While no more than a workgroup per compute unit is needed for one turn each,
 // a wavefront takes as few ids as that allows: 128 (up to 512 units), else 256, else 512.  A
 // small batch is bound by the chain of instructions and round trips in one workgroup, which fewer ids per lane shorten.  With
-// more groups than compute units each workgroup takes as many turns as bring their number back to one per compute unit (80 to 95
-// registers: five or six wavefronts per SIMD, of which a workgroup takes four, so that a second does not fit): its start, its share
-// of the merge and its look at the masses are then paid once for several turns, and a turn's loads overlap the sums of the turn
-// before.
+// more groups than compute units a sequence has as many groups as leave no more than one workgroup per compute unit (up to 112
+// registers: a second of 16 wavefronts does not fit): its start, its share of the merge and its look at the masses are then paid once
+// for several turns, and a turn's loads overlap the sums of the turn before.  (As many turns as brought the number of groups back
+// to one per compute unit, rounded up, left 200 sequences x 128256 ids with two groups, 368 workgroups: 104 us per step from the logits
+// where one group each takes 65.)
+// With more sequences than compute units a sequence has one workgroup.  Two of 8 wavefronts on a compute unit then take 300
+// sequences at once, where 16 wavefronts take 256 and then 44: what the 8 in a workgroup need for all turns is hardly more than what 16
+// need, as the loads bound both.  Taken where half of LDS holds the draft row's exponentials: 300 / 512 / 700 sequences x 32003 ids, us per
+// step from the logits with 16 / 8 wavefronts 43.7 / 38.1, 55.3 / 48.7, 75.3 / 69.1; 300 x 128256 109 / 108; with rows that do not fit
+// (32000 fp32 ids) 51.7 / 88.7.
 // Measured, us per step, 128 / 256 / 512 ids a wavefront: 6 rows x 32000 ids 53.9 / 54.1 / 55.2, 12 rows x 64000 (d = 1024) 39.4 /
 // 40.1 / 42.6, 24 x 152064 -- / 180.8 / 182.0, 80 x 32000 66.7 / 66.2 / 68.1, 6 x 152064 (d = 1024) -- / 69.2 / 70.7.
 // Above 4096 units of 512 ids a unit is as many blocks of 512 as leave no more than that, and a sequence's masses 33 KB of LDS at
@@ -163,24 +170,31 @@ __global__ __launch_bounds__(kDrawThreads) void accept_draw_kernel(StepArgs a, R
 // registers, us per step from the logits: 16 sequences of 2.2 million ids 116 -> 103, of 9 million 401 -> 344, one of 4.2 million
 // 27.3 -> 28.1.
 constexpr int kMaxUnits = 4096;
-template <int kPer> DrawSplit draw_split(int V_t, int B, int n_cu) {
+template <int kPer> DrawSplit draw_split(int V_t, int B, int n_cu, int waves = kDrawWaves) {
   DrawSplit s;
   s.n_units = ceil_div(V_t, 64 * kPer);
   s.blocks = kPer == 8 ? ceil_div(s.n_units, kMaxUnits) : 1;
   s.n_units = ceil_div(s.n_units, s.blocks);
-  const int64_t groups = (int64_t)ceil_div(s.n_units, kDrawWaves) * B;
-  s.group_units = kDrawWaves * std::max(1, ceil_div(groups, std::max(n_cu, 1)));
+  // as many groups a sequence as bring the workgroups to what the chip holds at once
+  const int groups = std::max(1, std::max(n_cu, 1) * (kDrawWaves / waves) / std::max(B, 1));
+  s.group_units = ceil_div(ceil_div(s.n_units, groups), waves) * waves;
   s.row_at = 0;
+  s.exps = false;
   return s;
 }
 
-// ids per lane and their split
-struct DrawPlan { int per; DrawSplit split; };
-DrawPlan draw_plan(int V_t, int B, int n_cu) {
+size_t draw_lds_bytes(const DrawSplit& s) { return (size_t)(draw_lds_doubles(s.n_units) + 1) / 2 * 2 * sizeof(double); }
+
+// ids per lane, their split, wavefronts per workgroup
+struct DrawPlan { int per; DrawSplit split; int waves; };
+DrawPlan draw_plan(int V_t, int V_d, int B, int n_cu) {
   const DrawSplit two = draw_split<2>(V_t, B, n_cu), four = draw_split<4>(V_t, B, n_cu);
-  if (two.group_units == kDrawWaves && two.n_units <= 512 && B <= kFusedMaxB) return {2, two};
-  if (four.group_units == kDrawWaves && B <= kFusedMaxB) return {4, four};
-  return {8, draw_split<8>(V_t, B, n_cu)};
+  if (two.group_units == kDrawWaves && two.n_units <= 512 && B <= kFusedMaxB) return {2, two, kDrawWaves};
+  if (four.group_units == kDrawWaves && B <= kFusedMaxB) return {4, four, kDrawWaves};
+  const DrawSplit eight = draw_split<8>(V_t, B, n_cu);
+  if (B > n_cu && eight.blocks == 1 && draw_lds_bytes(eight) + exps_bytes(V_d) <= kDrawLdsBytes / 2)
+    return {8, draw_split<8>(V_t, B, n_cu, 8), 8};
+  return {8, eight, kDrawWaves};
 }
 
 // Every group of units of a sequence repeats the merge of its rows' partials: M x nfine x 16 bytes per group.  Up to
@@ -191,17 +205,21 @@ bool test_has_its_launch(int hosted, int nfine, int M, const DrawSplit& s) {
 }
 
 // What was left by which launch: see StepArgs::hosted.  row_off_host holds the B + 1 row offsets.
-template <int kPer, bool kBlocks = false>
+template <int kPer, bool kBlocks = false, int kWaves = kDrawWaves>
 hipError_t launch_draw(const StepArgs& a, const int32_t* row_off_host, const DrawSplit& split, hipStream_t stream) {
+  constexpr size_t kLdsBytes = kWaves == kDrawWaves ? kDrawLdsBytes : kDrawLdsBytes / 2;
   DrawSplit s = split;
-  const dim3 grid(ceil_div(s.n_units, s.group_units), a.B), block(kDrawThreads);
-  size_t lds = (size_t)(draw_lds_doubles(s.n_units) + 1) / 2 * 2 * sizeof(double);
+  const dim3 grid(ceil_div(s.n_units, s.group_units), a.B), block(kWaves * 64);
+  size_t lds = draw_lds_bytes(s);
   // From two turns on the workgroup keeps the draft row in LDS where it fits: a gather from memory moves a 128-byte line
-  // per id, about 2 us of a turn, the copy costs that once (128 sequences x 128256 ids: 51 us without, 39 with).  Up to the largest
-  // copies (us per step from the logits, 20 / 128 sequences): 50257 bf16 ids 26.0 / 60 against 26.4 / 76 gathered, 75000 26.6 / 62
-  // against 28 / 89, 32000 fp32 ids 24.7 / 59 against 25.6 / 71.
-  const size_t row_bytes = (size_t)a.V_d * (a.dtype == OT_BF16 ? 2 : 4) + 32;
-  if (s.group_units > kDrawWaves && lds + row_bytes <= kDrawLdsBytes) {
+  // per id, about 2 us of a turn, the copy costs that once (128 sequences x 128256 ids: 51 us without, 39 with).  Its exponentials if
+  // those fit, formed once a workgroup and not once an id: the turns then wait for the target's logits and the inverse map alone.
+  // us per step from the logits, exponentials / logits as stored: 128 sequences x 128256 ids with 32000 draft ids 49.3 / 53.1, 300 x 32003
+  // with 8000 (16 wavefronts) 43.7 / 45.8.  Up to the largest copies (20 / 128 sequences): 50257 bf16 ids 26.0 / 60 against 26.4 / 76
+  // gathered, 75000 26.6 / 62 against 28 / 89.
+  s.exps = s.group_units > kWaves && lds + exps_bytes(a.V_d) <= kLdsBytes;
+  const size_t row_bytes = s.exps ? exps_bytes(a.V_d) : (size_t)a.V_d * (a.dtype == OT_BF16 ? 2 : 4) + 32;
+  if (s.group_units > kWaves && lds + row_bytes <= kLdsBytes) {
     s.row_at = (int)(lds / sizeof(double));
     lds += row_bytes;
   }
@@ -210,27 +228,27 @@ hipError_t launch_draw(const StepArgs& a, const int32_t* row_off_host, const Dra
   if (a.hosted == kHostsNothing) {
     if (a.B > kFusedMaxB) {
       if constexpr (kPer == 8)
-        hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, true, true, false, kBlocks>), grid, block, lds, stream, a, ro, s);
+        hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, true, true, false, kBlocks, kWaves>), grid, block, lds, stream, a, ro, s);
       else
         return hipErrorInvalidValue;
     } else if (a.nchd > kChunksAtOnce) {
-      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, true, false, kBlocks>), grid, block, lds, stream, a, ro, s);
+      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, true, false, kBlocks, kWaves>), grid, block, lds, stream, a, ro, s);
     } else {
-      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, false, false, kBlocks>), grid, block, lds, stream, a, ro, s);
+      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, false, false, kBlocks, kWaves>), grid, block, lds, stream, a, ro, s);
     }
     return hipGetLastError();
   }
   if (a.B > kFusedMaxB) return hipErrorInvalidValue;
   if (!test_has_its_launch(a.hosted, a.fused.nfine, a.M, s)) {
     if (a.hosted == kHostsAll)
-      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, false, false, false, true, kBlocks>), grid, block, lds, stream, a, ro, s);
+      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, false, false, false, true, kBlocks, kWaves>), grid, block, lds, stream, a, ro, s);
     else
-      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, true, true, kBlocks>), grid, block, lds, stream, a, ro, s);
+      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, true, true, kBlocks, kWaves>), grid, block, lds, stream, a, ro, s);
     return hipGetLastError();
   }
-  if (a.hosted == kHostsAll) hipLaunchKernelGGL((accept_draw_kernel<8, false, false>), dim3(1, a.B), block, 0, stream, a, ro, s);
-  else hipLaunchKernelGGL((accept_draw_kernel<8, false, true, false, true, true>), dim3(1, a.B), block, 0, stream, a, ro, s);
-  hipLaunchKernelGGL((final_draw_kernel<kPer, kBlocks>), grid, block, lds, stream, a, s);
+  if (a.hosted == kHostsAll) hipLaunchKernelGGL((accept_draw_kernel<8, false, false>), dim3(1, a.B), dim3(kDrawWaves * 64), 0, stream, a, ro, s);
+  else hipLaunchKernelGGL((accept_draw_kernel<8, false, true, false, true, true>), dim3(1, a.B), dim3(kDrawWaves * 64), 0, stream, a, ro, s);
+  hipLaunchKernelGGL((final_draw_kernel<kPer, kBlocks, kWaves>), grid, block, lds, stream, a, s);
   return hipGetLastError();
 }
 
@@ -238,15 +256,16 @@ hipError_t launch_draw(const StepArgs& a, const int32_t* row_off_host, const Dra
 
 hipError_t launch_final_draw(const StepArgs& a, const int32_t* row_off_host, int n_cu, hipStream_t stream) {
   if (a.B == 0) return hipSuccess;
-  const DrawPlan plan = draw_plan(a.V_t, a.B, n_cu);
+  const DrawPlan plan = draw_plan(a.V_t, a.V_d, a.B, n_cu);
   if (plan.per == 2) return launch_draw<2>(a, row_off_host, plan.split, stream);
   if (plan.per == 4) return launch_draw<4>(a, row_off_host, plan.split, stream);
+  if (plan.waves == 8) return launch_draw<8, false, 8>(a, row_off_host, plan.split, stream);
   if (plan.split.blocks == 1) return launch_draw<8>(a, row_off_host, plan.split, stream);
   return launch_draw<8, true>(a, row_off_host, plan.split, stream);
 }
 
-int final_draw_launches(int hosted, int nfine, int M, int V_t, int B, int n_cu) {
-  return test_has_its_launch(hosted, nfine, M, draw_plan(V_t, B, n_cu).split) ? 2 : 1;
+int final_draw_launches(int hosted, int nfine, int M, int V_t, int V_d, int B, int n_cu) {
+  return test_has_its_launch(hosted, nfine, M, draw_plan(V_t, V_d, B, n_cu).split) ? 2 : 1;
 }
 
 }  // namespace otv

@@ -1,0 +1,30 @@
+"""The final draw with the draft row's exponentials in LDS: workgroups that take several turns, of 16 wavefronts and (more sequences
+than compute units) of 8.  Edges: the last unit of 512 ids whole, of one id, of all but one; draft rows at every alignment, of one and
+of a few ids, the longest whose exponentials fit half of LDS or all of it and the next; n-gram overrides inside the units."""
+import numpy as np
+import pytest
+
+from test_gpu_parity import _run_and_compare
+from workloads import CaseSpec, make_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype,V_t,V_d,B", [
+    ("bf16", 4608, 1, 300),          # 8 wavefronts, the second turn holds one whole unit; a draft row of one id
+    ("bf16", 8193, 4001, 257),       # 8 wavefronts, the last unit of one id
+    ("f32", 12287, 3, 520),          # two rounds of 8 wavefronts, the last unit of 511 ids
+    ("bf16", 9001, 18979, 260),      # exponentials that just fit half of LDS (75916 bytes next to two sums of 64 masses)
+    ("bf16", 9001, 19500, 260),      # and that do not: 16 wavefronts
+    ("f32", 40000, 37500, 120),      # next to the masses about the longest that fit
+    ("bf16", 30011, 37903, 130),     # odd rows, copied as stored
+    ("bf16", 20480, 7, 200),         # 16 wavefronts, whole units only
+])
+def test_exponentials_in_lds(dtype, V_t, V_d, B):
+    rng = np.random.default_rng(V_t + V_d)
+    temps = rng.choice([1.0, 0.7, 0.0], size=B, p=[0.5, 0.4, 0.1]).tolist()
+    case = make_case(CaseSpec(name=f"exps_{dtype}_{V_t}_{V_d}", dtype=dtype, d=8, V_t=V_t, V_d=V_d, k=rng.integers(0, 3, size=B).tolist(),
+                              temperature=temps, n_direct=max(1, int(0.8 * min(V_d, V_t))), n_ngram=min(200, V_d * V_d // 2), ngram_len=(2, 2),
+                              plant_cover=0.4, align=0.5, data_seed=V_d, philox_seed=5, logits_only=True,
+                              draft_temperature=[0.0 if b % 17 == 3 else max(t, 0.5) for b, t in enumerate(temps)]))
+    _run_and_compare(case)
