@@ -19,9 +19,11 @@
 // target ids where a 32000-id drafter meets a 128256-id target, and the logits are still read in order.  With every target
 // id visited the launch took 39 us at 144 rows, bound by its binary64 instructions.  Now it is bound by the chain of round
 // trips in a workgroup: 60 to 100 rows of 128256 ids are 32 to 52 MB, 5 to 8 us at the rate of a large copy.
-// Measured, us per call: 144 rows x 128256 ids 21.5, against 42.8 for four launches (in the kernel trace: constants 7.6, tiles
+// Measured, us per call: 144 rows x 128256 ids 17.3 (20.8 before the places below, with overrides and bounds tested at every term and
+// the copy shared with the wavefront that forms the constants), against 42.8 for four launches (in the kernel trace: constants 7.6, tiles
 // of 1024 ids with the gather from memory 30.9, sums per row 4.8, totals 4.0); 9 rows x 100000 ids 12.6 / 19.7.
 #include <algorithm>
+#include <type_traits>
 
 #include "device_math.h"
 #include "otv_host.h"
@@ -150,8 +152,15 @@ __device__ inline void loss_totals(const LossArgs& a, double (*s_term)[kWaves], 
   }
   double t[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) t[i] = block_sum<kWaves>(term[i], s_term[i], wave, lane);
-  if (tid == 0) {
+  for (int i = 0; i < 4; ++i) {
+    t[i] = wave_sum(term[i]);
+    if (lane == 0) s_term[i][wave] = t[i];
+  }
+  __syncthreads();
+  if (wave != 0) return;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) t[i] = wave_sum(lane < kWaves ? s_term[i][lane] : 0.0);
+  if (lane == 0) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) a.out.totals[i] = t[i];
     a.out.totals[4] = (t[0] + t[1]) / fmax(1.0, t[2] + t[3]);
@@ -177,39 +186,68 @@ __device__ inline void load_terms(const LossArgs& a, bool pairs, int n, int firs
   }
 }
 
-// Grid: row r's workgroups (`groups` of them) run on XCD r % 8 back to back, so that they meet in its L2, where a draft row that
-// is gathered from memory stays while they do.
+// Row offsets of a few sequences as a kernel argument (the host has them); of more they come from memory, another round trip (256 of
+// them as an argument cost every call 0.3 us on the host).
+constexpr int kArgumentB = 31;
+struct LossRowOffsets { int32_t v[kArgumentB + 1]; };
+
+// Grid: the workgroups of a row (`groups` of them) run on one XCD back to back, so that they meet in its L2, where a draft row that
+// is gathered from memory stays while they do.  seq_rows > 0: places of seq_rows rows for every sequence, of which those past its
+// window end at once; a workgroup then knows its sequence and row without a load, and everything else about them comes with one
+// round trip of scalar loads, which do not wait behind the vector loads of its terms.  Most rows of a batch have no token with a KL
+// term, and what their workgroups take to find that out the others wait for (6.7 us of 21 with the row's sequence looked up behind
+// the first turn's loads, and what hangs on it loaded after that).  A sequence's last row never has a token: unless its q' row of
+// zeros is wanted, the place in front of it takes it along (16 windows of 8 tokens then are 512 workgroups, all on the chip at once,
+// and not 576).
+// 0: the rows one after the other (ragged windows that would leave most places empty).
+// n_arrivals: rows, or places with a row, that are counted in.
 template <int kThreads>
-__global__ __launch_bounds__(kThreads, 4) void loss_kernel(LossArgs a, int groups, int group_terms, int staged) {
+__global__ __launch_bounds__(kThreads, 4) void loss_kernel(LossArgs a, LossRowOffsets ro, int seq_rows, int n_arrivals, int groups, int group_terms, int staged) {
   constexpr int kWaves = kThreads / 64;
   __shared__ LossRow s_row;
   __shared__ double s_term[4][kWaves];
   __shared__ int s_last;
   const int tid = threadIdx.x, wave = uniform(tid >> 6), lane = tid & 63;
-  const int slot = (int)blockIdx.x >> 3, row = slot / groups * 8 + ((int)blockIdx.x & 7), grp = slot % groups;
+  const int slot = (int)blockIdx.x >> 3, place = slot / groups * 8 + ((int)blockIdx.x & 7), grp = slot % groups;
   if (a.M == 0) {                                        // an empty batch
     if (blockIdx.x == 0) loss_totals<kWaves>(a, s_term, tid, wave, lane);
     return;
   }
-  if (row >= a.M) return;                                // padding of the id space
+  int b, r0, row;
+  bool free_row = false;                                 // row + 1 is the sequence's last
+  if (seq_rows > 0) {
+    b = place / seq_rows;
+    if (b >= a.B) return;                                // padding of the id space
+    const bool argument = a.B <= kArgumentB;
+    r0 = argument ? ro.v[b] : a.row_off[b];
+    const int rows = (argument ? ro.v[b + 1] : a.row_off[b + 1]) - r0, at = place % seq_rows;
+    const bool fold = a.out.qprime == nullptr;
+    if (at >= (fold ? max(rows - 1, 1) : rows)) return;  // past the sequence's window
+    row = r0 + at;
+    free_row = fold && at == rows - 2;
+  } else {
+    row = place;
+    if (row >= a.M) return;
+    b = find_sequence(a.row_off, a.B, row, 0, lane);
+    r0 = a.row_off[b];
+  }
+  b = uniform(b); row = uniform(row);
+  const int j = row - r0;
+  const int s = a.span_start[row], L = a.span_len[row], t = a.mapped_ids[row];
+  const float T = a.temperature[b];
+  const float Td = a.draft_temperature ? a.draft_temperature[b] : T;
+  const int n_mapped = a.n_mapped[b], n_accept = a.n_accept[b];
   const bool pairs = a.out.qprime == nullptr;            // terms: the mapped pairs, or (q' is wanted everywhere) all ids
   const int n_terms = pairs ? a.n_pairs : a.V_t;
   const int i0 = grp * group_terms, i1 = min(i0 + group_terms, n_terms);
-  // the first turn's ids and logits depend on nothing else
+  // the first turn's ids depend on nothing else
   const float* z = a.Z + (int64_t)row * a.ldz;
   int2 id[kPerTurn], id_next[kPerTurn] = {};             // (target id, draft id or -1)
   float zv[kPerTurn];
   load_terms<kThreads>(a, pairs, n_terms, i0 + tid, id);
   if (i0 + kPerTurn * kThreads < i1) load_terms<kThreads>(a, pairs, n_terms, i0 + tid + kPerTurn * kThreads, id_next);
-#pragma unroll
-  for (int e = 0; e < kPerTurn; ++e) zv[e] = z[id[e].x];
-  const int s = a.span_start[row], L = a.span_len[row], t = a.mapped_ids[row];
-  const int b = find_sequence(a.row_off, a.B, row, 0, lane);
-  const int r0 = a.row_off[b], j = row - r0;
-  const float T = a.temperature[b];
-  const float Td = a.draft_temperature ? a.draft_temperature[b] : T;
   int kind = 0;
-  if (j < a.n_mapped[b] && T > 0.f && Td > 0.f) kind = L == 1 ? 1 : (!a.accepted_only || j < a.n_accept[b]) ? 2 : 0;
+  if (j < n_mapped && T > 0.f && Td > 0.f) kind = L == 1 ? 1 : (!a.accepted_only || j < n_accept) ? 2 : 0;
   kind = uniform(kind);
   const bool need_kl = kind == 1 || (kind == 2 && a.ngram_term == OT_NGRAM_TERM_APPROX_KL);
   const bool visit = need_kl || (kind != 0 && a.out.qprime != nullptr);
@@ -217,6 +255,8 @@ __global__ __launch_bounds__(kThreads, 4) void loss_kernel(LossArgs a, int group
   if (!visit && qprime)                                  // a row without a token exports zeros
     for (int v = i0 + tid; v < i1; v += kThreads) qprime[v] = 0.f;
   if (!visit && grp != 0) return;
+#pragma unroll
+  for (int e = 0; e < kPerTurn; ++e) zv[e] = z[id[e].x];
   const int drow = uniform(r0 - b + (kind != 0 ? s : 0));
   const char* zq = static_cast<const char*>(a.draft_logits) + (size_t)drow * a.V_d * (a.dtype == OT_BF16 ? 2 : 4);
   if (wave == 0) {
@@ -229,14 +269,22 @@ __global__ __launch_bounds__(kThreads, 4) void loss_kernel(LossArgs a, int group
       publish(a.out.kind + row, kind);
       publish(a.out.nll + row, nll);
       publish(a.out.weight + row, weight);
+      if (free_row) {
+        publish(a.out.kind + row + 1, 0);
+        publish(a.out.nll + row + 1, 0.0);
+        publish(a.out.weight + row + 1, 0.0);
+        publish(a.out.kl + row + 1, 0.0);
+      }
     }
   }
   double kl = 0.0;
   if (visit) {
     int lds_at = -1;
-    if (staged) lds_at = stage_draft_row<kThreads>(zq, a.dtype, a.V_d, tid, 0);
+    if (staged && wave > 0) lds_at = stage_draft_row<kThreads - 64>(zq, a.dtype, a.V_d, tid - 64, 0);
+    if (staged && wave == 0) lds_at = (int)(reinterpret_cast<uintptr_t>(zq) & 15);   // where that starts the copy
     __syncthreads();
     const LossRow R = s_row;
+    const bool plain_row = pairs && uniform(R.t_ng & R.t_pre) < 0;   // neither override (-1 both)
     for (int at = i0 + tid; at - tid < i1; at += kPerTurn * kThreads) {
       uint32_t xq[kPerTurn];
       int dv[kPerTurn];
@@ -250,21 +298,28 @@ __global__ __launch_bounds__(kThreads, 4) void loss_kernel(LossArgs a, int group
         for (int e = 0; e < kPerTurn; ++e) z_next[e] = z[id_next[e].x];
       }
       if (at - tid + 2 * kPerTurn * kThreads < i1) load_terms<kThreads>(a, pairs, n_terms, at + 2 * kPerTurn * kThreads, id_after);
+      // kPlain: mapped pairs, all of the turn's terms exist, no override among the row's ids
+      auto add_terms = [&](auto plain) {
+        constexpr bool kPlain = decltype(plain)::value;
 #pragma unroll
-      for (int e = 0; e < kPerTurn; ++e) {
-        const int v = id[e].x;
-        double q = 0.0, lq = 0.0;
-        if (dv[e] >= 0) {
-          lq = ((double)__uint_as_float(a.dtype == OT_BF16 ? xq[e] << 16 : xq[e]) - R.mxq) * R.invTd - R.lnSq;
-          q = exp_neg_fast(lq);
+        for (int e = 0; e < kPerTurn; ++e) {
+          const int v = id[e].x;
+          double q = 0.0, lq = 0.0;
+          if (kPlain || dv[e] >= 0) {
+            lq = ((double)__uint_as_float(a.dtype == OT_BF16 ? xq[e] << 16 : xq[e]) - R.mxq) * R.invTd - R.lnSq;
+            q = exp_neg_fast(lq);
+          }
+          if (!kPlain && v == R.t_pre) { q = R.q_pre; lq = R.ln_q_pre; }
+          if (!kPlain && v == R.t_ng) { q = R.pi; lq = R.ln_pi; }   // the n-gram case of Eq. 2 wins when both name the same id
+          const double lp = ((double)zv[e] - R.mx) * R.invT - R.lnS;
+          if ((kPlain || at + e * kThreads < i1) && q > 0.0) kl += q * (lq - lp);
+          if (!kPlain && qprime && at + e * kThreads < i1) qprime[v] = (float)q;
         }
-        if (v == R.t_pre) { q = R.q_pre; lq = R.ln_q_pre; }
-        if (v == R.t_ng) { q = R.pi; lq = R.ln_pi; }     // the n-gram case of Eq. 2 wins when both name the same id
-        const double lp = ((double)zv[e] - R.mx) * R.invT - R.lnS;
-        if (at + e * kThreads < i1 && q > 0.0) kl += q * (lq - lp);
-        if (qprime && at + e * kThreads < i1) qprime[v] = (float)q;
-        id[e] = id_next[e]; id_next[e] = id_after[e]; zv[e] = z_next[e];
-      }
+      };
+      if (plain_row && at - tid + kPerTurn * kThreads <= i1) add_terms(std::true_type());   // workgroup-uniform
+      else add_terms(std::false_type());
+#pragma unroll
+      for (int e = 0; e < kPerTurn; ++e) { id[e] = id_next[e]; id_next[e] = id_after[e]; zv[e] = z_next[e]; }
     }
     // the n-gram's target id, where it is no draft id's image and so in no pair
     if (pairs && grp == 0 && tid == 0 && R.t_ng >= 0 && a.tmap[R.t_ng] < 0 && R.pi > 0.0)
@@ -287,7 +342,7 @@ __global__ __launch_bounds__(kThreads, 4) void loss_kernel(LossArgs a, int group
       s_last = 0;
       if (row_done) {
         publish(a.out.kl + row, need_kl ? kl : 0.0);
-        s_last = arrive(a.count, a.M);
+        s_last = arrive(a.count, n_arrivals);
       }
     }
   }
@@ -370,11 +425,22 @@ int ot_distill_loss(ot_ctx* ctx, const ot_step_in* in, const ot_step_out* step, 
   const int n_terms = out->qprime ? a.V_t : a.n_pairs;
   const int64_t row_bytes = (int64_t)a.V_d * (a.dtype == OT_BF16 ? 2 : 4) + 32;
   const LossPlan p = loss_plan(M, n_terms, row_bytes, ctx->local_pairs, ctx->n_cu);
-  const dim3 grid((unsigned)(p.groups * ceil_div(std::max(M, 1), 8) * 8)), block(p.threads);
+  LossRowOffsets ro{};
+  int seq_rows = 0, n_places = 0;                        // of the longest window
+  for (int b = 0; b < in->B; ++b) {
+    const int rows = in->row_off_host[b + 1] - in->row_off_host[b], n = out->qprime ? rows : std::max(1, rows - 1);
+    seq_rows = std::max(seq_rows, n);
+    n_places += n;
+  }
+  if ((int64_t)seq_rows * in->B > 2 * (int64_t)n_places) seq_rows = 0;
+  const int n_arrivals = seq_rows > 0 ? n_places : M;
+  for (int b = 0; b <= in->B && in->B > 0 && in->B <= kArgumentB; ++b) ro.v[b] = in->row_off_host[b];
+  const int places = seq_rows > 0 ? seq_rows * in->B : std::max(M, 1);
+  const dim3 grid((unsigned)(p.groups * ceil_div(places, 8) * 8)), block(p.threads);
   const size_t lds = p.staged ? row_bytes : 16;
-  if (p.threads == 1024) hipLaunchKernelGGL(loss_kernel<1024>, grid, block, lds, st, a, p.groups, p.group_terms, p.staged);
-  else if (p.threads == 512) hipLaunchKernelGGL(loss_kernel<512>, grid, block, lds, st, a, p.groups, p.group_terms, p.staged);
-  else hipLaunchKernelGGL(loss_kernel<256>, grid, block, lds, st, a, p.groups, p.group_terms, p.staged);
+  if (p.threads == 1024) hipLaunchKernelGGL(loss_kernel<1024>, grid, block, lds, st, a, ro, seq_rows, n_arrivals, p.groups, p.group_terms, p.staged);
+  else if (p.threads == 512) hipLaunchKernelGGL(loss_kernel<512>, grid, block, lds, st, a, ro, seq_rows, n_arrivals, p.groups, p.group_terms, p.staged);
+  else hipLaunchKernelGGL(loss_kernel<256>, grid, block, lds, st, a, ro, seq_rows, n_arrivals, p.groups, p.group_terms, p.staged);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return ot_fail_hip(e, "ot_distill_loss: launch");
   return OT_OK;
