@@ -48,9 +48,10 @@ extern "C" {
 /* ---- storage types of hidden states, LM-head weights and draft logits --------------------------------- */
 /* OT_BF16 is the production type: the LM head runs on the matrix cores, bound by the weight stream.
  * OT_F32 exists for small problems that want fp32 arithmetic end to end (checks against an fp32 model, toy
- * vocabularies): its LM head runs on the fp32 matrix instructions, a sixteenth of the bf16 rate, and never hosts the
- * draft side, so a step costs several times the bf16 one where the rows are many (measured: about 7x at d = 4096,
- * V_t = 128256, 144 rows; 1.4x at d = 1024, V_t = 32000, 6 rows).  Nothing is refused for size.              */
+ * vocabularies): its LM head runs on the fp32 matrix instructions, a sixteenth of the bf16 rate, or, above 16 rows and
+ * from 384 hidden indices on, on the bf16 ones with every operand split into three (six products, no less accurate), so a
+ * step costs more than the bf16 one where the rows are many (1.4x at d = 1024, V_t = 32000, 6 rows).  Nothing is refused
+ * for size.                                                                                                   */
 #define OT_BF16 0
 #define OT_F32  1
 
