@@ -750,7 +750,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void l
 // are summed through LDS in a fixed order: a head of 1024 columns is 16 workgroups of 8 wavefronts, one of 32000 is 500
 // per row block.  The row blocks of a column tile run on the same XCD back to back and meet in its L2.
 // The launch also leaves softmax partials and takes the draft side (a workgroup per job, or packed into few: f32_row_front),
-// which spares the statistics launch: 57.2 -> 54.8 us per step at 64 rows, 17.4 -> 14.2 at 5.
+// which spares the statistics launch: 57.2 -> 54.8 us per step at 64 rows (before the thirds kernel below took those), 17.4 -> 14.2 at 5.
 // Measured (64 rows, d = 1024, V_t = 32000 / 5 rows, d = 256, V_t = 1024): 46 / 4.2 us, with the draft side 49.6 / 5.4, against 575 / 68 us of a kernel
 // whose threads owned one column each over all of the hidden dimension (1000 and 4 workgroups of serial chains); error
 // against 64 bits 4.7e-7 and 1.1e-7, with one long chain per logit 2e-6 and 6e-7.

@@ -6,8 +6,8 @@
 //                       sequence (one wavefront merges the partials of the draft rows and walks the window from the
 //                       probe record while the others merge the target rows' partials, one wavefront per row; then that
 //                       wavefront runs the test: a few microseconds of work on data that sits in L2, cheaper than a
-//                       launch of its own: with the draw of that time 300 sequences x 32003 ids took 42 us against
-//                       10.5 + 30.6 and a launch; it takes 33 now), then takes part in the draw.  The workgroups of
+//                       launch of its own: with an earlier draw 300 sequences x 32003 ids took 42 us against 10.5 + 30.6
+//                       and a launch; all of it takes 21 now), then takes part in the draw.  The workgroups of
 //                       a sequence reach the same outcome; only group 0 writes the outputs of the translation and the
 //                       test, the draft rows' merged statistics and the cache's use statistics.
 #include <algorithm>
