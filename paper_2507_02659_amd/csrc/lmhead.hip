@@ -878,29 +878,34 @@ __global__ __launch_bounds__(WAVES * 64) void lmhead_f32_kernel(const float* __r
 
 // ---------------------------------------------------------------------------------------------------------------
 // fp32 head of more than 16 rows and a longer hidden dimension (f32_plan), on the bf16 matrix instruction, which is sixteen times as
-// fast as the binary32 one.  A binary32 value is the sum of three bf16 values, its leading eight significant bits, the next eight
-// and the rest, exactly; of the nine products of two such triples the six largest are formed (each exact, added up in binary32),
-// what is left out is below 2^-23 of a product.  Fewer roundings than with the binary32 instruction, one per 32 products instead of
-// one per 4: error against 64 bits at d = 1024 2.4e-7 of the logits' norm, 2.9e-7 there.
+// fast as the binary32 one.  A binary32 value is the sum of three bf16 values, exactly: the nearest one, the nearest one to what is
+// left, and the rest (24 significant bits, of which each of the first two takes eight and leaves a remainder of either sign).  Of the
+// nine products of two such triples the six largest are formed (each exact, added up in binary32); what is left out is at most 2^-24 of
+// a product and leans to no side.  (Parts cut off instead of rounded all have the sign of the value: up to 2^-21 left out, always
+// towards zero, 4.5e-7 of the logit of a token that its hidden row lies along.)  A rounding per 32 products instead of one per 4: error
+// against 64 bits at 64 rows x 32000 columns, d = 1024, eight seeds, here / with the binary32 instruction: logits 2.3e-7 / 2.9e-7 of
+// their norm, probabilities of the proposed tokens 3.0e-7 / 3.2e-7, their ratios 2.4e-7 / 2.6e-7.
 // Same packed weights and the same split over four wavefronts as above; a step is two blocks of 16 hidden indices.  Bound by the
 // loads: of 36 us at 64 rows x 32000 columns (d = 1024; 45.8 with the binary32 instruction) 25 are left without the hidden rows' traffic (one L2
 // read of all rows per 64 columns), the splits and half of the products, 30 with the traffic alone.  Tried instead: the hidden rows'
 // thirds shared through LDS, wavefronts by columns and halves of the hidden dimension: 43 us, a barrier per 64 hidden indices and
 // longer chains of sums (3.4e-7).
 struct Thirds { bf16x8 part[3]; };
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ Thirds split_thirds(const float (&x)[8], float& largest) {
   uint32_t w[3][4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) largest = fmaxf(fmaxf(__builtin_fabsf(x[2 * i]), __builtin_fabsf(x[2 * i + 1])), largest);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    uint32_t a = __float_as_uint(x[2 * i]), b = __float_as_uint(x[2 * i + 1]);
+    float a = x[2 * i], b = x[2 * i + 1];
 #pragma unroll
     for (int t = 0; t < 3; ++t) {
-      w[t][i] = __builtin_amdgcn_perm(b, a, 0x07060302u);          // the upper halves of both
+      w[t][i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));   // to nearest
       if (t < 2) {
-        a = __float_as_uint(__uint_as_float(a) - __uint_as_float(a & 0xFFFF0000u));
-        b = __float_as_uint(__uint_as_float(b) - __uint_as_float(b & 0xFFFF0000u));
+        a -= __uint_as_float(w[t][i] << 16);
+        b -= __uint_as_float(w[t][i] & 0xFFFF0000u);
       }
     }
   }
@@ -1028,10 +1033,10 @@ __global__ __launch_bounds__(256, MT == 2 ? 3 : 2) void lmhead_f32_thirds_kernel
     fetch_rest();
     step(std::false_type(), 0, 0, 0);
   }
-  // An infinite or NaN operand does not survive the split (inf - inf), and 0 times an infinite part is no longer the product.  A
-  // denormal part counts as 0 in the multiplication: below 2^-126 of an operand, less than 2^-66 of a product with one below 2^60.
-  // A workgroup that ends up with a logit that is not finite, or met an operand of 2^60 or more, forms its tile again on the binary32
-  // matrix instruction.
+  // An infinite or NaN operand does not survive the split (inf - inf), and 0 times an infinite part is no longer the product.  The
+  // last part of an operand below 2^-110 is rounded to a multiple of 2^-133, the least bf16 value: less than 2^-73 of a product with
+  // an operand below 2^60.  A workgroup that ends up with a logit that is not finite, or met an operand of 2^60 or more, forms its tile
+  // again on the binary32 matrix instruction.
   auto sound = [&]() {
     bool ok = largest < 0x1p60f;
 #pragma unroll

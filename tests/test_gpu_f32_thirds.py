@@ -71,6 +71,45 @@ def test_operands_that_are_not_finite(d):
     assert np.all(np.abs(got[ok] - want[ok]) <= bound[ok] + 1e-30)
 
 
+def _row_tiles(M, V_t):
+    """Row tiles of the blocks that M rows run as: the plan's estimate written out again, so that a case that no longer reaches its
+    kernel is noticed."""
+    import torch
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    tiles, wtiles = -(-M // 16), -(-V_t // 64)
+    return min((2, 3, 4), key=lambda mt: -(-wtiles * -(-tiles // mt) // n_cu) * (2.0 + 2.5 * mt))
+
+
+@pytest.mark.parametrize("M,d,V_t,tiles", [(17, 512, 321, 2), (48, 543, 16001, 3), (50, 530, 8257, 4)])
+def test_single_products(M, d, V_t, tiles):
+    """Hidden rows with one value each: a logit is one product.  What the six products leave out is at most 2^-24 of it, the sum is
+    rounded to binary32 (at most 2^-23 of it, however), and neither leans to a side."""
+    assert _row_tiles(M, V_t) == tiles
+    case = _case(M, d, V_t)
+    rng = np.random.default_rng(M + d)
+
+    def values(shape):
+        mantissa = rng.integers(0, 1 << 23, size=shape)
+        mantissa.flat[::5] = 0x00FFFF                     # 1 + 2^-7 - 2^-23: the two lower thirds as large as they get
+        mantissa.flat[1::5] = 0x7FFFFF
+        return np.ldexp(1.0 + mantissa * 2.0 ** -23, rng.integers(-12, 13, size=shape)).astype(np.float32) * rng.choice([-1, 1], size=shape).astype(np.float32)
+
+    case.hidden[:] = 0
+    at = rng.integers(0, d, size=M)
+    at[:2] = 0, d - 1
+    case.hidden[np.arange(M), at] = values(M)
+    case.W[:] = values((d, V_t))
+    _say(f"thirds, single products M={M} d={d} V_t={V_t}")
+    got = _logits(case)[:, :V_t].astype(np.float64)
+    want = case.hidden[np.arange(M), at].astype(np.float64)[:, None] * case.W[at].astype(np.float64)
+    off = (got / want - 1) * 2.0 ** 24
+    assert np.abs(off).max() <= 3
+    # Where the weight's mantissa is random: 0.7 at most each, root mean square (0.58 of a rounding at the lower end of a binade, 0.3 left
+    # out), so that the mean of 3000 and more stays below 0.013 (one deviation)
+    random = (np.arange(d * V_t).reshape(d, V_t)[at] % 5 > 1)
+    assert random.sum() >= 3000 and abs(off[random].mean()) <= 0.1
+
+
 @pytest.mark.parametrize("up_hidden", [True, False])
 def test_operands_whose_lower_thirds_are_denormal(up_hidden):
     case = _case(40, 600, 300)
@@ -81,6 +120,19 @@ def test_operands_whose_lower_thirds_are_denormal(up_hidden):
     got = _logits(case)
     H, W = case.hidden.astype(np.float64), case.W.astype(np.float64)
     bound = 8 * 2.0 ** -24 * np.sqrt(600) * np.sqrt((H * H) @ (W * W)) + 3 * 2.0 ** -24 * (np.abs(H) @ np.abs(W))
+    assert np.all(np.abs(got - H @ W) <= bound)
+
+
+def test_small_logits():
+    """Weights about 2^-116 and ordinary hidden states: the last third of a weight is rounded to a multiple of 2^-133, to either side."""
+    case = _case(40, 600, 300)
+    case.W *= np.float32(2.0 ** -110)
+    _say("thirds, small logits")
+    got = _logits(case)
+    H, W = case.hidden.astype(np.float64), case.W.astype(np.float64)
+    # as in test_logits, 2^-24 of a product left out, and eight standard deviations of the roundings of the last thirds (0.29 * 2^-133 each)
+    bound = (8 * 2.0 ** -24 * np.sqrt(600) * np.sqrt((H * H) @ (W * W)) + 2.0 ** -24 * (np.abs(H) @ np.abs(W))
+             + 8 * 0.29 * 2.0 ** -133 * np.sqrt((H * H).sum(axis=1, keepdims=True)))
     assert np.all(np.abs(got - H @ W) <= bound)
 
 
