@@ -785,7 +785,7 @@ __global__ __launch_bounds__(WAVES * 64) void lmhead_f32_kernel(const float* __r
   const int wg = (int)blockIdx.x - (kStats ? n_front : 0);   // n_front is a multiple of 8: the XCDs below are those of the block ids
   if (kStats && wg < 0) {
     if (ds.plan.base == kDraftPieces) front_draft_side<float, WAVES>(ds, blockIdx.x, tid, sRed);
-    else front_draft_rows<float, WAVES>(ds, blockIdx.x, n_front, tid, sRed);
+    else front_draft_rows<float, WAVES, false>(ds, blockIdx.x, n_front, tid, sRed);
     return;
   }
   const int slot = wg >> 3;
@@ -931,7 +931,7 @@ __global__ __launch_bounds__(256, MT == 2 ? 3 : 2) void lmhead_f32_thirds_kernel
   const int wg = (int)blockIdx.x - (kStats ? n_front : 0);   // n_front is a multiple of 8: the XCDs below are those of the block ids
   if (kStats && wg < 0) {
     if (ds.plan.base == kDraftPieces) front_draft_side<float, kWaves>(ds, blockIdx.x, tid, sRed);
-    else front_draft_rows<float, kWaves, MT == 2 ? 8 : 16>(ds, blockIdx.x, n_front, tid, sRed);
+    else front_draft_rows<float, kWaves, true, MT == 2 ? 8 : 16>(ds, blockIdx.x, n_front, tid, sRed);
     return;
   }
   const int slot = wg >> 3;

@@ -446,41 +446,28 @@ __device__ __forceinline__ void front_draft_side(const StepArgs& a, int job, int
 
 // The same by few workgroups: front workgroup j of n takes the lookups of sequences, then every wavefront of it whole draft rows, or
 // halves (a.plan with one or two pieces per row).  Next to the other workgroups' streams a dependent load takes microseconds, so
-// that the chains of loads decide how long this lasts: a piece's first batch is asked for a piece ahead (the first one in front
-// of the lookups), and the sequences' row offsets and temperatures are held across the lanes (at most kFusedMaxB of them).
-template <typename TD, int kWaves, int kBatch = kPieceBatch>
+// that the chains of loads decide how long this lasts.
+// kAhead: a piece's first batch is asked for a piece ahead (the first one in front of the lookups), and the sequences' row offsets and
+// temperatures are held across the lanes (at most kFusedMaxB of them).  Takes 70 registers; a kernel whose multiplying workgroups
+// would lose a wavefront per SIMD to them goes without (fp32 head at d < 384: 64 rows x 32000 columns, d = 256 / 376, 26.1 -> 29.0 / 32.7
+// -> 37.5 us per step with kAhead).
+template <typename TD, int kWaves, bool kAhead, int kBatch = kPieceBatch>
 __device__ __forceinline__ void front_draft_rows(const StepArgs& a, int j, int n, int tid, void* lds) {
   const int lane = tid & 63, wave = uniform(tid >> 6), pieces = a.plan.base, jobs = a.K * pieces;
   const float* temps = a.draft_temperature ? a.draft_temperature : a.temperature;
   constexpr int kSeqRegs = (kFusedMaxB + 64) / 64;
   int seq_before[kSeqRegs];
   float seq_temp[kSeqRegs];
+  if constexpr (kAhead) {
 #pragma unroll
-  for (int i = 0; i < kSeqRegs; ++i) {
-    const int b = min(64 * i + lane, a.B - 1);
-    seq_before[i] = a.row_off[b] - b;
-    seq_temp[i] = temps[b];
+    for (int i = 0; i < kSeqRegs; ++i) {
+      const int b = min(64 * i + lane, a.B - 1);
+      seq_before[i] = a.row_off[b] - b;
+      seq_temp[i] = temps[b];
+    }
   }
-  auto piece = [&](int job, int* e0, int* len) {
-    PiecePlan::span(a.V_d, pieces, job % pieces, e0, len);
-    return static_cast<const TD*>(a.draft_logits) + (int64_t)(job / pieces) * a.V_d + *e0;
-  };
-  int job = n * kWaves - 1 - (j * kWaves + wave);       // from the last wavefront on: the first ones have the lookups
-  int e0, len;
-  RowFirstBatch<TD, kBatch> first, next;
-  const TD* x = piece(min(job, jobs - 1), &e0, &len);
-  row_first_batch_load<TD, kBatch>(x, len, lane, first);
-  DraftLds* L = static_cast<DraftLds*>(lds);
-  if (a.B <= n) {
-    if (j < a.B) lookup_sequence(a, j, tid, kWaves * 64, L);
-  } else {                                              // several sequences each: side by side, a wavefront on each
-    for (int b = j * kWaves + wave; b < a.B; b += n * kWaves) wave_lookup_sequence(a, b, lane, L + wave);
-  }
-  for (; job < jobs; job += n * kWaves) {
-    int e0_next, len_next;                              // past the end: the last piece again, looked at by nobody
-    const TD* x_next = piece(min(job + n * kWaves, jobs - 1), &e0_next, &len_next);
-    row_first_batch_load<TD, kBatch>(x_next, len_next, lane, next);
-    const int q = job / pieces;
+  auto temperature_of = [&](int q) {
+    if constexpr (!kAhead) return temps[find_sequence(a.row_off, a.B, q, 1, lane)];
     int owner = -1;
     float Td = 1.f;
 #pragma unroll
@@ -490,13 +477,40 @@ __device__ __forceinline__ void front_draft_rows(const StepArgs& a, int j, int n
       const float t = __shfl(seq_temp[i], owner & 63);
       if ((owner >> 6) == i) Td = t;
     }
+    return Td;
+  };
+  int e0, len;
+  auto piece = [&](int job) {
+    PiecePlan::span(a.V_d, pieces, job % pieces, &e0, &len);
+    return static_cast<const TD*>(a.draft_logits) + (int64_t)(job / pieces) * a.V_d + e0;
+  };
+  int job = n * kWaves - 1 - (j * kWaves + wave);       // from the last wavefront on: the first ones have the lookups
+  RowFirstBatch<TD, kBatch> first, next;
+  if constexpr (kAhead) {
+    const TD* x = piece(min(job, jobs - 1));
+    row_first_batch_load<TD, kBatch>(x, len, lane, next);
+  }
+  DraftLds* L = static_cast<DraftLds*>(lds);
+  if (a.B <= n) {
+    if (j < a.B) lookup_sequence(a, j, tid, kWaves * 64, L);
+  } else {                                              // several sequences each: side by side, a wavefront on each
+    for (int b = j * kWaves + wave; b < a.B; b += n * kWaves) wave_lookup_sequence(a, b, lane, L + wave);
+  }
+  for (; job < jobs; job += n * kWaves) {
+    if constexpr (kAhead) {                             // past the end: the last piece again, looked at by nobody
+      first = next;
+      const TD* x_next = piece(min(job + n * kWaves, jobs - 1));
+      row_first_batch_load<TD, kBatch>(x_next, len, lane, next);
+    }
+    const int q = job / pieces;
+    const float Td = temperature_of(q);
+    const TD* x = piece(job);
     DraftPiece r; r.mx = -INFINITY; r.arg = 0x7FFFFFFF; r.sum = 0.0;
     if (len > 0) {
-      wave_row_stats<TD, kBatch, true>(x, len, Td > 0.f ? kLog2eF / Td : kLog2eF, lane, &r.mx, &r.arg, &r.sum, &first);
+      wave_row_stats<TD, kBatch, kAhead>(x, len, Td > 0.f ? kLog2eF / Td : kLog2eF, lane, &r.mx, &r.arg, &r.sum, &first);
       if (r.mx != -INFINITY) r.arg += e0;
     }
     if (lane == 0) a.dpiece[(int64_t)q * kDraftPieces + job % pieces] = r;
-    x = x_next; e0 = e0_next; len = len_next; first = next;
   }
 }
 
