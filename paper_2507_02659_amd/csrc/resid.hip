@@ -18,8 +18,8 @@
 namespace otv {
 namespace {
 
-template <int kPer, bool kBlocks, int kWaves>
-__global__ __launch_bounds__(kWaves * 64) void final_draw_kernel(StepArgs a, DrawSplit s) {
+template <int kPer, bool kBlocks>
+__global__ __launch_bounds__(kDrawWaves * 64) void final_draw_kernel(StepArgs a, DrawSplit s) {
   const int b = blockIdx.y, grp = blockIdx.x, tid = threadIdx.x;
   const int wave = uniform(tid >> 6), lane = tid & 63;
   __shared__ DrawLds s_draw;
@@ -28,7 +28,7 @@ __global__ __launch_bounds__(kWaves * 64) void final_draw_kernel(StepArgs a, Dra
   load_tmap<kPer>(a.tmap, a.V_t, first + lane, 64, first + 64 * kPer <= a.V_t, dv);   // overlaps the next load
   const FinalInfo f = a.fin[b];
   if (f.mode == 0) return;                  // greedy or flagged sequence: nothing to draw
-  draw_final_token<kPer, kBlocks, kWaves>(a, b, grp, s, f, dv, &s_draw);
+  draw_final_token<kPer, kBlocks, kDrawWaves>(a, b, grp, s, f, dv, &s_draw);
 }
 
 // Row offsets of up to kFusedMaxB sequences as a kernel argument (the host has them): the workgroup knows its rows without
@@ -192,7 +192,7 @@ DrawPlan draw_plan(int V_t, int V_d, int B, int n_cu) {
   if (two.group_units == kDrawWaves && two.n_units <= 512 && B <= kFusedMaxB) return {2, two, kDrawWaves};
   if (four.group_units == kDrawWaves && B <= kFusedMaxB) return {4, four, kDrawWaves};
   const DrawSplit eight = draw_split<8>(V_t, B, n_cu);
-  if (B > n_cu && eight.blocks == 1 && draw_lds_bytes(eight) + exps_bytes(V_d) <= kDrawLdsBytes / 2)
+  if (B > n_cu && B > kFusedMaxB && eight.blocks == 1 && draw_lds_bytes(eight) + exps_bytes(V_d) <= kDrawLdsBytes / 2)
     return {8, draw_split<8>(V_t, B, n_cu, 8), 8};
   return {8, eight, kDrawWaves};
 }
@@ -225,30 +225,29 @@ hipError_t launch_draw(const StepArgs& a, const int32_t* row_off_host, const Dra
   }
   RowOffsets ro;
   for (int b = 0; b <= kFusedMaxB; ++b) ro.v[b] = row_off_host[b <= a.B ? b : a.B];
-  if (a.hosted == kHostsNothing) {
-    if (a.B > kFusedMaxB) {
-      if constexpr (kPer == 8)
-        hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, true, true, false, kBlocks, kWaves>), grid, block, lds, stream, a, ro, s);
-      else
-        return hipErrorInvalidValue;
-    } else if (a.nchd > kChunksAtOnce) {
-      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, true, false, kBlocks, kWaves>), grid, block, lds, stream, a, ro, s);
-    } else {
-      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, false, false, kBlocks, kWaves>), grid, block, lds, stream, a, ro, s);
-    }
-    return hipGetLastError();
-  }
-  if (a.B > kFusedMaxB) return hipErrorInvalidValue;
-  if (!test_has_its_launch(a.hosted, a.fused.nfine, a.M, s)) {
-    if (a.hosted == kHostsAll)
-      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, false, false, false, true, kBlocks, kWaves>), grid, block, lds, stream, a, ro, s);
+  if (a.B > kFusedMaxB) {
+    if (a.hosted != kHostsNothing) return hipErrorInvalidValue;
+    if constexpr (kPer == 8)
+      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, true, true, false, kBlocks, kWaves>), grid, block, lds, stream, a, ro, s);
     else
-      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, true, true, kBlocks, kWaves>), grid, block, lds, stream, a, ro, s);
-    return hipGetLastError();
+      return hipErrorInvalidValue;
+  } else if constexpr (kWaves != kDrawWaves) {
+    return hipErrorInvalidValue;                         // see draw_plan
+  } else if (a.hosted == kHostsNothing) {
+    if (a.nchd > kChunksAtOnce)
+      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, true, false, kBlocks>), grid, block, lds, stream, a, ro, s);
+    else
+      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, false, false, kBlocks>), grid, block, lds, stream, a, ro, s);
+  } else if (!test_has_its_launch(a.hosted, a.fused.nfine, a.M, s)) {
+    if (a.hosted == kHostsAll)
+      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, false, false, false, true, kBlocks>), grid, block, lds, stream, a, ro, s);
+    else
+      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, true, true, kBlocks>), grid, block, lds, stream, a, ro, s);
+  } else {
+    if (a.hosted == kHostsAll) hipLaunchKernelGGL((accept_draw_kernel<8, false, false>), dim3(1, a.B), block, 0, stream, a, ro, s);
+    else hipLaunchKernelGGL((accept_draw_kernel<8, false, true, false, true, true>), dim3(1, a.B), block, 0, stream, a, ro, s);
+    hipLaunchKernelGGL((final_draw_kernel<kPer, kBlocks>), grid, block, lds, stream, a, s);
   }
-  if (a.hosted == kHostsAll) hipLaunchKernelGGL((accept_draw_kernel<8, false, false>), dim3(1, a.B), dim3(kDrawWaves * 64), 0, stream, a, ro, s);
-  else hipLaunchKernelGGL((accept_draw_kernel<8, false, true, false, true, true>), dim3(1, a.B), dim3(kDrawWaves * 64), 0, stream, a, ro, s);
-  hipLaunchKernelGGL((final_draw_kernel<kPer, kBlocks, kWaves>), grid, block, lds, stream, a, s);
   return hipGetLastError();
 }
 

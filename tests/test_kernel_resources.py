@@ -33,9 +33,16 @@ def _kernels():
             yield from msgpack.unpackb(blob[desc:desc + desc_size], raw=False)["amdhsa.kernels"]
 
 
+pytestmark = pytest.mark.skipif(not os.path.exists(build.LIB_PATH), reason="not built")
+
+
+def test_draws_of_eight_wavefronts_are_those_of_many_sequences():
+    """The plan takes workgroups of eight wavefronts for more sequences than a launch in front can have hosted, which one kernel draws."""
+    draws = [k[".name"] for k in _kernels() if re.search(r"\d(accept|final)_draw_kernel", k[".name"]) and k[".max_flat_workgroup_size"] == 512]
+    assert len(draws) == 1, draws
+
+
 def test_fp32_heads_fit_a_compute_unit_as_planned():
-    if not os.path.exists(build.LIB_PATH):
-        pytest.skip("not built")
     seen = set()
     for k in _kernels():
         m = re.search(r"\d(lmhead_f32(?:_thirds)?_kernel)ILi(\d)E", k[".name"])
