@@ -397,7 +397,8 @@ __device__ inline UnitPick pick_unit(const double* s_mass, const double* s_sums,
 }
 
 // How the draw is split, see draw_split.  A unit is `blocks` (1 unless kBlocks) times 64 * kPer ids, at most 1024 blocks; row_at:
-// where the draft row's copy starts in the dynamic LDS, in doubles (0: no copy); exps: of its exponentials (stage_draft_exps).
+// where the draft row's copy starts in the dynamic LDS, in doubles (0: no copy); exps: of its exponentials (stage_draft_exps), for the
+// kernels that have their code (kExps).
 struct DrawSplit { int n_units, group_units, row_at, blocks; bool exps; };
 template <int kPer, bool kBlocks>
 __device__ inline int draw_first_id(const DrawSplit& s, int grp, int wave) {
@@ -409,7 +410,7 @@ __device__ inline int draw_first_id(const DrawSplit& s, int grp, int wave) {
 // draw_first_id + lane + e * 64, e < kPer).  The dynamic LDS holds 65 doubles for every 64 units begun (draw_lds_doubles) and, if
 // row_at > 0, from double row_at on room for the draft row and 32 bytes.
 __host__ __device__ inline int draw_lds_doubles(int n_units) { return (n_units + 63) / 64 * 65; }
-template <int kPer, bool kBlocks, int kWaves>
+template <int kPer, bool kBlocks, int kWaves, bool kExps>
 __device__ inline void draw_final_token(const StepArgs& a, int b, int grp, const DrawSplit& split, const FinalInfo& f, int* dv,
                                         DrawLds* L) {
   constexpr int kThreads = 64 * kWaves;
@@ -442,7 +443,7 @@ __device__ inline void draw_final_token(const StepArgs& a, int b, int grp, const
     }
   };
   if (row_at > 0 && R.residual && !R.greedy_draft) {     // workgroup-uniform
-    R.exps = kPer == 8 && split.exps;                    // several turns: draw_plan takes 512 ids a unit
+    R.exps = kExps && split.exps;
     if (R.exps && !kBlocks && n_whole > 0) fetch(unit);
     if (!R.exps) R.lds_at = stage_draft_row<kThreads>(R.zq, R.dtype, a.V_d, tid, 8 * row_at);
     else if (a.dtype == OT_BF16) R.lds_at = stage_draft_exps<kThreads, uint16_t>(R, a.V_d, tid, 8 * row_at);

@@ -18,7 +18,7 @@
 namespace otv {
 namespace {
 
-template <int kPer, bool kBlocks>
+template <int kPer, bool kBlocks, bool kExps>
 __global__ __launch_bounds__(kDrawWaves * 64) void final_draw_kernel(StepArgs a, DrawSplit s) {
   const int b = blockIdx.y, grp = blockIdx.x, tid = threadIdx.x;
   const int wave = uniform(tid >> 6), lane = tid & 63;
@@ -28,7 +28,7 @@ __global__ __launch_bounds__(kDrawWaves * 64) void final_draw_kernel(StepArgs a,
   load_tmap<kPer>(a.tmap, a.V_t, first + lane, 64, first + 64 * kPer <= a.V_t, dv);   // overlaps the next load
   const FinalInfo f = a.fin[b];
   if (f.mode == 0) return;                  // greedy or flagged sequence: nothing to draw
-  draw_final_token<kPer, kBlocks, kDrawWaves>(a, b, grp, s, f, dv, &s_draw);
+  draw_final_token<kPer, kBlocks, kDrawWaves, kExps>(a, b, grp, s, f, dv, &s_draw);
 }
 
 // Row offsets of up to kFusedMaxB sequences as a kernel argument (the host has them): the workgroup knows its rows without
@@ -44,8 +44,9 @@ constexpr int64_t kRepeatedMergeBytes = 32 << 20;
 // cost a single sequence 0.7 of 13 us).
 // kWide: draft rows of more than kChunksAtOnce chunks (merge_draft_chunks).
 // kBlocks: units of several blocks (draw_split).
+// kExps: a draw with the draft row's exponentials in LDS (launch_draw).  As a runtime flag it cost the others 0.5 to 0.9 of 10 to 12 us.
 template <int kPer, bool kDraw, bool kChunks, bool kMany = false, bool kWide = kMany, bool kFused = !kChunks, bool kBlocks = false,
-          int kWaves = kDrawWaves>
+          int kWaves = kDrawWaves, bool kExps = false>
 __global__ __launch_bounds__(kWaves * 64) void accept_draw_kernel(StepArgs a, RowOffsets ro, DrawSplit split) {
   const int b = blockIdx.y, grp = blockIdx.x, tid = threadIdx.x;
   const int wave = uniform(tid >> 6), lane = tid & 63;
@@ -147,7 +148,7 @@ __global__ __launch_bounds__(kWaves * 64) void accept_draw_kernel(StepArgs a, Ro
   if (!kDraw) return;
   const FinalInfo f = s_fin;
   if (f.mode == 0) return;
-  draw_final_token<kPer, kBlocks, kWaves>(a, b, grp, split, f, dv, &s_draw);
+  draw_final_token<kPer, kBlocks, kWaves, kExps>(a, b, grp, split, f, dv, &s_draw);
 }
 
 // Units of the draw and their share per workgroup.  While no more than a workgroup per compute unit is needed for one turn each,
@@ -204,20 +205,52 @@ bool test_has_its_launch(int hosted, int nfine, int M, const DrawSplit& s) {
   return hosted != kHostsNothing && (int64_t)M * nfine * (int64_t)sizeof(Partial) * ceil_div(s.n_units, s.group_units) > kRepeatedMergeBytes;
 }
 
-// What was left by which launch: see StepArgs::hosted.  row_off_host holds the B + 1 row offsets.
+// What was left by which launch: see StepArgs::hosted.
+template <int kPer, bool kBlocks, int kWaves, bool kExps>
+hipError_t launch_draw_kernels(const StepArgs& a, const RowOffsets& ro, const DrawSplit& s, dim3 grid, size_t lds, hipStream_t stream) {
+  const dim3 block(kWaves * 64);
+  if (a.B > kFusedMaxB) {
+    if (a.hosted != kHostsNothing) return hipErrorInvalidValue;
+    if constexpr (kPer == 8)
+      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, true, true, false, kBlocks, kWaves, kExps>), grid, block, lds, stream, a, ro, s);
+    else
+      return hipErrorInvalidValue;
+  } else if constexpr (kWaves != kDrawWaves) {
+    return hipErrorInvalidValue;                         // see draw_plan
+  } else if (a.hosted == kHostsNothing) {
+    if (a.nchd > kChunksAtOnce)
+      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, true, false, kBlocks, kWaves, kExps>), grid, block, lds, stream, a, ro, s);
+    else
+      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, false, false, kBlocks, kWaves, kExps>), grid, block, lds, stream, a, ro, s);
+  } else if (!test_has_its_launch(a.hosted, a.fused.nfine, a.M, s)) {
+    if (a.hosted == kHostsAll)
+      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, false, false, false, true, kBlocks, kWaves, kExps>), grid, block, lds, stream, a, ro, s);
+    else
+      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, true, true, kBlocks, kWaves, kExps>), grid, block, lds, stream, a, ro, s);
+  } else {
+    if (a.hosted == kHostsAll) hipLaunchKernelGGL((accept_draw_kernel<8, false, false>), dim3(1, a.B), block, 0, stream, a, ro, s);
+    else hipLaunchKernelGGL((accept_draw_kernel<8, false, true, false, true, true>), dim3(1, a.B), block, 0, stream, a, ro, s);
+    hipLaunchKernelGGL((final_draw_kernel<kPer, kBlocks, kExps>), grid, block, lds, stream, a, s);
+  }
+  return hipGetLastError();
+}
+
+// row_off_host holds the B + 1 row offsets.
 template <int kPer, bool kBlocks = false, int kWaves = kDrawWaves>
 hipError_t launch_draw(const StepArgs& a, const int32_t* row_off_host, const DrawSplit& split, hipStream_t stream) {
   constexpr size_t kLdsBytes = kWaves == kDrawWaves ? kDrawLdsBytes : kDrawLdsBytes / 2;
   DrawSplit s = split;
-  const dim3 grid(ceil_div(s.n_units, s.group_units), a.B), block(kWaves * 64);
+  const dim3 grid(ceil_div(s.n_units, s.group_units), a.B);
   size_t lds = draw_lds_bytes(s);
   // From two turns on the workgroup keeps the draft row in LDS where it fits: a gather from memory moves a 128-byte line
-  // per id, about 2 us of a turn, the copy costs that once (128 sequences x 128256 ids: 51 us without, 39 with).  Its exponentials if
-  // those fit, formed once a workgroup and not once an id: the turns then wait for the target's logits and the inverse map alone.
-  // us per step from the logits, exponentials / logits as stored: 128 sequences x 128256 ids with 32000 draft ids 49.3 / 53.1, 300 x 32003
-  // with 8000 (16 wavefronts) 43.7 / 45.8.  Up to the largest copies (20 / 128 sequences): 50257 bf16 ids 26.0 / 60 against 26.4 / 76
-  // gathered, 75000 26.6 / 62 against 28 / 89.
-  s.exps = s.group_units > kWaves && lds + exps_bytes(a.V_d) <= kLdsBytes;
+  // per id, about 2 us of a turn, the copy costs that once (128 sequences x 128256 ids: 51 us without, 39 with).  From three turns on
+  // its exponentials if those fit, formed once a workgroup and not once an id: the turns then wait for the target's logits and the
+  // inverse map alone.  us per step from the logits, exponentials / logits as stored, with one turn and a part of one 17.6 / 16.8
+  // (200 sequences x 9000 ids, draft rows of 8000), with two 23.8 / 23.0 (128 x 32003, 32000) or even (draft rows of 1000), with two and a
+  // half 20.9 / 21.2 (200 x 20011, 8000), with eight 48.3 / 52.3 (128 x 128256, 32000); workgroups of 8 wavefronts with two turns 33.2 /
+  // 26.9 (700 x 6500, 4000).  Up to the largest copies (20 / 128 sequences): 50257 bf16 ids 26.0 / 60 against 26.4 / 76 gathered, 75000
+  // 26.6 / 62 against 28 / 89.
+  s.exps = kPer == 8 && s.group_units > 2 * kWaves && lds + exps_bytes(a.V_d) <= kLdsBytes;
   const size_t row_bytes = s.exps ? exps_bytes(a.V_d) : (size_t)a.V_d * (a.dtype == OT_BF16 ? 2 : 4) + 32;
   if (s.group_units > kWaves && lds + row_bytes <= kLdsBytes) {
     s.row_at = (int)(lds / sizeof(double));
@@ -225,30 +258,9 @@ hipError_t launch_draw(const StepArgs& a, const int32_t* row_off_host, const Dra
   }
   RowOffsets ro;
   for (int b = 0; b <= kFusedMaxB; ++b) ro.v[b] = row_off_host[b <= a.B ? b : a.B];
-  if (a.B > kFusedMaxB) {
-    if (a.hosted != kHostsNothing) return hipErrorInvalidValue;
-    if constexpr (kPer == 8)
-      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, true, true, false, kBlocks, kWaves>), grid, block, lds, stream, a, ro, s);
-    else
-      return hipErrorInvalidValue;
-  } else if constexpr (kWaves != kDrawWaves) {
-    return hipErrorInvalidValue;                         // see draw_plan
-  } else if (a.hosted == kHostsNothing) {
-    if (a.nchd > kChunksAtOnce)
-      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, true, false, kBlocks>), grid, block, lds, stream, a, ro, s);
-    else
-      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, false, false, kBlocks>), grid, block, lds, stream, a, ro, s);
-  } else if (!test_has_its_launch(a.hosted, a.fused.nfine, a.M, s)) {
-    if (a.hosted == kHostsAll)
-      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, false, false, false, true, kBlocks>), grid, block, lds, stream, a, ro, s);
-    else
-      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, true, true, kBlocks>), grid, block, lds, stream, a, ro, s);
-  } else {
-    if (a.hosted == kHostsAll) hipLaunchKernelGGL((accept_draw_kernel<8, false, false>), dim3(1, a.B), block, 0, stream, a, ro, s);
-    else hipLaunchKernelGGL((accept_draw_kernel<8, false, true, false, true, true>), dim3(1, a.B), block, 0, stream, a, ro, s);
-    hipLaunchKernelGGL((final_draw_kernel<kPer, kBlocks>), grid, block, lds, stream, a, s);
-  }
-  return hipGetLastError();
+  if constexpr (kPer == 8)                               // several turns: draw_plan takes 512 ids a unit
+    if (s.exps) return launch_draw_kernels<kPer, kBlocks, kWaves, true>(a, ro, s, grid, lds, stream);
+  return launch_draw_kernels<kPer, kBlocks, kWaves, false>(a, ro, s, grid, lds, stream);
 }
 
 }  // namespace

@@ -1,6 +1,7 @@
-"""The final draw with the draft row's exponentials in LDS: workgroups that take several turns, of 16 wavefronts and (more sequences
-than compute units) of 8.  Edges: the last unit of 512 ids whole, of one id, of all but one; draft rows at every alignment, of one and
-of a few ids, the longest whose exponentials fit half of LDS or all of it and the next; n-gram overrides inside the units."""
+"""The final draw with the draft row in LDS, as stored or (three turns and more) its exponentials: workgroups that take several
+turns, of 16 wavefronts and (more sequences than compute units) of 8.  Edges: the last unit of 512 ids whole, of one id, of all but one;
+draft rows at every alignment, of one and of a few ids, the longest whose exponentials fit half of LDS or all of it and the next; n-gram
+overrides inside the units."""
 import numpy as np
 import pytest
 
@@ -18,20 +19,25 @@ def _copy(dtype, V_t, V_d, B):
     masses = (-(-units // 64) * 65 + 1) // 2 * 16
     exps = masses + 4 * (V_d + 20)
     waves = 8 if B > max(n_cu, 255) and exps <= lds // 2 else 16
-    assert -(-units // max(1, n_cu * (16 // waves) // B)) > waves            # several turns
-    if exps <= lds // (16 // waves):
+    turns = -(-(-(-units // max(1, n_cu * (16 // waves) // B))) // waves)
+    assert turns > 1
+    if turns > 2 and exps <= lds // (16 // waves):
         return waves, "exponentials"
     return waves, "stored" if masses + V_d * (2 if dtype == "bf16" else 4) + 32 <= lds else "nothing"
 
 
 @pytest.mark.parametrize("dtype,V_t,V_d,B,copy", [
-    ("bf16", 4608, 1, 300, (8, "exponentials")),         # the second turn holds one whole unit; a draft row of one id
-    ("bf16", 8193, 4001, 257, (8, "exponentials")),      # the last unit of one id
+    ("bf16", 4608, 1, 300, (8, "stored")),               # the second turn holds one whole unit; a draft row of one id
+    ("bf16", 8192, 4001, 257, (8, "stored")),            # two whole turns
+    ("bf16", 8193, 4001, 257, (8, "exponentials")),      # a third one, of one id
     ("f32", 12287, 3, 520, (8, "exponentials")),         # two rounds of 8 wavefronts, the last unit of 511 ids
+    ("bf16", 8704, 1, 300, (8, "exponentials")),         # a draft row of one id, whole units only
     ("bf16", 9001, 18979, 260, (8, "exponentials")),
     ("bf16", 9001, 19048, 260, (8, "exponentials")),     # exponentials that just fit half of LDS next to 65 doubles of masses
-    ("bf16", 9001, 19049, 260, (16, "exponentials")),    # and that do not
-    ("bf16", 9001, 19500, 260, (16, "exponentials")),
+    ("bf16", 9001, 19049, 260, (16, "stored")),          # and that do not
+    ("bf16", 9001, 19500, 260, (16, "stored")),
+    ("bf16", 16384, 19049, 260, (16, "stored")),         # two whole turns
+    ("bf16", 16385, 19049, 260, (16, "exponentials")),
     ("f32", 40000, 37500, 120, (16, "exponentials")),
     ("bf16", 30011, 37903, 130, (16, "exponentials")),   # rows at every 2-byte alignment
     ("bf16", 30011, 38248, 130, (16, "exponentials")),   # the longest row whose exponentials fit
