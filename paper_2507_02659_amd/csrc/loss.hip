@@ -196,10 +196,10 @@ struct LossRowOffsets { int32_t v[kArgumentB + 1]; };
 // window end at once; a workgroup then knows its sequence and row without a load, and everything else about them comes with one
 // round trip of scalar loads, which do not wait behind the vector loads of its terms.  Most rows of a batch have no token with a KL
 // term, and what their workgroups take to find that out the others wait for (6.7 us of 21 with the row's sequence looked up behind
-// the first turn's loads, and what hangs on it loaded after that).  A sequence's last row never has a token: unless its q' row of
-// zeros is wanted, the place in front of it takes it along (16 windows of 8 tokens then are 512 workgroups, all on the chip at once,
-// and not 576).
-// 0: the rows one after the other (ragged windows that would leave most places empty).
+// the first turn's loads, and what hangs on it loaded after that).  A sequence's last row never has a token: the
+// place in front of it takes it along (16 windows of 8 tokens then are 512 workgroups, all on the chip at once, and not 576).
+// 0: the rows one after the other: ragged windows that would leave most places empty, and where the q' rows are wanted, which
+// every row's workgroups write (us per call, rows / places: 16 windows of 1 to 10 tokens x 50257 ids 20.2 / 20.9, 48 of them 35.2 / 36.7).
 // n_arrivals: rows, or places with a row, that are counted in.
 template <int kThreads>
 __global__ __launch_bounds__(kThreads, 4) void loss_kernel(LossArgs a, LossRowOffsets ro, int seq_rows, int n_arrivals, int groups, int group_terms, int staged) {
@@ -221,10 +221,9 @@ __global__ __launch_bounds__(kThreads, 4) void loss_kernel(LossArgs a, LossRowOf
     const bool argument = a.B <= kArgumentB;
     r0 = argument ? ro.v[b] : a.row_off[b];
     const int rows = (argument ? ro.v[b + 1] : a.row_off[b + 1]) - r0, at = place % seq_rows;
-    const bool fold = a.out.qprime == nullptr;
-    if (at >= (fold ? max(rows - 1, 1) : rows)) return;  // past the sequence's window
+    if (at >= max(rows - 1, 1)) return;                  // past the sequence's window
     row = r0 + at;
-    free_row = fold && at == rows - 2;
+    free_row = at == rows - 2;
   } else {
     row = place;
     if (row >= a.M) return;
@@ -428,11 +427,11 @@ int ot_distill_loss(ot_ctx* ctx, const ot_step_in* in, const ot_step_out* step, 
   LossRowOffsets ro{};
   int seq_rows = 0, n_places = 0;                        // of the longest window
   for (int b = 0; b < in->B; ++b) {
-    const int rows = in->row_off_host[b + 1] - in->row_off_host[b], n = out->qprime ? rows : std::max(1, rows - 1);
+    const int n = std::max(1, in->row_off_host[b + 1] - in->row_off_host[b] - 1);
     seq_rows = std::max(seq_rows, n);
     n_places += n;
   }
-  if ((int64_t)seq_rows * in->B > 2 * (int64_t)n_places) seq_rows = 0;
+  if (out->qprime || (int64_t)seq_rows * in->B > 2 * (int64_t)n_places) seq_rows = 0;
   const int n_arrivals = seq_rows > 0 ? n_places : M;
   for (int b = 0; b <= in->B && in->B > 0 && in->B <= kArgumentB; ++b) ro.v[b] = in->row_off_host[b];
   const int places = seq_rows > 0 ? seq_rows * in->B : std::max(M, 1);

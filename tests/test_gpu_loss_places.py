@@ -1,6 +1,6 @@
-"""The loss launch's places: workgroups for every token (with the q' rows: every row) of the longest window and sequence (windows of 0
-and 1 token among longer ones), row offsets as an argument up to 31 sequences; or rows one after the other (windows that would leave
-most places empty); rows without a token, the last of a window among them, with and without the q' rows."""
+"""The loss launch's places: workgroups for every token of the longest window and sequence (windows of 0 and 1 token among longer ones),
+row offsets as an argument up to 31 sequences; or rows one after the other (the q' rows are wanted, or windows that would leave most places
+empty); rows without a token, the last of a window among them, with and without the q' rows."""
 import pytest
 
 from test_gpu_distill import _compare
@@ -12,6 +12,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("ks,qprime", [
     ([0], True), ([1], True), ([0, 0, 0], False),
     ([3, 0, 5, 1, 0, 4, 4, 2, 5], True),
+    ([3, 0, 5, 1, 0, 4, 4, 2, 5], False),
+    ([0], False), ([1], False),
     ([2] * 30 + [1], False),                  # the most sequences whose row offsets travel with the launch
     ([2] * 31 + [1], False),
     ([2, 0, 3] * 100, False),
