@@ -49,9 +49,10 @@ extern "C" {
 /* OT_BF16 is the production type: the LM head runs on the matrix cores, bound by the weight stream.
  * OT_F32 exists for small problems that want fp32 arithmetic end to end (checks against an fp32 model, toy
  * vocabularies): its LM head runs on the fp32 matrix instructions, a sixteenth of the bf16 rate, or, above 16 rows and
- * from 384 hidden indices on, on the bf16 ones with every operand split into three (six products, no less accurate), so a
- * step costs more than the bf16 one where the rows are many (1.4x at d = 1024, V_t = 32000, 6 rows).  Nothing is refused
- * for size.                                                                                                   */
+ * from 384 hidden indices on, on the bf16 ones with every operand split into three, exactly, and the six largest of nine
+ * products (what is left out is at most 2^-24 of a product, to either side; the error of the logits is below that of the
+ * fp32 instructions).  A step costs more than the bf16 one where the rows are many (1.4x at d = 1024, V_t = 32000, 6 rows).
+ * Nothing is refused for size.                                                                                */
 #define OT_BF16 0
 #define OT_F32  1
 
@@ -164,7 +165,9 @@ typedef struct ot_step_in {
   int32_t         B;                  /* number of sequences, 0 <= B <= max_batch                             */
   uint32_t        step;               /* Philox counter word 1                                                */
   const int32_t*  row_off;            /* DEVICE [B+1]                                                         */
-  const int32_t*  row_off_host;       /* HOST   [B+1], same values; used for validation and launch sizes      */
+  const int32_t*  row_off_host;       /* HOST   [B+1], same values; used for validation, for launch sizes and, of
+                                         up to 255 sequences, as arguments of the launches (so that a captured
+                                         call keeps the windows that it was captured with)                    */
   const void*     hidden;             /* DEVICE [M, d] row-major, cfg.dtype                                   */
   const void*     draft_logits;       /* DEVICE [K, V_d] row-major, cfg.dtype                                 */
   const int32_t*  draft_ids;          /* DEVICE [K] drafted ids d_i                                           */

@@ -739,9 +739,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void l
 }
 
 // ---------------------------------------------------------------------------------------------------------------
-// fp32 head of up to 16 rows or a short hidden dimension, on v_mfma_f32_16x16x4_f32 (binary32 products and sums, twice the rate of the vector units' fused
-// multiply-adds).  Bound by the matrix cores from about 48 rows on (147 TFLOP/s is what a large fp32 product reaches on
-// this card), by the weight stream below.  W is re-tiled once at init so that a wavefront's loads are contiguous:
+// fp32 head of up to 16 rows or less than 384 hidden indices (f32_plan), on v_mfma_f32_16x16x4_f32 (binary32 products and sums, twice the
+// rate of the vector units' fused multiply-adds).  Bound by the matrix cores from about 48 rows on (147 TFLOP/s is what a large fp32
+// product reaches on this card), by the weight stream below.  W is re-tiled once at init so that a wavefront's loads are contiguous:
 // unit(wt, kb, s, lane), one float4, holds W[16*kb + 4*(lane/16) + s][64*wt + 4*(lane%16) + 0..3], zero outside [d, V_t].
 // The four floats of a lane feed four MFMAs, one per interleaved set of 16 columns {64*wt + 4*i + nw}, and a lane's
 // float4 of hidden values H[row][16*kb + 4*(lane/16) + 0..3] feeds the four steps s: the hidden index that a lane group
@@ -749,11 +749,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void l
 // A workgroup owns 64 columns and up to 48 rows and splits the hidden dimension over its wavefronts, whose partial tiles
 // are summed through LDS in a fixed order: a head of 1024 columns is 16 workgroups of 8 wavefronts, one of 32000 is 500
 // per row block.  The row blocks of a column tile run on the same XCD back to back and meet in its L2.
-// The launch also leaves softmax partials and takes the draft side (a workgroup per job, or packed into few: f32_row_front),
-// which spares the statistics launch: 57.2 -> 54.8 us per step at 64 rows (before the thirds kernel below took those), 17.4 -> 14.2 at 5.
-// Measured (64 rows, d = 1024, V_t = 32000 / 5 rows, d = 256, V_t = 1024): 46 / 4.2 us, with the draft side 49.6 / 5.4, against 575 / 68 us of a kernel
-// whose threads owned one column each over all of the hidden dimension (1000 and 4 workgroups of serial chains); error
-// against 64 bits 4.7e-7 and 1.1e-7, with one long chain per logit 2e-6 and 6e-7.
+// The launch also leaves softmax partials and takes the draft side (a workgroup per job, or packed into few: f32_row_front), which
+// spares the statistics launch: 17.4 -> 14.2 us per step at 5 rows, d = 256, V_t = 1024.  Its registers for that leave four workgroups
+// with two row tiles on a compute unit, three with three (f32_plan counts on it).
+// Measured with the draft side: 64 rows, d = 256, V_t = 32000 18.9 us; 5 rows, d = 256, V_t = 1024 4.9 to 5.4 us, where a kernel whose
+// threads owned one column each over all of the hidden dimension took 68 (4 workgroups of serial chains) and its one long chain per
+// logit was off by 6e-7 against 64 bits instead of 1.1e-7.
 __global__ __launch_bounds__(256) void pack_w_f32_kernel(const float* __restrict__ W, int d, int V_t,
                                                          float4* __restrict__ Wp, int nkb, int64_t n_units) {
   const int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -886,10 +887,10 @@ __global__ __launch_bounds__(WAVES * 64) void lmhead_f32_kernel(const float* __r
 // against 64 bits at 64 rows x 32000 columns, d = 1024, eight seeds, here / with the binary32 instruction: logits 2.3e-7 / 2.9e-7 of
 // their norm, probabilities of the proposed tokens 3.0e-7 / 3.2e-7, their ratios 2.4e-7 / 2.6e-7.
 // Same packed weights and the same split over four wavefronts as above; a step is two blocks of 16 hidden indices.  Bound by the
-// loads: of 36 us at 64 rows x 32000 columns (d = 1024; 45.8 with the binary32 instruction) 25 are left without the hidden rows' traffic (one L2
-// read of all rows per 64 columns), the splits and half of the products, 30 with the traffic alone.  Tried instead: the hidden rows'
-// thirds shared through LDS, wavefronts by columns and halves of the hidden dimension: 43 us, a barrier per 64 hidden indices and
-// longer chains of sums (3.4e-7).
+// loads: of 36 us at 64 rows x 32000 columns (d = 1024; 45.8 with the binary32 instruction; 0.3 less with parts cut off) 25 are left
+// without the hidden rows' traffic (one L2 read of all rows per 64 columns), the splits and half of the products, 30 with the traffic
+// alone.  Tried instead: the hidden rows' thirds shared through LDS, wavefronts by columns and halves of the hidden dimension: 43 us, a
+// barrier per 64 hidden indices and longer chains of sums (3.4e-7).
 struct Thirds { bf16x8 part[3]; };
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));

@@ -202,7 +202,8 @@ struct LossRowOffsets { int32_t v[kArgumentB + 1]; };
 // every row's workgroups write (us per call, rows / places: 16 windows of 1 to 10 tokens x 50257 ids 20.2 / 20.9, 48 of them 35.2 / 36.7).
 // n_arrivals: rows, or places with a row, that are counted in.
 template <int kThreads>
-__global__ __launch_bounds__(kThreads, 4) void loss_kernel(LossArgs a, LossRowOffsets ro, int seq_rows, int n_arrivals, int groups, int group_terms, int staged) {
+__global__ __launch_bounds__(kThreads, 4) void loss_kernel(LossArgs a, LossRowOffsets ro, int seq_rows, int n_arrivals, int groups,
+                                                          int group_terms, int staged) {
   constexpr int kWaves = kThreads / 64;
   __shared__ LossRow s_row;
   __shared__ double s_term[4][kWaves];
@@ -437,9 +438,8 @@ int ot_distill_loss(ot_ctx* ctx, const ot_step_in* in, const ot_step_out* step, 
   const int places = seq_rows > 0 ? seq_rows * in->B : std::max(M, 1);
   const dim3 grid((unsigned)(p.groups * ceil_div(places, 8) * 8)), block(p.threads);
   const size_t lds = p.staged ? row_bytes : 16;
-  if (p.threads == 1024) hipLaunchKernelGGL(loss_kernel<1024>, grid, block, lds, st, a, ro, seq_rows, n_arrivals, p.groups, p.group_terms, p.staged);
-  else if (p.threads == 512) hipLaunchKernelGGL(loss_kernel<512>, grid, block, lds, st, a, ro, seq_rows, n_arrivals, p.groups, p.group_terms, p.staged);
-  else hipLaunchKernelGGL(loss_kernel<256>, grid, block, lds, st, a, ro, seq_rows, n_arrivals, p.groups, p.group_terms, p.staged);
+  const auto kernel = p.threads == 1024 ? loss_kernel<1024> : p.threads == 512 ? loss_kernel<512> : loss_kernel<256>;
+  hipLaunchKernelGGL(kernel, grid, block, lds, st, a, ro, seq_rows, n_arrivals, p.groups, p.group_terms, p.staged);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return ot_fail_hip(e, "ot_distill_loss: launch");
   return OT_OK;

@@ -295,7 +295,9 @@ __device__ inline int stage_draft_exps(const FinalRow& R, int V_d, int tid, int 
     for (int e = 0; e < kVec; e += 4)
       *(__attribute__((address_space(3))) f32x4*)(s_row + (c * kVec + e) * 4) = f32x4{t[e], t[e + 1], t[e + 2], t[e + 3]};
   };
-  auto bits = [](const u32x4& raw, int e) { return sizeof(T) == 4 ? raw[e & 3] : e & 1 ? raw[(e / 2) & 3] & 0xFFFF0000u : raw[(e / 2) & 3] << 16; };
+  auto bits = [](const u32x4& raw, int e) {
+    return sizeof(T) == 4 ? raw[e & 3] : e & 1 ? raw[(e / 2) & 3] & 0xFFFF0000u : raw[(e / 2) & 3] << 16;
+  };
   for (int c0 = tid; c0 < chunks; c0 += kAtOnce * kThreads) {
     u32x4 raw[kAtOnce];
 #pragma unroll
@@ -323,7 +325,8 @@ __device__ inline int stage_draft_exps(const FinalRow& R, int V_d, int tid, int 
       put(c, x);
     }
   }
-  if (tid == 0) *(__attribute__((address_space(3))) float*)(s_row + (head - 1) * 4) = FinalRow::exponential(kFarBelow, R.mxq, R.scq_hi, R.scq_lo);
+  if (tid == 0)
+    *(__attribute__((address_space(3))) float*)(s_row + (head - 1) * 4) = FinalRow::exponential(kFarBelow, R.mxq, R.scq_hi, R.scq_lo);
   return at + 16 + head * 4;
 }
 

@@ -44,7 +44,8 @@ constexpr int64_t kRepeatedMergeBytes = 32 << 20;
 // cost a single sequence 0.7 of 13 us).
 // kWide: draft rows of more than kChunksAtOnce chunks (merge_draft_chunks).
 // kBlocks: units of several blocks (draw_split).
-// kExps: a draw with the draft row's exponentials in LDS (launch_draw).  As a runtime flag it cost the others 0.5 to 0.9 of 10 to 12 us.
+// kExps: a draw with the draft row's exponentials in LDS (launch_draw).  As a runtime flag it cost the others 0.5 to 0.9 us of 10 to 12
+// (112 registers instead of 94).
 template <int kPer, bool kDraw, bool kChunks, bool kMany = false, bool kWide = kMany, bool kFused = !kChunks, bool kBlocks = false,
           int kWaves = kDrawWaves, bool kExps = false>
 __global__ __launch_bounds__(kWaves * 64) void accept_draw_kernel(StepArgs a, RowOffsets ro, DrawSplit split) {
@@ -209,27 +210,22 @@ bool test_has_its_launch(int hosted, int nfine, int M, const DrawSplit& s) {
 template <int kPer, bool kBlocks, int kWaves, bool kExps>
 hipError_t launch_draw_kernels(const StepArgs& a, const RowOffsets& ro, const DrawSplit& s, dim3 grid, size_t lds, hipStream_t stream) {
   const dim3 block(kWaves * 64);
+  auto test_and_draw = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, lds, stream, a, ro, s); };
   if (a.B > kFusedMaxB) {
     if (a.hosted != kHostsNothing) return hipErrorInvalidValue;
-    if constexpr (kPer == 8)
-      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, true, true, false, kBlocks, kWaves, kExps>), grid, block, lds, stream, a, ro, s);
-    else
-      return hipErrorInvalidValue;
+    if constexpr (kPer == 8) test_and_draw(accept_draw_kernel<kPer, true, true, true, true, false, kBlocks, kWaves, kExps>);
+    else return hipErrorInvalidValue;
   } else if constexpr (kWaves != kDrawWaves) {
     return hipErrorInvalidValue;                         // see draw_plan
   } else if (a.hosted == kHostsNothing) {
-    if (a.nchd > kChunksAtOnce)
-      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, true, false, kBlocks, kWaves, kExps>), grid, block, lds, stream, a, ro, s);
-    else
-      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, false, false, kBlocks, kWaves, kExps>), grid, block, lds, stream, a, ro, s);
+    if (a.nchd > kChunksAtOnce) test_and_draw(accept_draw_kernel<kPer, true, true, false, true, false, kBlocks, kWaves, kExps>);
+    else test_and_draw(accept_draw_kernel<kPer, true, true, false, false, false, kBlocks, kWaves, kExps>);
   } else if (!test_has_its_launch(a.hosted, a.fused.nfine, a.M, s)) {
-    if (a.hosted == kHostsAll)
-      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, false, false, false, true, kBlocks, kWaves, kExps>), grid, block, lds, stream, a, ro, s);
-    else
-      hipLaunchKernelGGL((accept_draw_kernel<kPer, true, true, false, true, true, kBlocks, kWaves, kExps>), grid, block, lds, stream, a, ro, s);
+    if (a.hosted == kHostsAll) test_and_draw(accept_draw_kernel<kPer, true, false, false, false, true, kBlocks, kWaves, kExps>);
+    else test_and_draw(accept_draw_kernel<kPer, true, true, false, true, true, kBlocks, kWaves, kExps>);
   } else {
-    if (a.hosted == kHostsAll) hipLaunchKernelGGL((accept_draw_kernel<8, false, false>), dim3(1, a.B), block, 0, stream, a, ro, s);
-    else hipLaunchKernelGGL((accept_draw_kernel<8, false, true, false, true, true>), dim3(1, a.B), block, 0, stream, a, ro, s);
+    const auto test = a.hosted == kHostsAll ? accept_draw_kernel<8, false, false> : accept_draw_kernel<8, false, true, false, true, true>;
+    hipLaunchKernelGGL(test, dim3(1, a.B), block, 0, stream, a, ro, s);
     hipLaunchKernelGGL((final_draw_kernel<kPer, kBlocks, kExps>), grid, block, lds, stream, a, s);
   }
   return hipGetLastError();
